@@ -35,6 +35,7 @@ struct msk_mesh {
   int depth = 0, leaf_size = 4, top_nodes = 85;
   Node4* d_nodes = nullptr;
   TriRec* d_tris = nullptr;
+  QuickTri* d_quick = nullptr;
   int32_t* d_slot = nullptr;
   int32_t* d_faces = nullptr;
   std::vector<float> vrel;       // float offsets from the centre (host copy)
@@ -138,6 +139,15 @@ void dfree(T*& p) {
   p = nullptr;
 }
 
+// The prefilter records of n triangles, complete when it returns (a mesh may
+// be used from other streams afterwards).
+hipError_t make_quick(msk_ctx* ctx, const TriRec* tris, int64_t n, double radius, QuickTri** out) {
+  hipError_t e = dalloc(out, (size_t)n + kQuickPad);
+  if (e == hipSuccess) e = launch_quick_prepare(tris, n, radius, *out, ctx->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  return e;
+}
+
 uint64_t spread3(uint64_t x) {
   x &= 0x1FFFFF;
   x = (x | x << 32) & 0x1F00000000FFFFull;
@@ -236,7 +246,8 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   if ((he = upload(ctx, &m->d_nodes, B.nodes.data(), B.nodes.size())) != hipSuccess ||
       (he = upload(ctx, &m->d_tris, B.tris.data(), B.tris.size())) != hipSuccess ||
       (he = upload(ctx, &m->d_slot, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
-      (he = upload(ctx, &m->d_faces, F, (size_t)n_tris * 3)) != hipSuccess) {
+      (he = upload(ctx, &m->d_faces, F, (size_t)n_tris * 3)) != hipSuccess ||
+      (he = make_quick(ctx, m->d_tris, n_tris, m->radius, &m->d_quick)) != hipSuccess) {
     msk_mesh_destroy(m);
     return fail(ctx, he == hipErrorOutOfMemory ? MSK_ERR_OOM : MSK_ERR_DEVICE,
                 std::string("mesh upload: ") + hipGetErrorString(he));
@@ -264,6 +275,7 @@ extern "C" void msk_mesh_destroy(msk_mesh* m) {
   if (!m) return;
   dfree(m->d_nodes);
   dfree(m->d_tris);
+  dfree(m->d_quick);
   dfree(m->d_slot);
   dfree(m->d_faces);
   delete m;
@@ -274,8 +286,8 @@ extern "C" msk_status msk_closest_points(msk_ctx* ctx, const msk_mesh* m, const 
   if (!ctx || !m) return MSK_ERR_INVALID_ARG;
   if (nq < 0 || (nq > 0 && (!Q || !tri || !d2 || !bary))) return fail(ctx, MSK_ERR_INVALID_ARG, "bad query arrays");
   if (nq == 0) return MSK_OK;
-  HIP_TRY(ctx, launch_closest_points(m->d_nodes, m->d_tris, (float)m->radius, m->centre, Q, nq, tri, d2, bary,
-                                     ctx->stream));
+  HIP_TRY(ctx, launch_closest_points(m->d_nodes, m->d_tris, m->d_quick, m->leaf_size, (float)m->radius, m->centre, Q,
+                                     nq, ctx->n_cu, tri, d2, bary, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return MSK_OK;
 }
@@ -646,6 +658,8 @@ MeshDev make_meshdev(const msk_mesh* m, const msk_rows* r, const msk_basis* b, m
   std::memset(&M, 0, sizeof(M));
   M.nodes = m->d_nodes;
   M.tris = m->d_tris;
+  M.quick = m->d_quick;
+  M.leaf = m->leaf_size;
   M.slot_of_tri = m->d_slot;
   M.faces = m->d_faces;
   M.n_tris = m->nf;
@@ -702,6 +716,35 @@ QueueInit make_queues(int64_t n_slots, int64_t W) {
 
 }  // namespace
 
+// The persistent launch's shape. A launch of fewer walks than the resident
+// wavefronts (4 per SIMD) have lanes gives each of them as few walks as still
+// cover all, in queue chunks that divide a slot's walks where a divisor is
+// near (a chunk then has one row, which takes a row table).
+static void shape_launch(WalkLaunch& L, const std::vector<MeshDev>& meshes, const msk_dtn_opts& o, int n_cu) {
+  const int64_t total = L.n_slots * L.walks_per_slot, waves = 16ll * n_cu;
+  L.chunk = std::max(1, o.chunk);
+  L.max_owners = 64;
+  if (total < 64 * waves) {
+    int32_t own = (int32_t)std::max<int64_t>(1, (total + waves - 1) / waves);
+    for (int32_t c = own; 2 * c > own; --c)
+      if (L.walks_per_slot % c == 0) {
+        own = c;
+        break;
+      }
+    L.max_owners = own;
+    L.chunk = std::min(L.chunk, own);
+  }
+  L.regen_min = std::min(std::max(1, 3 * L.max_owners / 8), std::min(64, std::max(1, o.regen_min)));
+  if (L.max_owners == 64) L.regen_min = std::min(64, std::max(1, o.regen_min));
+  int32_t leaf = 1;
+  L.knn = 0;
+  for (const MeshDev& md : meshes) {
+    leaf = std::max(leaf, md.leaf);
+    L.knn |= md.knn.k > 0 ? 1 : 0;
+  }
+  L.unit_shift = leaf <= 4 ? 2 : 3;
+}
+
 struct LaunchBuffers {
   MeshDev* d_meshes = nullptr;
   RowSlot* d_slots = nullptr;
@@ -740,12 +783,10 @@ static msk_status run_walks(msk_ctx* ctx, const std::vector<MeshDev>& meshes, co
   L.seed_hi = (uint32_t)(o.seed >> 32);
   L.queue_next = lb.d_qnext;
   L.queue_end = lb.d_qend;
-  L.chunk = std::max(1, o.chunk);
-  L.regen_min = std::min(64, std::max(1, o.regen_min));
   L.use_lds_top = use_lds_top;
   L.n_top = n_top;
   L.accum = o.accum;
-  for (const MeshDev& md : meshes) L.knn |= md.knn.k > 0 ? 1 : 0;
+  shape_launch(L, meshes, o, ctx->n_cu);
   if (o.collect_stats) {
     HIP_TRY(ctx, dalloc(&lb.d_stats, 3));
     HIP_TRY(ctx, launch_fill_u64(lb.d_stats, 3, 0, ctx->stream));
@@ -1055,12 +1096,10 @@ extern "C" msk_status msk_estimate_dtn_noalloc(msk_ctx* ctx, const msk_mesh* m, 
   L.seed_hi = (uint32_t)(o.seed >> 32);
   L.queue_next = d_qn;
   L.queue_end = d_qe;
-  L.chunk = std::max(1, o.chunk);
-  L.regen_min = std::min(64, std::max(1, o.regen_min));
   L.use_lds_top = (o.form == MSK_FORM_PERSISTENT && m->top_nodes > 0) ? 1 : 0;
   L.n_top = m->top_nodes;
   L.accum = o.accum;
-  L.knn = b->knn_mesh ? 1 : 0;
+  shape_launch(L, {M}, o, ctx->n_cu);
   HIP_TRY(ctx, launch_init_queues(d_qn, d_qe, make_queues(L.n_slots, walks), s));
   if (o.form == MSK_FORM_PLAIN)
     HIP_TRY(ctx, launch_walk_plain(L, s));
@@ -1158,11 +1197,9 @@ static hipError_t enqueue_batch(msk_batch* B, hipStream_t s, int part) {
     L.seed_hi = (uint32_t)(B->o.seed >> 32);
     L.queue_next = B->lb.d_qnext;
     L.queue_end = B->lb.d_qend;
-    L.chunk = std::max(1, B->o.chunk);
-    L.regen_min = std::min(64, std::max(1, B->o.regen_min));
     L.accum = B->o.accum;
-    for (const MeshDev& md : B->md) L.knn |= md.knn.k > 0 ? 1 : 0;
     for (msk_dtn* d : B->dtns) L.n_slots += d->n;
+    shape_launch(L, B->md, B->o, B->ctx->n_cu);
     if (B->o.collect_stats) L.stats = B->lb.d_stats;
     if (B->o.form == MSK_FORM_PLAIN) return launch_walk_plain(L, s);
     return launch_walk_persistent(L, std::max(1, B->ctx->n_cu * std::max(1, B->o.blocks_per_cu)), s);
@@ -2253,20 +2290,25 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   Node4* dn = nullptr;
   TriRec* dt = nullptr;
   int32_t* ds = nullptr;
+  QuickTri* dq = nullptr;
   hipError_t he;
   if ((he = upload(ctx, &dn, B.nodes.data(), B.nodes.size())) != hipSuccess ||
       (he = upload(ctx, &dt, B.tris.data(), B.tris.size())) != hipSuccess ||
-      (he = upload(ctx, &ds, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess) {
+      (he = upload(ctx, &ds, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
+      (he = make_quick(ctx, dt, m->nf, m->radius, &dq)) != hipSuccess) {
     dfree(dn);
     dfree(dt);
     dfree(ds);
+    dfree(dq);
     return fail(ctx, MSK_ERR_DEVICE, std::string("rebuild upload: ") + hipGetErrorString(he));
   }
   dfree(m->d_nodes);
   dfree(m->d_tris);
   dfree(m->d_slot);
+  dfree(m->d_quick);
   m->d_nodes = dn;
   m->d_tris = dt;
+  m->d_quick = dq;
   m->d_slot = ds;
   m->n_nodes = (int64_t)B.nodes.size();
   m->depth = B.depth;

@@ -27,6 +27,17 @@ struct alignas(16) TriRec {
 };
 static_assert(sizeof(TriRec) == 48, "triangle record must be 48 bytes");
 
+// Prefilter record of a triangle, in slot order (kQuickPad records that no
+// query accepts follow the last): the triangle in its own frame and the
+// margins of the squared distance computed from it (quick_prepare_kernel).
+// r0 = vertex a, c1; r1 = x axis (along ab), s1; r2 = y axis (towards c), l1;
+// r3 = normal, c2; r4 = s2, l2, F, G: unit directions (c1, s1) of ac and (c2,
+// s2) of bc in the plane, their lengths l1 and l2, margin F |p - a|^2 + G.
+struct alignas(16) QuickTri {
+  float4 r[5];
+};
+constexpr int kQuickPad = 8;
+
 constexpr int kStackDepth = 64;     // traversal stack entries per lane
 constexpr int kMaxTableNnz = 32;    // basis entries per vertex
 constexpr int kMaxTop = 85;         // BVH nodes a workgroup may keep in LDS (3 levels)
@@ -82,10 +93,12 @@ struct KnnDev {
 struct MeshDev {
   const Node4* nodes;
   const TriRec* tris;
+  const QuickTri* quick;
   const int32_t* slot_of_tri;  // original face -> slot
   const int32_t* faces;        // original faces (n_tris x 3)
   int64_t n_tris;
   int32_t n_top;               // nodes of this mesh that may be read from LDS
+  int32_t leaf;                // most triangles of a leaf
   int32_t mode;                // RowMode
   float radius;                // bounding-sphere radius (float)
   double radius_d;
@@ -149,6 +162,8 @@ struct WalkLaunch {
   const unsigned long long* queue_end;  // 8 bounds
   int32_t chunk;
   int32_t regen_min;
+  int32_t max_owners;          // persistent form: lanes of a wavefront that carry a walk (1..64)
+  int32_t unit_shift;          // persistent form: triangles of a listed leaf unit, 2^unit_shift >= the leaf widths
   int32_t use_lds_top;         // single-mesh launch: stage mesh 0's top nodes in LDS
   int32_t n_top;
   unsigned long long* stats;   // optional: [nodes visited, triangles tested, FP32 operations]
@@ -197,8 +212,11 @@ hipError_t launch_discard_batch(const MeshDev* meshes, const RowRange* ranges, i
 hipError_t launch_row_totals(const RowCounters* sets, int32_t n_sets, unsigned long long* out, hipStream_t s);
 hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, const float* Nq, int64_t n, int32_t* idx,
                            float* w, hipStream_t s);
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, float radius, const double* c, const float* Q,
-                                 int64_t nq, int32_t* tri, float* d2, float* bary, hipStream_t s);
+// quick: n + kQuickPad records
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, QuickTri* quick, hipStream_t s);
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const QuickTri* quick, int32_t leaf,
+                                 float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
+                                 float* d2, float* bary, hipStream_t s);
 hipError_t launch_finalize(const MeshDev& M, int64_t n_rows, const int64_t* walks, const double* w, double* S,
                            double* se, hipStream_t s, int32_t jump_only = 0);
 

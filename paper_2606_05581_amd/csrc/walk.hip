@@ -309,27 +309,83 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
   }
 }
 
+// ---- prefilter of the exact triangle test
+// Squared distance from p to the triangle in its own frame (a branch-free
+// handful of fused operations instead of the region tests and divisions of
+// tri_dist2) with its error margin `m`: the exact test's value D of the same
+// triangle satisfies sqrt(D) >= sqrt(max(0, d2 - m)) - delta, and for all but
+// nearly degenerate triangles sqrt(D) <= sqrt(d2 + m) + delta, delta = 2^-21 R
+// covering the exact test's roundings at the size of the coordinates. The
+// frame and margins are prepared by quick_prepare_kernel, whose comment
+// derives them.
+__device__ __forceinline__ void quick_dist(float px, float py, float pz, const QuickTri* __restrict__ T, float& d2,
+                                           float& m) {
+  const float4 r0 = T->r[0], r1 = T->r[1], r2 = T->r[2], r3 = T->r[3], r4 = T->r[4];
+  const float gx = px - r0.x, gy = py - r0.y, gz = pz - r0.z;
+  const float x = r1.x * gx + r1.y * gy + r1.z * gz;
+  const float y = r2.x * gx + r2.y * gy + r2.z * gz;
+  const float z = r3.x * gx + r3.y * gy + r3.z * gz;
+  const float c1 = r0.w, s1 = r1.w, l1 = r2.w, c2 = r3.w, s2 = r4.x, l2 = r4.y;
+  const float b = c1 * l1 - c2 * l2;  // vertex b lies at (b, 0), vertex c at l1 (c1, s1)
+  const float t0 = x - __builtin_amdgcn_fmed3f(x, 0.0f, b);
+  const float q1 = x * c1 + y * s1, h1 = x * s1 - y * c1;
+  const float t1 = q1 - __builtin_amdgcn_fmed3f(q1, 0.0f, l1);
+  const float xb = x - b;
+  const float q2 = xb * c2 + y * s2, h2 = y * c2 - xb * s2;
+  const float t2 = q2 - __builtin_amdgcn_fmed3f(q2, 0.0f, l2);
+  const float e = fminf(fminf(y * y + t0 * t0, h1 * h1 + t1 * t1), h2 * h2 + t2 * t2);
+  const float in = fminf(fminf(y, h1), h2);
+  d2 = z * z + (in >= 0.0f ? 0.0f : e);
+  m = r4.z * (gx * gx + gy * gy + gz * gz) + r4.w;
+}
+
+// Largest squared value d2 - m of a triangle that may still beat or tie a
+// query whose bound is m2 = min(d2 + m): sqrt(d2 - m) <= sqrt(m2) + 2 delta
+// (two_delta = 2 delta; the square root has one ulp).
+__device__ __forceinline__ float keep_bound(float m2, float two_delta) {
+  const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + two_delta;
+  return s * s * (1.0f + 0x1p-20f);
+}
+
 // Wavefront-cooperative leaf tests (same result as the lane-private
 // bvh_nearest, bit for bit). All 64 lanes take part; each lane walks its own
 // nodes, but the triangles of the leaves it reaches are listed in LDS and
-// tested 64 at a time by the whole wavefront, so the long triangle test runs
-// with most lanes busy instead of a few. A task's (squared distance, original
-// index) goes to its owner through a 64-bit LDS atomic minimum, which
-// realises the lexicographic order exactly; the task that holds the minimum
-// writes its barycentrics for the owner. Work is listed in units of up to 4
-// consecutive triangle slots of one owner (one word: first slot << 6 | owner
-// lane, so meshes have fewer than 2^26 triangles); 4 lanes take a unit.
-constexpr int kCoopUnits = 64;  // units per listing window (4 passes of 64 lanes)
+// tested 64 at a time by the whole wavefront. Work is listed in units of
+// 2^unit_shift (4 or 8, at least the leaf width) consecutive triangle slots of
+// one owner, one lane each (one word: first slot << 6 | owner lane, so meshes
+// have fewer than 2^26 triangles); the lanes past a shorter leaf test the
+// following slots, which cannot change a minimum over the mesh, so a unit
+// needs no count.
+//
+// A listed triangle takes the prefilter only. Its upper value d2 + m lowers
+// the owner's bound m2 through an LDS minimum; if its lower value d2 - m still
+// reaches that bound it goes to the wavefront's pending list, and the exact
+// test runs on the pending triangles that are left once their owner's
+// traversal has ended (or the list is full): about two per query instead of
+// all of them. The exact (squared distance, original index) goes to its owner
+// through a 64-bit LDS minimum, which realises the lexicographic order
+// exactly. Should the exact minimum lie above what m2 promised (possible only
+// for nearly degenerate triangles), the owner's search runs again with m2 at
+// that minimum and lowered by exact values only (negative pt.w), so the
+// result never rests on the upper margin.
+//
+// The exact tests were bound by VALU issue: about 190 wavefront instructions
+// per round of 64 tests, every region's path among them. The prefilter takes
+// about 60.
+constexpr int kUnitCap = 64 * 5;  // per lane four leaf children and a warm-start candidate
+constexpr int kPendCap = 128;
 struct CoopScratch {
-  uint32_t unit[kCoopUnits];
-  uint8_t ucnt[kCoopUnits];
+  uint32_t unit[kUnitCap];
+  float4 pt[64];             // owner's query point; w = 2 delta, negative: m2 lowered by exact values only
+  const QuickTri* quick[64];  // owner's arrays (batched meshes differ per lane)
+  const TriRec* tris[64];
+  const Node4* nodes[64];
+  uint32_t m2[64];           // bound on the owner's squared distance (float bits)
   unsigned long long key[64];
-  float4 pt[64];           // owner's query point and early-reject bound
-  const TriRec* tris[64];  // lane's triangle array (batched meshes differ per lane)
-  const Node4* nodes[64];  // lane's node array
   int32_t rec_slot[64];
   float rec_l1[64], rec_l2[64], rec_den[64];
-  uint32_t flops[64];  // statistics kernels only
+  uint32_t pend[kPendCap];
+  float pend_l2[kPendCap];
 };
 
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
@@ -342,12 +398,12 @@ __device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
 // scratch accesses).
 __device__ __forceinline__ void lds_order() { __asm__ __volatile__("" ::: "memory"); }
 
-// Exclusive prefix sum over the wavefront of a count below 64 (bit-sliced
+// Exclusive prefix sum over the wavefront of a count below 8 (bit-sliced
 // ballots); `total` receives the wavefront's sum.
 __device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t& total) {
   uint32_t pre = 0, tot = 0;
 #pragma unroll
-  for (int b = 0; b < 6; ++b) {
+  for (int b = 0; b < 3; ++b) {
     const uint64_t m = __ballot((v >> b) & 1u);
     pre += mbcnt64(m) << b;
     tot += (uint32_t)__popcll(m) << b;
@@ -356,38 +412,263 @@ __device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t& tota
   return pre;
 }
 
+// Exact tests of the pending triangles whose owner is in `done` (all lanes
+// call it); those of other owners stay listed, those that no longer reach
+// their owner's bound are dropped. Returns the new list length.
 template <bool kStats>
-__device__ void coop_unit_round(CoopScratch* W, uint32_t lane, uint32_t nunit) {
-  for (uint32_t u0 = 0; u0 < nunit; u0 += 16) {
-    const uint32_t u = u0 + (lane >> 2), off = lane & 3u;
-    if (u < nunit && off < (uint32_t)W->ucnt[u]) {
-      const uint32_t pk = W->unit[u];
-      const int32_t s = (int32_t)(pk >> 6) + (int32_t)off;
-      const uint32_t o = pk & 63u;
-      const float4 q = W->pt[o];
+__device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane, uint32_t n, uint64_t done,
+                                                  TravCount& cnt) {
+  uint32_t kept = 0;
+  for (uint32_t b = 0; b < n; b += 64) {
+    const bool in = b + lane < n;
+    const uint32_t word = in ? W->pend[b + lane] : 0u;
+    const float l2 = in ? W->pend_l2[b + lane] : INFINITY;
+    const uint32_t o = word & 63u;
+    const float4 q = W->pt[o];
+    const bool live = in && l2 <= keep_bound(__uint_as_float(W->m2[o]), fabsf(q.w));
+    const bool now = live && ((done >> o) & 1ull);
+    const bool later = live && !now;
+    const uint64_t mk = __ballot(later);
+    lds_order();
+    if (later) {  // at most b + lane: never over an entry that is still to be read
+      const uint32_t p = kept + mbcnt64(mk);
+      W->pend[p] = word;
+      W->pend_l2[p] = l2;
+    }
+    kept += (uint32_t)__popcll(mk);
+    if (now) {
+      const int32_t s = (int32_t)(word >> 6);
       const TriRec T = W->tris[o][s];
-      float l1 = 0.0f, l2 = 0.0f, den = 1.0f;
+      const float reject = __uint_as_float((uint32_t)(W->key[o] >> 32));
+      float l1 = 0.0f, lb = 0.0f, den = 1.0f;
       int region = 0;
-      const float d = tri_dist2(q.x, q.y, q.z, T, q.w, l1, l2, den, region);
-      if (kStats) atomicAdd(&W->flops[o], kTriFlops[region & 7]);
-      if (d <= q.w) {
+      const float d = tri_dist2(q.x, q.y, q.z, T, reject, l1, lb, den, region);
+      if (kStats) cnt.flops += kTriFlops[region & 7];
+      if (d <= reject) {
         int32_t orig;
         memcpy(&orig, &T.a.w, 4);
         const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)orig;
         atomicMin(&W->key[o], key);
+        atomicMin(&W->m2[o], __float_as_uint(d));
         lds_order();
         if (W->key[o] == key) {
           W->rec_slot[o] = s;
           W->rec_l1[o] = l1;
-          W->rec_l2[o] = l2;
+          W->rec_l2[o] = lb;
           W->rec_den[o] = den;
         }
       }
     }
     lds_order();
   }
+  return kept;
 }
 
+// FP32 operations of one prefilter test (quick_dist and the two bounds).
+constexpr uint32_t kQuickFlops = 58;
+
+// A lane's traversal: the next node, and the stack with its top entry in
+// registers (tn, tl) and the rest in private memory: a pop takes the
+// registers and starts reading the next entry, which is not needed before
+// the following pop.
+struct LaneTrav {
+  int32_t node, sp, tn, warm;
+  float tl, slack;
+};
+
+// Starts lane `lane`'s search at (x, y, z), warm-start candidate `warm`.
+__device__ __forceinline__ void trav_start(CoopScratch* W, uint32_t lane, LaneTrav& t, const Node4* nodes,
+                                           const QuickTri* quick, const TriRec* tris, float radius, float x, float y,
+                                           float z, int32_t warm) {
+  const float pm = fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z)));
+  // the margins hold for |p| <= 3 R (quick_prepare_kernel); farther points
+  // take the exact test on every triangle
+  const float two_delta = pm <= 1.7f * radius ? 0x1p-20f * radius : -INFINITY;
+  W->pt[lane] = make_float4(x, y, z, two_delta);
+  W->m2[lane] = __float_as_uint(INFINITY);
+  W->key[lane] = ((unsigned long long)__float_as_uint(INFINITY) << 32) | (uint32_t)INT_MAX;
+  W->rec_slot[lane] = -1;
+  W->rec_l1[lane] = 0.0f;
+  W->rec_l2[lane] = 0.0f;
+  W->rec_den[lane] = 1.0f;
+  W->nodes[lane] = nodes;
+  W->quick[lane] = quick;
+  W->tris[lane] = tris;
+  t.node = 0;
+  t.sp = 0;
+  t.tn = -1;
+  t.warm = warm;
+  t.slack = 0x1p-18f * (radius + pm) + 0x1p-20f * radius;
+}
+
+// Answer of a lane whose traversal has ended and whose pending tests are
+// done. Returns false if the exact minimum lies above what the prefilter's
+// bound promised: the search has been set up to run again (t), from then on
+// on exact values.
+__device__ __forceinline__ bool trav_answer(CoopScratch* W, uint32_t lane, LaneTrav& t, Nearest& h) {
+  const unsigned long long k = W->key[lane];
+  h.d2 = __uint_as_float((uint32_t)(k >> 32));
+  h.orig = (int32_t)(uint32_t)k;
+  h.slot = W->rec_slot[lane];
+  h.l1 = W->rec_l1[lane];
+  h.l2 = W->rec_l2[lane];
+  h.den = W->rec_den[lane];
+  const float w = fabsf(W->pt[lane].w);
+  if (h.d2 > keep_bound(__uint_as_float(W->m2[lane]), w)) {
+    W->m2[lane] = __float_as_uint(h.d2);
+    W->pt[lane].w = -w;
+    t.node = 0;
+    t.sp = 0;
+    t.tn = -1;
+    t.warm = h.slot;
+    return false;
+  }
+  return true;
+}
+
+// One node of every lane with `tr` (all lanes of the wavefront call it):
+// four box lower bounds, the triangles of the leaf children within the bound
+// (and a new query's warm-start candidate) through the wavefront's prefilter
+// rounds, then the inner children sorted: the nearest is next, the others
+// are pushed farthest first. Returns false once the lane's traversal ends.
+template <bool kStats>
+__device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr, LaneTrav& t, StackEntry* stk, float px,
+                                          float py, float pz, const Node4* top, int32_t n_lds, int unit_shift,
+                                          uint32_t& npend, TravCount& cnt) {
+  float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
+  int32_t cc[4] = {0, 0, 0, 0};
+  uint32_t nu = 0;
+  uint32_t uw[4] = {~0u, ~0u, ~0u, ~0u};  // leaf children within the bound: unit words
+  if (tr) {
+    const float m2 = __uint_as_float(W->m2[lane]);
+    const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + t.slack;
+    const float thr = s * s * (1.0f + 0x1p-20f);
+    float4 lox, loy, loz, hix, hiy, hiz;
+    int4 ch, ct;
+    if (kStats) {
+      ++cnt.nodes;
+      cnt.flops += 4 * kBoxFlops;
+    }
+    if (t.node < n_lds) {
+      const float4* N = (const float4*)&top[t.node];
+      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
+      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
+    } else {
+      const float4* N = (const float4*)&W->nodes[lane][t.node];
+      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
+      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
+    }
+    const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
+                lz[4] = {loz.x, loz.y, loz.z, loz.w};
+    const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
+                hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
+    const int32_t c4[4] = {ch.x, ch.y, ch.z, ch.w}, n4[4] = {ct.x, ct.y, ct.z, ct.w};
+    nu = t.warm >= 0 ? 1u : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float gx = fmaxf(fmaxf(lx[k] - px, px - hx[k]), 0.0f);
+      const float gy = fmaxf(fmaxf(ly[k] - py, py - hy[k]), 0.0f);
+      const float gz = fmaxf(fmaxf(lz[k] - pz, pz - hz[k]), 0.0f);
+      const float l = gx * gx + gy * gy + gz * gz;
+      // an unused slot has count 0, child < 0 and an empty box
+      if (c4[k] >= 0) {
+        lb[k] = l;
+        cc[k] = c4[k];
+      } else if (l <= thr && n4[k] > 0) {
+        uw[k] = ((uint32_t)(-c4[k] - 1) << 6) | lane;
+        ++nu;
+      }
+    }
+  }
+  bool force = false;
+  if (__ballot(nu > 0) != 0) {
+    uint32_t total;
+    uint32_t pos = wave_prefix_small(nu, total);
+    if (tr && t.warm >= 0) W->unit[pos++] = ((uint32_t)t.warm << 6) | lane;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (uw[k] != ~0u) W->unit[pos++] = uw[k];
+    if (kStats && nu > 0) {
+      cnt.tris += nu << unit_shift;
+      cnt.flops += (nu << unit_shift) * kQuickFlops;
+    }
+    lds_order();
+    const uint32_t upr = 64u >> unit_shift;  // units per round
+    for (uint32_t u0 = 0; u0 < total; u0 += upr) {
+      if (npend > (uint32_t)(kPendCap - 64)) npend = flush_pending<kStats>(W, lane, npend, ~0ull, cnt);
+      const uint32_t u = u0 + (lane >> unit_shift);
+      bool cand = false;
+      uint32_t word = 0;
+      float l2 = 0.0f;
+      if (u < total) {
+        const uint32_t pk = W->unit[u];
+        const uint32_t o = pk & 63u;
+        const uint32_t sl = (pk >> 6) + (lane & ((1u << unit_shift) - 1u));
+        const float4 q = W->pt[o];
+        float d2, m;
+        quick_dist(q.x, q.y, q.z, W->quick[o] + sl, d2, m);
+        if (q.w >= 0.0f) atomicMin(&W->m2[o], __float_as_uint(d2 + m));
+        lds_order();
+        l2 = d2 - m;
+        cand = l2 <= keep_bound(__uint_as_float(W->m2[o]), fabsf(q.w));
+        force |= cand && (m > 1e28f || q.w < 0.0f);
+        word = (sl << 6) | o;
+      }
+      const uint64_t mk = __ballot(cand);
+      if (cand) {
+        const uint32_t p = npend + mbcnt64(mk);
+        W->pend[p] = word;
+        W->pend_l2[p] = l2;
+      }
+      npend += (uint32_t)__popcll(mk);
+      lds_order();
+    }
+    // triangles without an upper value bound nothing until they are tested
+    if (__ballot(force) != 0) npend = flush_pending<kStats>(W, lane, npend, ~0ull, cnt);
+  }
+  if (!tr) return false;
+  t.warm = -1;
+  const float m2 = __uint_as_float(W->m2[lane]);
+  const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + t.slack;
+  const float thr = s * s * (1.0f + 0x1p-20f);
+#define MSK_CX(i, j)                                                        \
+  if (lb[j] < lb[i]) {                                                      \
+    float tl = lb[i]; lb[i] = lb[j]; lb[j] = tl;                            \
+    int32_t tc = cc[i]; cc[i] = cc[j]; cc[j] = tc;                          \
+  }
+  MSK_CX(0, 1) MSK_CX(2, 3) MSK_CX(0, 2) MSK_CX(1, 3) MSK_CX(1, 2)
+#undef MSK_CX
+  // leaf children and unused slots carry lb = inf here; a search without a
+  // finite bound yet (thr = inf) must not take them for inner children
+#pragma unroll
+  for (int k = 3; k >= 1; --k) {
+    if (lb[k] <= thr && lb[k] < INFINITY) {
+      if (t.tn >= 0 && t.sp < kStackDepth) stk[t.sp++] = StackEntry{t.tn, t.tl};
+      t.tn = cc[k];
+      t.tl = lb[k];
+    }
+  }
+  if (lb[0] <= thr && lb[0] < INFINITY) {
+    t.node = cc[0];
+    return true;
+  }
+  while (t.tn >= 0) {
+    const int32_t cand = t.tn;
+    const float cl = t.tl;
+    if (t.sp > 0) {
+      --t.sp;
+      t.tn = stk[t.sp].node;
+      t.tl = stk[t.sp].lb;
+    } else {
+      t.tn = -1;
+    }
+    if (cl <= thr) {
+      t.node = cand;
+      return true;
+    }
+  }
+  return false;
+}
 
 // ------------------------------------------------------ walk machinery
 
@@ -997,9 +1278,13 @@ __device__ unsigned long long g_phase_cycles[16];
 // Streaming form of the persistent kernel: every loop trip advances each
 // traversing lane by one BVH node (its leaf triangles tested by the whole
 // wavefront), so a lane whose query is long does not hold the others: lanes
-// whose query is answered wait until enough of them do (L.regen_min), then
-// finish their step, start the next one or take a new walk together. The
-// walks, their queries and their results are those of the other forms.
+// whose query is answered wait until enough of them do (kStepMin), then
+// finish their step and start the next query together; ended walks and idle
+// lanes wait for the next bookkeeping pass (L.regen_min). At most
+// L.max_owners lanes of a wavefront carry a walk: a launch of few walks
+// spreads them over all wavefronts, whose other lanes help with the triangle
+// tests. The walks, their queries and their results are those of the other
+// forms.
 template <bool kStats, typename AccT, bool kKnn = false>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   extern __shared__ Node4 top[];  // kLdsTop nodes when L.use_lds_top, else none
@@ -1022,6 +1307,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   }
   __syncthreads();
   const uint32_t lane = __lane_id();
+  const bool owner = lane < (uint32_t)L.max_owners;
+  const int unit_shift = L.unit_shift;
   const int qhome = blockIdx.x & 7;
   int qi = 0;  // queues tried so far (uniform)
   uint64_t cur = 0, cend = 0;
@@ -1031,52 +1318,43 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   LaneWalk w;
   w.active = 0;
   w.tab = -1;
-  Nearest hit;
-  hit.d2 = INFINITY;
-  hit.orig = INT_MAX;
-  hit.slot = -1;
-  hit.l1 = hit.l2 = 0.0f;
-  // lane's state: mode 0 no walk, 1 traversing, 2 query answered (hit holds
-  // it), 3 walk ended (hit and fin_status hold its result until the next
-  // bookkeeping pass records it)
-  int32_t mode = 0, node = -1, sp = 0, warm = -1, fin_status = -1;
-  float thr = INFINITY, slack = 0.0f;
+  // lane's state: mode 0 no walk, 1 traversing, 2 traversal ended, 3 walk
+  // ended (its result stays in the wavefront's scratch, fin_status, until the
+  // next bookkeeping pass records it)
+  int32_t mode = 0, fin_status = -1;
+  LaneTrav t;
+  t.node = 0;
+  t.sp = 0;
+  t.tn = -1;
+  t.warm = -1;
+  t.tl = 0.0f;
+  t.slack = 0.0f;
   bool capped = false;
-  // traversal stack: its top entry in registers (tn, tl), the rest in
-  // private memory; a pop takes the registers and starts reading the next
-  // entry, which is not needed before the following pop
   StackEntry stk[kStackDepth];
-  int32_t tn = -1;
-  float tl = 0.0f;
+  uint32_t npend = 0;  // pending exact tests of the wavefront (uniform)
+  TravCount cnt;       // statistics kernels: this lane's share of the work
   bool drained = false;
 #if MSK_PHASE_TIMING
   uint64_t ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #endif
   auto start_query = [&](const MeshDev& M) {
-    hit.d2 = INFINITY;
-    hit.orig = INT_MAX;
-    hit.slot = -1;
-    warm = w.slot;
-    node = 0;
-    sp = 0;
-    tn = -1;
-    thr = INFINITY;
-    slack = 0x1p-18f * (M.radius + fmaxf(fabsf(w.x), fmaxf(fabsf(w.y), fabsf(w.z))));
-    W->nodes[lane] = M.nodes;
-    W->tris[lane] = M.tris;
+    trav_start(W, lane, t, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z, w.slot);
     mode = 1;
   };
   while (true) {
     // ---- bookkeeping, when enough lanes wait or none traverses: ended walks
     // are recorded and idle lanes take new walks
     MSK_TICK(tk0);
-    // ---- steps whose query is answered: finish the step and start the next
-    // one, once kStepMin lanes wait or none traverses; an ended walk waits
-    // for the bookkeeping pass below
+    // ---- steps whose traversal has ended: run their pending exact tests,
+    // finish the step and start the next one, once kStepMin lanes wait (a
+    // quarter of the wavefront's walks if that is less) or none traverses; an
+    // ended walk waits for the bookkeeping pass below
     {
-      const uint64_t pend = __ballot(mode == 2);
-      if (pend != 0 && (__ballot(mode == 1) == 0 || (int)__popcll(pend) >= kStepMin)) {
-        if (mode == 2) {
+      const uint64_t pend = __ballot(mode == 2), trav = __ballot(mode == 1);
+      if (pend != 0 && (trav == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(trav | pend) + 3) >> 2))) {
+        if (npend != 0) npend = flush_pending<kStats>(W, lane, npend, pend, cnt);
+        Nearest hit;
+        if (mode == 2 && trav_answer(W, lane, t, hit)) {
           const MeshDev& M = L.meshes[w.mesh];
           int32_t st = walk_end(M, w, capped, hit);
           if (st < 0) {
@@ -1087,13 +1365,17 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
             fin_status = st;
             mode = 3;
           }
+        } else if (mode == 2) {
+          mode = 1;
         }
       }
     }
     MSK_TICK(tk0b);
     MSK_ACC(5, tk0, tk0b);
     const uint64_t trav = __ballot(mode == 1);
-    if (trav == 0 || (int)__popcll(__ballot(mode == 0 || mode == 3)) >= L.regen_min) {
+    // (once the queues are empty there is nothing to hand out: ended walks
+    // then wait for the last one)
+    if (trav == 0 || (!drained && (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min)) {
 #if MSK_PHASE_TIMING
       ph[7] += 1;
 #endif
@@ -1101,6 +1383,14 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
       int32_t fin_tab = -1;
       if (mode == 3) {
         const MeshDev& M = L.meshes[w.mesh];
+        Nearest hit;
+        const unsigned long long k = W->key[lane];
+        hit.d2 = __uint_as_float((uint32_t)(k >> 32));
+        hit.orig = (int32_t)(uint32_t)k;
+        hit.slot = W->rec_slot[lane];
+        hit.l1 = W->rec_l1[lane];
+        hit.l2 = W->rec_l2[lane];
+        hit.den = W->rec_den[lane];
         if (w.tab >= 0)
           walk_finish_table<AccT, kKnn>(L, M, w, fin_status, hit, T, wi);
         else
@@ -1111,17 +1401,17 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         w.tab = -1;
         mode = 0;
       }
-      for (int t = 0; t < 2; ++t) {
-        t_out[t] -= (int32_t)__popcll(__ballot(fin && fin_tab == t));
+      for (int t2 = 0; t2 < 2; ++t2) {
+        t_out[t2] -= (int32_t)__popcll(__ballot(fin && fin_tab == t2));
         // flush once the table's walks are done and its chunk hands out no more
-        if (t_used[t] && t_out[t] == 0 && !(t == c_tab && cur < cend)) {
-          table_flush(L, T, wi, t, t_mesh[t], t_row[t]);
-          t_used[t] = 0;
-          if (c_tab == t) c_tab = -1;
+        if (t_used[t2] && t_out[t2] == 0 && !(t2 == c_tab && cur < cend)) {
+          table_flush(L, T, wi, t2, t_mesh[t2], t_row[t2]);
+          t_used[t2] = 0;
+          if (c_tab == t2) c_tab = -1;
         }
       }
       // refill idle lanes from the queue chunks
-      uint64_t idle = __ballot(!w.active);
+      uint64_t idle = __ballot(owner && !w.active);
       while (idle != 0 && !drained) {
         if (cur >= cend) {
           uint64_t start = 0;
@@ -1144,15 +1434,15 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           c_mesh = rs.mesh;
           c_row = rs.row;
           c_tab = -1;
-          for (int t = 0; t < 2; ++t)
-            if (t_used[t] && t_mesh[t] == c_mesh && t_row[t] == c_row) c_tab = t;
+          for (int t2 = 0; t2 < 2; ++t2)
+            if (t_used[t2] && t_mesh[t2] == c_mesh && t_row[t2] == c_row) c_tab = t2;
           if (c_tab < 0) {
-            for (int t = 0; t < 2; ++t)
-              if (!t_used[t] && c_tab < 0) {
-                c_tab = t;
-                t_used[t] = 1;
-                t_mesh[t] = c_mesh;
-                t_row[t] = c_row;
+            for (int t2 = 0; t2 < 2; ++t2)
+              if (!t_used[t2] && c_tab < 0) {
+                c_tab = t2;
+                t_used[t2] = 1;
+                t_mesh[t2] = c_mesh;
+                t_row[t2] = c_row;
               }
           }
         }
@@ -1160,7 +1450,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         const uint64_t avail = cend - cur;
         const uint32_t take = (uint32_t)min(avail, (uint64_t)__popcll(idle));
         bool fresh = false;
-        if (!w.active && rank < take) {
+        if (owner && !w.active && rank < take) {
           decode_walk(L, cur + rank, w);
           int32_t face;
           double lam[3];
@@ -1173,6 +1463,11 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
               start_query(M);
               fresh = w.tab >= 0;
             } else {  // left the bounding sphere at once and escaped
+              Nearest hit;
+              hit.d2 = INFINITY;
+              hit.orig = INT_MAX;
+              hit.slot = -1;
+              hit.l1 = hit.l2 = 0.0f;
               if (w.tab >= 0)
                 walk_finish_table<AccT, kKnn>(L, M, w, s0, hit, T, wi);
               else
@@ -1184,15 +1479,15 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         }
         if (c_tab >= 0) t_out[c_tab] += (int32_t)__popcll(__ballot(fresh));
         cur += take;
-        idle = __ballot(!w.active);
+        idle = __ballot(owner && !w.active);
         // lanes whose row was discarded, or whose walk ended at once, stay idle
       }
       if (__ballot(w.active) == 0) {
         if (drained) {
-          for (int t = 0; t < 2; ++t)
-            if (t_used[t]) {
-              table_flush(L, T, wi, t, t_mesh[t], t_row[t]);
-              t_used[t] = 0;
+          for (int t2 = 0; t2 < 2; ++t2)
+            if (t_used[t2]) {
+              table_flush(L, T, wi, t2, t_mesh[t2], t_row[t2]);
+              t_used[t2] = 0;
             }
           break;
         }
@@ -1207,156 +1502,16 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
 #endif
     // ---- one node of every traversing lane
     const bool tr = mode == 1;
-    float lb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int32_t cc[4] = {-1, -1, -1, -1}, cn[4] = {0, 0, 0, 0};
-    if (tr) {
-      const int32_t nl = w.mesh == 0 ? n_lds : 0;
-      float4 lox, loy, loz, hix, hiy, hiz;
-      int4 ch, ct;
-      if (kStats) {
-        ++w.cnt.nodes;
-        w.cnt.flops += 4 * kBoxFlops;
-      }
-      if (node < nl) {
-        const float4* N = (const float4*)&top[node];
-        lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-        ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-      } else {
-        const float4* N = (const float4*)&W->nodes[lane][node];
-        lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-        ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-      }
-      const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
-                  lz[4] = {loz.x, loz.y, loz.z, loz.w};
-      const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
-                  hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
-      const int32_t c4[4] = {ch.x, ch.y, ch.z, ch.w}, n4[4] = {ct.x, ct.y, ct.z, ct.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float gx = fmaxf(fmaxf(lx[k] - w.x, w.x - hx[k]), 0.0f);
-        const float gy = fmaxf(fmaxf(ly[k] - w.y, w.y - hy[k]), 0.0f);
-        const float gz = fmaxf(fmaxf(lz[k] - w.z, w.z - hz[k]), 0.0f);
-        lb[k] = gx * gx + gy * gy + gz * gz;
-        cc[k] = c4[k];
-        cn[k] = n4[k];
-      }
-#define MSK_CX(i, j)                                                        \
-  if (lb[j] < lb[i]) {                                                      \
-    float tl = lb[i]; lb[i] = lb[j]; lb[j] = tl;                            \
-    int32_t tc = cc[i]; cc[i] = cc[j]; cc[j] = tc;                          \
-    int32_t tn = cn[i]; cn[i] = cn[j]; cn[j] = tn;                          \
-  }
-      MSK_CX(0, 1) MSK_CX(2, 3) MSK_CX(0, 2) MSK_CX(1, 3) MSK_CX(1, 2)
-#undef MSK_CX
-    }
-    MSK_TICK(tk2);
-    MSK_ACC(1, tk1, tk2);
-    // this lane's triangles: the warm-start candidate of a new query, then
-    // the leaf children within the bound
-    const int32_t hw = (tr && warm >= 0) ? 1 : 0;
-    int32_t nl4[4], tot = hw;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      nl4[k] = (tr && cc[k] < 0 && cn[k] > 0 && lb[k] <= thr) ? cn[k] : 0;
-      tot += nl4[k];
-    }
-    if (__ballot(tot > 0) != 0) {
-      W->pt[lane] = make_float4(w.x, w.y, w.z, hit.d2);
-      W->key[lane] = ((unsigned long long)__float_as_uint(hit.d2) << 32) | (uint32_t)hit.orig;
-      if (kStats) W->flops[lane] = 0;
-      // lay the units out by a prefix sum over the lanes, in windows of kCoopUnits
-      int32_t nu = hw;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) nu += (nl4[k] + 3) >> 2;
-      uint32_t total;
-      const uint32_t pre = wave_prefix_small((uint32_t)nu, total);
-      for (uint32_t w0 = 0; w0 < total; w0 += (uint32_t)kCoopUnits) {
-        const uint32_t w1 = w0 + (uint32_t)kCoopUnits;
-        if (nu > 0 && pre < w1 && pre + (uint32_t)nu > w0) {
-          uint32_t pos = pre;
-          auto put = [&](uint32_t first, uint32_t cnt) {
-            if (pos >= w0 && pos < w1) {
-              W->unit[pos - w0] = (first << 6) | lane;
-              W->ucnt[pos - w0] = (uint8_t)cnt;
-            }
-            ++pos;
-          };
-          if (hw) put((uint32_t)warm, 1u);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            uint32_t first = (uint32_t)(-cc[k] - 1);
-            for (int32_t c = nl4[k]; c > 0; c -= 4, first += 4) put(first, (uint32_t)min(c, 4));
-          }
-        }
-        lds_order();
-        MSK_TICK(tr0);
-        coop_unit_round<kStats>(W, lane, min(total - w0, (uint32_t)kCoopUnits));
-        MSK_TICK(tr1);
-        MSK_ACC(3, tr0, tr1);
-      }
-      if (tot > 0) {
-        if (kStats) {
-          w.cnt.tris += (uint32_t)tot;
-          w.cnt.flops += W->flops[lane];
-        }
-        const unsigned long long k2 = W->key[lane];
-        const float d = __uint_as_float((uint32_t)(k2 >> 32));
-        const int32_t orig = (int32_t)(uint32_t)k2;
-        if (d < hit.d2 || (d == hit.d2 && orig < hit.orig)) {
-          hit.d2 = d;
-          hit.orig = orig;
-          hit.slot = W->rec_slot[lane];
-          hit.l1 = W->rec_l1[lane];
-          hit.l2 = W->rec_l2[lane];
-          hit.den = W->rec_den[lane];
-          thr = prune_bound(hit.d2, slack);
-        }
-      }
-    }
-    MSK_TICK(tk3);
-    MSK_ACC(2, tk2, tk3);
-    if (tr) {
-      warm = -1;
-      // the nearest surviving inner child is next; the others are pushed
-      // farthest first; the query is answered when the stack runs out
-      int32_t next = -1;
-      float next_lb = 0.0f;
-#pragma unroll
-      for (int k = 3; k >= 0; --k) {
-        if (cc[k] >= 0 && lb[k] <= thr) {
-          if (next >= 0) {  // push the farther candidate
-            if (tn >= 0 && sp < kStackDepth) stk[sp++] = StackEntry{tn, tl};
-            tn = next;
-            tl = next_lb;
-          }
-          next = cc[k];
-          next_lb = lb[k];
-        }
-      }
-      if (next >= 0) {
-        node = next;
-      } else {
-        node = -1;
-        while (tn >= 0) {
-          const int32_t cand = tn;
-          const float cl = tl;
-          if (sp > 0) {
-            --sp;
-            tn = stk[sp].node;
-            tl = stk[sp].lb;
-          } else {
-            tn = -1;
-          }
-          if (cl <= thr) {
-            node = cand;
-            break;
-          }
-        }
-        if (node < 0) mode = 2;  // query answered
-      }
-    }
+    const bool more = trav_trip<kStats>(W, lane, tr, t, stk, w.x, w.y, w.z, top, w.mesh == 0 ? n_lds : 0, unit_shift,
+                                        npend, cnt);
+    if (tr && !more) mode = 2;
     MSK_TICK(tk4);
-    MSK_ACC(4, tk3, tk4);
+    MSK_ACC(1, tk1, tk4);
+  }
+  if (kStats && L.stats) {
+    atomicAdd(L.stats, (unsigned long long)cnt.nodes);
+    atomicAdd(L.stats + 1, (unsigned long long)cnt.tris);
+    atomicAdd(L.stats + 2, (unsigned long long)cnt.flops);
   }
 #if MSK_PHASE_TIMING
   if (lane == 0)
@@ -1533,21 +1688,135 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
   }
 }
 
-__global__ void closest_points_kernel(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris, float radius,
-                                      double cx, double cy, double cz, const float* __restrict__ Q, int64_t nq,
-                                      int32_t* tri, float* d2, float* bary) {
+// Prefilter records (QuickTri) of a mesh. With u = 2^-24, w = |p - a|, L the
+// longest edge and |p| <= 3 R (so w <= 4 R):
+//   * quick_dist's own error: p - a, the frame, the in-plane coordinates and
+//     the edge terms are off by at most about 12 u (w + L) in distance, so its
+//     squared value by 24 u (w + L)^2;
+//   * tri_dist2's face value (n.ap)^2 / (n.n): n = ab x ac is off by 5 u |ab|
+//     |ac| = 5 u |n| / sin(angle), n.ap by 4 u |n| w more: u w^2 (20 / sin + 16)
+//     in the square; a region taken wrongly near an edge moves the foot by at
+//     most 24 u w^2 over the smallest altitude, whose square is at most w^2
+//     (4 R)^2 (24 u / altitude)^2;
+//   * its edge and vertex values add roundings at the size of the coordinates,
+//     delta = 2^-21 R in distance, which keep_bound carries.
+// Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2). A triangle
+// whose smallest angle has sin < 0.01, or whose F is large, gets margins that
+// send every test of it to the exact one.
+__global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, double radius,
+                                     QuickTri* __restrict__ quick) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nq) return;
-  const float x = (float)((double)Q[3 * i] - cx);
-  const float y = (float)((double)Q[3 * i + 1] - cy);
-  const float z = (float)((double)Q[3 * i + 2] - cz);
-  Nearest h;
-  h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
+  if (i >= n + kQuickPad) return;
+  QuickTri q;
+  if (i >= n) {  // a pad's d2 - m is NaN and its d2 + m no minimum
+    q.r[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+    for (int k = 1; k < 5; ++k) q.r[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    quick[i] = q;
+    return;
+  }
+  const TriRec T = tris[i];
+  const double abx = (double)T.b.x - T.a.x, aby = (double)T.b.y - T.a.y, abz = (double)T.b.z - T.a.z;
+  const double acx = (double)T.c.x - T.a.x, acy = (double)T.c.y - T.a.y, acz = (double)T.c.z - T.a.z;
+  const double bcx = acx - abx, bcy = acy - aby, bcz = acz - abz;
+  const double nx = aby * acz - abz * acy, ny = abz * acx - abx * acz, nz = abx * acy - aby * acx;
+  const double ab = sqrt(abx * abx + aby * aby + abz * abz), ac = sqrt(acx * acx + acy * acy + acz * acz);
+  const double bc = sqrt(bcx * bcx + bcy * bcy + bcz * bcz), nn = sqrt(nx * nx + ny * ny + nz * nz);
+  const double lmax = fmax(ab, fmax(ac, bc)), prod = ab * ac * bc;
+  const double smin = nn * fmin(ab, fmin(ac, bc)) / prod;  // sin of the smallest angle
+  const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
+  const double F = u * (128.0 + 64.0 / smin) + far * far;
+  if (!(smin >= 0.01) || !(F <= 0.01)) {
+    q.r[0] = make_float4(T.a.x, T.a.y, T.a.z, 0.0f);
+    for (int k = 1; k < 4; ++k) q.r[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    q.r[4] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
+    quick[i] = q;
+    return;
+  }
+  const double ux = abx / ab, uy = aby / ab, uz = abz / ab;
+  const double mx = nx / nn, my = ny / nn, mz = nz / nn;
+  const double vx = my * uz - mz * uy, vy = mz * ux - mx * uz, vz = mx * uy - my * ux;
+  const double cx = acx * ux + acy * uy + acz * uz, cy = acx * vx + acy * vy + acz * vz;
+  q.r[0] = make_float4(T.a.x, T.a.y, T.a.z, (float)(cx / ac));
+  q.r[1] = make_float4((float)ux, (float)uy, (float)uz, (float)(cy / ac));
+  q.r[2] = make_float4((float)vx, (float)vy, (float)vz, (float)ac);
+  q.r[3] = make_float4((float)mx, (float)my, (float)mz, (float)((cx - ab) / bc));
+  q.r[4] = make_float4((float)(cy / bc), (float)bc, (float)F, (float)(F * lmax * lmax));
+  quick[i] = q;
+}
+
+// Closest points of nq queries, on the walk kernel's traversal: lanes with an
+// answered query wait until a quarter of the wavefront's queries do, then
+// write their answers and take the next queries together. At most 2^own_shift
+// lanes of a wavefront carry a query: a small call spreads over all
+// wavefronts, whose other lanes help with the triangle tests. Block k of
+// wavefront g holds the queries from ((k G + g) << own_shift) on, G the
+// number of wavefronts.
+__global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
+    query_stream_kernel(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris,
+                        const QuickTri* __restrict__ quick, float radius, double cx, double cy, double cz,
+                        const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t unit_shift,
+                        int32_t* __restrict__ tri, float* __restrict__ d2, float* __restrict__ bary) {
+  __shared__ CoopScratch coop[kWaves];
+  const int wi = threadIdx.x >> 6;
+  CoopScratch* W = &coop[wi];
+  const uint32_t lane = __lane_id();
+  const int64_t G = (int64_t)gridDim.x * kWaves, g = (int64_t)blockIdx.x * kWaves + wi;
+  const bool owner = lane < (1u << own_shift);
+  int64_t next = 0;  // queries handed out (uniform)
+  bool drained = false;
+  int32_t mode = 0;  // 0 idle, 1 traversing, 2 traversal ended
+  int64_t qi = 0;
+  float x = 0.0f, y = 0.0f, z = 0.0f;
+  LaneTrav t;
+  t.node = 0;
+  t.sp = 0;
+  t.tn = -1;
+  t.warm = -1;
+  t.tl = 0.0f;
+  t.slack = 0.0f;
+  StackEntry stk[kStackDepth];
+  uint32_t npend = 0;
   TravCount cnt;
-  bvh_nearest<false>(nodes, tris, nullptr, 0, x, y, z, radius, h, cnt);
-  tri[i] = h.orig;
-  d2[i] = h.d2;
-  nearest_bary(h, bary[2 * i], bary[2 * i + 1]);
+  while (true) {
+    const uint64_t pend = __ballot(mode == 2), trav = __ballot(mode == 1);
+    if (trav == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(trav | pend) + 3) >> 2)) {
+      if (npend != 0) npend = flush_pending<false>(W, lane, npend, pend, cnt);
+      if (mode == 2) {
+        Nearest h;
+        mode = 1;
+        if (trav_answer(W, lane, t, h)) {
+          tri[qi] = h.orig;
+          d2[qi] = h.d2;
+          nearest_bary(h, bary[2 * qi], bary[2 * qi + 1]);
+          mode = 0;
+        }
+      }
+      const uint64_t idle = __ballot(mode == 0 && owner);
+      if (!drained && idle != 0) {
+        const int64_t pos = next + mbcnt64(idle);
+        const int64_t q = ((((pos >> own_shift) * G) + g) << own_shift) + (pos & ((1ll << own_shift) - 1));
+        const bool take = mode == 0 && owner && q < nq;
+        if (take) {
+          qi = q;
+          x = (float)((double)Q[3 * qi] - cx);
+          y = (float)((double)Q[3 * qi + 1] - cy);
+          z = (float)((double)Q[3 * qi + 2] - cz);
+          trav_start(W, lane, t, nodes, quick, tris, radius, x, y, z, -1);
+          mode = 1;
+        }
+        const uint32_t got = (uint32_t)__popcll(__ballot(take));
+        drained = got < (uint32_t)__popcll(idle);
+        next += got;
+      }
+      if (__ballot(mode == 1) == 0) {
+        if (drained) break;
+        continue;
+      }
+    }
+    const bool tr = mode == 1;
+    const bool more = trav_trip<false>(W, lane, tr, t, stk, x, y, z, nullptr, 0, unit_shift, npend, cnt);
+    if (tr && !more) mode = 2;
+  }
 }
 
 // S_ij = (w_i / h) mean_ij, se_ij = (w_i / h) sqrt(var_ij / W_i), var with
@@ -1766,12 +2035,24 @@ hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, in
   return hipGetLastError();
 }
 
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, float radius, const double* c, const float* Q,
-                                 int64_t nq, int32_t* tri, float* d2, float* bary, hipStream_t s) {
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, QuickTri* quick, hipStream_t s) {
+  hipLaunchKernelGGL(quick_prepare_kernel, dim3((unsigned)((n + kQuickPad + 255) / 256)), dim3(256), 0, s, tris, n,
+                     radius, quick);
+  return hipGetLastError();
+}
+
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const QuickTri* quick, int32_t leaf,
+                                 float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
+                                 float* d2, float* bary, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
-  if ((nq + 127) / 128 > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(closest_points_kernel, dim3((unsigned)((nq + 127) / 128)), dim3(128), 0, s, nodes, tris, radius,
-                     c[0], c[1], c[2], Q, nq, tri, d2, bary);
+  // as many wavefronts as are resident at once (4 per SIMD), each with as few
+  // queries at a time as still covers nq, up to one per lane
+  const int64_t waves = 16ll * n_cu;
+  int own_shift = 0;
+  while (own_shift < 6 && (waves << own_shift) < nq) ++own_shift;
+  const int64_t blocks = std::min<int64_t>(4ll * n_cu, (((nq - 1) >> own_shift) / kWaves) + 1);
+  hipLaunchKernelGGL(query_stream_kernel, dim3((unsigned)blocks), dim3(256), 0, s, nodes, tris, quick, radius, c[0],
+                     c[1], c[2], Q, nq, own_shift, leaf <= 4 ? 2 : 3, tri, d2, bary);
   return hipGetLastError();
 }
 

@@ -320,4 +320,28 @@ std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t
   return "";
 }
 
+void align_leaves(HostBvh& b) {
+  const int32_t align = b.leaf_size <= 4 ? 4 : 8;
+  TriRec pad;
+  pad.a = pad.b = pad.c = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int32_t pad_index = kPadTri;
+  std::memcpy(&pad.a.w, &pad_index, 4);
+  std::vector<TriRec> tris;
+  tris.reserve(b.tris.size() * 3 / 2 + 8);
+  for (Node4& w : b.nodes)
+    for (int k = 0; k < 4; ++k) {
+      if (w.child[k] >= 0 || w.count[k] == 0) continue;
+      const int32_t first = -w.child[k] - 1;
+      w.child[k] = -(int32_t)tris.size() - 1;
+      for (int32_t i = first; i < first + w.count[k]; ++i) {
+        int32_t t;
+        std::memcpy(&t, &b.tris[i].a.w, 4);
+        b.slot_of_tri[t] = (int32_t)tris.size();
+        tris.push_back(b.tris[i]);
+      }
+      while (tris.size() % align) tris.push_back(pad);
+    }
+  b.tris.swap(tris);
+}
+
 }  // namespace msk

@@ -35,7 +35,7 @@ struct msk_mesh {
   int depth = 0, leaf_size = 4, top_nodes = 85;
   Node4* d_nodes = nullptr;
   TriRec* d_tris = nullptr;
-  QuickTri* d_quick = nullptr;
+  float4* d_quick = nullptr;  // prefilter records
   int32_t* d_slot = nullptr;
   int32_t* d_faces = nullptr;
   std::vector<float> vrel;       // float offsets from the centre (host copy)
@@ -139,11 +139,11 @@ void dfree(T*& p) {
   p = nullptr;
 }
 
-// The prefilter records of n triangles, complete when it returns (a mesh may
-// be used from other streams afterwards).
-hipError_t make_quick(msk_ctx* ctx, const TriRec* tris, int64_t n, double radius, QuickTri** out) {
-  hipError_t e = dalloc(out, (size_t)n + kQuickPad);
-  if (e == hipSuccess) e = launch_quick_prepare(tris, n, radius, *out, ctx->stream);
+// The prefilter records of n triangle slots, complete when it returns (a mesh
+// may be used from other streams afterwards).
+hipError_t make_quick(msk_ctx* ctx, const TriRec* tris, size_t n, double radius, float4** out) {
+  hipError_t e = dalloc(out, 5 * (n + kQuickPad));
+  if (e == hipSuccess) e = launch_quick_prepare(tris, (int64_t)n, radius, *out, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   return e;
 }
@@ -226,6 +226,7 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   HostBvh B;
   std::string e = build_bvh_host(V, n_verts, F, n_tris, leaf, B);
   if (!e.empty()) return fail(ctx, MSK_ERR_INVALID_ARG, e);
+  align_leaves(B);
   msk_mesh* m = new msk_mesh();
   m->ctx = ctx;
   std::memcpy(m->centre, B.centre, sizeof(m->centre));
@@ -247,7 +248,7 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
       (he = upload(ctx, &m->d_tris, B.tris.data(), B.tris.size())) != hipSuccess ||
       (he = upload(ctx, &m->d_slot, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
       (he = upload(ctx, &m->d_faces, F, (size_t)n_tris * 3)) != hipSuccess ||
-      (he = make_quick(ctx, m->d_tris, n_tris, m->radius, &m->d_quick)) != hipSuccess) {
+      (he = make_quick(ctx, m->d_tris, B.tris.size(), m->radius, &m->d_quick)) != hipSuccess) {
     msk_mesh_destroy(m);
     return fail(ctx, he == hipErrorOutOfMemory ? MSK_ERR_OOM : MSK_ERR_DEVICE,
                 std::string("mesh upload: ") + hipGetErrorString(he));
@@ -2287,15 +2288,16 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   HostBvh B;
   std::string e = build_bvh_host(m->vworld.data(), m->nv, m->faces.data(), m->nf, leaf, B);
   if (!e.empty()) return fail(ctx, MSK_ERR_INVALID_ARG, e);
+  align_leaves(B);
   Node4* dn = nullptr;
   TriRec* dt = nullptr;
   int32_t* ds = nullptr;
-  QuickTri* dq = nullptr;
+  float4* dq = nullptr;
   hipError_t he;
   if ((he = upload(ctx, &dn, B.nodes.data(), B.nodes.size())) != hipSuccess ||
       (he = upload(ctx, &dt, B.tris.data(), B.tris.size())) != hipSuccess ||
       (he = upload(ctx, &ds, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
-      (he = make_quick(ctx, dt, m->nf, m->radius, &dq)) != hipSuccess) {
+      (he = make_quick(ctx, dt, B.tris.size(), m->radius, &dq)) != hipSuccess) {
     dfree(dn);
     dfree(dt);
     dfree(ds);

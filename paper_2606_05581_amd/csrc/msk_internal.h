@@ -27,16 +27,21 @@ struct alignas(16) TriRec {
 };
 static_assert(sizeof(TriRec) == 48, "triangle record must be 48 bytes");
 
-// Prefilter record of a triangle, in slot order (kQuickPad records that no
-// query accepts follow the last): the triangle in its own frame and the
-// margins of the squared distance computed from it (quick_prepare_kernel).
-// r0 = vertex a, c1; r1 = x axis (along ab), s1; r2 = y axis (towards c), l1;
-// r3 = normal, c2; r4 = s2, l2, F, G: unit directions (c1, s1) of ac and (c2,
-// s2) of bc in the plane, their lengths l1 and l2, margin F |p - a|^2 + G.
-struct alignas(16) QuickTri {
-  float4 r[5];
-};
+// A slot past the end of a leaf holds a record with this index; no query
+// accepts it.
+constexpr int32_t kPadTri = -1;
+
+// Prefilter record of a triangle (quick_prepare_kernel): the triangle in its
+// own frame and the margins of the squared distance computed from it, as five
+// float4: vertex a, c1; x axis (along ab), s1; y axis (towards c), l1; normal,
+// c2; s2, l2, F, G. (c1, s1) and (c2, s2) are the unit directions of ac and bc
+// in the plane, l1 and l2 their lengths; the margin is F |p - a|^2 + G.
+// Records lie in blocks of 4 slots, field by field (20 float4 a block: field j
+// of slot s is float4 4 j + s % 4 of block s / 4), so that the 4 lanes of a
+// unit read 64 contiguous bytes per field. kQuickPad pad records follow the
+// last slot.
 constexpr int kQuickPad = 8;
+__host__ __device__ inline int64_t quick_index(int64_t slot) { return (slot >> 2) * 20 + (slot & 3); }
 
 constexpr int kStackDepth = 64;     // traversal stack entries per lane
 constexpr int kMaxTableNnz = 32;    // basis entries per vertex
@@ -57,6 +62,12 @@ struct HostBvh {
 // Builds the scene frame and a 4-wide BVH over float offsets from the
 // centre. Returns an empty string on success, else an error message.
 std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t nf, int leaf_size, HostBvh& out);
+
+// Moves the triangles so that every leaf starts at a slot that is a multiple
+// of 4 (8 for leaves wider than 4), pads (kPadTri) filling the slots past a
+// shorter leaf: a leaf's prefilter records, which lie in blocks of 4 slots,
+// then fill whole cache lines.
+void align_leaves(HostBvh& b);
 
 // The same binned-SAH build and 4-wide collapse over any elements given by
 // their boxes and centroids (n x 3 floats): the nodes in breadth-first order
@@ -93,7 +104,7 @@ struct KnnDev {
 struct MeshDev {
   const Node4* nodes;
   const TriRec* tris;
-  const QuickTri* quick;
+  const float4* quick;         // prefilter records
   const int32_t* slot_of_tri;  // original face -> slot
   const int32_t* faces;        // original faces (n_tris x 3)
   int64_t n_tris;
@@ -212,9 +223,9 @@ hipError_t launch_discard_batch(const MeshDev* meshes, const RowRange* ranges, i
 hipError_t launch_row_totals(const RowCounters* sets, int32_t n_sets, unsigned long long* out, hipStream_t s);
 hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, const float* Nq, int64_t n, int32_t* idx,
                            float* w, hipStream_t s);
-// quick: n + kQuickPad records
-hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, QuickTri* quick, hipStream_t s);
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const QuickTri* quick, int32_t leaf,
+// n slots (a multiple of 4); quick: 5 (n + kQuickPad) float4
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, float4* quick, hipStream_t s);
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t leaf,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s);
 hipError_t launch_finalize(const MeshDev& M, int64_t n_rows, const int64_t* walks, const double* w, double* S,

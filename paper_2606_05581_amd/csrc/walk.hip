@@ -318,9 +318,9 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
 // covering the exact test's roundings at the size of the coordinates. The
 // frame and margins are prepared by quick_prepare_kernel, whose comment
 // derives them.
-__device__ __forceinline__ void quick_dist(float px, float py, float pz, const QuickTri* __restrict__ T, float& d2,
+__device__ __forceinline__ void quick_dist(float px, float py, float pz, const float4* __restrict__ T, float& d2,
                                            float& m) {
-  const float4 r0 = T->r[0], r1 = T->r[1], r2 = T->r[2], r3 = T->r[3], r4 = T->r[4];
+  const float4 r0 = T[0], r1 = T[4], r2 = T[8], r3 = T[12], r4 = T[16];
   const float gx = px - r0.x, gy = py - r0.y, gz = pz - r0.z;
   const float x = r1.x * gx + r1.y * gy + r1.z * gz;
   const float y = r2.x * gx + r2.y * gy + r2.z * gz;
@@ -352,10 +352,11 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
 // nodes, but the triangles of the leaves it reaches are listed in LDS and
 // tested 64 at a time by the whole wavefront. Work is listed in units of
 // 2^unit_shift (4 or 8, at least the leaf width) consecutive triangle slots of
-// one owner, one lane each (one word: first slot << 6 | owner lane, so meshes
-// have fewer than 2^26 triangles); the lanes past a shorter leaf test the
-// following slots, which cannot change a minimum over the mesh, so a unit
-// needs no count.
+// one owner, one lane each (one word: first slot / 4 << 6 | owner lane; leaves
+// start at multiples of 4 slots and hold at least one triangle, so meshes have
+// fewer than 2^26 triangles). The lanes past a shorter leaf meet pads, or
+// triangles of the next leaf, which cannot change a minimum over the mesh: a
+// unit needs no count.
 //
 // A listed triangle takes the prefilter only. Its upper value d2 + m lowers
 // the owner's bound m2 through an LDS minimum; if its lower value d2 - m still
@@ -375,9 +376,9 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
 constexpr int kUnitCap = 64 * 5;  // per lane four leaf children and a warm-start candidate
 constexpr int kPendCap = 128;
 struct CoopScratch {
-  uint32_t unit[kUnitCap];
+  uint32_t unit[kUnitCap];    // block << 6 | owner lane
   float4 pt[64];             // owner's query point; w = 2 delta, negative: m2 lowered by exact values only
-  const QuickTri* quick[64];  // owner's arrays (batched meshes differ per lane)
+  const float4* quick[64];    // owner's arrays (batched meshes differ per lane)
   const TriRec* tris[64];
   const Node4* nodes[64];
   uint32_t m2[64];           // bound on the owner's squared distance (float bits)
@@ -437,7 +438,7 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
     }
     kept += (uint32_t)__popcll(mk);
     if (now) {
-      const int32_t s = (int32_t)(word >> 6);
+      const int32_t s = (int32_t)(word >> 6 << 2 | (__float_as_uint(l2) & 3u));
       const TriRec T = W->tris[o][s];
       const float reject = __uint_as_float((uint32_t)(W->key[o] >> 32));
       float l1 = 0.0f, lb = 0.0f, den = 1.0f;
@@ -478,7 +479,7 @@ struct LaneTrav {
 
 // Starts lane `lane`'s search at (x, y, z), warm-start candidate `warm`.
 __device__ __forceinline__ void trav_start(CoopScratch* W, uint32_t lane, LaneTrav& t, const Node4* nodes,
-                                           const QuickTri* quick, const TriRec* tris, float radius, float x, float y,
+                                           const float4* quick, const TriRec* tris, float radius, float x, float y,
                                            float z, int32_t warm) {
   const float pm = fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z)));
   // the margins hold for |p| <= 3 R (quick_prepare_kernel); farther points
@@ -575,7 +576,7 @@ __device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr
         lb[k] = l;
         cc[k] = c4[k];
       } else if (l <= thr && n4[k] > 0) {
-        uw[k] = ((uint32_t)(-c4[k] - 1) << 6) | lane;
+        uw[k] = ((uint32_t)(-c4[k] - 1) >> 2 << 6) | lane;
         ++nu;
       }
     }
@@ -584,7 +585,7 @@ __device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr
   if (__ballot(nu > 0) != 0) {
     uint32_t total;
     uint32_t pos = wave_prefix_small(nu, total);
-    if (tr && t.warm >= 0) W->unit[pos++] = ((uint32_t)t.warm << 6) | lane;
+    if (tr && t.warm >= 0) W->unit[pos++] = ((uint32_t)t.warm >> 2 << 6) | lane;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (uw[k] != ~0u) W->unit[pos++] = uw[k];
@@ -603,16 +604,18 @@ __device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr
       if (u < total) {
         const uint32_t pk = W->unit[u];
         const uint32_t o = pk & 63u;
-        const uint32_t sl = (pk >> 6) + (lane & ((1u << unit_shift) - 1u));
+        const uint32_t bl = (pk >> 6) + ((lane & ((1u << unit_shift) - 1u)) >> 2);
         const float4 q = W->pt[o];
         float d2, m;
-        quick_dist(q.x, q.y, q.z, W->quick[o] + sl, d2, m);
+        quick_dist(q.x, q.y, q.z, W->quick[o] + (uint64_t)bl * 20u + (lane & 3u), d2, m);
         if (q.w >= 0.0f) atomicMin(&W->m2[o], __float_as_uint(d2 + m));
         lds_order();
         l2 = d2 - m;
         cand = l2 <= keep_bound(__uint_as_float(W->m2[o]), fabsf(q.w));
         force |= cand && (m > 1e28f || q.w < 0.0f);
-        word = (sl << 6) | o;
+        word = (bl << 6) | o;
+        // the slot within its block goes into the low bits of the lower value
+        l2 = __uint_as_float((__float_as_uint(l2 - fabsf(l2) * 0x1p-20f) & ~3u) | (lane & 3u));
       }
       const uint64_t mk = __ballot(cand);
       if (cand) {
@@ -1688,7 +1691,7 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
   }
 }
 
-// Prefilter records (QuickTri) of a mesh. With u = 2^-24, w = |p - a|, L the
+// Prefilter records of a mesh. With u = 2^-24, w = |p - a|, L the
 // longest edge and |p| <= 3 R (so w <= 4 R):
 //   * quick_dist's own error: p - a, the frame, the in-plane coordinates and
 //     the edge terms are off by at most about 12 u (w + L) in distance, so its
@@ -1704,17 +1707,21 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
 // whose smallest angle has sin < 0.01, or whose F is large, gets margins that
 // send every test of it to the exact one.
 __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, double radius,
-                                     QuickTri* __restrict__ quick) {
+                                     float4* __restrict__ quick) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n + kQuickPad) return;
-  QuickTri q;
-  if (i >= n) {  // a pad's d2 - m is NaN and its d2 + m no minimum
-    q.r[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-    for (int k = 1; k < 5; ++k) q.r[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    quick[i] = q;
+  float4* q = quick + quick_index(i);
+  TriRec T;
+  int32_t index = kPadTri;
+  if (i < n) {
+    T = tris[i];
+    memcpy(&index, &T.a.w, 4);
+  }
+  if (index == kPadTri) {  // a pad's d2 - m is NaN and its d2 + m no minimum
+    q[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+    for (int k = 1; k < 5; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     return;
   }
-  const TriRec T = tris[i];
   const double abx = (double)T.b.x - T.a.x, aby = (double)T.b.y - T.a.y, abz = (double)T.b.z - T.a.z;
   const double acx = (double)T.c.x - T.a.x, acy = (double)T.c.y - T.a.y, acz = (double)T.c.z - T.a.z;
   const double bcx = acx - abx, bcy = acy - aby, bcz = acz - abz;
@@ -1726,22 +1733,20 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
   const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
   const double F = u * (128.0 + 64.0 / smin) + far * far;
   if (!(smin >= 0.01) || !(F <= 0.01)) {
-    q.r[0] = make_float4(T.a.x, T.a.y, T.a.z, 0.0f);
-    for (int k = 1; k < 4; ++k) q.r[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    q.r[4] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
-    quick[i] = q;
+    q[0] = make_float4(T.a.x, T.a.y, T.a.z, 0.0f);
+    for (int k = 1; k < 4; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    q[16] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
     return;
   }
   const double ux = abx / ab, uy = aby / ab, uz = abz / ab;
   const double mx = nx / nn, my = ny / nn, mz = nz / nn;
   const double vx = my * uz - mz * uy, vy = mz * ux - mx * uz, vz = mx * uy - my * ux;
   const double cx = acx * ux + acy * uy + acz * uz, cy = acx * vx + acy * vy + acz * vz;
-  q.r[0] = make_float4(T.a.x, T.a.y, T.a.z, (float)(cx / ac));
-  q.r[1] = make_float4((float)ux, (float)uy, (float)uz, (float)(cy / ac));
-  q.r[2] = make_float4((float)vx, (float)vy, (float)vz, (float)ac);
-  q.r[3] = make_float4((float)mx, (float)my, (float)mz, (float)((cx - ab) / bc));
-  q.r[4] = make_float4((float)(cy / bc), (float)bc, (float)F, (float)(F * lmax * lmax));
-  quick[i] = q;
+  q[0] = make_float4(T.a.x, T.a.y, T.a.z, (float)(cx / ac));
+  q[4] = make_float4((float)ux, (float)uy, (float)uz, (float)(cy / ac));
+  q[8] = make_float4((float)vx, (float)vy, (float)vz, (float)ac);
+  q[12] = make_float4((float)mx, (float)my, (float)mz, (float)((cx - ab) / bc));
+  q[16] = make_float4((float)(cy / bc), (float)bc, (float)F, (float)(F * lmax * lmax));
 }
 
 // Closest points of nq queries, on the walk kernel's traversal: lanes with an
@@ -1753,7 +1758,7 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
 // number of wavefronts.
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris,
-                        const QuickTri* __restrict__ quick, float radius, double cx, double cy, double cz,
+                        const float4* __restrict__ quick, float radius, double cx, double cy, double cz,
                         const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t unit_shift,
                         int32_t* __restrict__ tri, float* __restrict__ d2, float* __restrict__ bary) {
   __shared__ CoopScratch coop[kWaves];
@@ -2035,13 +2040,13 @@ hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, in
   return hipGetLastError();
 }
 
-hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, QuickTri* quick, hipStream_t s) {
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, float4* quick, hipStream_t s) {
   hipLaunchKernelGGL(quick_prepare_kernel, dim3((unsigned)((n + kQuickPad + 255) / 256)), dim3(256), 0, s, tris, n,
                      radius, quick);
   return hipGetLastError();
 }
 
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const QuickTri* quick, int32_t leaf,
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t leaf,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s) {
   if (nq <= 0) return hipSuccess;

@@ -33,9 +33,9 @@ struct msk_mesh {
   double radius = 0, area = 0;
   int64_t nv = 0, nf = 0, n_nodes = 0;
   int depth = 0, leaf_size = 4, top_nodes = 85;
-  Node4* d_nodes = nullptr;
-  TriRec* d_tris = nullptr;
-  float4* d_quick = nullptr;  // prefilter records
+  Node4* d_nodes = nullptr;   // one allocation holds the nodes,
+  TriRec* d_tris = nullptr;   // the triangles
+  float4* d_quick = nullptr;  // and their prefilter records
   int32_t* d_slot = nullptr;
   int32_t* d_faces = nullptr;
   std::vector<float> vrel;       // float offsets from the centre (host copy)
@@ -139,12 +139,27 @@ void dfree(T*& p) {
   p = nullptr;
 }
 
-// The prefilter records of n triangle slots, complete when it returns (a mesh
-// may be used from other streams afterwards).
-hipError_t make_quick(msk_ctx* ctx, const TriRec* tris, size_t n, double radius, float4** out) {
-  hipError_t e = dalloc(out, 5 * (n + kQuickPad));
-  if (e == hipSuccess) e = launch_quick_prepare(tris, (int64_t)n, radius, *out, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+// A mesh's device arrays, complete when it returns (a mesh may be used from
+// other streams afterwards), in one allocation that starts with the nodes (the
+// walk kernels address the others by their offset from them, in 256 B); only
+// `nodes` is to be freed.
+hipError_t upload_mesh(msk_ctx* ctx, const HostBvh& B, Node4** nodes, TriRec** tris, float4** quick) {
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t nq = up(5 * (B.tris.size() + kQuickPad) * sizeof(float4)), nn = up(B.nodes.size() * sizeof(Node4));
+  char* base = nullptr;
+  hipError_t e = dalloc(&base, nn + nq + B.tris.size() * sizeof(TriRec));
+  if (e != hipSuccess) return e;
+  *nodes = (Node4*)base;
+  *quick = (float4*)(base + nn);
+  *tris = (TriRec*)(base + nn + nq);
+  hipStream_t s = ctx->stream;
+  if ((e = hipMemcpyAsync(*nodes, B.nodes.data(), B.nodes.size() * sizeof(Node4), hipMemcpyHostToDevice, s)) ==
+          hipSuccess &&
+      (e = hipMemcpyAsync(*tris, B.tris.data(), B.tris.size() * sizeof(TriRec), hipMemcpyHostToDevice, s)) ==
+          hipSuccess &&
+      (e = launch_quick_prepare(*tris, (int64_t)B.tris.size(), B.radius, *quick, s)) == hipSuccess)
+    e = hipStreamSynchronize(s);
+  if (e != hipSuccess) dfree(*nodes);
   return e;
 }
 
@@ -244,11 +259,9 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   m->faces.assign(F, F + 3 * n_tris);
   m->vworld.assign(V, V + 3 * n_verts);
   hipError_t he;
-  if ((he = upload(ctx, &m->d_nodes, B.nodes.data(), B.nodes.size())) != hipSuccess ||
-      (he = upload(ctx, &m->d_tris, B.tris.data(), B.tris.size())) != hipSuccess ||
+  if ((he = upload_mesh(ctx, B, &m->d_nodes, &m->d_tris, &m->d_quick)) != hipSuccess ||
       (he = upload(ctx, &m->d_slot, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
-      (he = upload(ctx, &m->d_faces, F, (size_t)n_tris * 3)) != hipSuccess ||
-      (he = make_quick(ctx, m->d_tris, B.tris.size(), m->radius, &m->d_quick)) != hipSuccess) {
+      (he = upload(ctx, &m->d_faces, F, (size_t)n_tris * 3)) != hipSuccess) {
     msk_mesh_destroy(m);
     return fail(ctx, he == hipErrorOutOfMemory ? MSK_ERR_OOM : MSK_ERR_DEVICE,
                 std::string("mesh upload: ") + hipGetErrorString(he));
@@ -275,8 +288,6 @@ extern "C" msk_status msk_mesh_get_info(const msk_mesh* m, msk_mesh_info* info) 
 extern "C" void msk_mesh_destroy(msk_mesh* m) {
   if (!m) return;
   dfree(m->d_nodes);
-  dfree(m->d_tris);
-  dfree(m->d_quick);
   dfree(m->d_slot);
   dfree(m->d_faces);
   delete m;
@@ -2294,20 +2305,14 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   int32_t* ds = nullptr;
   float4* dq = nullptr;
   hipError_t he;
-  if ((he = upload(ctx, &dn, B.nodes.data(), B.nodes.size())) != hipSuccess ||
-      (he = upload(ctx, &dt, B.tris.data(), B.tris.size())) != hipSuccess ||
-      (he = upload(ctx, &ds, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess ||
-      (he = make_quick(ctx, dt, B.tris.size(), m->radius, &dq)) != hipSuccess) {
+  if ((he = upload_mesh(ctx, B, &dn, &dt, &dq)) != hipSuccess ||
+      (he = upload(ctx, &ds, B.slot_of_tri.data(), B.slot_of_tri.size())) != hipSuccess) {
     dfree(dn);
-    dfree(dt);
     dfree(ds);
-    dfree(dq);
     return fail(ctx, MSK_ERR_DEVICE, std::string("rebuild upload: ") + hipGetErrorString(he));
   }
   dfree(m->d_nodes);
-  dfree(m->d_tris);
   dfree(m->d_slot);
-  dfree(m->d_quick);
   m->d_nodes = dn;
   m->d_tris = dt;
   m->d_quick = dq;

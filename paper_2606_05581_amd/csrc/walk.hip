@@ -347,44 +347,61 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
   return s * s * (1.0f + 0x1p-20f);
 }
 
-// Wavefront-cooperative leaf tests (same result as the lane-private
-// bvh_nearest, bit for bit). All 64 lanes take part; each lane walks its own
-// nodes, but the triangles of the leaves it reaches are listed in LDS and
-// tested 64 at a time by the whole wavefront. Work is listed in units of
-// 2^unit_shift (4 or 8, at least the leaf width) consecutive triangle slots of
-// one owner, one lane each (one word: first slot / 4 << 6 | owner lane; leaves
-// start at multiples of 4 slots and hold at least one triangle, so meshes have
-// fewer than 2^26 triangles). The lanes past a shorter leaf meet pads, or
-// triangles of the next leaf, which cannot change a minimum over the mesh: a
-// unit needs no count.
+// Wavefront-shared nearest-triangle search (same result as the lane-private
+// bvh_nearest, bit for bit). Up to 64 queries of a wavefront, one per owner
+// lane, share one stack of (node, owner) items in LDS. A trip takes up to 64
+// items from its top, one per lane whoever their owners are, tests the four
+// child boxes, lists the leaf children's triangles, tests those 64 at a time
+// with the whole wavefront, and pushes the inner children that still reach
+// their owner's bound, the nearest ones of all lanes on top. A query ends when
+// none of its items is left (`open`).
+//   The search of a point far from every surface visits hundreds to thousands
+// of nodes. On a stack per lane it held its wavefront for that many trips
+// with one lane busy: 256,000 walks on a 500,000-face sphere took 15.6 ms,
+// 16.4M walks 153 ms, so that 17 of the 51 ms of 4.1M walks were such tails.
+// Here all lanes share its nodes.
+//
+// Triangles are listed in units of 2^unit_shift (4 or 8, at least the leaf
+// width) consecutive slots of one owner, one lane each (one word: first slot
+// / 4 << 6 | owner lane; leaves start at multiples of 4 slots and hold at
+// least one triangle, so meshes have fewer than 2^26 triangles). The lanes
+// past a shorter leaf meet pads, or triangles of the next leaf, which cannot
+// change a minimum over the mesh: a unit needs no count.
 //
 // A listed triangle takes the prefilter only. Its upper value d2 + m lowers
 // the owner's bound m2 through an LDS minimum; if its lower value d2 - m still
 // reaches that bound it goes to the wavefront's pending list, and the exact
-// test runs on the pending triangles that are left once their owner's
-// traversal has ended (or the list is full): about two per query instead of
-// all of them. The exact (squared distance, original index) goes to its owner
-// through a 64-bit LDS minimum, which realises the lexicographic order
-// exactly. Should the exact minimum lie above what m2 promised (possible only
-// for nearly degenerate triangles), the owner's search runs again with m2 at
-// that minimum and lowered by exact values only (negative pt.w), so the
-// result never rests on the upper margin.
+// test runs on the pending triangles that are left once their owner's search
+// has ended (or the list is full): about two per query instead of all of
+// them. The exact (squared distance, original index) goes to its owner through
+// a 64-bit LDS minimum, which realises the lexicographic order exactly. Should
+// the exact minimum lie above what m2 promised (possible only for nearly
+// degenerate triangles), the owner's search runs again with m2 at that minimum
+// and lowered by exact values only (negative pt.w), so the result never rests
+// on the upper margin.
+//   Exact tests of all listed triangles were bound by VALU issue: about 190
+// wavefront instructions per round of 64 tests, every region's path among
+// them. The prefilter takes about 60.
 //
-// The exact tests were bound by VALU issue: about 190 wavefront instructions
-// per round of 64 tests, every region's path among them. The prefilter takes
-// about 60.
-constexpr int kUnitCap = 64 * 5;  // per lane four leaf children and a warm-start candidate
+// The stack holds kItemCap items; a trip takes as few as keeps it below
+// kItemLimit (one at least: its subtree then adds at most 3 items a level, and
+// 3 x depth + 5 <= kStackDepth), and new queries start only up to kRootLimit.
+// The units of a trip lie above the stack's top (at most 4 per taken item and
+// one per new query, which kItemLimit leaves room for).
+constexpr int kItemCap = 512, kItemLimit = kItemCap - 64, kRootLimit = kItemLimit - 72;
+static_assert(kItemLimit + kStackDepth <= kItemCap, "one item's subtree must fit above the limit");
 constexpr int kPendCap = 128;
 struct CoopScratch {
-  uint32_t unit[kUnitCap];    // block << 6 | owner lane
+  uint32_t item[kItemCap];   // node << 6 | owner; above the top: units, block << 6 | owner
+  uint16_t lb[kItemCap];     // item's box lower bound, FP32 cut to 16 bits
   float4 pt[64];             // owner's query point; w = 2 delta, negative: m2 lowered by exact values only
-  const float4* quick[64];    // owner's arrays (batched meshes differ per lane)
-  const TriRec* tris[64];
-  const Node4* nodes[64];
+  const char* base[64];      // owner's mesh (batched meshes differ per lane): its nodes,
+  uint32_t off_quick[64];    // and its prefilter records
+  uint32_t off_tris[64];     // and triangles, in 256 B from the nodes
   uint32_t m2[64];           // bound on the owner's squared distance (float bits)
+  uint32_t open[64];         // owner's items on the stack
   unsigned long long key[64];
   int32_t rec_slot[64];
-  float rec_l1[64], rec_l2[64], rec_den[64];
   uint32_t pend[kPendCap];
   float pend_l2[kPendCap];
 };
@@ -439,9 +456,9 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
     kept += (uint32_t)__popcll(mk);
     if (now) {
       const int32_t s = (int32_t)(word >> 6 << 2 | (__float_as_uint(l2) & 3u));
-      const TriRec T = W->tris[o][s];
+      const TriRec T = ((const TriRec*)(W->base[o] + ((uint64_t)W->off_tris[o] << 8)))[s];
       const float reject = __uint_as_float((uint32_t)(W->key[o] >> 32));
-      float l1 = 0.0f, lb = 0.0f, den = 1.0f;
+      float l1, lb, den;
       int region = 0;
       const float d = tri_dist2(q.x, q.y, q.z, T, reject, l1, lb, den, region);
       if (kStats) cnt.flops += kTriFlops[region & 7];
@@ -452,12 +469,7 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
         atomicMin(&W->key[o], key);
         atomicMin(&W->m2[o], __float_as_uint(d));
         lds_order();
-        if (W->key[o] == key) {
-          W->rec_slot[o] = s;
-          W->rec_l1[o] = l1;
-          W->rec_l2[o] = lb;
-          W->rec_den[o] = den;
-        }
+        if (W->key[o] == key) W->rec_slot[o] = s;
       }
     }
     lds_order();
@@ -468,127 +480,135 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
 // FP32 operations of one prefilter test (quick_dist and the two bounds).
 constexpr uint32_t kQuickFlops = 58;
 
-// A lane's traversal: the next node, and the stack with its top entry in
-// registers (tn, tl) and the rest in private memory: a pop takes the
-// registers and starts reading the next entry, which is not needed before
-// the following pop.
-struct LaneTrav {
-  int32_t node, sp, tn, warm;
-  float tl, slack;
-};
+// Box bound of a query: no triangle in a box whose squared distance exceeds it
+// beats or ties the bound m2 (prune_bound's argument, with delta more: m2
+// bounds the prefilter's value).
+__device__ __forceinline__ float box_bound(float m2, const float4& q) {
+  const float w = fabsf(q.w);  // 2^-20 R
+  const float slack = 5.0f * w + 0x1p-18f * fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z)));
+  const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + slack;
+  return s * s * (1.0f + 0x1p-20f);
+}
 
-// Starts lane `lane`'s search at (x, y, z), warm-start candidate `warm`.
-__device__ __forceinline__ void trav_start(CoopScratch* W, uint32_t lane, LaneTrav& t, const Node4* nodes,
-                                           const float4* quick, const TriRec* tris, float radius, float x, float y,
-                                           float z, int32_t warm) {
-  const float pm = fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z)));
-  // the margins hold for |p| <= 3 R (quick_prepare_kernel); farther points
-  // take the exact test on every triangle
-  const float two_delta = pm <= 1.7f * radius ? 0x1p-20f * radius : -INFINITY;
-  W->pt[lane] = make_float4(x, y, z, two_delta);
+// Sets up owner `lane`'s search at (x, y, z), |p| <= 3 R; search_push puts its
+// root on the stack.
+__device__ __forceinline__ void search_start(CoopScratch* W, uint32_t lane, const Node4* nodes, const float4* quick,
+                                             const TriRec* tris, float radius, float x, float y, float z) {
+  W->pt[lane] = make_float4(x, y, z, 0x1p-20f * radius);
   W->m2[lane] = __float_as_uint(INFINITY);
   W->key[lane] = ((unsigned long long)__float_as_uint(INFINITY) << 32) | (uint32_t)INT_MAX;
   W->rec_slot[lane] = -1;
-  W->rec_l1[lane] = 0.0f;
-  W->rec_l2[lane] = 0.0f;
-  W->rec_den[lane] = 1.0f;
-  W->nodes[lane] = nodes;
-  W->quick[lane] = quick;
-  W->tris[lane] = tris;
-  t.node = 0;
-  t.sp = 0;
-  t.tn = -1;
-  t.warm = warm;
-  t.slack = 0x1p-18f * (radius + pm) + 0x1p-20f * radius;
+  W->base[lane] = (const char*)nodes;
+  W->off_quick[lane] = (uint32_t)(((const char*)quick - (const char*)nodes) >> 8);
+  W->off_tris[lane] = (uint32_t)(((const char*)tris - (const char*)nodes) >> 8);
 }
 
-// Answer of a lane whose traversal has ended and whose pending tests are
-// done. Returns false if the exact minimum lies above what the prefilter's
-// bound promised: the search has been set up to run again (t), from then on
-// on exact values.
-__device__ __forceinline__ bool trav_answer(CoopScratch* W, uint32_t lane, LaneTrav& t, Nearest& h) {
+// Pushes the roots of the lanes with `fresh` (all lanes of the wavefront call
+// it, with size <= kRootLimit).
+__device__ __forceinline__ void search_push(CoopScratch* W, uint32_t lane, bool fresh, uint32_t& size) {
+  const uint64_t m = __ballot(fresh);
+  if (fresh) {
+    const uint32_t p = size + mbcnt64(m);
+    W->item[p] = lane;
+    W->lb[p] = 0;
+    W->open[lane] = 1;
+  }
+  size += (uint32_t)__popcll(m);
+}
+
+// Answer of an owner whose search has ended and whose pending tests are done.
+// Returns false if the exact minimum lies above what the prefilter's bound
+// promised: the search has been set up to run again (its root is to be
+// pushed), from then on on exact values.
+__device__ __forceinline__ bool search_answer(CoopScratch* W, uint32_t lane, Nearest& h) {
   const unsigned long long k = W->key[lane];
   h.d2 = __uint_as_float((uint32_t)(k >> 32));
   h.orig = (int32_t)(uint32_t)k;
   h.slot = W->rec_slot[lane];
-  h.l1 = W->rec_l1[lane];
-  h.l2 = W->rec_l2[lane];
-  h.den = W->rec_den[lane];
   const float w = fabsf(W->pt[lane].w);
   if (h.d2 > keep_bound(__uint_as_float(W->m2[lane]), w)) {
     W->m2[lane] = __float_as_uint(h.d2);
     W->pt[lane].w = -w;
-    t.node = 0;
-    t.sp = 0;
-    t.tn = -1;
-    t.warm = h.slot;
     return false;
   }
   return true;
 }
 
-// One node of every lane with `tr` (all lanes of the wavefront call it):
-// four box lower bounds, the triangles of the leaf children within the bound
-// (and a new query's warm-start candidate) through the wavefront's prefilter
-// rounds, then the inner children sorted: the nearest is next, the others
-// are pushed farthest first. Returns false once the lane's traversal ends.
+// The answer's barycentrics: the exact test of its triangle once more.
+__device__ __forceinline__ void answer_bary(const TriRec* __restrict__ tris, float px, float py, float pz, Nearest& h) {
+  h.l1 = h.l2 = 0.0f;
+  h.den = 1.0f;
+  if (h.slot < 0) return;
+  float l1 = 0.0f, l2 = 0.0f, den = 1.0f;
+  int region = 0;
+  (void)tri_dist2(px, py, pz, tris[h.slot], INFINITY, l1, l2, den, region);
+  h.l1 = l1;
+  h.l2 = l2;
+  if (region == 6) h.den = den;
+}
+
+// One trip of the wavefront (all lanes call it). `warm` names the warm-start
+// slot of an owner whose search was just started (else negative; cleared).
 template <bool kStats>
-__device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr, LaneTrav& t, StackEntry* stk, float px,
-                                          float py, float pz, const Node4* top, int32_t n_lds, int unit_shift,
-                                          uint32_t& npend, TravCount& cnt) {
+__device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint32_t& size, int32_t& warm,
+                                            int unit_shift, uint32_t& npend, TravCount& cnt) {
+  const int32_t room = ((int32_t)kItemLimit - (int32_t)size) / 3;
+  const uint32_t n = min(min(64u, size), (uint32_t)max(room, 1));
+  const bool tr = lane < n;
   float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
   int32_t cc[4] = {0, 0, 0, 0};
-  uint32_t nu = 0;
   uint32_t uw[4] = {~0u, ~0u, ~0u, ~0u};  // leaf children within the bound: unit words
+  uint32_t nu = 0, o = 0;
+  float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  bool live = false;
   if (tr) {
-    const float m2 = __uint_as_float(W->m2[lane]);
-    const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + t.slack;
-    const float thr = s * s * (1.0f + 0x1p-20f);
-    float4 lox, loy, loz, hix, hiy, hiz;
-    int4 ch, ct;
-    if (kStats) {
-      ++cnt.nodes;
-      cnt.flops += 4 * kBoxFlops;
-    }
-    if (t.node < n_lds) {
-      const float4* N = (const float4*)&top[t.node];
-      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-    } else {
-      const float4* N = (const float4*)&W->nodes[lane][t.node];
-      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-    }
-    const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
-                lz[4] = {loz.x, loz.y, loz.z, loz.w};
-    const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
-                hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
-    const int32_t c4[4] = {ch.x, ch.y, ch.z, ch.w}, n4[4] = {ct.x, ct.y, ct.z, ct.w};
-    nu = t.warm >= 0 ? 1u : 0u;
+    const uint32_t word = W->item[size - 1u - lane];
+    const float l0 = __uint_as_float((uint32_t)W->lb[size - 1u - lane] << 16);
+    o = word & 63u;
+    q = W->pt[o];
+    const float thr = box_bound(__uint_as_float(W->m2[o]), q);
+    live = l0 <= thr;
+    if (live) {
+      if (kStats) {
+        ++cnt.nodes;
+        cnt.flops += 4 * kBoxFlops;
+      }
+      const float4* N = (const float4*)(W->base[o] + ((uint64_t)(word >> 6) << 7));
+      const float4 lox = N[0], loy = N[1], loz = N[2], hix = N[3], hiy = N[4], hiz = N[5];
+      const int4 ch = ((const int4*)N)[6], ct = ((const int4*)N)[7];
+      const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
+                  lz[4] = {loz.x, loz.y, loz.z, loz.w};
+      const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
+                  hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
+      const int32_t c4[4] = {ch.x, ch.y, ch.z, ch.w}, n4[4] = {ct.x, ct.y, ct.z, ct.w};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float gx = fmaxf(fmaxf(lx[k] - px, px - hx[k]), 0.0f);
-      const float gy = fmaxf(fmaxf(ly[k] - py, py - hy[k]), 0.0f);
-      const float gz = fmaxf(fmaxf(lz[k] - pz, pz - hz[k]), 0.0f);
-      const float l = gx * gx + gy * gy + gz * gz;
-      // an unused slot has count 0, child < 0 and an empty box
-      if (c4[k] >= 0) {
-        lb[k] = l;
-        cc[k] = c4[k];
-      } else if (l <= thr && n4[k] > 0) {
-        uw[k] = ((uint32_t)(-c4[k] - 1) >> 2 << 6) | lane;
-        ++nu;
+      for (int k = 0; k < 4; ++k) {
+        const float gx = fmaxf(fmaxf(lx[k] - q.x, q.x - hx[k]), 0.0f);
+        const float gy = fmaxf(fmaxf(ly[k] - q.y, q.y - hy[k]), 0.0f);
+        const float gz = fmaxf(fmaxf(lz[k] - q.z, q.z - hz[k]), 0.0f);
+        const float l = gx * gx + gy * gy + gz * gz;
+        // an unused slot has count 0, child < 0 and an empty box
+        if (c4[k] >= 0) {
+          lb[k] = l;
+          cc[k] = c4[k];
+        } else if (l <= thr && n4[k] > 0) {
+          uw[k] = ((uint32_t)(-c4[k] - 1) >> 2 << 6) | o;
+          ++nu;
+        }
       }
     }
   }
+  size -= n;
+  nu += warm >= 0 ? 1u : 0u;
   bool force = false;
   if (__ballot(nu > 0) != 0) {
     uint32_t total;
-    uint32_t pos = wave_prefix_small(nu, total);
-    if (tr && t.warm >= 0) W->unit[pos++] = ((uint32_t)t.warm >> 2 << 6) | lane;
+    uint32_t pos = size + wave_prefix_small(nu, total);
+    lds_order();
+    if (warm >= 0) W->item[pos++] = ((uint32_t)warm >> 2 << 6) | lane;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (uw[k] != ~0u) W->unit[pos++] = uw[k];
+      if (uw[k] != ~0u) W->item[pos++] = uw[k];
     if (kStats && nu > 0) {
       cnt.tris += nu << unit_shift;
       cnt.flops += (nu << unit_shift) * kQuickFlops;
@@ -602,18 +622,19 @@ __device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr
       uint32_t word = 0;
       float l2 = 0.0f;
       if (u < total) {
-        const uint32_t pk = W->unit[u];
-        const uint32_t o = pk & 63u;
+        const uint32_t pk = W->item[size + u];
+        const uint32_t uo = pk & 63u;
         const uint32_t bl = (pk >> 6) + ((lane & ((1u << unit_shift) - 1u)) >> 2);
-        const float4 q = W->pt[o];
+        const float4 p = W->pt[uo];
+        const float4* T = (const float4*)(W->base[uo] + ((uint64_t)W->off_quick[uo] << 8));
         float d2, m;
-        quick_dist(q.x, q.y, q.z, W->quick[o] + (uint64_t)bl * 20u + (lane & 3u), d2, m);
-        if (q.w >= 0.0f) atomicMin(&W->m2[o], __float_as_uint(d2 + m));
+        quick_dist(p.x, p.y, p.z, T + (uint64_t)bl * 20u + (lane & 3u), d2, m);
+        if (p.w >= 0.0f) atomicMin(&W->m2[uo], __float_as_uint(d2 + m));
         lds_order();
         l2 = d2 - m;
-        cand = l2 <= keep_bound(__uint_as_float(W->m2[o]), fabsf(q.w));
-        force |= cand && (m > 1e28f || q.w < 0.0f);
-        word = (bl << 6) | o;
+        cand = l2 <= keep_bound(__uint_as_float(W->m2[uo]), fabsf(p.w));
+        force |= cand && (m > 1e28f || p.w < 0.0f);
+        word = (bl << 6) | uo;
         // the slot within its block goes into the low bits of the lower value
         l2 = __uint_as_float((__float_as_uint(l2 - fabsf(l2) * 0x1p-20f) & ~3u) | (lane & 3u));
       }
@@ -629,48 +650,37 @@ __device__ __forceinline__ bool trav_trip(CoopScratch* W, uint32_t lane, bool tr
     // triangles without an upper value bound nothing until they are tested
     if (__ballot(force) != 0) npend = flush_pending<kStats>(W, lane, npend, ~0ull, cnt);
   }
-  if (!tr) return false;
-  t.warm = -1;
-  const float m2 = __uint_as_float(W->m2[lane]);
-  const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + t.slack;
-  const float thr = s * s * (1.0f + 0x1p-20f);
+  warm = -1;
+  uint32_t pushed = 0;
+  bool put[4] = {false, false, false, false};
+  if (live) {
+    const float thr = box_bound(__uint_as_float(W->m2[o]), q);
 #define MSK_CX(i, j)                                                        \
   if (lb[j] < lb[i]) {                                                      \
     float tl = lb[i]; lb[i] = lb[j]; lb[j] = tl;                            \
     int32_t tc = cc[i]; cc[i] = cc[j]; cc[j] = tc;                          \
   }
-  MSK_CX(0, 1) MSK_CX(2, 3) MSK_CX(0, 2) MSK_CX(1, 3) MSK_CX(1, 2)
+    MSK_CX(0, 1) MSK_CX(2, 3) MSK_CX(0, 2) MSK_CX(1, 3) MSK_CX(1, 2)
 #undef MSK_CX
-  // leaf children and unused slots carry lb = inf here; a search without a
-  // finite bound yet (thr = inf) must not take them for inner children
 #pragma unroll
-  for (int k = 3; k >= 1; --k) {
-    if (lb[k] <= thr && lb[k] < INFINITY) {
-      if (t.tn >= 0 && t.sp < kStackDepth) stk[t.sp++] = StackEntry{t.tn, t.tl};
-      t.tn = cc[k];
-      t.tl = lb[k];
+    for (int k = 0; k < 4; ++k) {  // leaf children and unused slots carry lb = inf
+      put[k] = lb[k] <= thr && lb[k] < INFINITY;
+      pushed += put[k] ? 1u : 0u;
     }
   }
-  if (lb[0] <= thr && lb[0] < INFINITY) {
-    t.node = cc[0];
-    return true;
-  }
-  while (t.tn >= 0) {
-    const int32_t cand = t.tn;
-    const float cl = t.tl;
-    if (t.sp > 0) {
-      --t.sp;
-      t.tn = stk[t.sp].node;
-      t.tl = stk[t.sp].lb;
-    } else {
-      t.tn = -1;
+  lds_order();
+#pragma unroll
+  for (int k = 3; k >= 0; --k) {
+    const uint64_t m = __ballot(put[k]);
+    if (put[k]) {
+      const uint32_t p = size + mbcnt64(m);
+      W->item[p] = ((uint32_t)cc[k] << 6) | o;
+      W->lb[p] = (uint16_t)(__float_as_uint(lb[k]) >> 16);
     }
-    if (cl <= thr) {
-      t.node = cand;
-      return true;
-    }
+    size += (uint32_t)__popcll(m);
   }
-  return false;
+  if (tr && pushed != 1u) atomicAdd(&W->open[o], pushed - 1u);
+  lds_order();
 }
 
 // ------------------------------------------------------ walk machinery
@@ -1278,19 +1288,16 @@ __device__ unsigned long long g_phase_cycles[16];
 #define MSK_ACC(i, a, b)
 #endif
 
-// Streaming form of the persistent kernel: every loop trip advances each
-// traversing lane by one BVH node (its leaf triangles tested by the whole
-// wavefront), so a lane whose query is long does not hold the others: lanes
-// whose query is answered wait until enough of them do (kStepMin), then
-// finish their step and start the next query together; ended walks and idle
-// lanes wait for the next bookkeeping pass (L.regen_min). At most
-// L.max_owners lanes of a wavefront carry a walk: a launch of few walks
-// spreads them over all wavefronts, whose other lanes help with the triangle
-// tests. The walks, their queries and their results are those of the other
-// forms.
+// Streaming form of the persistent kernel: the queries of a wavefront's walks
+// run on its shared search (search_trip), so a walk whose query is long does
+// not hold the others: walks whose query is answered wait until enough of them
+// do (kStepMin), then finish their step and start the next query together;
+// ended walks and idle lanes wait for the next bookkeeping pass (L.regen_min).
+// At most L.max_owners lanes of a wavefront carry a walk: a launch of few
+// walks spreads them over all wavefronts. The walks, their queries and their
+// results are those of the other forms.
 template <bool kStats, typename AccT, bool kKnn = false>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
-  extern __shared__ Node4 top[];  // kLdsTop nodes when L.use_lds_top, else none
   __shared__ WaveTables<AccT> T;
   __shared__ CoopScratch coop[kWaves];
   const int wi = threadIdx.x >> 6;
@@ -1301,13 +1308,6 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
     (&T.v2[0][0][0])[i] = acc_zero<AccT>();
   }
   for (int i = threadIdx.x; i < kWaves * 2 * 3; i += blockDim.x) (&T.cnt[0][0][0])[i] = 0;
-  int32_t n_lds = 0;
-  if (L.use_lds_top) {
-    n_lds = min(L.n_top, kLdsTop);
-    const int4* src = (const int4*)L.meshes[0].nodes;
-    int4* dst = (int4*)top;
-    for (int i = threadIdx.x; i < n_lds * 8; i += blockDim.x) dst[i] = src[i];
-  }
   __syncthreads();
   const uint32_t lane = __lane_id();
   const bool owner = lane < (uint32_t)L.max_owners;
@@ -1321,64 +1321,64 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   LaneWalk w;
   w.active = 0;
   w.tab = -1;
-  // lane's state: mode 0 no walk, 1 traversing, 2 traversal ended, 3 walk
-  // ended (its result stays in the wavefront's scratch, fin_status, until the
-  // next bookkeeping pass records it)
-  int32_t mode = 0, fin_status = -1;
-  LaneTrav t;
-  t.node = 0;
-  t.sp = 0;
-  t.tn = -1;
-  t.warm = -1;
-  t.tl = 0.0f;
-  t.slack = 0.0f;
+  // lane's state: mode 0 no walk, 1 searching, 2 search ended, 3 walk ended
+  // (its result stays in the wavefront's scratch, fin_status, until the next
+  // bookkeeping pass records it)
+  int32_t mode = 0, fin_status = -1, warm = -1;
   bool capped = false;
-  StackEntry stk[kStackDepth];
-  uint32_t npend = 0;  // pending exact tests of the wavefront (uniform)
+  uint32_t npend = 0, size = 0;  // pending exact tests and stack items of the wavefront (uniform)
   TravCount cnt;       // statistics kernels: this lane's share of the work
   bool drained = false;
 #if MSK_PHASE_TIMING
   uint64_t ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #endif
   auto start_query = [&](const MeshDev& M) {
-    trav_start(W, lane, t, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z, w.slot);
+    search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z);
+    warm = w.slot;
     mode = 1;
   };
   while (true) {
     // ---- bookkeeping, when enough lanes wait or none traverses: ended walks
     // are recorded and idle lanes take new walks
     MSK_TICK(tk0);
-    // ---- steps whose traversal has ended: run their pending exact tests,
-    // finish the step and start the next one, once kStepMin lanes wait (a
-    // quarter of the wavefront's walks if that is less) or none traverses; an
-    // ended walk waits for the bookkeeping pass below
+    // ---- steps whose search has ended: run their pending exact tests, finish
+    // the step and start the next one, once kStepMin lanes wait (a quarter of
+    // the wavefront's walks if that is less) or the stack is empty; an ended
+    // walk waits for the bookkeeping pass below
     {
-      const uint64_t pend = __ballot(mode == 2), trav = __ballot(mode == 1);
-      if (pend != 0 && (trav == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(trav | pend) + 3) >> 2))) {
+      if (mode == 1 && W->open[lane] == 0) mode = 2;
+      const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
+      if (pend != 0 && size <= (uint32_t)kRootLimit &&
+          (size == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2))) {
         if (npend != 0) npend = flush_pending<kStats>(W, lane, npend, pend, cnt);
-        Nearest hit;
-        if (mode == 2 && trav_answer(W, lane, t, hit)) {
-          const MeshDev& M = L.meshes[w.mesh];
-          int32_t st = walk_end(M, w, capped, hit);
-          if (st < 0) {
-            st = walk_begin(L, M, w, capped);
-            if (st < 0) start_query(M);
-          }
-          if (st >= 0) {
-            fin_status = st;
-            mode = 3;
-          }
-        } else if (mode == 2) {
+        bool fresh = false;
+        if (mode == 2) {
+          Nearest hit;
+          fresh = true;
           mode = 1;
+          if (search_answer(W, lane, hit)) {
+            const MeshDev& M = L.meshes[w.mesh];
+            int32_t st = walk_end(M, w, capped, hit);
+            if (st < 0) {
+              st = walk_begin(L, M, w, capped);
+              if (st < 0) start_query(M);
+            }
+            if (st >= 0) {
+              fin_status = st;
+              mode = 3;
+              fresh = false;
+            }
+          }
         }
+        search_push(W, lane, fresh, size);
       }
     }
     MSK_TICK(tk0b);
     MSK_ACC(5, tk0, tk0b);
-    const uint64_t trav = __ballot(mode == 1);
     // (once the queues are empty there is nothing to hand out: ended walks
     // then wait for the last one)
-    if (trav == 0 || (!drained && (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min)) {
+    if (size == 0 || (!drained && size <= (uint32_t)kRootLimit &&
+                      (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min)) {
 #if MSK_PHASE_TIMING
       ph[7] += 1;
 #endif
@@ -1391,9 +1391,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         hit.d2 = __uint_as_float((uint32_t)(k >> 32));
         hit.orig = (int32_t)(uint32_t)k;
         hit.slot = W->rec_slot[lane];
-        hit.l1 = W->rec_l1[lane];
-        hit.l2 = W->rec_l2[lane];
-        hit.den = W->rec_den[lane];
+        const float4 q = W->pt[lane];
+        answer_bary(M.tris, q.x, q.y, q.z, hit);
         if (w.tab >= 0)
           walk_finish_table<AccT, kKnn>(L, M, w, fin_status, hit, T, wi);
         else
@@ -1452,7 +1451,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         const uint32_t rank = __popcll(idle & ((1ull << lane) - 1ull));
         const uint64_t avail = cend - cur;
         const uint32_t take = (uint32_t)min(avail, (uint64_t)__popcll(idle));
-        bool fresh = false;
+        bool fresh = false, root = false;
         if (owner && !w.active && rank < take) {
           decode_walk(L, cur + rank, w);
           int32_t face;
@@ -1464,6 +1463,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
             const int32_t s0 = walk_begin(L, M, w, capped);
             if (s0 < 0) {
               start_query(M);
+              root = true;
               fresh = w.tab >= 0;
             } else {  // left the bounding sphere at once and escaped
               Nearest hit;
@@ -1480,6 +1480,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
             }
           }
         }
+        search_push(W, lane, root, size);
         if (c_tab >= 0) t_out[c_tab] += (int32_t)__popcll(__ballot(fresh));
         cur += take;
         idle = __ballot(owner && !w.active);
@@ -1499,15 +1500,11 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
     }
     MSK_TICK(tk1);
     MSK_ACC(0, tk0, tk1);
-    if (__ballot(mode == 1) == 0) continue;
+    if (size == 0) continue;
 #if MSK_PHASE_TIMING
     ph[6] += 1;
 #endif
-    // ---- one node of every traversing lane
-    const bool tr = mode == 1;
-    const bool more = trav_trip<kStats>(W, lane, tr, t, stk, w.x, w.y, w.z, top, w.mesh == 0 ? n_lds : 0, unit_shift,
-                                        npend, cnt);
-    if (tr && !more) mode = 2;
+    search_trip<kStats>(W, lane, size, warm, unit_shift, npend, cnt);
     MSK_TICK(tk4);
     MSK_ACC(1, tk1, tk4);
   }
@@ -1769,31 +1766,29 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
   const bool owner = lane < (1u << own_shift);
   int64_t next = 0;  // queries handed out (uniform)
   bool drained = false;
-  int32_t mode = 0;  // 0 idle, 1 traversing, 2 traversal ended
+  int32_t mode = 0, warm = -1;  // 0 idle, 1 searching, 2 search ended
   int64_t qi = 0;
-  float x = 0.0f, y = 0.0f, z = 0.0f;
-  LaneTrav t;
-  t.node = 0;
-  t.sp = 0;
-  t.tn = -1;
-  t.warm = -1;
-  t.tl = 0.0f;
-  t.slack = 0.0f;
-  StackEntry stk[kStackDepth];
-  uint32_t npend = 0;
+  uint32_t npend = 0, size = 0;
   TravCount cnt;
   while (true) {
-    const uint64_t pend = __ballot(mode == 2), trav = __ballot(mode == 1);
-    if (trav == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(trav | pend) + 3) >> 2)) {
+    if (mode == 1 && W->open[lane] == 0) mode = 2;
+    const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
+    if (size == 0 || (size <= (uint32_t)kRootLimit &&
+                      (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2))) {
       if (npend != 0) npend = flush_pending<false>(W, lane, npend, pend, cnt);
+      bool fresh = false;
       if (mode == 2) {
         Nearest h;
-        mode = 1;
-        if (trav_answer(W, lane, t, h)) {
+        if (search_answer(W, lane, h)) {
+          const float4 q = W->pt[lane];
+          answer_bary(tris, q.x, q.y, q.z, h);
           tri[qi] = h.orig;
           d2[qi] = h.d2;
           nearest_bary(h, bary[2 * qi], bary[2 * qi + 1]);
           mode = 0;
+        } else {
+          mode = 1;
+          fresh = true;
         }
       }
       const uint64_t idle = __ballot(mode == 0 && owner);
@@ -1803,24 +1798,33 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
         const bool take = mode == 0 && owner && q < nq;
         if (take) {
           qi = q;
-          x = (float)((double)Q[3 * qi] - cx);
-          y = (float)((double)Q[3 * qi + 1] - cy);
-          z = (float)((double)Q[3 * qi + 2] - cz);
-          trav_start(W, lane, t, nodes, quick, tris, radius, x, y, z, -1);
-          mode = 1;
+          const float x = (float)((double)Q[3 * qi] - cx);
+          const float y = (float)((double)Q[3 * qi + 1] - cy);
+          const float z = (float)((double)Q[3 * qi + 2] - cz);
+          if (fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))) <= 1.7f * radius) {
+            search_start(W, lane, nodes, quick, tris, radius, x, y, z);
+            mode = 1;
+            fresh = true;
+          } else {  // the prefilter's margins hold for |p| <= 3 R
+            Nearest h;
+            h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
+            bvh_nearest<false>(nodes, tris, nullptr, 0, x, y, z, radius, h, cnt);
+            tri[qi] = h.orig;
+            d2[qi] = h.d2;
+            nearest_bary(h, bary[2 * qi], bary[2 * qi + 1]);
+          }
         }
         const uint32_t got = (uint32_t)__popcll(__ballot(take));
         drained = got < (uint32_t)__popcll(idle);
         next += got;
       }
-      if (__ballot(mode == 1) == 0) {
-        if (drained) break;
+      search_push(W, lane, fresh, size);
+      if (size == 0) {
+        if (drained && __ballot(mode != 0) == 0) break;
         continue;
       }
     }
-    const bool tr = mode == 1;
-    const bool more = trav_trip<false>(W, lane, tr, t, stk, x, y, z, nullptr, 0, unit_shift, npend, cnt);
-    if (tr && !more) mode = 2;
+    search_trip<false>(W, lane, size, warm, unit_shift, npend, cnt);
   }
 }
 
@@ -1905,29 +1909,28 @@ hipError_t launch_walk_plain(const WalkLaunch& L, hipStream_t s) {
 hipError_t launch_walk_persistent(const WalkLaunch& L, int grid, hipStream_t s) {
   if (L.knn && L.stats) return hipErrorInvalidValue;  // the point basis has no counting instantiation
   if (L.accum < 0 || L.accum > 2) return hipErrorInvalidValue;
-  const size_t lds = L.use_lds_top && kLdsTop > 0 ? sizeof(Node4) * kLdsTop : 0;
   if (L.knn) {  // point basis: instantiations carrying the k-NN evaluation
     if (L.accum == 1)
-      hipLaunchKernelGGL((walk_stream_kernel<false, float, true>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, float, true>), dim3(grid), dim3(256), 0, s, L);
     else if (L.accum == 2)
-      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32, true>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32, true>), dim3(grid), dim3(256), 0, s, L);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, double, true>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, double, true>), dim3(grid), dim3(256), 0, s, L);
   } else if (L.accum == 1) {
     if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, float>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, float>), dim3(grid), dim3(256), 0, s, L);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, float>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, float>), dim3(grid), dim3(256), 0, s, L);
   } else if (L.accum == 2) {
     if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, CompF32>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, CompF32>), dim3(grid), dim3(256), 0, s, L);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32>), dim3(grid), dim3(256), 0, s, L);
   } else {
     if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, double>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, double>), dim3(grid), dim3(256), 0, s, L);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, double>), dim3(grid), dim3(256), lds, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<false, double>), dim3(grid), dim3(256), 0, s, L);
   }
   return hipGetLastError();
 }

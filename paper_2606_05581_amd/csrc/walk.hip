@@ -19,6 +19,33 @@
 
 namespace msk {
 
+// Device memory behind a pointer that was itself read from memory: such a
+// pointer is generic to the compiler, and its flat accesses count as LDS
+// accesses too, so that every wait for LDS data would wait for them.
+#define MSK_GLOBAL __attribute__((address_space(1)))
+typedef const MSK_GLOBAL MeshDev GlobalMesh;
+
+template <typename T>
+__device__ __forceinline__ T gload(const T* p, int64_t i) {
+  return ((const MSK_GLOBAL T*)p)[i];
+}
+__device__ __forceinline__ float4 gload4(const void* p, int64_t i) {
+  typedef float V __attribute__((ext_vector_type(4)));
+  const V v = ((const MSK_GLOBAL V*)p)[i];
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ TriRec gload_tri(const TriRec* tris, int64_t i) {
+  return TriRec{gload4(tris, 3 * i), gload4(tris, 3 * i + 1), gload4(tris, 3 * i + 2)};
+}
+template <typename T>
+__device__ __forceinline__ void gstore(T* p, int64_t i, T v) {
+  ((MSK_GLOBAL T*)p)[i] = v;
+}
+template <typename T>
+__device__ __forceinline__ void gadd(T* p, int64_t i, T v) {
+  (void)__hip_atomic_fetch_add((MSK_GLOBAL T*)p + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ uint4 draw(const WalkLaunch& L, uint32_t row, uint32_t walk, uint32_t step,
                                       uint32_t purpose, uint32_t mesh) {
   return philox10(make_uint4(row, walk, step, (purpose << 24) | (mesh & 0xFFFFFFu)), L.seed_lo, L.seed_hi);
@@ -318,9 +345,10 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
 // covering the exact test's roundings at the size of the coordinates. The
 // frame and margins are prepared by quick_prepare_kernel, whose comment
 // derives them.
-__device__ __forceinline__ void quick_dist(float px, float py, float pz, const float4* __restrict__ T, float& d2,
+__device__ __forceinline__ void quick_dist(float px, float py, float pz, const void* quick, int64_t i, float& d2,
                                            float& m) {
-  const float4 r0 = T[0], r1 = T[4], r2 = T[8], r3 = T[12], r4 = T[16];
+  const float4 r0 = gload4(quick, i), r1 = gload4(quick, i + 4), r2 = gload4(quick, i + 8),
+               r3 = gload4(quick, i + 12), r4 = gload4(quick, i + 16);
   const float gx = px - r0.x, gy = py - r0.y, gz = pz - r0.z;
   const float x = r1.x * gx + r1.y * gy + r1.z * gz;
   const float y = r2.x * gx + r2.y * gy + r2.z * gz;
@@ -456,7 +484,7 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
     kept += (uint32_t)__popcll(mk);
     if (now) {
       const int32_t s = (int32_t)(word >> 6 << 2 | (__float_as_uint(l2) & 3u));
-      const TriRec T = ((const TriRec*)(W->base[o] + ((uint64_t)W->off_tris[o] << 8)))[s];
+      const TriRec T = gload_tri((const TriRec*)(W->base[o] + ((uint64_t)W->off_tris[o] << 8)), s);
       const float reject = __uint_as_float((uint32_t)(W->key[o] >> 32));
       float l1, lb, den;
       int region = 0;
@@ -535,13 +563,13 @@ __device__ __forceinline__ bool search_answer(CoopScratch* W, uint32_t lane, Nea
 }
 
 // The answer's barycentrics: the exact test of its triangle once more.
-__device__ __forceinline__ void answer_bary(const TriRec* __restrict__ tris, float px, float py, float pz, Nearest& h) {
+__device__ __forceinline__ void answer_bary(const TriRec* tris, float px, float py, float pz, Nearest& h) {
   h.l1 = h.l2 = 0.0f;
   h.den = 1.0f;
   if (h.slot < 0) return;
   float l1 = 0.0f, l2 = 0.0f, den = 1.0f;
   int region = 0;
-  (void)tri_dist2(px, py, pz, tris[h.slot], INFINITY, l1, l2, den, region);
+  (void)tri_dist2(px, py, pz, gload_tri(tris, h.slot), INFINITY, l1, l2, den, region);
   h.l1 = l1;
   h.l2 = l2;
   if (region == 6) h.den = den;
@@ -573,9 +601,13 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
         ++cnt.nodes;
         cnt.flops += 4 * kBoxFlops;
       }
-      const float4* N = (const float4*)(W->base[o] + ((uint64_t)(word >> 6) << 7));
-      const float4 lox = N[0], loy = N[1], loz = N[2], hix = N[3], hiy = N[4], hiz = N[5];
-      const int4 ch = ((const int4*)N)[6], ct = ((const int4*)N)[7];
+      const char* N = W->base[o] + ((uint64_t)(word >> 6) << 7);
+      const float4 lox = gload4(N, 0), loy = gload4(N, 1), loz = gload4(N, 2), hix = gload4(N, 3), hiy = gload4(N, 4),
+                   hiz = gload4(N, 5), chf = gload4(N, 6), ctf = gload4(N, 7);
+      const int4 ch = make_int4(__float_as_int(chf.x), __float_as_int(chf.y), __float_as_int(chf.z),
+                                __float_as_int(chf.w));
+      const int4 ct = make_int4(__float_as_int(ctf.x), __float_as_int(ctf.y), __float_as_int(ctf.z),
+                                __float_as_int(ctf.w));
       const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
                   lz[4] = {loz.x, loz.y, loz.z, loz.w};
       const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
@@ -626,9 +658,9 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
         const uint32_t uo = pk & 63u;
         const uint32_t bl = (pk >> 6) + ((lane & ((1u << unit_shift) - 1u)) >> 2);
         const float4 p = W->pt[uo];
-        const float4* T = (const float4*)(W->base[uo] + ((uint64_t)W->off_quick[uo] << 8));
         float d2, m;
-        quick_dist(p.x, p.y, p.z, T + (uint64_t)bl * 20u + (lane & 3u), d2, m);
+        quick_dist(p.x, p.y, p.z, W->base[uo] + ((uint64_t)W->off_quick[uo] << 8), (uint64_t)bl * 20u + (lane & 3u), d2,
+                   m);
         if (p.w >= 0.0f) atomicMin(&W->m2[uo], __float_as_uint(d2 + m));
         lds_order();
         l2 = d2 - m;
@@ -710,12 +742,13 @@ __device__ __forceinline__ void onb(double nx, double ny, double nz, double e1[3
 // proportional to 1 / u^2 on [sin(theta0 / 2), 1], inverted in closed form,
 // and the azimuth is uniform. Walks 2j and 2j + 1 are the antithetic pair j
 // (azimuth and azimuth + pi). Returns false if the row has no tangent ball.
-__device__ bool ball_start(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, int32_t& face) {
-  const double r = (double)M.ball_r[w.row];
+template <typename MD>
+__device__ bool ball_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_t& face) {
+  const double r = (double)gload(M.ball_r, w.row);
   if (!(r > 0.0)) return false;
-  face = M.tri[w.row];
-  const double sx = M.p[3 * w.row], sy = M.p[3 * w.row + 1], sz = M.p[3 * w.row + 2];
-  double nx = M.n[3 * w.row], ny = M.n[3 * w.row + 1], nz = M.n[3 * w.row + 2];
+  face = gload(M.tri, w.row);
+  const double sx = gload(M.p, 3 * w.row), sy = gload(M.p, 3 * w.row + 1), sz = gload(M.p, 3 * w.row + 2);
+  double nx = gload(M.n, 3 * w.row), ny = gload(M.n, 3 * w.row + 1), nz = gload(M.n, 3 * w.row + 2);
   const double nl = sqrt(nx * nx + ny * ny + nz * nz);
   nx /= nl; ny /= nl; nz /= nl;
   const double cx = sx - r * nx, cy = sy - r * ny, cz = sz - r * nz;
@@ -730,7 +763,7 @@ __device__ bool ball_start(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, i
   w.x = (float)(cx + r * (ct * nx + st * (cp * e1[0] + sp * e2[0])));
   w.y = (float)(cy + r * (ct * ny + st * (cp * e1[1] + sp * e2[1])));
   w.z = (float)(cz + r * (ct * nz + st * (cp * e1[2] + sp * e2[2])));
-  w.slot = M.slot_of_tri[face];
+  w.slot = gload(M.slot_of_tri, face);
   w.step = 0;
   w.queries = 0;
   w.cnt = TravCount();
@@ -740,46 +773,48 @@ __device__ bool ball_start(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, i
 // Start of a walk: sample s (point rows: the fixed sample; hat rows:
 // s ~ phi_i / A_i on the vertex's one-ring), inset it along the face normal.
 // Returns false if the row is discarded.
-__device__ bool walk_start(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, int32_t& face, double lam[3]) {
+template <typename MD>
+__device__ bool walk_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_t& face, double lam[3]) {
   if (M.ball_r) return ball_start(L, M, w, face);
   const float sgn = M.side ? 1.0f : -1.0f;
   float sx, sy, sz, nx, ny, nz;
   if (M.mode == kRowsPoint) {
-    if (M.discarded[w.row]) return false;
-    face = M.tri[w.row];
-    sx = M.p[3 * w.row]; sy = M.p[3 * w.row + 1]; sz = M.p[3 * w.row + 2];
-    nx = M.n[3 * w.row]; ny = M.n[3 * w.row + 1]; nz = M.n[3 * w.row + 2];
-    lam[0] = M.bary[3 * w.row]; lam[1] = M.bary[3 * w.row + 1]; lam[2] = M.bary[3 * w.row + 2];
+    if (gload(M.discarded, w.row)) return false;
+    face = gload(M.tri, w.row);
+    sx = gload(M.p, 3 * w.row); sy = gload(M.p, 3 * w.row + 1); sz = gload(M.p, 3 * w.row + 2);
+    nx = gload(M.n, 3 * w.row); ny = gload(M.n, 3 * w.row + 1); nz = gload(M.n, 3 * w.row + 2);
+    lam[0] = gload(M.bary, 3 * w.row); lam[1] = gload(M.bary, 3 * w.row + 1); lam[2] = gload(M.bary, 3 * w.row + 2);
   } else {
     const uint4 u = draw(L, (uint32_t)w.row, w.walk, 0, kPurposeHatStart, (uint32_t)M.mesh_id);
     const uint4 v = draw(L, (uint32_t)w.row, w.walk, 0, kPurposeSplit, (uint32_t)M.mesh_id);
-    const int32_t b0 = M.ring_ptr[w.row], b1 = M.ring_ptr[w.row + 1];
-    const double target = (double)unit_f(u.x) * M.ring_cum[b1 - 1];
+    const int32_t b0 = gload(M.ring_ptr, w.row), b1 = gload(M.ring_ptr, w.row + 1);
+    const double target = (double)unit_f(u.x) * gload(M.ring_cum, b1 - 1);
     int32_t e = b0;
-    while (e < b1 - 1 && !(M.ring_cum[e] > target)) ++e;
-    face = M.ring_tri[e];
+    while (e < b1 - 1 && !(gload(M.ring_cum, e) > target)) ++e;
+    face = gload(M.ring_tri, e);
     const float m1 = unit_f(u.y), m2 = unit_f(u.z), m3 = unit_f(u.w);
     const float li = fmaxf(fminf(m1, m2), fminf(fmaxf(m1, m2), m3));  // median: Beta(2,2)
     const float sv = unit_f(v.x);
-    const int32_t* f = M.faces + 3 * (int64_t)face;
+    const int64_t f3 = 3 * (int64_t)face;
+    const int32_t f[3] = {gload(M.faces, f3), gload(M.faces, f3 + 1), gload(M.faces, f3 + 2)};
     const int corner = f[0] == w.row ? 0 : (f[1] == w.row ? 1 : 2);
     // products of 24-bit values are exact in FP64: the weights sum to 1
     const double la = (1.0 - (double)li) * (double)sv, lb = (1.0 - (double)li) * (1.0 - (double)sv);
     lam[0] = corner == 0 ? (double)li : la;
     lam[1] = corner == 1 ? (double)li : (corner == 0 ? la : lb);
     lam[2] = corner == 2 ? (double)li : lb;
-    const TriRec T = M.tris[M.slot_of_tri[face]];
+    const TriRec T = gload_tri(M.tris, gload(M.slot_of_tri, face));
     const float l0 = (float)lam[0], l1 = (float)lam[1], l2 = (float)lam[2];
     sx = l0 * T.a.x + l1 * T.b.x + l2 * T.c.x;
     sy = l0 * T.a.y + l1 * T.b.y + l2 * T.c.y;
     sz = l0 * T.a.z + l1 * T.b.z + l2 * T.c.z;
-    nx = M.face_normals[3 * face]; ny = M.face_normals[3 * face + 1]; nz = M.face_normals[3 * face + 2];
+    nx = gload(M.face_normals, 3 * face); ny = gload(M.face_normals, 3 * face + 1); nz = gload(M.face_normals, 3 * face + 2);
   }
   const float h = M.inset;
   w.x = sx + sgn * h * nx;
   w.y = sy + sgn * h * ny;
   w.z = sz + sgn * h * nz;
-  w.slot = M.slot_of_tri[face];
+  w.slot = gload(M.slot_of_tri, face);
   w.step = 0;
   w.queries = 0;
   w.cnt = TravCount();
@@ -788,15 +823,15 @@ __device__ bool walk_start(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, i
 
 // Sparse merge of up to NH sorted table rows with weights: emits each column
 // once with sum_h weight_h * value_h (FP64).
-template <int NH, typename Emit>
-__device__ __forceinline__ void merge_rows(const MeshDev& M, const int32_t (&vtx)[NH], const double (&wt)[NH],
+template <int NH, typename MD, typename Emit>
+__device__ __forceinline__ void merge_rows(const MD& M, const int32_t (&vtx)[NH], const double (&wt)[NH],
                                            Emit emit) {
   int32_t p[NH], e[NH];
 #pragma unroll
   for (int k = 0; k < NH; ++k) {
     if (vtx[k] >= 0 && wt[k] != 0.0) {
-      p[k] = M.b_rowptr[vtx[k]];
-      e[k] = M.b_rowptr[vtx[k] + 1];
+      p[k] = gload(M.b_rowptr, vtx[k]);
+      e[k] = gload(M.b_rowptr, vtx[k] + 1);
     } else {
       p[k] = 0;
       e[k] = 0;
@@ -807,7 +842,7 @@ __device__ __forceinline__ void merge_rows(const MeshDev& M, const int32_t (&vtx
     int32_t col[NH];
 #pragma unroll
     for (int k = 0; k < NH; ++k) {
-      col[k] = p[k] < e[k] ? M.b_col[p[k]] : INT_MAX;
+      col[k] = p[k] < e[k] ? gload(M.b_col, p[k]) : INT_MAX;
       cmin = min(cmin, col[k]);
     }
     if (cmin == INT_MAX) break;
@@ -815,7 +850,7 @@ __device__ __forceinline__ void merge_rows(const MeshDev& M, const int32_t (&vtx
 #pragma unroll
     for (int k = 0; k < NH; ++k) {
       if (col[k] == cmin) {
-        v += wt[k] * (double)M.b_val[p[k]];
+        v += wt[k] * (double)gload(M.b_val, p[k]);
         ++p[k];
       }
     }
@@ -855,9 +890,9 @@ __device__ __noinline__ int knn_eval(const KnnDev& G, float qx, float qy, float 
           const int x = c[0] + dx;
           if (x >= 0 && x < G.dim[0]) {
             const int64_t cid = ((int64_t)z * G.dim[1] + y) * G.dim[0] + x;
-            for (int32_t e = G.cell_start[cid]; e < G.cell_start[cid + 1]; ++e) {
-              const int32_t j = G.cell_pts[e];
-              const float4 pj = G.pts[j];
+            for (int32_t e = gload(G.cell_start, cid); e < gload(G.cell_start, cid + 1); ++e) {
+              const int32_t j = gload(G.cell_pts, e);
+              const float4 pj = gload4(G.pts, j);
               const float ex = qx - pj.x, ey = qy - pj.y, ez = qz - pj.z;
               float d2 = ex * ex;
               d2 = d2 + ey * ey;
@@ -889,7 +924,7 @@ __device__ __noinline__ int knn_eval(const KnnDev& G, float qx, float qy, float 
   }
   double sum = 0.0;
   for (int a = 0; a < m; ++a) {
-    const float4 nj = G.nrm[idx[a]];
+    const float4 nj = gload4(G.nrm, idx[a]);
     w[a] = exp(-(double)bd[a] * G.inv2s2) * exp(-(1.0 - (nqx * nj.x + nqy * nj.y + nqz * nj.z)) * G.inv_tau);
     sum += w[a];
   }
@@ -903,7 +938,7 @@ __device__ __noinline__ int knn_eval(const KnnDev& G, float qx, float qy, float 
 __device__ __noinline__ int knn_at_hit(const MeshDev& M, const Nearest& hit, int32_t idx[kMaxKnn],
                                        double w[kMaxKnn]) {
   double t[3], n[3];
-  const TriRec T = M.tris[hit.slot];
+  const TriRec T = gload_tri(M.tris, hit.slot);
   float b1, b2;
   nearest_bary(hit, b1, b2);
   const double l1 = b1, l2 = b2, l0 = (1.0 - l1) - l2;
@@ -926,8 +961,8 @@ __device__ __noinline__ int knn_at_hit(const MeshDev& M, const Nearest& hit, int
 // Contribution of a finished walk to its row, emitted once per column:
 // point rows emit b(t) (the start is fixed per row; the finalisation folds
 // in b(s)), hat rows emit c = b(s) - b(t). Escaped walks have b(t) = 0.
-template <bool kKnn, typename Emit>
-__device__ void walk_contrib(const WalkLaunch& L, const MeshDev& M, const LaneWalk& w, bool has_t, const Nearest& hit,
+template <bool kKnn, typename MD, typename Emit>
+__device__ void walk_contrib(const WalkLaunch& L, const MD& M, const LaneWalk& w, bool has_t, const Nearest& hit,
                              Emit emit) {
   if (M.ball_r) return;  // PSD walks: the rank-one updates are formed from the walk log
   if constexpr (kKnn) {  // point basis: b(t) from the hit point's k nearest samples (point rows)
@@ -935,7 +970,7 @@ __device__ void walk_contrib(const WalkLaunch& L, const MeshDev& M, const LaneWa
       if (has_t) {
         int32_t idx[kMaxKnn];
         double wk[kMaxKnn];
-        const int m = knn_at_hit(M, hit, idx, wk);
+        const int m = knn_at_hit(*(const MeshDev*)&M, hit, idx, wk);
         for (int a = 0; a < m; ++a) emit(idx[a], wk[a]);
       }
       return;
@@ -944,7 +979,8 @@ __device__ void walk_contrib(const WalkLaunch& L, const MeshDev& M, const LaneWa
   int32_t tv[3] = {-1, -1, -1};
   double tw[3] = {0.0, 0.0, 0.0};
   if (has_t) {
-    const int32_t* f = M.faces + 3 * (int64_t)hit.orig;
+    const int64_t f3 = 3 * (int64_t)hit.orig;
+    const int32_t f[3] = {gload(M.faces, f3), gload(M.faces, f3 + 1), gload(M.faces, f3 + 2)};
     tv[0] = f[0]; tv[1] = f[1]; tv[2] = f[2];
     float b1, b2;
     nearest_bary(hit, b1, b2);
@@ -958,7 +994,8 @@ __device__ void walk_contrib(const WalkLaunch& L, const MeshDev& M, const LaneWa
     double lam[3];
     LaneWalk tmp = w;
     walk_start(L, M, tmp, face, lam);
-    const int32_t* f = M.faces + 3 * (int64_t)face;
+    const int64_t f3 = 3 * (int64_t)face;
+    const int32_t f[3] = {gload(M.faces, f3), gload(M.faces, f3 + 1), gload(M.faces, f3 + 2)};
     const int32_t vv[6] = {f[0], f[1], f[2], tv[0], tv[1], tv[2]};
     const double ww[6] = {lam[0], lam[1], lam[2], -tw[0], -tw[1], -tw[2]};
     merge_rows<6>(M, vv, ww, emit);
@@ -966,7 +1003,8 @@ __device__ void walk_contrib(const WalkLaunch& L, const MeshDev& M, const LaneWa
 }
 
 // Walk log and traversal statistics of a finished walk.
-__device__ void walk_record(const WalkLaunch& L, const MeshDev& M, const LaneWalk& w, int32_t status, bool has_t,
+template <typename MD>
+__device__ void walk_record(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status, bool has_t,
                             const Nearest& hit) {
   if (L.stats) {
     atomicAdd(L.stats, (unsigned long long)w.cnt.nodes);
@@ -975,34 +1013,35 @@ __device__ void walk_record(const WalkLaunch& L, const MeshDev& M, const LaneWal
   }
   if (M.log_status) {
     const int64_t li = (int64_t)w.row * M.walks_per_row + ((int64_t)w.walk - L.walk_offset);
-    M.log_status[li] = status;
-    M.log_tri[li] = has_t ? hit.orig : -1;
+    gstore(M.log_status, li, status);
+    gstore(M.log_tri, li, has_t ? hit.orig : -1);
     float b1, b2;
     nearest_bary(hit, b1, b2);
-    M.log_bary[2 * li] = has_t ? b1 : 0.0f;
-    M.log_bary[2 * li + 1] = has_t ? b2 : 0.0f;
-    M.log_queries[li] = w.queries;
+    gstore(M.log_bary, 2 * li, has_t ? b1 : 0.0f);
+    gstore(M.log_bary, 2 * li + 1, has_t ? b2 : 0.0f);
+    gstore(M.log_queries, li, w.queries);
   }
 }
 
-__device__ __forceinline__ bool walk_has_t(const MeshDev& M, int32_t status, const Nearest& hit) {
+template <typename MD>
+__device__ __forceinline__ bool walk_has_t(const MD& M, int32_t status, const Nearest& hit) {
   return status != kEscaped && hit.orig >= 0 && hit.orig < M.n_tris;
 }
 
 // Scatter a finished walk straight into its row with FP64 device atomics.
-template <bool kKnn = false>
-__device__ void walk_finish_global(const WalkLaunch& L, const MeshDev& M, const LaneWalk& w, int32_t status,
+template <bool kKnn = false, typename MD>
+__device__ void walk_finish_global(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status,
                                    const Nearest& hit) {
   const bool has_t = walk_has_t(M, status, hit);
   double* a1 = M.acc1 + (int64_t)w.row * M.K;
   double* a2 = M.acc2 + (int64_t)w.row * M.K;
   walk_contrib<kKnn>(L, M, w, has_t, hit, [&](int32_t j, double v) {
-    atomicAdd(a1 + j, v);
-    atomicAdd(a2 + j, v * v);
+    gadd(a1, j, v);
+    gadd(a2, j, v * v);
   });
-  atomicAdd(M.row_queries + w.row, (unsigned long long)w.queries);
-  if (status == kEscaped) atomicAdd(M.row_escaped + w.row, 1ull);
-  if (status == kCapped) atomicAdd(M.row_capped + w.row, 1ull);
+  gadd(M.row_queries, w.row, (unsigned long long)w.queries);
+  if (status == kEscaped) gadd(M.row_escaped, w.row, 1ull);
+  if (status == kCapped) gadd(M.row_capped, w.row, 1ull);
   walk_record(L, M, w, status, has_t, hit);
 }
 
@@ -1094,12 +1133,12 @@ __device__ __forceinline__ void table_add(WaveTables<AccT>& T, int wi, int t, in
       return;
     }
   }
-  atomicAdd(g1 + j, v);  // table full along this probe sequence
-  atomicAdd(g2 + j, v * v);
+  gadd(g1, j, v);  // table full along this probe sequence
+  gadd(g2, j, v * v);
 }
 
-template <typename AccT, bool kKnn = false>
-__device__ void walk_finish_table(const WalkLaunch& L, const MeshDev& M, const LaneWalk& w, int32_t status,
+template <typename AccT, bool kKnn = false, typename MD>
+__device__ void walk_finish_table(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status,
                                   const Nearest& hit, WaveTables<AccT>& T, int wi) {
   const bool has_t = walk_has_t(M, status, hit);
   double* a1 = M.acc1 + (int64_t)w.row * M.K;
@@ -1115,23 +1154,23 @@ __device__ void walk_finish_table(const WalkLaunch& L, const MeshDev& M, const L
 template <typename AccT>
 __device__ void table_flush(const WalkLaunch& L, WaveTables<AccT>& T, int wi, int t, int32_t mesh, int32_t row) {
   __builtin_amdgcn_wave_barrier();
-  const MeshDev& F = L.meshes[mesh];
+  GlobalMesh& F = ((GlobalMesh*)L.meshes)[mesh];
   double* a1 = F.acc1 + (int64_t)row * F.K;
   double* a2 = F.acc2 + (int64_t)row * F.K;
   for (int i = (int)__lane_id(); i < kSlots; i += 64) {
     const int32_t j = T.key[wi][t][i];
     if (j != kEmptyKey) {
-      atomicAdd(a1 + j, acc_value(T.v1[wi][t][i]));
-      atomicAdd(a2 + j, acc_value(T.v2[wi][t][i]));
+      gadd(a1, j, acc_value(T.v1[wi][t][i]));
+      gadd(a2, j, acc_value(T.v2[wi][t][i]));
       T.key[wi][t][i] = kEmptyKey;
       T.v1[wi][t][i] = acc_zero<AccT>();
       T.v2[wi][t][i] = acc_zero<AccT>();
     }
   }
   if (__lane_id() == 0) {
-    if (T.cnt[wi][t][0]) atomicAdd(F.row_queries + row, T.cnt[wi][t][0]);
-    if (T.cnt[wi][t][1]) atomicAdd(F.row_escaped + row, T.cnt[wi][t][1]);
-    if (T.cnt[wi][t][2]) atomicAdd(F.row_capped + row, T.cnt[wi][t][2]);
+    if (T.cnt[wi][t][0]) gadd(F.row_queries, row, T.cnt[wi][t][0]);
+    if (T.cnt[wi][t][1]) gadd(F.row_escaped, row, T.cnt[wi][t][1]);
+    if (T.cnt[wi][t][2]) gadd(F.row_capped, row, T.cnt[wi][t][2]);
     T.cnt[wi][t][0] = T.cnt[wi][t][1] = T.cnt[wi][t][2] = 0;
   }
   __builtin_amdgcn_wave_barrier();
@@ -1151,7 +1190,8 @@ __device__ __forceinline__ void onb(double nx, double ny, double nz, double e1[3
 // cap, and outside the bounding sphere escape or re-entry. Returns kEscaped
 // when the walk ends here, else -1: the walk needs the nearest-triangle
 // query at (w.x, w.y, w.z); `capped` marks the query that ends a capped walk.
-__device__ int32_t walk_begin(const WalkLaunch& L, const MeshDev& M, LaneWalk& w, bool& capped) {
+template <typename MD>
+__device__ int32_t walk_begin(const WalkLaunch& L, const MD& M, LaneWalk& w, bool& capped) {
   capped = w.step >= M.max_steps;
   // step cap: the walk ends at the nearest boundary point of its position
   if (capped) return -1;
@@ -1190,7 +1230,8 @@ __device__ int32_t walk_begin(const WalkLaunch& L, const MeshDev& M, LaneWalk& w
 // Second half: with the query's answer in `hit`, stop in the eps-shell or
 // take the ball step r (shrunk by the conservative guard) along a uniform
 // direction. Returns kCapped / kHit when the walk ends, else -1.
-__device__ int32_t walk_end(const MeshDev& M, LaneWalk& w, bool capped, const Nearest& hit) {
+template <typename MD>
+__device__ int32_t walk_end(const MD& M, LaneWalk& w, bool capped, const Nearest& hit) {
   ++w.queries;
   if (capped) return kCapped;
   w.slot = hit.slot;
@@ -1209,8 +1250,8 @@ __device__ int32_t walk_end(const MeshDev& M, LaneWalk& w, bool capped, const Ne
 }
 
 // One whole step with a lane-private query (plain kernel).
-template <bool kStats>
-__device__ int32_t walk_step(const WalkLaunch& L, const MeshDev& M, const Node4* lds, int32_t n_lds, LaneWalk& w,
+template <bool kStats, typename MD>
+__device__ int32_t walk_step(const WalkLaunch& L, const MD& M, const Node4* lds, int32_t n_lds, LaneWalk& w,
                              Nearest& hit) {
   bool capped;
   const int32_t st = walk_begin(L, M, w, capped);
@@ -1224,7 +1265,7 @@ __device__ int32_t walk_step(const WalkLaunch& L, const MeshDev& M, const Node4*
 
 __device__ __forceinline__ void decode_walk(const WalkLaunch& L, uint64_t g, LaneWalk& w) {
   const uint64_t slot = g / (uint64_t)L.walks_per_slot;
-  const RowSlot rs = L.slots[slot];
+  const auto& rs = ((const MSK_GLOBAL RowSlot*)L.slots)[slot];
   w.mesh = rs.mesh;
   w.row = rs.row;
   w.walk = (uint32_t)((int64_t)(g - slot * (uint64_t)L.walks_per_slot) + L.walk_offset + rs.walk0);
@@ -1239,7 +1280,7 @@ __global__ void __launch_bounds__(256) walk_plain_kernel(WalkLaunch L) {
   if (g >= (uint64_t)L.n_slots * (uint64_t)L.walks_per_slot) return;
   LaneWalk w;
   decode_walk(L, g, w);
-  const MeshDev& M = L.meshes[w.mesh];
+  GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
   int32_t face;
   double lam[3];
   if (!walk_start(L, M, w, face, lam)) return;
@@ -1332,7 +1373,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
 #if MSK_PHASE_TIMING
   uint64_t ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #endif
-  auto start_query = [&](const MeshDev& M) {
+  auto start_query = [&](GlobalMesh& M) {
     search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z);
     warm = w.slot;
     mode = 1;
@@ -1357,7 +1398,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           fresh = true;
           mode = 1;
           if (search_answer(W, lane, hit)) {
-            const MeshDev& M = L.meshes[w.mesh];
+            GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
             int32_t st = walk_end(M, w, capped, hit);
             if (st < 0) {
               st = walk_begin(L, M, w, capped);
@@ -1384,8 +1425,9 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
 #endif
       bool fin = false;
       int32_t fin_tab = -1;
+      MSK_TICK(tb0);
       if (mode == 3) {
-        const MeshDev& M = L.meshes[w.mesh];
+        GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
         Nearest hit;
         const unsigned long long k = W->key[lane];
         hit.d2 = __uint_as_float((uint32_t)(k >> 32));
@@ -1403,6 +1445,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         w.tab = -1;
         mode = 0;
       }
+      MSK_TICK(tb1);
+      MSK_ACC(2, tb0, tb1);
       for (int t2 = 0; t2 < 2; ++t2) {
         t_out[t2] -= (int32_t)__popcll(__ballot(fin && fin_tab == t2));
         // flush once the table's walks are done and its chunk hands out no more
@@ -1412,6 +1456,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           if (c_tab == t2) c_tab = -1;
         }
       }
+      MSK_TICK(tb2);
+      MSK_ACC(3, tb1, tb2);
       // refill idle lanes from the queue chunks
       uint64_t idle = __ballot(owner && !w.active);
       while (idle != 0 && !drained) {
@@ -1419,11 +1465,12 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           uint64_t start = 0;
           if (lane == 0) {
             const int q = (qhome + qi) & 7;
-            start = atomicAdd(L.queue_next + q, (unsigned long long)L.chunk);
+            start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + q,
+                                           (unsigned long long)L.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
           start = (uint64_t)__shfl((unsigned long long)start, 0);
           const int q = (qhome + qi) & 7;
-          const uint64_t qend = L.queue_end[q];
+          const uint64_t qend = gload(L.queue_end, q);
           if (start >= qend) {
             ++qi;
             if (qi >= 8) drained = true;
@@ -1432,7 +1479,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           cur = start;
           cend = min(start + (uint64_t)L.chunk, qend);
           // the chunk's row takes the table it already has, else a free one
-          const RowSlot rs = L.slots[start / (uint64_t)L.walks_per_slot];
+          const auto& rs = ((const MSK_GLOBAL RowSlot*)L.slots)[start / (uint64_t)L.walks_per_slot];
           c_mesh = rs.mesh;
           c_row = rs.row;
           c_tab = -1;
@@ -1456,7 +1503,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           decode_walk(L, cur + rank, w);
           int32_t face;
           double lam[3];
-          const MeshDev& M = L.meshes[w.mesh];
+          GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
           w.active = walk_start(L, M, w, face, lam) ? 1 : 0;
           w.tab = (w.active && c_tab >= 0 && w.mesh == c_mesh && w.row == c_row) ? c_tab : -1;
           if (w.active) {
@@ -1486,6 +1533,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         idle = __ballot(owner && !w.active);
         // lanes whose row was discarded, or whose walk ended at once, stay idle
       }
+      MSK_TICK(tb3);
+      MSK_ACC(4, tb2, tb3);
       if (__ballot(w.active) == 0) {
         if (drained) {
           for (int t2 = 0; t2 < 2; ++t2)

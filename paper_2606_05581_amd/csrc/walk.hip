@@ -434,6 +434,9 @@ struct CoopScratch {
   float pend_l2[kPendCap];
 };
 
+// A value that all lanes of the wavefront share, in a scalar register.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
@@ -465,6 +468,7 @@ template <bool kStats>
 __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane, uint32_t n, uint64_t done,
                                                   TravCount& cnt) {
   uint32_t kept = 0;
+  n = uniform(n);
   for (uint32_t b = 0; b < n; b += 64) {
     const bool in = b + lane < n;
     const uint32_t word = in ? W->pend[b + lane] : 0u;
@@ -481,7 +485,7 @@ __device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane,
       W->pend[p] = word;
       W->pend_l2[p] = l2;
     }
-    kept += (uint32_t)__popcll(mk);
+    kept = uniform(kept + (uint32_t)__popcll(mk));
     if (now) {
       const int32_t s = (int32_t)(word >> 6 << 2 | (__float_as_uint(l2) & 3u));
       const TriRec T = gload_tri((const TriRec*)(W->base[o] + ((uint64_t)W->off_tris[o] << 8)), s);
@@ -510,12 +514,13 @@ constexpr uint32_t kQuickFlops = 58;
 
 // Box bound of a query: no triangle in a box whose squared distance exceeds it
 // beats or ties the bound m2 (prune_bound's argument, with delta more: m2
-// bounds the prefilter's value).
+// bounds the prefilter's value). Finite, so that an infinite lower bound never
+// passes.
 __device__ __forceinline__ float box_bound(float m2, const float4& q) {
   const float w = fabsf(q.w);  // 2^-20 R
   const float slack = 5.0f * w + 0x1p-18f * fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z)));
   const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + slack;
-  return s * s * (1.0f + 0x1p-20f);
+  return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);
 }
 
 // Sets up owner `lane`'s search at (x, y, z), |p| <= 3 R; search_push puts its
@@ -580,6 +585,8 @@ __device__ __forceinline__ void answer_bary(const TriRec* tris, float px, float 
 template <bool kStats>
 __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint32_t& size, int32_t& warm,
                                             int unit_shift, uint32_t& npend, TravCount& cnt) {
+  size = uniform(size);
+  npend = uniform(npend);
   const int32_t room = ((int32_t)kItemLimit - (int32_t)size) / 3;
   const uint32_t n = min(min(64u, size), (uint32_t)max(room, 1));
   const bool tr = lane < n;
@@ -603,30 +610,24 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
       }
       const char* N = W->base[o] + ((uint64_t)(word >> 6) << 7);
       const float4 lox = gload4(N, 0), loy = gload4(N, 1), loz = gload4(N, 2), hix = gload4(N, 3), hiy = gload4(N, 4),
-                   hiz = gload4(N, 5), chf = gload4(N, 6), ctf = gload4(N, 7);
-      const int4 ch = make_int4(__float_as_int(chf.x), __float_as_int(chf.y), __float_as_int(chf.z),
-                                __float_as_int(chf.w));
-      const int4 ct = make_int4(__float_as_int(ctf.x), __float_as_int(ctf.y), __float_as_int(ctf.z),
-                                __float_as_int(ctf.w));
+                   hiz = gload4(N, 5), ch = gload4(N, 6);
       const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
                   lz[4] = {loz.x, loz.y, loz.z, loz.w};
       const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
                   hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
-      const int32_t c4[4] = {ch.x, ch.y, ch.z, ch.w}, n4[4] = {ct.x, ct.y, ct.z, ct.w};
+      const int32_t c4[4] = {__float_as_int(ch.x), __float_as_int(ch.y), __float_as_int(ch.z), __float_as_int(ch.w)};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float gx = fmaxf(fmaxf(lx[k] - q.x, q.x - hx[k]), 0.0f);
         const float gy = fmaxf(fmaxf(ly[k] - q.y, q.y - hy[k]), 0.0f);
         const float gz = fmaxf(fmaxf(lz[k] - q.z, q.z - hz[k]), 0.0f);
         const float l = gx * gx + gy * gy + gz * gz;
-        // an unused slot has count 0, child < 0 and an empty box
-        if (c4[k] >= 0) {
-          lb[k] = l;
-          cc[k] = c4[k];
-        } else if (l <= thr && n4[k] > 0) {
-          uw[k] = ((uint32_t)(-c4[k] - 1) >> 2 << 6) | o;
-          ++nu;
-        }
+        // an unused slot has child < 0 and an empty box (l = inf > thr)
+        const bool leaf = c4[k] < 0, hit = leaf && l <= thr;
+        lb[k] = leaf ? INFINITY : l;
+        cc[k] = c4[k];
+        uw[k] = hit ? (((uint32_t)~c4[k] >> 2) << 6) | o : ~0u;
+        nu += hit ? 1u : 0u;
       }
     }
   }
@@ -696,7 +697,7 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
 #undef MSK_CX
 #pragma unroll
     for (int k = 0; k < 4; ++k) {  // leaf children and unused slots carry lb = inf
-      put[k] = lb[k] <= thr && lb[k] < INFINITY;
+      put[k] = lb[k] <= thr;
       pushed += put[k] ? 1u : 0u;
     }
   }

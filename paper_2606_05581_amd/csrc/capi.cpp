@@ -675,7 +675,6 @@ MeshDev make_meshdev(const msk_mesh* m, const msk_rows* r, const msk_basis* b, m
   M.slot_of_tri = m->d_slot;
   M.faces = m->d_faces;
   M.n_tris = m->nf;
-  M.n_top = m->top_nodes;
   M.mode = r->mode;
   M.radius = (float)m->radius;
   M.radius_d = m->radius;
@@ -750,11 +749,15 @@ static void shape_launch(WalkLaunch& L, const std::vector<MeshDev>& meshes, cons
   if (L.max_owners == 64) L.regen_min = std::min(64, std::max(1, o.regen_min));
   int32_t leaf = 1;
   L.knn = 0;
+  bool points = true, balls = true;
   for (const MeshDev& md : meshes) {
+    points = points && md.mode == kRowsPoint && !md.ball_r;
+    balls = balls && md.ball_r;
     leaf = std::max(leaf, md.leaf);
     L.knn |= md.knn.k > 0 ? 1 : 0;
   }
   L.unit_shift = leaf <= 4 ? 2 : 3;
+  L.rows = balls ? 2 : (points ? 1 : 0);
 }
 
 struct LaunchBuffers {
@@ -775,8 +778,7 @@ struct LaunchBuffers {
 // Runs the walk kernel over `slots` (walks [offset, offset + W) of each
 // slot's row) and returns its duration in milliseconds.
 static msk_status run_walks(msk_ctx* ctx, const std::vector<MeshDev>& meshes, const std::vector<RowSlot>& slots,
-                            int64_t W, int64_t offset, const msk_dtn_opts& o, int use_lds_top, int n_top,
-                            double* ms, int64_t stats_out[3]) {
+                            int64_t W, int64_t offset, const msk_dtn_opts& o, double* ms, int64_t stats_out[3]) {
   *ms = 0;
   if (slots.empty()) return MSK_OK;
   LaunchBuffers lb;
@@ -795,8 +797,6 @@ static msk_status run_walks(msk_ctx* ctx, const std::vector<MeshDev>& meshes, co
   L.seed_hi = (uint32_t)(o.seed >> 32);
   L.queue_next = lb.d_qnext;
   L.queue_end = lb.d_qend;
-  L.use_lds_top = use_lds_top;
-  L.n_top = n_top;
   L.accum = o.accum;
   shape_launch(L, meshes, o, ctx->n_cu);
   if (o.collect_stats) {
@@ -944,12 +944,11 @@ extern "C" msk_status msk_estimate_dtn(msk_ctx* ctx, const msk_mesh* m, const ms
   std::vector<MeshDev> meshes{M};
   std::vector<RowSlot> slots(r->order.size());
   for (size_t i = 0; i < slots.size(); ++i) slots[i] = RowSlot{0, r->order[i], 0u};
-  const int use_lds = (o.form == MSK_FORM_PERSISTENT && m->top_nodes > 0) ? 1 : 0;
   double ms = 0;
   d->info.walk_launches = 0;
   d->info.walk_kernel_ms = 0;
   int64_t stats[3] = {0, 0, 0};
-  TRY_D(run_walks(ctx, meshes, slots, walks, o.walk_offset, o, use_lds, m->top_nodes, &ms, stats));
+  TRY_D(run_walks(ctx, meshes, slots, walks, o.walk_offset, o, &ms, stats));
   d->info.walk_kernel_ms += ms;
   d->info.walk_launches += 1;
   if (adaptive) {
@@ -982,7 +981,7 @@ extern "C" msk_status msk_estimate_dtn(msk_ctx* ctx, const msk_mesh* m, const ms
         add[i] = batches * walks;
       }
       if (act.empty()) break;
-      TRY_D(run_walks(ctx, meshes, act, walks, o.walk_offset, o, use_lds, m->top_nodes, &ms, stats));
+      TRY_D(run_walks(ctx, meshes, act, walks, o.walk_offset, o, &ms, stats));
       d->info.walk_kernel_ms += ms;
       d->info.walk_launches += 1;
       for (int32_t i : r->order) wdone[i] += add[i];
@@ -1108,8 +1107,6 @@ extern "C" msk_status msk_estimate_dtn_noalloc(msk_ctx* ctx, const msk_mesh* m, 
   L.seed_hi = (uint32_t)(o.seed >> 32);
   L.queue_next = d_qn;
   L.queue_end = d_qe;
-  L.use_lds_top = (o.form == MSK_FORM_PERSISTENT && m->top_nodes > 0) ? 1 : 0;
-  L.n_top = m->top_nodes;
   L.accum = o.accum;
   shape_launch(L, {M}, o, ctx->n_cu);
   HIP_TRY(ctx, launch_init_queues(d_qn, d_qe, make_queues(L.n_slots, walks), s));
@@ -1625,11 +1622,10 @@ extern "C" msk_status msk_estimate_psd(msk_ctx* ctx, const msk_mesh* m, const ms
   std::vector<MeshDev> meshes{M};
   std::vector<RowSlot> slots(r->order.size());
   for (size_t i = 0; i < slots.size(); ++i) slots[i] = RowSlot{0, r->order[i], 0u};
-  const int use_lds = (o.form == MSK_FORM_PERSISTENT && m->top_nodes > 0) ? 1 : 0;
   double walk_ms = 0;
   int64_t stats[3] = {0, 0, 0};
   {
-    msk_status ws = run_walks(ctx, meshes, slots, W, 0, o, use_lds, m->top_nodes, &walk_ms, stats);
+    msk_status ws = run_walks(ctx, meshes, slots, W, 0, o, &walk_ms, stats);
     if (ws != MSK_OK) return cleanup(ws);
   }
   HIP_P(hipEventRecord(ev[2], s));
@@ -2444,12 +2440,11 @@ extern "C" msk_status msk_autotune(msk_ctx* ctx, int32_t n, msk_mesh* const* mes
     oc.chunk = chunk;
     oc.regen_min = regen;
     oc.blocks_per_cu = bpc;
-    const int use_lds = (n == 1 && meshes[0]->top_nodes > 0) ? 1 : 0;
     double best = 1e300;
     for (int r = 0; r < std::max(1, sp.repeats); ++r) {
       double ms = 0;
       int64_t st3[3] = {0, 0, 0};
-      msk_status st = run_walks(ctx, mds, slots, sp.trial_walks, 0, oc, use_lds, meshes[0]->top_nodes, &ms, st3);
+      msk_status st = run_walks(ctx, mds, slots, sp.trial_walks, 0, oc, &ms, st3);
       if (st != MSK_OK) return st;
       best = std::min(best, ms);
       ++trials;

@@ -108,7 +108,6 @@ struct MeshDev {
   const int32_t* slot_of_tri;  // original face -> slot
   const int32_t* faces;        // original faces (n_tris x 3)
   int64_t n_tris;
-  int32_t n_top;               // nodes of this mesh that may be read from LDS
   int32_t leaf;                // most triangles of a leaf
   int32_t mode;                // RowMode
   float radius;                // bounding-sphere radius (float)
@@ -175,8 +174,7 @@ struct WalkLaunch {
   int32_t regen_min;
   int32_t max_owners;          // persistent form: lanes of a wavefront that carry a walk (1..64)
   int32_t unit_shift;          // persistent form: triangles of a listed leaf unit, 2^unit_shift >= the leaf widths
-  int32_t use_lds_top;         // single-mesh launch: stage mesh 0's top nodes in LDS
-  int32_t n_top;
+  int32_t rows;                // persistent form: 1 all meshes have point rows, 2 tangent balls (PSD), else 0
   unsigned long long* stats;   // optional: [nodes visited, triangles tested, FP32 operations]
   int32_t accum;               // persistent form, wavefront row-table partial sums:
                                // 0 FP64, 1 FP32, 2 compensated FP32 (double-float pairs)

@@ -430,12 +430,21 @@ struct CoopScratch {
   uint32_t open[64];         // owner's items on the stack
   unsigned long long key[64];
   int32_t rec_slot[64];
-  uint32_t pend[kPendCap];
-  float pend_l2[kPendCap];
+  union {
+    struct {
+      uint32_t pend[kPendCap];
+      float pend_l2[kPendCap];
+    };
+    double sum[2][64];  // record_point_walks, with nothing pending
+  };
 };
 
 // A value that all lanes of the wavefront share, in a scalar register.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
+}
 
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -580,15 +589,19 @@ __device__ __forceinline__ void answer_bary(const TriRec* tris, float px, float 
   if (region == 6) h.den = den;
 }
 
-// One trip of the wavefront (all lanes call it). `warm` names the warm-start
-// slot of an owner whose search was just started (else negative; cleared).
+// One pass of the wavefront (all lanes call it). With `trip` it is a trip of
+// the search; without, it only runs the pending exact tests of the owners in
+// `done`. `warm` names the warm-start slot of an owner whose search was just
+// started (else negative; cleared by a trip). Both kinds share one copy of the
+// exact test: the walk kernel's loop is long enough to miss the instruction
+// cache.
 template <bool kStats>
-__device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint32_t& size, int32_t& warm,
-                                            int unit_shift, uint32_t& npend, TravCount& cnt) {
+__device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool trip, uint64_t done, uint32_t& size,
+                                            int32_t& warm, int unit_shift, uint32_t& npend, TravCount& cnt) {
   size = uniform(size);
   npend = uniform(npend);
   const int32_t room = ((int32_t)kItemLimit - (int32_t)size) / 3;
-  const uint32_t n = min(min(64u, size), (uint32_t)max(room, 1));
+  const uint32_t n = trip ? min(min(64u, size), (uint32_t)max(room, 1)) : 0u;
   const bool tr = lane < n;
   float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
   int32_t cc[4] = {0, 0, 0, 0};
@@ -632,10 +645,11 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
     }
   }
   size -= n;
-  nu += warm >= 0 ? 1u : 0u;
+  uint32_t total = 0;
   bool force = false;
-  if (__ballot(nu > 0) != 0) {
-    uint32_t total;
+  if (trip) {
+    done = ~0ull;
+    nu += warm >= 0 ? 1u : 0u;
     uint32_t pos = size + wave_prefix_small(nu, total);
     lds_order();
     if (warm >= 0) W->item[pos++] = ((uint32_t)warm >> 2 << 6) | lane;
@@ -647,9 +661,15 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
       cnt.flops += (nu << unit_shift) * kQuickFlops;
     }
     lds_order();
-    const uint32_t upr = 64u >> unit_shift;  // units per round
-    for (uint32_t u0 = 0; u0 < total; u0 += upr) {
-      if (npend > (uint32_t)(kPendCap - 64)) npend = flush_pending<kStats>(W, lane, npend, ~0ull, cnt);
+  }
+  const uint32_t upr = 64u >> unit_shift;  // units per round
+  bool flush = !trip && npend != 0;
+  uint32_t u0 = 0;
+  while (true) {
+    if (flush || (npend > (uint32_t)(kPendCap - 64) && u0 < total)) {
+      npend = flush_pending<kStats>(W, lane, npend, done, cnt);
+      flush = false;
+    } else if (u0 < total) {
       const uint32_t u = u0 + (lane >> unit_shift);
       bool cand = false;
       uint32_t word = 0;
@@ -679,10 +699,14 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
       }
       npend += (uint32_t)__popcll(mk);
       lds_order();
+      u0 += upr;
+      // triangles without an upper value bound nothing until they are tested
+      flush = u0 >= total && __ballot(force) != 0;
+    } else {
+      break;
     }
-    // triangles without an upper value bound nothing until they are tested
-    if (__ballot(force) != 0) npend = flush_pending<kStats>(W, lane, npend, ~0ull, cnt);
   }
+  if (!trip) return;
   warm = -1;
   uint32_t pushed = 0;
   bool put[4] = {false, false, false, false};
@@ -717,6 +741,11 @@ __device__ __forceinline__ void search_trip(CoopScratch* W, uint32_t lane, uint3
 }
 
 // ------------------------------------------------------ walk machinery
+
+// Rows that a launch's walks start from: the instantiations for point rows and
+// for the PSD estimator's tangent balls leave the other starts and
+// contributions out of the persistent kernel's code.
+enum RowKind { kRowsAny, kRowsPoints, kRowsBalls };
 
 struct LaneWalk {
   float x, y, z;
@@ -774,12 +803,12 @@ __device__ bool ball_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_
 // Start of a walk: sample s (point rows: the fixed sample; hat rows:
 // s ~ phi_i / A_i on the vertex's one-ring), inset it along the face normal.
 // Returns false if the row is discarded.
-template <typename MD>
+template <RowKind kRows, typename MD>
 __device__ bool walk_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_t& face, double lam[3]) {
-  if (M.ball_r) return ball_start(L, M, w, face);
+  if (kRows == kRowsBalls || (kRows == kRowsAny && M.ball_r)) return ball_start(L, M, w, face);
   const float sgn = M.side ? 1.0f : -1.0f;
   float sx, sy, sz, nx, ny, nz;
-  if (M.mode == kRowsPoint) {
+  if (kRows == kRowsPoints || M.mode == kRowsPoint) {
     if (gload(M.discarded, w.row)) return false;
     face = gload(M.tri, w.row);
     sx = gload(M.p, 3 * w.row); sy = gload(M.p, 3 * w.row + 1); sz = gload(M.p, 3 * w.row + 2);
@@ -962,10 +991,10 @@ __device__ __noinline__ int knn_at_hit(const MeshDev& M, const Nearest& hit, int
 // Contribution of a finished walk to its row, emitted once per column:
 // point rows emit b(t) (the start is fixed per row; the finalisation folds
 // in b(s)), hat rows emit c = b(s) - b(t). Escaped walks have b(t) = 0.
-template <bool kKnn, typename MD, typename Emit>
+template <bool kKnn, RowKind kRows, typename MD, typename Emit>
 __device__ void walk_contrib(const WalkLaunch& L, const MD& M, const LaneWalk& w, bool has_t, const Nearest& hit,
                              Emit emit) {
-  if (M.ball_r) return;  // PSD walks: the rank-one updates are formed from the walk log
+  if (kRows == kRowsBalls || (kRows == kRowsAny && M.ball_r)) return;  // PSD walks: the rank-one updates are formed from the walk log
   if constexpr (kKnn) {  // point basis: b(t) from the hit point's k nearest samples (point rows)
     if (M.knn.k > 0) {
       if (has_t) {
@@ -988,13 +1017,13 @@ __device__ void walk_contrib(const WalkLaunch& L, const MD& M, const LaneWalk& w
     const double l1 = b1, l2 = b2;
     tw[0] = (1.0 - l1) - l2; tw[1] = l1; tw[2] = l2;
   }
-  if (M.mode == kRowsPoint) {
+  if (kRows == kRowsPoints || M.mode == kRowsPoint) {
     if (has_t) merge_rows<3>(M, tv, tw, emit);
   } else {
     int32_t face;
     double lam[3];
     LaneWalk tmp = w;
-    walk_start(L, M, tmp, face, lam);
+    walk_start<kRows>(L, M, tmp, face, lam);
     const int64_t f3 = 3 * (int64_t)face;
     const int32_t f[3] = {gload(M.faces, f3), gload(M.faces, f3 + 1), gload(M.faces, f3 + 2)};
     const int32_t vv[6] = {f[0], f[1], f[2], tv[0], tv[1], tv[2]};
@@ -1036,7 +1065,7 @@ __device__ void walk_finish_global(const WalkLaunch& L, const MD& M, const LaneW
   const bool has_t = walk_has_t(M, status, hit);
   double* a1 = M.acc1 + (int64_t)w.row * M.K;
   double* a2 = M.acc2 + (int64_t)w.row * M.K;
-  walk_contrib<kKnn>(L, M, w, has_t, hit, [&](int32_t j, double v) {
+  walk_contrib<kKnn, kRowsAny>(L, M, w, has_t, hit, [&](int32_t j, double v) {
     gadd(a1, j, v);
     gadd(a2, j, v * v);
   });
@@ -1065,6 +1094,7 @@ __device__ void walk_finish_global(const WalkLaunch& L, const MD& M, const LaneW
 #define MSK_TABLE_SLOT_BITS 6
 #endif
 constexpr int kSlotBits = MSK_TABLE_SLOT_BITS, kSlots = 1 << kSlotBits, kProbes = 8, kWaves = 4;
+static_assert(kSlots == 64, "record_point_walks harvests one slot per lane");
 constexpr int32_t kEmptyKey = -1;
 
 // Compensated FP32 partial sum: the value is hi + lo, a double-float pair.
@@ -1112,6 +1142,11 @@ __device__ __forceinline__ void lds_acc_add(CompF32* p, double v) {
   } while (old != seen);
 }
 
+// The same additions where one lane alone adds to the slot.
+__device__ __forceinline__ void slot_add(double* p, double v) { *p += v; }
+__device__ __forceinline__ void slot_add(float* p, double v) { *p += (float)v; }
+__device__ __forceinline__ void slot_add(CompF32* p, double v) { lds_acc_add(p, v); }
+
 template <typename AccT>
 struct WaveTables {
   int32_t key[kWaves][2][kSlots];
@@ -1138,17 +1173,127 @@ __device__ __forceinline__ void table_add(WaveTables<AccT>& T, int wi, int t, in
   gadd(g2, j, v * v);
 }
 
-template <typename AccT, bool kKnn = false, typename MD>
-__device__ void walk_finish_table(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status,
-                                  const Nearest& hit, WaveTables<AccT>& T, int wi) {
+// Records an ended walk: its row's counters and log, and (with `contrib`) its
+// contribution, into its row table if it has one, else into the row itself.
+template <typename AccT, bool kKnn, RowKind kRows, typename MD>
+__device__ void walk_finish(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status, bool contrib,
+                            const Nearest& hit, WaveTables<AccT>& T, int wi) {
   const bool has_t = walk_has_t(M, status, hit);
-  double* a1 = M.acc1 + (int64_t)w.row * M.K;
-  double* a2 = M.acc2 + (int64_t)w.row * M.K;
-  walk_contrib<kKnn>(L, M, w, has_t, hit, [&](int32_t j, double v) { table_add(T, wi, w.tab, j, v, a1, a2); });
-  atomicAdd(&T.cnt[wi][w.tab][0], (unsigned long long)w.queries);
-  if (status == kEscaped) atomicAdd(&T.cnt[wi][w.tab][1], 1ull);
-  if (status == kCapped) atomicAdd(&T.cnt[wi][w.tab][2], 1ull);
+  const bool tab = w.tab >= 0;
+  if (contrib) {
+    double* a1 = M.acc1 + (int64_t)w.row * M.K;
+    double* a2 = M.acc2 + (int64_t)w.row * M.K;
+    walk_contrib<kKnn, kRows>(L, M, w, has_t, hit, [&](int32_t j, double v) {
+      if (tab) {
+        table_add(T, wi, w.tab, j, v, a1, a2);
+      } else {
+        gadd(a1, j, v);
+        gadd(a2, j, v * v);
+      }
+    });
+  }
+  if (tab) {
+    atomicAdd(&T.cnt[wi][w.tab][0], (unsigned long long)w.queries);
+    if (status == kEscaped) atomicAdd(&T.cnt[wi][w.tab][1], 1ull);
+    if (status == kCapped) atomicAdd(&T.cnt[wi][w.tab][2], 1ull);
+  } else {
+    gadd(M.row_queries, w.row, (unsigned long long)w.queries);
+    if (status == kEscaped) gadd(M.row_escaped, w.row, 1ull);
+    if (status == kCapped) gadd(M.row_capped, w.row, 1ull);
+  }
   walk_record(L, M, w, status, has_t, hit);
+}
+
+__device__ __forceinline__ double shfl_f64(double v, int src) {
+  const int lo = __shfl(__double2loint(v), src), hi = __shfl(__double2hiint(v), src);
+  return __hiloint2double(hi, lo);
+}
+
+// Contributions of ended point-row walks with a row table and a per-vertex
+// basis table, two walks at a time, 32 lanes each (all lanes of the wavefront
+// call it; `mine`: this lane's walk is one). The entries of the hit triangle's
+// three table rows are read at once, one per lane; equal columns meet in the
+// row table's slots, where their FP64 sum v forms before it goes into sum v and
+// sum v^2. Merged by one lane per walk, entry by entry, each of up to 24
+// columns waited for a load and a chain of LDS atomics: 13% of the soup
+// operator's time. Walks whose columns do not fit their row table are left for
+// walk_finish: the lanes whose walk is done get true.
+template <typename AccT, typename MD>
+__device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, uint32_t lane, bool mine, int32_t tab,
+                                                   const Nearest& hit, WaveTables<AccT>& T, int wi) {
+  int32_t p[3] = {0, 0, 0}, n[3] = {0, 0, 0};
+  double wt[3] = {0.0, 0.0, 0.0};
+  if (mine) {
+    float b1, b2;
+    nearest_bary(hit, b1, b2);
+    wt[1] = b1;
+    wt[2] = b2;
+    wt[0] = (1.0 - wt[1]) - wt[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int32_t v = gload(M.faces, 3 * (int64_t)hit.orig + k);
+      p[k] = gload(M.b_rowptr, v);
+      n[k] = wt[k] != 0.0 ? gload(M.b_rowptr, v + 1) - p[k] : 0;
+    }
+  }
+  W->sum[0][lane] = 0.0;
+  W->sum[1][lane] = 0.0;
+  lds_order();
+  const int half = (int)(lane >> 5);
+  bool ok = mine;
+  // the wavefront's walks lie on one mesh (their base and table pointers
+  // differ otherwise): those of the others wait for their own turn
+  for (uint64_t todo = __ballot(mine); todo != 0;) {
+    const int a = __ffsll((unsigned long long)todo) - 1;
+    todo &= todo - 1;
+    const int b = todo != 0 ? __ffsll((unsigned long long)todo) - 1 : -1;
+    todo &= todo - (b >= 0 ? 1 : 0);
+    const int src = half ? max(b, 0) : a;
+    const bool valid = half == 0 || b >= 0;
+    const int32_t n0 = __shfl(n[0], src), n1 = __shfl(n[1], src), n2 = __shfl(n[2], src);
+    const int32_t p0 = __shfl(p[0], src), p1 = __shfl(p[1], src), p2 = __shfl(p[2], src);
+    const double w0 = shfl_f64(wt[0], src), w1 = shfl_f64(wt[1], src), w2 = shfl_f64(wt[2], src);
+    const uint64_t cp = (uint64_t)__shfl((unsigned long long)(uintptr_t)M.b_col, src);
+    const uint64_t vp = (uint64_t)__shfl((unsigned long long)(uintptr_t)M.b_val, src);
+    const int32_t t = __shfl(tab, src);
+    const int32_t tot = valid ? n0 + n1 + n2 : 0;
+    bool fail = false;
+    for (int32_t e = (int32_t)(lane & 31u); __ballot(e < tot) != 0; e += 32) {
+      if (e < tot) {
+        const int32_t i = e < n0 ? p0 + e : (e < n0 + n1 ? p1 + e - n0 : p2 + e - n0 - n1);
+        const double wk = e < n0 ? w0 : (e < n0 + n1 ? w1 : w2);
+        const int32_t j = gload((const int32_t*)cp, i);
+        const double v = wk * (double)gload((const float*)vp, i);
+        const uint32_t h = ((uint32_t)j * 2654435761u) >> (32 - kSlotBits);
+        bool placed = false;
+        for (int q = 0; q < kProbes && !placed; ++q) {
+          const uint32_t si = (h + (uint32_t)q) & (kSlots - 1);
+          const int32_t old = atomicCAS(&T.key[wi][t][si], kEmptyKey, j);
+          placed = old == kEmptyKey || old == j;
+          if (placed) atomicAdd(&W->sum[half][si], v);
+        }
+        fail |= !placed;
+      }
+    }
+    lds_order();
+    const uint64_t bad = __ballot(fail);
+    const int32_t ta = __shfl(tab, a), tb = __shfl(tab, max(b, 0));
+    const double xa = W->sum[0][lane], xb = W->sum[1][lane];
+    if (xa != 0.0 && (uint32_t)bad == 0u) {
+      slot_add(&T.v1[wi][ta][lane], xa);
+      slot_add(&T.v2[wi][ta][lane], xa * xa);
+    }
+    if (xb != 0.0 && (uint32_t)(bad >> 32) == 0u) {
+      slot_add(&T.v1[wi][tb][lane], xb);
+      slot_add(&T.v2[wi][tb][lane], xb * xb);
+    }
+    W->sum[0][lane] = 0.0;
+    W->sum[1][lane] = 0.0;
+    if ((uint32_t)bad != 0u && (int)lane == a) ok = false;
+    if ((uint32_t)(bad >> 32) != 0u && (int)lane == b) ok = false;
+    lds_order();
+  }
+  return ok;
 }
 
 // Wavefront-cooperative flush of table t into row `row` of mesh `mesh`.
@@ -1284,7 +1429,7 @@ __global__ void __launch_bounds__(256) walk_plain_kernel(WalkLaunch L) {
   GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
   int32_t face;
   double lam[3];
-  if (!walk_start(L, M, w, face, lam)) return;
+  if (!walk_start<kRowsAny>(L, M, w, face, lam)) return;
   Nearest hit;
   int32_t st;
   do {
@@ -1338,11 +1483,11 @@ __device__ unsigned long long g_phase_cycles[16];
 // At most L.max_owners lanes of a wavefront carry a walk: a launch of few
 // walks spreads them over all wavefronts. The walks, their queries and their
 // results are those of the other forms.
-template <bool kStats, typename AccT, bool kKnn = false>
+template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   __shared__ WaveTables<AccT> T;
   __shared__ CoopScratch coop[kWaves];
-  const int wi = threadIdx.x >> 6;
+  const int wi = (int)uniform(threadIdx.x >> 6);
   CoopScratch* W = &coop[wi];
   for (int i = threadIdx.x; i < kWaves * 2 * kSlots; i += blockDim.x) {
     (&T.key[0][0][0])[i] = kEmptyKey;
@@ -1364,87 +1509,99 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   w.active = 0;
   w.tab = -1;
   // lane's state: mode 0 no walk, 1 searching, 2 search ended, 3 walk ended
-  // (its result stays in the wavefront's scratch, fin_status, until the next
-  // bookkeeping pass records it)
+  // (its answer stays in the wavefront's scratch until the next bookkeeping
+  // pass records it), 4 at its start
   int32_t mode = 0, fin_status = -1, warm = -1;
   bool capped = false;
   uint32_t npend = 0, size = 0;  // pending exact tests and stack items of the wavefront (uniform)
-  TravCount cnt;       // statistics kernels: this lane's share of the work
+  TravCount cnt;                 // statistics kernels: this lane's share of the work
   bool drained = false;
 #if MSK_PHASE_TIMING
   uint64_t ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #endif
-  auto start_query = [&](GlobalMesh& M) {
-    search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z);
-    warm = w.slot;
-    mode = 1;
-  };
   while (true) {
-    // ---- bookkeeping, when enough lanes wait or none traverses: ended walks
-    // are recorded and idle lanes take new walks
     MSK_TICK(tk0);
-    // ---- steps whose search has ended: run their pending exact tests, finish
-    // the step and start the next one, once kStepMin lanes wait (a quarter of
-    // the wavefront's walks if that is less) or the stack is empty; an ended
-    // walk waits for the bookkeeping pass below
-    {
-      if (mode == 1 && W->open[lane] == 0) mode = 2;
-      const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
-      if (pend != 0 && size <= (uint32_t)kRootLimit &&
-          (size == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2))) {
-        if (npend != 0) npend = flush_pending<kStats>(W, lane, npend, pend, cnt);
-        bool fresh = false;
-        if (mode == 2) {
-          Nearest hit;
+    if (mode == 1 && W->open[lane] == 0) mode = 2;
+    // ---- what this pass does: `step` finishes the steps whose search has
+    // ended and starts the next ones, once kStepMin lanes wait (a quarter of
+    // the wavefront's walks if that is less) or the stack is empty; `book`
+    // records ended walks and hands out new ones, once L.regen_min lanes wait
+    // (those of ended walks no longer count when the queues are empty: they
+    // wait for the last one) or no search is left; else a trip of the search
+    const uint64_t pend = __ballot(mode == 2 || mode == 4), busy = __ballot(mode == 1) | pend;
+    const bool step = pend != 0 && size <= (uint32_t)kRootLimit &&
+                      (size == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
+    const bool book =
+        !step && (size == 0 || (!drained && (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min));
+    search_pass<kStats>(W, lane, !step && !book, step ? pend : ~0ull, size, warm, unit_shift, npend, cnt);
+    MSK_TICK(tk1);
+    MSK_ACC(1, tk0, tk1);
+#if MSK_PHASE_TIMING
+    ph[6] += !step && !book;
+    ph[7] += book;
+#endif
+    if (step) {
+      bool fresh = false;
+      int32_t st = -1;
+      GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.active ? w.mesh : 0];
+      bool go = mode == 4;
+      if (mode == 2) {
+        Nearest hit;
+        if (search_answer(W, lane, hit)) {
+          st = walk_end(M, w, capped, hit);
+          go = st < 0;
+        } else {
           fresh = true;
           mode = 1;
-          if (search_answer(W, lane, hit)) {
-            GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
-            int32_t st = walk_end(M, w, capped, hit);
-            if (st < 0) {
-              st = walk_begin(L, M, w, capped);
-              if (st < 0) start_query(M);
-            }
-            if (st >= 0) {
-              fin_status = st;
-              mode = 3;
-              fresh = false;
-            }
-          }
         }
-        search_push(W, lane, fresh, size);
       }
+      if (go) {
+        st = walk_begin(L, M, w, capped);
+        if (st < 0) {
+          search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z);
+          warm = w.slot;
+          fresh = true;
+          mode = 1;
+        }
+      }
+      if (st >= 0) {
+        fin_status = st;
+        mode = 3;
+      }
+      search_push(W, lane, fresh, size);
+      MSK_TICK(tk2);
+      MSK_ACC(5, tk1, tk2);
     }
-    MSK_TICK(tk0b);
-    MSK_ACC(5, tk0, tk0b);
-    // (once the queues are empty there is nothing to hand out: ended walks
-    // then wait for the last one)
-    if (size == 0 || (!drained && size <= (uint32_t)kRootLimit &&
-                      (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min)) {
-#if MSK_PHASE_TIMING
-      ph[7] += 1;
-#endif
-      bool fin = false;
-      int32_t fin_tab = -1;
+    if (book) {
       MSK_TICK(tb0);
-      if (mode == 3) {
-        GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
+      const bool fin = mode == 3;
+      const int32_t fin_tab = fin ? w.tab : -1;
+      {
+        GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.active ? w.mesh : 0];
         Nearest hit;
-        const unsigned long long k = W->key[lane];
-        hit.d2 = __uint_as_float((uint32_t)(k >> 32));
-        hit.orig = (int32_t)(uint32_t)k;
-        hit.slot = W->rec_slot[lane];
-        const float4 q = W->pt[lane];
-        answer_bary(M.tris, q.x, q.y, q.z, hit);
-        if (w.tab >= 0)
-          walk_finish_table<AccT, kKnn>(L, M, w, fin_status, hit, T, wi);
-        else
-          walk_finish_global<kKnn>(L, M, w, fin_status, hit);
-        fin = true;
-        fin_tab = w.tab;
-        w.active = 0;
-        w.tab = -1;
-        mode = 0;
+        hit.d2 = INFINITY;
+        hit.orig = INT_MAX;
+        hit.slot = -1;
+        hit.l1 = hit.l2 = 0.0f;
+        if (fin && fin_status != kEscaped) {
+          const unsigned long long k = W->key[lane];
+          hit.d2 = __uint_as_float((uint32_t)(k >> 32));
+          hit.orig = (int32_t)(uint32_t)k;
+          hit.slot = W->rec_slot[lane];
+          const float4 q = W->pt[lane];
+          answer_bary(M.tris, q.x, q.y, q.z, hit);
+        }
+        bool done = false;
+        if constexpr (kRows == kRowsPoints && !kKnn) {
+          const bool mine = fin && w.tab >= 0 && walk_has_t(M, fin_status, hit);
+          done = record_point_walks(M, W, lane, mine, w.tab, hit, T, wi);
+        }
+        if (fin) {
+          walk_finish<AccT, kKnn, kRows>(L, M, w, fin_status, !done, hit, T, wi);
+          w.active = 0;
+          w.tab = -1;
+          mode = 0;
+        }
       }
       MSK_TICK(tb1);
       MSK_ACC(2, tb0, tb1);
@@ -1469,9 +1626,9 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
             start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + q,
                                            (unsigned long long)L.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
-          start = (uint64_t)__shfl((unsigned long long)start, 0);
+          start = uniform64(start);  // the first lane's
           const int q = (qhome + qi) & 7;
-          const uint64_t qend = gload(L.queue_end, q);
+          const uint64_t qend = uniform64(gload(L.queue_end, q));
           if (start >= qend) {
             ++qi;
             if (qi >= 8) drained = true;
@@ -1481,8 +1638,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           cend = min(start + (uint64_t)L.chunk, qend);
           // the chunk's row takes the table it already has, else a free one
           const auto& rs = ((const MSK_GLOBAL RowSlot*)L.slots)[start / (uint64_t)L.walks_per_slot];
-          c_mesh = rs.mesh;
-          c_row = rs.row;
+          c_mesh = (int32_t)uniform((uint32_t)rs.mesh);
+          c_row = (int32_t)uniform((uint32_t)rs.row);
           c_tab = -1;
           for (int t2 = 0; t2 < 2; ++t2)
             if (t_used[t2] && t_mesh[t2] == c_mesh && t_row[t2] == c_row) c_tab = t2;
@@ -1499,64 +1656,34 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         const uint32_t rank = __popcll(idle & ((1ull << lane) - 1ull));
         const uint64_t avail = cend - cur;
         const uint32_t take = (uint32_t)min(avail, (uint64_t)__popcll(idle));
-        bool fresh = false, root = false;
+        bool fresh = false;
         if (owner && !w.active && rank < take) {
           decode_walk(L, cur + rank, w);
           int32_t face;
           double lam[3];
           GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
-          w.active = walk_start(L, M, w, face, lam) ? 1 : 0;
+          w.active = walk_start<kRows>(L, M, w, face, lam) ? 1 : 0;
           w.tab = (w.active && c_tab >= 0 && w.mesh == c_mesh && w.row == c_row) ? c_tab : -1;
-          if (w.active) {
-            const int32_t s0 = walk_begin(L, M, w, capped);
-            if (s0 < 0) {
-              start_query(M);
-              root = true;
-              fresh = w.tab >= 0;
-            } else {  // left the bounding sphere at once and escaped
-              Nearest hit;
-              hit.d2 = INFINITY;
-              hit.orig = INT_MAX;
-              hit.slot = -1;
-              hit.l1 = hit.l2 = 0.0f;
-              if (w.tab >= 0)
-                walk_finish_table<AccT, kKnn>(L, M, w, s0, hit, T, wi);
-              else
-                walk_finish_global<kKnn>(L, M, w, s0, hit);
-              w.active = 0;
-              w.tab = -1;
-            }
-          }
+          mode = w.active ? 4 : 0;
+          fresh = w.tab >= 0;
         }
-        search_push(W, lane, root, size);
         if (c_tab >= 0) t_out[c_tab] += (int32_t)__popcll(__ballot(fresh));
         cur += take;
         idle = __ballot(owner && !w.active);
-        // lanes whose row was discarded, or whose walk ended at once, stay idle
+        // lanes whose row was discarded stay idle
       }
       MSK_TICK(tb3);
       MSK_ACC(4, tb2, tb3);
-      if (__ballot(w.active) == 0) {
-        if (drained) {
-          for (int t2 = 0; t2 < 2; ++t2)
-            if (t_used[t2]) {
-              table_flush(L, T, wi, t2, t_mesh[t2], t_row[t2]);
-              t_used[t2] = 0;
-            }
-          break;
-        }
-        continue;
+      MSK_ACC(0, tb0, tb3);
+      if (drained && __ballot(w.active) == 0) {
+        for (int t2 = 0; t2 < 2; ++t2)
+          if (t_used[t2]) {
+            table_flush(L, T, wi, t2, t_mesh[t2], t_row[t2]);
+            t_used[t2] = 0;
+          }
+        break;
       }
     }
-    MSK_TICK(tk1);
-    MSK_ACC(0, tk0, tk1);
-    if (size == 0) continue;
-#if MSK_PHASE_TIMING
-    ph[6] += 1;
-#endif
-    search_trip<kStats>(W, lane, size, warm, unit_shift, npend, cnt);
-    MSK_TICK(tk4);
-    MSK_ACC(1, tk1, tk4);
   }
   if (kStats && L.stats) {
     atomicAdd(L.stats, (unsigned long long)cnt.nodes);
@@ -1809,7 +1936,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
                         const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t unit_shift,
                         int32_t* __restrict__ tri, float* __restrict__ d2, float* __restrict__ bary) {
   __shared__ CoopScratch coop[kWaves];
-  const int wi = threadIdx.x >> 6;
+  const int wi = (int)uniform(threadIdx.x >> 6);
   CoopScratch* W = &coop[wi];
   const uint32_t lane = __lane_id();
   const int64_t G = (int64_t)gridDim.x * kWaves, g = (int64_t)blockIdx.x * kWaves + wi;
@@ -1823,9 +1950,10 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
   while (true) {
     if (mode == 1 && W->open[lane] == 0) mode = 2;
     const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
-    if (size == 0 || (size <= (uint32_t)kRootLimit &&
-                      (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2))) {
-      if (npend != 0) npend = flush_pending<false>(W, lane, npend, pend, cnt);
+    const bool step = size == 0 || (size <= (uint32_t)kRootLimit &&
+                                    (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
+    search_pass<false>(W, lane, !step, pend, size, warm, unit_shift, npend, cnt);
+    if (step) {
       bool fresh = false;
       if (mode == 2) {
         Nearest h;
@@ -1869,12 +1997,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
         next += got;
       }
       search_push(W, lane, fresh, size);
-      if (size == 0) {
-        if (drained && __ballot(mode != 0) == 0) break;
-        continue;
-      }
+      if (drained && __ballot(mode != 0) == 0) break;
     }
-    search_trip<false>(W, lane, size, warm, unit_shift, npend, cnt);
   }
 }
 
@@ -1959,29 +2083,38 @@ hipError_t launch_walk_plain(const WalkLaunch& L, hipStream_t s) {
 hipError_t launch_walk_persistent(const WalkLaunch& L, int grid, hipStream_t s) {
   if (L.knn && L.stats) return hipErrorInvalidValue;  // the point basis has no counting instantiation
   if (L.accum < 0 || L.accum > 2) return hipErrorInvalidValue;
-  if (L.knn) {  // point basis: instantiations carrying the k-NN evaluation
+  const dim3 g(grid), t(256);
+#define MSK_LAUNCH(AccT, knn, rows) hipLaunchKernelGGL((walk_stream_kernel<false, AccT, knn, rows>), g, t, 0, s, L)
+#define MSK_LAUNCH_ACC(knn, rows)                                              \
+  do {                                                                         \
+    if (L.accum == 1)                                                          \
+      MSK_LAUNCH(float, knn, rows);                                            \
+    else if (L.accum == 2)                                                     \
+      MSK_LAUNCH(CompF32, knn, rows);                                          \
+    else                                                                       \
+      MSK_LAUNCH(double, knn, rows);                                           \
+  } while (0)
+  if (L.stats) {
     if (L.accum == 1)
-      hipLaunchKernelGGL((walk_stream_kernel<false, float, true>), dim3(grid), dim3(256), 0, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, float, false, kRowsAny>), g, t, 0, s, L);
     else if (L.accum == 2)
-      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32, true>), dim3(grid), dim3(256), 0, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, CompF32, false, kRowsAny>), g, t, 0, s, L);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, double, true>), dim3(grid), dim3(256), 0, s, L);
-  } else if (L.accum == 1) {
-    if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, float>), dim3(grid), dim3(256), 0, s, L);
+      hipLaunchKernelGGL((walk_stream_kernel<true, double, false, kRowsAny>), g, t, 0, s, L);
+  } else if (L.rows == 2) {  // PSD walks: no contributions, no row tables
+    MSK_LAUNCH(double, false, kRowsBalls);
+  } else if (L.knn) {  // point basis: instantiations carrying the k-NN evaluation
+    if (L.rows == 1)
+      MSK_LAUNCH_ACC(true, kRowsPoints);
     else
-      hipLaunchKernelGGL((walk_stream_kernel<false, float>), dim3(grid), dim3(256), 0, s, L);
-  } else if (L.accum == 2) {
-    if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, CompF32>), dim3(grid), dim3(256), 0, s, L);
-    else
-      hipLaunchKernelGGL((walk_stream_kernel<false, CompF32>), dim3(grid), dim3(256), 0, s, L);
+      MSK_LAUNCH_ACC(true, kRowsAny);
+  } else if (L.rows == 1) {
+    MSK_LAUNCH_ACC(false, kRowsPoints);
   } else {
-    if (L.stats)
-      hipLaunchKernelGGL((walk_stream_kernel<true, double>), dim3(grid), dim3(256), 0, s, L);
-    else
-      hipLaunchKernelGGL((walk_stream_kernel<false, double>), dim3(grid), dim3(256), 0, s, L);
+    MSK_LAUNCH_ACC(false, kRowsAny);
   }
+#undef MSK_LAUNCH_ACC
+#undef MSK_LAUNCH
   return hipGetLastError();
 }
 

@@ -321,7 +321,6 @@ std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t
 }
 
 void align_leaves(HostBvh& b) {
-  const int32_t align = b.leaf_size <= 4 ? 4 : 8;
   TriRec pad;
   pad.a = pad.b = pad.c = make_float4(0.f, 0.f, 0.f, 0.f);
   const int32_t pad_index = kPadTri;
@@ -332,16 +331,26 @@ void align_leaves(HostBvh& b) {
     for (int k = 0; k < 4; ++k) {
       if (w.child[k] >= 0 || w.count[k] == 0) continue;
       const int32_t first = -w.child[k] - 1;
-      w.child[k] = -(int32_t)tris.size() - 1;
+      w.child[k] = -((int32_t)tris.size() + (w.count[k] - 1) / 4) - 1;
       for (int32_t i = first; i < first + w.count[k]; ++i) {
         int32_t t;
         std::memcpy(&t, &b.tris[i].a.w, 4);
         b.slot_of_tri[t] = (int32_t)tris.size();
         tris.push_back(b.tris[i]);
       }
-      while (tris.size() % align) tris.push_back(pad);
+      while (tris.size() % 4) tris.push_back(pad);
     }
   b.tris.swap(tris);
+  // levels 0, 1, 2 (nodes 0; 1-4; 5-20) with four inner children each
+  b.entry = 1;
+  for (size_t level = 1, i = 0; level <= 16; level *= 4) {
+    bool full = i + level <= b.nodes.size();
+    for (size_t j = i; full && j < i + level; ++j)
+      for (int k = 0; k < 4; ++k) full = full && b.nodes[j].child[k] >= 0;
+    if (!full) break;
+    b.entry = (int)(4 * level);
+    i += level;
+  }
 }
 
 }  // namespace msk

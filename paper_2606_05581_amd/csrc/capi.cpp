@@ -32,7 +32,7 @@ struct msk_mesh {
   double centre[3] = {0, 0, 0};
   double radius = 0, area = 0;
   int64_t nv = 0, nf = 0, n_nodes = 0;
-  int depth = 0, leaf_size = 4, top_nodes = 85;
+  int depth = 0, leaf_size = 4, entry = 1, top_nodes = 85;
   Node4* d_nodes = nullptr;   // one allocation holds the nodes,
   TriRec* d_tris = nullptr;   // the triangles
   float4* d_quick = nullptr;  // and their prefilter records
@@ -252,6 +252,7 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   m->n_nodes = (int64_t)B.nodes.size();
   m->depth = B.depth;
   m->leaf_size = leaf;
+  m->entry = B.entry;
   m->top_nodes = (int)std::min<int64_t>(top, m->n_nodes);
   m->vrel.resize((size_t)n_verts * 3);
   for (int64_t i = 0; i < n_verts; ++i)
@@ -298,7 +299,7 @@ extern "C" msk_status msk_closest_points(msk_ctx* ctx, const msk_mesh* m, const 
   if (!ctx || !m) return MSK_ERR_INVALID_ARG;
   if (nq < 0 || (nq > 0 && (!Q || !tri || !d2 || !bary))) return fail(ctx, MSK_ERR_INVALID_ARG, "bad query arrays");
   if (nq == 0) return MSK_OK;
-  HIP_TRY(ctx, launch_closest_points(m->d_nodes, m->d_tris, m->d_quick, m->leaf_size, (float)m->radius, m->centre, Q,
+  HIP_TRY(ctx, launch_closest_points(m->d_nodes, m->d_tris, m->d_quick, m->entry, (float)m->radius, m->centre, Q,
                                      nq, ctx->n_cu, tri, d2, bary, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return MSK_OK;
@@ -671,7 +672,7 @@ MeshDev make_meshdev(const msk_mesh* m, const msk_rows* r, const msk_basis* b, m
   M.nodes = m->d_nodes;
   M.tris = m->d_tris;
   M.quick = m->d_quick;
-  M.leaf = m->leaf_size;
+  M.entry = m->entry;
   M.slot_of_tri = m->d_slot;
   M.faces = m->d_faces;
   M.n_tris = m->nf;
@@ -747,16 +748,13 @@ static void shape_launch(WalkLaunch& L, const std::vector<MeshDev>& meshes, cons
   }
   L.regen_min = std::min(std::max(1, 3 * L.max_owners / 8), std::min(64, std::max(1, o.regen_min)));
   if (L.max_owners == 64) L.regen_min = std::min(64, std::max(1, o.regen_min));
-  int32_t leaf = 1;
   L.knn = 0;
   bool points = true, balls = true;
   for (const MeshDev& md : meshes) {
     points = points && md.mode == kRowsPoint && !md.ball_r;
     balls = balls && md.ball_r;
-    leaf = std::max(leaf, md.leaf);
     L.knn |= md.knn.k > 0 ? 1 : 0;
   }
-  L.unit_shift = leaf <= 4 ? 2 : 3;
   L.rows = balls ? 2 : (points ? 1 : 0);
 }
 
@@ -2316,6 +2314,7 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   m->n_nodes = (int64_t)B.nodes.size();
   m->depth = B.depth;
   m->leaf_size = leaf;
+  m->entry = B.entry;
   m->top_nodes = (int)std::min<int64_t>(kMaxTop, m->n_nodes);
   return MSK_OK;
 }

@@ -57,6 +57,7 @@ struct HostBvh {
   std::vector<int32_t> slot_of_tri;  // original triangle -> leaf-order slot
   int depth = 0;                     // levels of 4-wide nodes
   int leaf_size = 4;
+  int entry = 1;                     // align_leaves: nodes of the deepest level whose levels above are full
 };
 
 // Builds the scene frame and a 4-wide BVH over float offsets from the
@@ -64,9 +65,10 @@ struct HostBvh {
 std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t nf, int leaf_size, HostBvh& out);
 
 // Moves the triangles so that every leaf starts at a slot that is a multiple
-// of 4 (8 for leaves wider than 4), pads (kPadTri) filling the slots past a
-// shorter leaf: a leaf's prefilter records, which lie in blocks of 4 slots,
-// then fill whole cache lines.
+// of 4, pads (kPadTri) filling the slots past a shorter leaf: a leaf's
+// prefilter records, which lie in blocks of 4 slots, then fill whole cache
+// lines. Leaf references change to -child - 1 = first slot + (blocks - 1).
+// Also finds `entry`.
 void align_leaves(HostBvh& b);
 
 // The same binned-SAH build and 4-wide collapse over any elements given by
@@ -108,7 +110,7 @@ struct MeshDev {
   const int32_t* slot_of_tri;  // original face -> slot
   const int32_t* faces;        // original faces (n_tris x 3)
   int64_t n_tris;
-  int32_t leaf;                // most triangles of a leaf
+  int32_t entry;               // nodes of the deepest full level of the tree: 1, 4, 16 or 64 (HostBvh)
   int32_t mode;                // RowMode
   float radius;                // bounding-sphere radius (float)
   double radius_d;
@@ -173,7 +175,6 @@ struct WalkLaunch {
   int32_t chunk;
   int32_t regen_min;
   int32_t max_owners;          // persistent form: lanes of a wavefront that carry a walk (1..64)
-  int32_t unit_shift;          // persistent form: triangles of a listed leaf unit, 2^unit_shift >= the leaf widths
   int32_t rows;                // persistent form: 1 all meshes have point rows, 2 tangent balls (PSD), else 0
   unsigned long long* stats;   // optional: [nodes visited, triangles tested, FP32 operations]
   int32_t accum;               // persistent form, wavefront row-table partial sums:
@@ -223,7 +224,7 @@ hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, con
                            float* w, hipStream_t s);
 // n slots (a multiple of 4); quick: 5 (n + kQuickPad) float4
 hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, float4* quick, hipStream_t s);
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t leaf,
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t entry,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s);
 hipError_t launch_finalize(const MeshDev& M, int64_t n_rows, const int64_t* walks, const double* w, double* S,

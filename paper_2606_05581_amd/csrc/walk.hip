@@ -297,7 +297,7 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (cc[k] < 0 && cn[k] > 0 && lb[k] <= thr) {
-        const int32_t first = -cc[k] - 1;
+        const int32_t first = (-cc[k] - 1) & ~3;
         const float before = h.d2;
         for (int32_t s = first; s < first + cn[k]; ++s) test_tri<kStats>(tris, s, px, py, pz, h, cnt);
         if (h.d2 != before) {
@@ -389,12 +389,11 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
 // 16.4M walks 153 ms, so that 17 of the 51 ms of 4.1M walks were such tails.
 // Here all lanes share its nodes.
 //
-// Triangles are listed in units of 2^unit_shift (4 or 8, at least the leaf
-// width) consecutive slots of one owner, one lane each (one word: first slot
-// / 4 << 6 | owner lane; leaves start at multiples of 4 slots and hold at
-// least one triangle, so meshes have fewer than 2^26 triangles). The lanes
-// past a shorter leaf meet pads, or triangles of the next leaf, which cannot
-// change a minimum over the mesh: a unit needs no count.
+// Triangles are listed in units of one block of 4 slots of one owner, one
+// lane each (one word: block << 6 | owner lane; leaves start at a block and
+// hold at least one triangle, so meshes have fewer than 2^26 triangles). The
+// lanes past a shorter leaf meet pads. A leaf wider than 4 lists its second
+// block once the first ones are done.
 //
 // A listed triangle takes the prefilter only. Its upper value d2 + m lowers
 // the owner's bound m2 through an LDS minimum; if its lower value d2 - m still
@@ -414,10 +413,11 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
 // The stack holds kItemCap items; a trip takes as few as keeps it below
 // kItemLimit (one at least: its subtree then adds at most 3 items a level, and
 // 3 x depth + 5 <= kStackDepth), and new queries start only up to kRootLimit.
-// The units of a trip lie above the stack's top (at most 4 per taken item and
-// one per new query, which kItemLimit leaves room for).
+// The units of a trip lie above the stack's top (at most 4 per taken item,
+// which the room for its children covers).
 constexpr int kItemCap = 512, kItemLimit = kItemCap - 64, kRootLimit = kItemLimit - 72;
 static_assert(kItemLimit + kStackDepth <= kItemCap, "one item's subtree must fit above the limit");
+static_assert(kRootLimit + 64 <= kItemLimit, "new queries must fit below the limit");
 constexpr int kPendCap = 128;
 struct CoopScratch {
   uint32_t item[kItemCap];   // node << 6 | owner; above the top: units, block << 6 | owner
@@ -532,12 +532,20 @@ __device__ __forceinline__ float box_bound(float m2, const float4& q) {
   return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);
 }
 
-// Sets up owner `lane`'s search at (x, y, z), |p| <= 3 R; search_push puts its
-// root on the stack.
+// Sets up owner `lane`'s search at (x, y, z), |p| <= 3 R; search_push puts it
+// on the stack. `warm` names a slot whose triangle's upper value is the first
+// bound (negative: none).
 __device__ __forceinline__ void search_start(CoopScratch* W, uint32_t lane, const Node4* nodes, const float4* quick,
-                                             const TriRec* tris, float radius, float x, float y, float z) {
+                                             const TriRec* tris, float radius, float x, float y, float z,
+                                             int32_t warm) {
+  float m2 = INFINITY;
+  if (warm >= 0) {
+    float d2, m;
+    quick_dist(x, y, z, quick, quick_index(warm), d2, m);
+    m2 = d2 + m;
+  }
   W->pt[lane] = make_float4(x, y, z, 0x1p-20f * radius);
-  W->m2[lane] = __float_as_uint(INFINITY);
+  W->m2[lane] = __float_as_uint(m2);
   W->key[lane] = ((unsigned long long)__float_as_uint(INFINITY) << 32) | (uint32_t)INT_MAX;
   W->rec_slot[lane] = -1;
   W->base[lane] = (const char*)nodes;
@@ -545,17 +553,31 @@ __device__ __forceinline__ void search_start(CoopScratch* W, uint32_t lane, cons
   W->off_tris[lane] = (uint32_t)(((const char*)tris - (const char*)nodes) >> 8);
 }
 
-// Pushes the roots of the lanes with `fresh` (all lanes of the wavefront call
-// it, with size <= kRootLimit).
-__device__ __forceinline__ void search_push(CoopScratch* W, uint32_t lane, bool fresh, uint32_t& size) {
+// Pushes the searches of the lanes with `fresh` (all lanes of the wavefront
+// call it, with size <= kRootLimit): the root, or, while the stack has fewer
+// items than the wavefront lanes, all nodes of the deepest full level of the
+// tree (`entry` = 1, 4, 16 or 64 of them, consecutive in breadth-first order)
+// that still fits: the levels above cost a trip each and answer nothing.
+__device__ __forceinline__ void search_push(CoopScratch* W, uint32_t lane, bool fresh, int32_t entry, uint32_t& size) {
   const uint64_t m = __ballot(fresh);
+  const uint32_t nf = (uint32_t)__popcll(m);
+  uint32_t es = 0;
+#pragma unroll
+  for (uint32_t e = 2; e <= 6; e += 2)
+    if (size + (nf << e) <= 64u && __ballot(fresh && entry < (1 << e)) == 0) es = e;
   if (fresh) {
-    const uint32_t p = size + mbcnt64(m);
-    W->item[p] = lane;
-    W->lb[p] = 0;
-    W->open[lane] = 1;
+    W->lb[kItemLimit + mbcnt64(m)] = (uint16_t)lane;  // above any item of such a pass
+    W->open[lane] = 1u << es;
   }
-  size += (uint32_t)__popcll(m);
+  lds_order();
+  const uint32_t first = ((1u << es) - 1u) / 3u;
+  if (lane < nf << es) {
+    const uint32_t o = W->lb[kItemLimit + (lane >> es)];
+    W->item[size + lane] = (first + (lane & ((1u << es) - 1u))) << 6 | o;
+    W->lb[size + lane] = 0;
+  }
+  lds_order();
+  size += nf << es;
 }
 
 // Answer of an owner whose search has ended and whose pending tests are done.
@@ -591,13 +613,11 @@ __device__ __forceinline__ void answer_bary(const TriRec* tris, float px, float 
 
 // One pass of the wavefront (all lanes call it). With `trip` it is a trip of
 // the search; without, it only runs the pending exact tests of the owners in
-// `done`. `warm` names the warm-start slot of an owner whose search was just
-// started (else negative; cleared by a trip). Both kinds share one copy of the
-// exact test: the walk kernel's loop is long enough to miss the instruction
-// cache.
+// `done`. Both kinds share one copy of the exact test: the walk kernel's loop
+// is long enough to miss the instruction cache.
 template <bool kStats>
 __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool trip, uint64_t done, uint32_t& size,
-                                            int32_t& warm, int unit_shift, uint32_t& npend, TravCount& cnt) {
+                                            uint32_t& npend, TravCount& cnt) {
   size = uniform(size);
   npend = uniform(npend);
   const int32_t room = ((int32_t)kItemLimit - (int32_t)size) / 3;
@@ -605,8 +625,9 @@ __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool 
   const bool tr = lane < n;
   float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
   int32_t cc[4] = {0, 0, 0, 0};
-  uint32_t uw[4] = {~0u, ~0u, ~0u, ~0u};  // leaf children within the bound: unit words
-  uint32_t nu = 0, o = 0;
+  // leaf children within the bound: unit words, and whether a second block follows
+  uint32_t uw[4] = {~0u, ~0u, ~0u, ~0u};
+  uint32_t nu = 0, n2 = 0, o = 0;
   float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   bool live = false;
   if (tr) {
@@ -641,6 +662,7 @@ __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool 
         cc[k] = c4[k];
         uw[k] = hit ? (((uint32_t)~c4[k] >> 2) << 6) | o : ~0u;
         nu += hit ? 1u : 0u;
+        n2 += hit ? (uint32_t)~c4[k] & 1u : 0u;
       }
     }
   }
@@ -649,20 +671,17 @@ __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool 
   bool force = false;
   if (trip) {
     done = ~0ull;
-    nu += warm >= 0 ? 1u : 0u;
     uint32_t pos = size + wave_prefix_small(nu, total);
     lds_order();
-    if (warm >= 0) W->item[pos++] = ((uint32_t)warm >> 2 << 6) | lane;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (uw[k] != ~0u) W->item[pos++] = uw[k];
     if (kStats && nu > 0) {
-      cnt.tris += nu << unit_shift;
-      cnt.flops += (nu << unit_shift) * kQuickFlops;
+      cnt.tris += (nu + n2) << 2;
+      cnt.flops += ((nu + n2) << 2) * kQuickFlops;
     }
     lds_order();
   }
-  const uint32_t upr = 64u >> unit_shift;  // units per round
   bool flush = !trip && npend != 0;
   uint32_t u0 = 0;
   while (true) {
@@ -670,14 +689,14 @@ __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool 
       npend = flush_pending<kStats>(W, lane, npend, done, cnt);
       flush = false;
     } else if (u0 < total) {
-      const uint32_t u = u0 + (lane >> unit_shift);
+      const uint32_t u = u0 + (lane >> 2);
       bool cand = false;
       uint32_t word = 0;
       float l2 = 0.0f;
       if (u < total) {
         const uint32_t pk = W->item[size + u];
         const uint32_t uo = pk & 63u;
-        const uint32_t bl = (pk >> 6) + ((lane & ((1u << unit_shift) - 1u)) >> 2);
+        const uint32_t bl = pk >> 6;
         const float4 p = W->pt[uo];
         float d2, m;
         quick_dist(p.x, p.y, p.z, W->base[uo] + ((uint64_t)W->off_quick[uo] << 8), (uint64_t)bl * 20u + (lane & 3u), d2,
@@ -699,15 +718,22 @@ __device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool 
       }
       npend += (uint32_t)__popcll(mk);
       lds_order();
-      u0 += upr;
+      u0 += 16;
       // triangles without an upper value bound nothing until they are tested
       flush = u0 >= total && __ballot(force) != 0;
+    } else if (__ballot(n2 > 0) != 0) {  // the second blocks of wide leaves
+      uint32_t pos = size + wave_prefix_small(n2, total);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (uw[k] != ~0u && ((uint32_t)~cc[k] & 1u)) W->item[pos++] = uw[k] + 64u;
+      lds_order();
+      n2 = 0;
+      u0 = 0;
     } else {
       break;
     }
   }
   if (!trip) return;
-  warm = -1;
   uint32_t pushed = 0;
   bool put[4] = {false, false, false, false};
   if (live) {
@@ -1498,7 +1524,6 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   __syncthreads();
   const uint32_t lane = __lane_id();
   const bool owner = lane < (uint32_t)L.max_owners;
-  const int unit_shift = L.unit_shift;
   const int qhome = blockIdx.x & 7;
   int qi = 0;  // queues tried so far (uniform)
   uint64_t cur = 0, cend = 0;
@@ -1511,7 +1536,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   // lane's state: mode 0 no walk, 1 searching, 2 search ended, 3 walk ended
   // (its answer stays in the wavefront's scratch until the next bookkeeping
   // pass records it), 4 at its start
-  int32_t mode = 0, fin_status = -1, warm = -1;
+  int32_t mode = 0, fin_status = -1;
   bool capped = false;
   uint32_t npend = 0, size = 0;  // pending exact tests and stack items of the wavefront (uniform)
   TravCount cnt;                 // statistics kernels: this lane's share of the work
@@ -1533,7 +1558,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
                       (size == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
     const bool book =
         !step && (size == 0 || (!drained && (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min));
-    search_pass<kStats>(W, lane, !step && !book, step ? pend : ~0ull, size, warm, unit_shift, npend, cnt);
+    search_pass<kStats>(W, lane, !step && !book, step ? pend : ~0ull, size, npend, cnt);
     MSK_TICK(tk1);
     MSK_ACC(1, tk0, tk1);
 #if MSK_PHASE_TIMING
@@ -1558,8 +1583,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
       if (go) {
         st = walk_begin(L, M, w, capped);
         if (st < 0) {
-          search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z);
-          warm = w.slot;
+          search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z, w.slot);
           fresh = true;
           mode = 1;
         }
@@ -1568,7 +1592,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         fin_status = st;
         mode = 3;
       }
-      search_push(W, lane, fresh, size);
+      search_push(W, lane, fresh, M.entry, size);
       MSK_TICK(tk2);
       MSK_ACC(5, tk1, tk2);
     }
@@ -1933,7 +1957,7 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris,
                         const float4* __restrict__ quick, float radius, double cx, double cy, double cz,
-                        const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t unit_shift,
+                        const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t entry,
                         int32_t* __restrict__ tri, float* __restrict__ d2, float* __restrict__ bary) {
   __shared__ CoopScratch coop[kWaves];
   const int wi = (int)uniform(threadIdx.x >> 6);
@@ -1943,7 +1967,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
   const bool owner = lane < (1u << own_shift);
   int64_t next = 0;  // queries handed out (uniform)
   bool drained = false;
-  int32_t mode = 0, warm = -1;  // 0 idle, 1 searching, 2 search ended
+  int32_t mode = 0;  // 0 idle, 1 searching, 2 search ended
   int64_t qi = 0;
   uint32_t npend = 0, size = 0;
   TravCount cnt;
@@ -1952,7 +1976,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
     const bool step = size == 0 || (size <= (uint32_t)kRootLimit &&
                                     (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
-    search_pass<false>(W, lane, !step, pend, size, warm, unit_shift, npend, cnt);
+    search_pass<false>(W, lane, !step, pend, size, npend, cnt);
     if (step) {
       bool fresh = false;
       if (mode == 2) {
@@ -1980,7 +2004,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
           const float y = (float)((double)Q[3 * qi + 1] - cy);
           const float z = (float)((double)Q[3 * qi + 2] - cz);
           if (fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))) <= 1.7f * radius) {
-            search_start(W, lane, nodes, quick, tris, radius, x, y, z);
+            search_start(W, lane, nodes, quick, tris, radius, x, y, z, -1);
             mode = 1;
             fresh = true;
           } else {  // the prefilter's margins hold for |p| <= 3 R
@@ -1996,7 +2020,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
         drained = got < (uint32_t)__popcll(idle);
         next += got;
       }
-      search_push(W, lane, fresh, size);
+      search_push(W, lane, fresh, entry, size);
       if (drained && __ballot(mode != 0) == 0) break;
     }
   }
@@ -2232,7 +2256,7 @@ hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, fl
   return hipGetLastError();
 }
 
-hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t leaf,
+hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t entry,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
@@ -2243,7 +2267,7 @@ hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const f
   while (own_shift < 6 && (waves << own_shift) < nq) ++own_shift;
   const int64_t blocks = std::min<int64_t>(4ll * n_cu, (((nq - 1) >> own_shift) / kWaves) + 1);
   hipLaunchKernelGGL(query_stream_kernel, dim3((unsigned)blocks), dim3(256), 0, s, nodes, tris, quick, radius, c[0],
-                     c[1], c[2], Q, nq, own_shift, leaf <= 4 ? 2 : 3, tri, d2, bary);
+                     c[1], c[2], Q, nq, own_shift, entry, tri, d2, bary);
   return hipGetLastError();
 }
 

@@ -23,7 +23,10 @@ namespace msk {
 // pointer is generic to the compiler, and its flat accesses count as LDS
 // accesses too, so that every wait for LDS data would wait for them.
 #define MSK_GLOBAL __attribute__((address_space(1)))
-typedef const MSK_GLOBAL MeshDev GlobalMesh;
+
+// A mesh's descriptor, which no kernel writes: read through the scalar cache
+// where the mesh is the same for all lanes (wave_meshes).
+typedef const __attribute__((address_space(4))) MeshDev ConstMesh;
 
 template <typename T>
 __device__ __forceinline__ T gload(const T* p, int64_t i) {
@@ -791,6 +794,21 @@ struct LaneWalk {
 // Duff et al. 2017).
 __device__ __forceinline__ void onb(double nx, double ny, double nz, double e1[3], double e2[3]);
 
+// Calls f(mesh) for each mesh among the lanes with `in`, the lanes of other
+// meshes masked (all lanes call it; f gets whether the lane takes part). The
+// lanes of a wavefront nearly always share one mesh, whose descriptor then
+// comes through scalar loads: read per lane, a dozen dependent global loads
+// stood in every walk step.
+template <typename F>
+__device__ __forceinline__ void wave_meshes(const WalkLaunch& L, bool in, int32_t mesh, F f) {
+  for (uint64_t todo = __ballot(in); todo != 0;) {
+    const int32_t m = __builtin_amdgcn_readlane(mesh, __ffsll((unsigned long long)todo) - 1);
+    const bool mine = in && mesh == m;
+    f(((ConstMesh*)L.meshes)[m], mine);
+    todo &= ~__ballot(mine);
+  }
+}
+
 // Start of a walk of the PSD estimator (Sec. 3.2, Alg. 2): a point z on the
 // tangent ball of row i's sample s (centre c = s - r n), drawn with density
 // proportional to the ball's jump kernel 1 / (2 pi |s - z|^3) outside the cap
@@ -1267,8 +1285,6 @@ __device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, 
   lds_order();
   const int half = (int)(lane >> 5);
   bool ok = mine;
-  // the wavefront's walks lie on one mesh (their base and table pointers
-  // differ otherwise): those of the others wait for their own turn
   for (uint64_t todo = __ballot(mine); todo != 0;) {
     const int a = __ffsll((unsigned long long)todo) - 1;
     todo &= todo - 1;
@@ -1279,8 +1295,6 @@ __device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, 
     const int32_t n0 = __shfl(n[0], src), n1 = __shfl(n[1], src), n2 = __shfl(n[2], src);
     const int32_t p0 = __shfl(p[0], src), p1 = __shfl(p[1], src), p2 = __shfl(p[2], src);
     const double w0 = shfl_f64(wt[0], src), w1 = shfl_f64(wt[1], src), w2 = shfl_f64(wt[2], src);
-    const uint64_t cp = (uint64_t)__shfl((unsigned long long)(uintptr_t)M.b_col, src);
-    const uint64_t vp = (uint64_t)__shfl((unsigned long long)(uintptr_t)M.b_val, src);
     const int32_t t = __shfl(tab, src);
     const int32_t tot = valid ? n0 + n1 + n2 : 0;
     bool fail = false;
@@ -1288,8 +1302,8 @@ __device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, 
       if (e < tot) {
         const int32_t i = e < n0 ? p0 + e : (e < n0 + n1 ? p1 + e - n0 : p2 + e - n0 - n1);
         const double wk = e < n0 ? w0 : (e < n0 + n1 ? w1 : w2);
-        const int32_t j = gload((const int32_t*)cp, i);
-        const double v = wk * (double)gload((const float*)vp, i);
+        const int32_t j = gload(M.b_col, i);
+        const double v = wk * (double)gload(M.b_val, i);
         const uint32_t h = ((uint32_t)j * 2654435761u) >> (32 - kSlotBits);
         bool placed = false;
         for (int q = 0; q < kProbes && !placed; ++q) {
@@ -1326,7 +1340,7 @@ __device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, 
 template <typename AccT>
 __device__ void table_flush(const WalkLaunch& L, WaveTables<AccT>& T, int wi, int t, int32_t mesh, int32_t row) {
   __builtin_amdgcn_wave_barrier();
-  GlobalMesh& F = ((GlobalMesh*)L.meshes)[mesh];
+  ConstMesh& F = ((ConstMesh*)L.meshes)[mesh];
   double* a1 = F.acc1 + (int64_t)row * F.K;
   double* a2 = F.acc2 + (int64_t)row * F.K;
   for (int i = (int)__lane_id(); i < kSlots; i += 64) {
@@ -1452,7 +1466,7 @@ __global__ void __launch_bounds__(256) walk_plain_kernel(WalkLaunch L) {
   if (g >= (uint64_t)L.n_slots * (uint64_t)L.walks_per_slot) return;
   LaneWalk w;
   decode_walk(L, g, w);
-  GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
+  ConstMesh& M = ((ConstMesh*)L.meshes)[w.mesh];
   int32_t face;
   double lam[3];
   if (!walk_start<kRowsAny>(L, M, w, face, lam)) return;
@@ -1525,7 +1539,6 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   const uint32_t lane = __lane_id();
   const bool owner = lane < (uint32_t)L.max_owners;
   const int qhome = blockIdx.x & 7;
-  int qi = 0;  // queues tried so far (uniform)
   uint64_t cur = 0, cend = 0;
   // wave-uniform table bookkeeping
   int32_t t_used[2] = {0, 0}, t_mesh[2] = {0, 0}, t_row[2] = {0, 0}, t_out[2] = {0, 0};
@@ -1567,32 +1580,36 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
 #endif
     if (step) {
       bool fresh = false;
-      int32_t st = -1;
-      GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.active ? w.mesh : 0];
-      bool go = mode == 4;
-      if (mode == 2) {
-        Nearest hit;
-        if (search_answer(W, lane, hit)) {
-          st = walk_end(M, w, capped, hit);
-          go = st < 0;
-        } else {
-          fresh = true;
-          mode = 1;
+      int32_t entry = 1;
+      wave_meshes(L, mode == 2 || mode == 4, w.mesh, [&](ConstMesh& M, bool mine) {
+        if (!mine) return;
+        int32_t st = -1;
+        bool go = mode == 4;
+        if (mode == 2) {
+          Nearest hit;
+          if (search_answer(W, lane, hit)) {
+            st = walk_end(M, w, capped, hit);
+            go = st < 0;
+          } else {
+            fresh = true;
+            mode = 1;
+          }
         }
-      }
-      if (go) {
-        st = walk_begin(L, M, w, capped);
-        if (st < 0) {
-          search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z, w.slot);
-          fresh = true;
-          mode = 1;
+        if (go) {
+          st = walk_begin(L, M, w, capped);
+          if (st < 0) {
+            search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, w.x, w.y, w.z, w.slot);
+            fresh = true;
+            mode = 1;
+          }
         }
-      }
-      if (st >= 0) {
-        fin_status = st;
-        mode = 3;
-      }
-      search_push(W, lane, fresh, M.entry, size);
+        if (st >= 0) {
+          fin_status = st;
+          mode = 3;
+        }
+        entry = M.entry;
+      });
+      search_push(W, lane, fresh, entry, size);
       MSK_TICK(tk2);
       MSK_ACC(5, tk1, tk2);
     }
@@ -1600,14 +1617,13 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
       MSK_TICK(tb0);
       const bool fin = mode == 3;
       const int32_t fin_tab = fin ? w.tab : -1;
-      {
-        GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.active ? w.mesh : 0];
+      wave_meshes(L, fin, w.mesh, [&](ConstMesh& M, bool mine) {
         Nearest hit;
         hit.d2 = INFINITY;
         hit.orig = INT_MAX;
         hit.slot = -1;
         hit.l1 = hit.l2 = 0.0f;
-        if (fin && fin_status != kEscaped) {
+        if (mine && fin_status != kEscaped) {
           const unsigned long long k = W->key[lane];
           hit.d2 = __uint_as_float((uint32_t)(k >> 32));
           hit.orig = (int32_t)(uint32_t)k;
@@ -1616,16 +1632,14 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           answer_bary(M.tris, q.x, q.y, q.z, hit);
         }
         bool done = false;
-        if constexpr (kRows == kRowsPoints && !kKnn) {
-          const bool mine = fin && w.tab >= 0 && walk_has_t(M, fin_status, hit);
-          done = record_point_walks(M, W, lane, mine, w.tab, hit, T, wi);
-        }
-        if (fin) {
-          walk_finish<AccT, kKnn, kRows>(L, M, w, fin_status, !done, hit, T, wi);
-          w.active = 0;
-          w.tab = -1;
-          mode = 0;
-        }
+        if constexpr (kRows == kRowsPoints && !kKnn)
+          done = record_point_walks(M, W, lane, mine && w.tab >= 0 && walk_has_t(M, fin_status, hit), w.tab, hit, T, wi);
+        if (mine) walk_finish<AccT, kKnn, kRows>(L, M, w, fin_status, !done, hit, T, wi);
+      });
+      if (fin) {
+        w.active = 0;
+        w.tab = -1;
+        mode = 0;
       }
       MSK_TICK(tb1);
       MSK_ACC(2, tb0, tb1);
@@ -1644,20 +1658,28 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
       uint64_t idle = __ballot(owner && !w.active);
       while (idle != 0 && !drained) {
         if (cur >= cend) {
-          uint64_t start = 0;
-          if (lane == 0) {
-            const int q = (qhome + qi) & 7;
-            start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + q,
-                                           (unsigned long long)L.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          // the first queue from the home queue on that is not empty: all
+          // counters are read at once, so that a wavefront takes its end from
+          // one load instead of an atomic on each queue
+          bool left = false;
+          if (lane < 8u) {
+            const int q = (qhome + (int)lane) & 7;
+            left = __hip_atomic_load((MSK_GLOBAL unsigned long long*)L.queue_next + q, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT) < gload(L.queue_end, q);
           }
-          start = uniform64(start);  // the first lane's
-          const int q = (qhome + qi) & 7;
-          const uint64_t qend = uniform64(gload(L.queue_end, q));
-          if (start >= qend) {
-            ++qi;
-            if (qi >= 8) drained = true;
+          const uint64_t some = __ballot(left);
+          if (some == 0) {
+            drained = true;
             continue;
           }
+          const int q = (qhome + __ffsll((unsigned long long)some) - 1) & 7;
+          uint64_t start = 0;
+          if (lane == 0)
+            start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + q,
+                                           (unsigned long long)L.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          start = uniform64(start);  // the first lane's
+          const uint64_t qend = uniform64(gload(L.queue_end, q));
+          if (start >= qend) continue;  // another wavefront took the last chunk
           cur = start;
           cend = min(start + (uint64_t)L.chunk, qend);
           // the chunk's row takes the table it already has, else a free one
@@ -1681,16 +1703,17 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         const uint64_t avail = cend - cur;
         const uint32_t take = (uint32_t)min(avail, (uint64_t)__popcll(idle));
         bool fresh = false;
-        if (owner && !w.active && rank < take) {
-          decode_walk(L, cur + rank, w);
+        const bool start = owner && !w.active && rank < take;
+        if (start) decode_walk(L, cur + rank, w);
+        wave_meshes(L, start, w.mesh, [&](ConstMesh& M, bool mine) {
+          if (!mine) return;
           int32_t face;
           double lam[3];
-          GlobalMesh& M = ((GlobalMesh*)L.meshes)[w.mesh];
           w.active = walk_start<kRows>(L, M, w, face, lam) ? 1 : 0;
           w.tab = (w.active && c_tab >= 0 && w.mesh == c_mesh && w.row == c_row) ? c_tab : -1;
           mode = w.active ? 4 : 0;
           fresh = w.tab >= 0;
-        }
+        });
         if (c_tab >= 0) t_out[c_tab] += (int32_t)__popcll(__ballot(fresh));
         cur += take;
         idle = __ballot(owner && !w.active);

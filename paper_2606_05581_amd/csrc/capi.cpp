@@ -728,12 +728,18 @@ QueueInit make_queues(int64_t n_slots, int64_t W) {
 
 }  // namespace
 
-// The persistent launch's shape. A launch of fewer walks than the resident
-// wavefronts (4 per SIMD) have lanes gives each of them as few walks as still
+// Workgroups of a persistent launch: at most the 4 a CU holds at once (LDS and
+// registers), since each has a first chunk of its own.
+static int persistent_grid(const msk_dtn_opts& o, int n_cu) {
+  return std::max(1, n_cu * std::min(4, std::max(1, o.blocks_per_cu)));
+}
+
+// The persistent launch's shape. A launch of fewer walks than its wavefronts
+// have lanes gives each of them as few walks as still
 // cover all, in queue chunks that divide a slot's walks where a divisor is
 // near (a chunk then has one row, which takes a row table).
 static void shape_launch(WalkLaunch& L, const std::vector<MeshDev>& meshes, const msk_dtn_opts& o, int n_cu) {
-  const int64_t total = L.n_slots * L.walks_per_slot, waves = 16ll * n_cu;
+  const int64_t total = L.n_slots * L.walks_per_slot, waves = 4ll * persistent_grid(o, n_cu);
   L.chunk = std::max(1, o.chunk);
   L.max_owners = 64;
   if (total < 64 * waves) {
@@ -782,8 +788,8 @@ static msk_status run_walks(msk_ctx* ctx, const std::vector<MeshDev>& meshes, co
   LaunchBuffers lb;
   HIP_TRY(ctx, upload(ctx, &lb.d_meshes, meshes.data(), meshes.size()));
   HIP_TRY(ctx, upload(ctx, &lb.d_slots, slots.data(), slots.size()));
-  HIP_TRY(ctx, dalloc(&lb.d_qnext, 8));
-  HIP_TRY(ctx, dalloc(&lb.d_qend, 8));
+  HIP_TRY(ctx, dalloc(&lb.d_qnext, 8 * kQueueStride));
+  HIP_TRY(ctx, dalloc(&lb.d_qend, 16));
   WalkLaunch L;
   std::memset(&L, 0, sizeof(L));
   L.meshes = lb.d_meshes;
@@ -814,8 +820,7 @@ static msk_status run_walks(msk_ctx* ctx, const std::vector<MeshDev>& meshes, co
   if (o.form == MSK_FORM_PLAIN) {
     le = launch_walk_plain(L, ctx->stream);
   } else {
-    const int grid = std::max(1, ctx->n_cu * std::max(1, o.blocks_per_cu));
-    le = launch_walk_persistent(L, grid, ctx->stream);
+    le = launch_walk_persistent(L, persistent_grid(o, ctx->n_cu), ctx->stream);
   }
   HIP_TRY(ctx, le);
   HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
@@ -1042,7 +1047,7 @@ extern "C" msk_status msk_estimate_dtn_noalloc(msk_ctx* ctx, const msk_mesh* m, 
   const size_t off_acc1 = 0, off_acc2 = off_acc1 + up(nk * 8), off_q = off_acc2 + up(nk * 8);
   const size_t off_esc = off_q + up((size_t)n * 8), off_cap = off_esc + up((size_t)n * 8);
   const size_t off_walks = off_cap + up((size_t)n * 8), off_disc = off_walks + up((size_t)n * 8);
-  const size_t off_nonf = off_disc + up((size_t)n * 4), off_qn = off_nonf + 256, off_qe = off_qn + 256;
+  const size_t off_nonf = off_disc + up((size_t)n * 4), off_qn = off_nonf + 256, off_qe = off_qn + 64 * kQueueStride;
   const size_t off_mesh = off_qe + 256, off_slots = off_mesh + up(sizeof(MeshDev));
   const size_t need = off_slots + up((size_t)n * sizeof(RowSlot));
   if (need > msk::kNoallocScratchBytes)
@@ -1111,7 +1116,7 @@ extern "C" msk_status msk_estimate_dtn_noalloc(msk_ctx* ctx, const msk_mesh* m, 
   if (o.form == MSK_FORM_PLAIN)
     HIP_TRY(ctx, launch_walk_plain(L, s));
   else
-    HIP_TRY(ctx, launch_walk_persistent(L, std::max(1, ctx->n_cu * std::max(1, o.blocks_per_cu)), s));
+    HIP_TRY(ctx, launch_walk_persistent(L, persistent_grid(o, ctx->n_cu), s));
   HIP_TRY(ctx, launch_finalize(M, n, d.d_walks, r->d_w, S, se, s, o.jump_only));
   HIP_TRY(ctx, launch_count_nonfinite(S, (int64_t)nk, d.d_nonfinite, s));
   HIP_TRY(ctx, launch_count_nonfinite(se, (int64_t)nk, d.d_nonfinite, s));
@@ -1209,7 +1214,7 @@ static hipError_t enqueue_batch(msk_batch* B, hipStream_t s, int part) {
     shape_launch(L, B->md, B->o, B->ctx->n_cu);
     if (B->o.collect_stats) L.stats = B->lb.d_stats;
     if (B->o.form == MSK_FORM_PLAIN) return launch_walk_plain(L, s);
-    return launch_walk_persistent(L, std::max(1, B->ctx->n_cu * std::max(1, B->o.blocks_per_cu)), s);
+    return launch_walk_persistent(L, persistent_grid(B->o, B->ctx->n_cu), s);
   }
   for (int32_t i = 0; i < B->n; ++i) {
     msk_dtn* d = B->dtns[i];
@@ -1292,7 +1297,7 @@ extern "C" msk_status msk_batch_create(msk_ctx* ctx, int32_t n_meshes, const msk
       (he = upload(ctx, &B->d_ranges, ranges.data(), ranges.size())) != hipSuccess ||
       (he = upload(ctx, &B->d_counters, counters.data(), counters.size())) != hipSuccess ||
       (he = dalloc(&B->d_totals, 6 * (size_t)n_meshes)) != hipSuccess ||
-      (he = dalloc(&B->lb.d_qnext, 8)) != hipSuccess || (he = dalloc(&B->lb.d_qend, 8)) != hipSuccess ||
+      (he = dalloc(&B->lb.d_qnext, 8 * kQueueStride)) != hipSuccess || (he = dalloc(&B->lb.d_qend, 16)) != hipSuccess ||
       (he = dalloc(&B->lb.d_stats, 3)) != hipSuccess) {
     delete B;
     return fail(ctx, MSK_ERR_DEVICE, std::string("batch setup: ") + hipGetErrorString(he));

@@ -162,6 +162,9 @@ struct RowSlot {
   uint32_t walk0;  // the slot's first walk, after the launch's walk_offset
 };
 
+// A queue counter has a cache line of its own.
+constexpr int kQueueStride = 16;
+
 struct WalkLaunch {
   const MeshDev* meshes;       // device array
   const RowSlot* slots;        // device array, n_slots
@@ -170,8 +173,8 @@ struct WalkLaunch {
   int64_t walk_offset;         // first walk index
   uint32_t seed_lo, seed_hi;
   // persistent form: 8 queues over contiguous slot ranges
-  unsigned long long* queue_next;  // 8 counters (walk ids)
-  const unsigned long long* queue_end;  // 8 bounds
+  unsigned long long* queue_next;  // 8 counters (walk ids), kQueueStride apart
+  const unsigned long long* queue_end;  // 8 ends, then 8 beginnings
   int32_t chunk;
   int32_t regen_min;
   int32_t max_owners;          // persistent form: lanes of a wavefront that carry a walk (1..64)

@@ -1539,7 +1539,17 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   const uint32_t lane = __lane_id();
   const bool owner = lane < (uint32_t)L.max_owners;
   const int qhome = blockIdx.x & 7;
-  uint64_t cur = 0, cend = 0;
+  // the wavefront's first chunk has its place in the home queue; the counters
+  // hand out those after the first chunks of all (4096 atomics on 8 counters
+  // at once took as long as a launch of few walks)
+  const auto queue_first = [&](int q) {
+    return (uint64_t)((gridDim.x + 7u - (uint32_t)q) >> 3) * kWaves * (uint64_t)L.chunk;
+  };
+  uint64_t cur = gload(L.queue_end, 8 + qhome) + (uint64_t)((blockIdx.x >> 3) * kWaves + wi) * (uint64_t)L.chunk;
+  uint64_t cend = min(cur + (uint64_t)L.chunk, (uint64_t)gload(L.queue_end, qhome));
+  cur = uniform64(min(cur, cend));
+  cend = uniform64(cend);
+  bool fresh_chunk = cur < cend;  // cur .. cend is a chunk whose table is not chosen yet
   // wave-uniform table bookkeeping
   int32_t t_used[2] = {0, 0}, t_mesh[2] = {0, 0}, t_row[2] = {0, 0}, t_out[2] = {0, 0};
   int32_t c_tab = -1, c_mesh = -1, c_row = -1;  // current chunk's row and table
@@ -1560,6 +1570,10 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
   while (true) {
     MSK_TICK(tk0);
     if (mode == 1 && W->open[lane] == 0) mode = 2;
+    // (uniform by construction; said again so that all control flow below is
+    // scalar)
+    size = uniform(size);
+    drained = uniform(drained ? 1u : 0u) != 0;
     // ---- what this pass does: `step` finishes the steps whose search has
     // ended and starts the next ones, once kStepMin lanes wait (a quarter of
     // the wavefront's walks if that is less) or the stack is empty; `book`
@@ -1664,8 +1678,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           bool left = false;
           if (lane < 8u) {
             const int q = (qhome + (int)lane) & 7;
-            left = __hip_atomic_load((MSK_GLOBAL unsigned long long*)L.queue_next + q, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT) < gload(L.queue_end, q);
+            left = __hip_atomic_load((MSK_GLOBAL unsigned long long*)L.queue_next + kQueueStride * q, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT) + queue_first(q) < gload(L.queue_end, q);
           }
           const uint64_t some = __ballot(left);
           if (some == 0) {
@@ -1675,15 +1689,19 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
           const int q = (qhome + __ffsll((unsigned long long)some) - 1) & 7;
           uint64_t start = 0;
           if (lane == 0)
-            start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + q,
+            start = __hip_atomic_fetch_add((MSK_GLOBAL unsigned long long*)L.queue_next + kQueueStride * q,
                                            (unsigned long long)L.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          start = uniform64(start);  // the first lane's
+          start = uniform64(start) + queue_first(q);  // the first lane's
           const uint64_t qend = uniform64(gload(L.queue_end, q));
           if (start >= qend) continue;  // another wavefront took the last chunk
           cur = start;
           cend = min(start + (uint64_t)L.chunk, qend);
+          fresh_chunk = true;
+        }
+        if (fresh_chunk) {
+          fresh_chunk = false;
           // the chunk's row takes the table it already has, else a free one
-          const auto& rs = ((const MSK_GLOBAL RowSlot*)L.slots)[start / (uint64_t)L.walks_per_slot];
+          const auto& rs = ((const MSK_GLOBAL RowSlot*)L.slots)[cur / (uint64_t)L.walks_per_slot];
           c_mesh = (int32_t)uniform((uint32_t)rs.mesh);
           c_row = (int32_t)uniform((uint32_t)rs.row);
           c_tab = -1;
@@ -1746,8 +1764,9 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
 __global__ void init_queues_kernel(unsigned long long* next, unsigned long long* end, QueueInit q) {
   const int i = threadIdx.x;
   if (i < 8) {
-    next[i] = q.begin[i];
+    next[kQueueStride * i] = q.begin[i];
     end[i] = q.end[i];
+    end[8 + i] = q.begin[i];
   }
 }
 

@@ -28,7 +28,7 @@ def walk_sources_sha() -> str:
     results and measured traffic records are keyed by it, so that any edit
     of the kernels invalidates them."""
     h = hashlib.sha256()
-    for name in ("walk.hip", "msk_internal.h", "philox.h"):
+    for name in ("walk.hip", "search.h", "msk_internal.h", "philox.h"):
         with open(os.path.join(CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

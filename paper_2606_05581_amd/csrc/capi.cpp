@@ -942,7 +942,7 @@ extern "C" msk_status msk_estimate_dtn(msk_ctx* ctx, const msk_mesh* m, const ms
   HIP_D(launch_fill_u32(d->d_disc, d->n, 0u, ctx->stream));
   if (o.mesh_id < 0 || o.mesh_id > 0xFFFFFF) return cleanup(fail(ctx, MSK_ERR_INVALID_ARG, "mesh_id must be < 2^24"));
   MeshDev M = make_meshdev(m, r, b, d, eps, inset_h, side, o, o.mesh_id);
-  if (r->mode == MSK_ROWS_POINT) HIP_D(launch_discard(M, d->n, d->d_disc, ctx->stream));
+  if (r->mode == MSK_ROWS_POINT) HIP_D(launch_discard(M, d->n, ctx->n_cu, d->d_disc, ctx->stream));
   HIP_D(hipStreamSynchronize(ctx->stream));
   std::vector<MeshDev> meshes{M};
   std::vector<RowSlot> slots(r->order.size());
@@ -1094,7 +1094,7 @@ extern "C" msk_status msk_estimate_dtn_noalloc(msk_ctx* ctx, const msk_mesh* m, 
   HIP_TRY(ctx, launch_fill_u32(d.d_disc, n, 0u, s));
   HIP_TRY(ctx, launch_fill_u64(d.d_nonfinite, 1, 0, s));
   MeshDev M = make_meshdev(m, r, b, &d, eps, inset_h, side, o, o.mesh_id);
-  if (r->mode == MSK_ROWS_POINT) HIP_TRY(ctx, launch_discard(M, n, d.d_disc, s));
+  if (r->mode == MSK_ROWS_POINT) HIP_TRY(ctx, launch_discard(M, n, ctx->n_cu, d.d_disc, s));
   std::vector<RowSlot> slots(r->order.size());
   for (size_t i = 0; i < slots.size(); ++i) slots[i] = RowSlot{0, r->order[i], 0u};
   HIP_TRY(ctx, hipMemcpyAsync(d_mesh, &M, sizeof(MeshDev), hipMemcpyHostToDevice, s));
@@ -1189,7 +1189,8 @@ static hipError_t enqueue_batch(msk_batch* B, hipStream_t s, int part) {
       if ((e = launch_fill_u64(d->d_walks, d->n, (unsigned long long)B->W, s)) != hipSuccess) return e;
       if ((e = launch_fill_u32(d->d_disc, d->n, 0u, s)) != hipSuccess) return e;
     }
-    if ((e = launch_discard_batch(B->lb.d_meshes, B->d_ranges, B->n_ranges, B->n_point_rows, s)) != hipSuccess)
+    if ((e = launch_discard_batch(B->lb.d_meshes, B->d_ranges, B->n_ranges, B->n_point_rows,
+                                  B->ctx->n_cu, s)) != hipSuccess)
       return e;
     int64_t n_slots = 0;
     for (msk_dtn* d : B->dtns) n_slots += d->n;
@@ -1619,7 +1620,7 @@ extern "C" msk_status msk_estimate_psd(msk_ctx* ctx, const msk_mesh* m, const ms
   M.ball_r = d_rad;
   M.ball_u0 = std::sin(0.5 * po.cap_deg * M_PI / 180.0);
   // tangent balls (tolerance: half the termination shell)
-  HIP_P(launch_tangent_ball(M, n, (float)r_max, po.bisect_iters, (float)(0.5 * eps), d_rad, s));
+  HIP_P(launch_tangent_ball(M, n, (float)r_max, po.bisect_iters, (float)(0.5 * eps), ctx->n_cu, d_rad, s));
   HIP_P(hipEventRecord(ev[1], s));
   // walks from the balls
   std::vector<MeshDev> meshes{M};

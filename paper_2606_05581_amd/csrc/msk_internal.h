@@ -216,11 +216,11 @@ hipError_t launch_count_nonfinite(const double* a, int64_t n, unsigned long long
 hipError_t launch_init_queues(unsigned long long* next, unsigned long long* end, const QueueInit& q, hipStream_t s);
 hipError_t launch_fill_u64(void* p, int64_t n, unsigned long long v, hipStream_t s);
 hipError_t launch_fill_u32(void* p, int64_t n, uint32_t v, hipStream_t s);
-hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, int32_t iters, float tol, float* radius,
-                               hipStream_t s);
-hipError_t launch_discard(const MeshDev& M, int64_t n_rows, int32_t* discarded, hipStream_t s);
+hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, int32_t iters, float tol, int32_t n_cu,
+                               float* radius, hipStream_t s);
+hipError_t launch_discard(const MeshDev& M, int64_t n_rows, int32_t n_cu, int32_t* discarded, hipStream_t s);
 hipError_t launch_discard_batch(const MeshDev* meshes, const RowRange* ranges, int32_t n_ranges, int64_t n_total,
-                                hipStream_t s);
+                                int32_t n_cu, hipStream_t s);
 // out: 6 x n_sets counts (queries, escaped, capped, discarded rows, walks of kept rows, non-finite entries)
 hipError_t launch_row_totals(const RowCounters* sets, int32_t n_sets, unsigned long long* out, hipStream_t s);
 hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, const float* Nq, int64_t n, int32_t* idx,

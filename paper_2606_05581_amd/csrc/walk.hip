@@ -16,39 +16,17 @@
 
 #include "msk_internal.h"
 #include "philox.h"
+#include "search.h"
 
 namespace msk {
-
-// Device memory behind a pointer that was itself read from memory: such a
-// pointer is generic to the compiler, and its flat accesses count as LDS
-// accesses too, so that every wait for LDS data would wait for them.
-#define MSK_GLOBAL __attribute__((address_space(1)))
 
 // A mesh's descriptor, which no kernel writes: read through the scalar cache
 // where the mesh is the same for all lanes (wave_meshes).
 typedef const __attribute__((address_space(4))) MeshDev ConstMesh;
 
-template <typename T>
-__device__ __forceinline__ T gload(const T* p, int64_t i) {
-  return ((const MSK_GLOBAL T*)p)[i];
-}
-__device__ __forceinline__ float4 gload4(const void* p, int64_t i) {
-  typedef float V __attribute__((ext_vector_type(4)));
-  const V v = ((const MSK_GLOBAL V*)p)[i];
-  return make_float4(v.x, v.y, v.z, v.w);
-}
 __device__ __forceinline__ TriRec gload_tri(const TriRec* tris, int64_t i) {
   return TriRec{gload4(tris, 3 * i), gload4(tris, 3 * i + 1), gload4(tris, 3 * i + 2)};
 }
-template <typename T>
-__device__ __forceinline__ void gstore(T* p, int64_t i, T v) {
-  ((MSK_GLOBAL T*)p)[i] = v;
-}
-template <typename T>
-__device__ __forceinline__ void gadd(T* p, int64_t i, T v) {
-  (void)__hip_atomic_fetch_add((MSK_GLOBAL T*)p + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ uint4 draw(const WalkLaunch& L, uint32_t row, uint32_t walk, uint32_t step,
                                       uint32_t purpose, uint32_t mesh) {
   return philox10(make_uint4(row, walk, step, (purpose << 24) | (mesh & 0xFFFFFFu)), L.seed_lo, L.seed_hi);
@@ -193,15 +171,8 @@ __host__ __device__ __forceinline__ void nearest_bary(const Nearest& h, float& l
 }
 
 // FP32 operations of tri_dist2 up to each exit (vertex a, vertex b, edge ab,
-// vertex c, edge ac, edge bc, face, zero-area fallback); a box lower bound
-// costs 17 (6 subtractions, 6 maxima, 3 products, 2 sums).
+// vertex c, edge ac, edge bc, face, zero-area fallback).
 constexpr uint32_t kTriFlops[8] = {24, 37, 71, 73, 98, 117, 114, 175};
-constexpr uint32_t kBoxFlops = 17;
-
-struct TravCount {
-  uint32_t nodes = 0, tris = 0, flops = 0;
-};
-
 template <bool kStats>
 __host__ __device__ __forceinline__ void test_tri(const TriRec* __restrict__ tris, int32_t s, float px, float py, float pz,
                                          Nearest& h, TravCount& cnt) {
@@ -237,10 +208,9 @@ struct StackEntry {
   float lb;
 };
 
-template <bool kStats, bool kStopBelow = false>
-__host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris, const Node4* lds,
-                                     int32_t n_lds, float px, float py, float pz, float radius, Nearest& h,
-                                     TravCount& cnt, float stop_below = 0.0f) {
+template <bool kStats>
+__host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris, float px,
+                                     float py, float pz, float radius, Nearest& h, TravCount& cnt) {
   const float slack = 0x1p-18f * (radius + fmaxf(fabsf(px), fmaxf(fabsf(py), fabsf(pz))));
   if (h.slot >= 0) {
     const int32_t s = h.slot;
@@ -260,15 +230,9 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
       ++cnt.nodes;
       cnt.flops += 4 * kBoxFlops;
     }
-    if (node < n_lds) {
-      const float4* N = (const float4*)&lds[node];
-      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-    } else {
-      const float4* N = (const float4*)&nodes[node];
-      lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
-      ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
-    }
+    const float4* N = (const float4*)&nodes[node];
+    lox = N[0]; loy = N[1]; loz = N[2]; hix = N[3]; hiy = N[4]; hiz = N[5];
+    ch = ((const int4*)N)[6]; ct = ((const int4*)N)[7];
     float lb[4];
     int32_t cc[4], cn[4];
     {
@@ -305,9 +269,6 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
         for (int32_t s = first; s < first + cn[k]; ++s) test_tri<kStats>(tris, s, px, py, pz, h, cnt);
         if (h.d2 != before) {
           thr = prune_bound(h.d2, slack);
-          // kStopBelow: only whether some triangle lies closer than
-          // stop_below is asked, and this one does
-          if (kStopBelow && sqrtf(h.d2) < stop_below) return;
         }
       }
     }
@@ -378,167 +339,70 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
   return s * s * (1.0f + 0x1p-20f);
 }
 
-// Wavefront-shared nearest-triangle search (same result as the lane-private
-// bvh_nearest, bit for bit). Up to 64 queries of a wavefront, one per owner
-// lane, share one stack of (node, owner) items in LDS. A trip takes up to 64
-// items from its top, one per lane whoever their owners are, tests the four
-// child boxes, lists the leaf children's triangles, tests those 64 at a time
-// with the whole wavefront, and pushes the inner children that still reach
-// their owner's bound, the nearest ones of all lanes on top. A query ends when
-// none of its items is left (`open`).
-//   The search of a point far from every surface visits hundreds to thousands
-// of nodes. On a stack per lane it held its wavefront for that many trips
-// with one lane busy: 256,000 walks on a 500,000-face sphere took 15.6 ms,
-// 16.4M walks 153 ms, so that 17 of the 51 ms of 4.1M walks were such tails.
-// Here all lanes share its nodes.
-//
-// Triangles are listed in units of one block of 4 slots of one owner, one
-// lane each (one word: block << 6 | owner lane; leaves start at a block and
-// hold at least one triangle, so meshes have fewer than 2^26 triangles). The
-// lanes past a shorter leaf meet pads. A leaf wider than 4 lists its second
-// block once the first ones are done.
-//
-// A listed triangle takes the prefilter only. Its upper value d2 + m lowers
-// the owner's bound m2 through an LDS minimum; if its lower value d2 - m still
-// reaches that bound it goes to the wavefront's pending list, and the exact
-// test runs on the pending triangles that are left once their owner's search
-// has ended (or the list is full): about two per query instead of all of
-// them. The exact (squared distance, original index) goes to its owner through
-// a 64-bit LDS minimum, which realises the lexicographic order exactly. Should
-// the exact minimum lie above what m2 promised (possible only for nearly
-// degenerate triangles), the owner's search runs again with m2 at that minimum
-// and lowered by exact values only (negative pt.w), so the result never rests
-// on the upper margin.
-//   Exact tests of all listed triangles were bound by VALU issue: about 190
-// wavefront instructions per round of 64 tests, every region's path among
-// them. The prefilter takes about 60.
-//
-// The stack holds kItemCap items; a trip takes as few as keeps it below
-// kItemLimit (one at least: its subtree then adds at most 3 items a level, and
-// 3 x depth + 5 <= kStackDepth), and new queries start only up to kRootLimit.
-// The units of a trip lie above the stack's top (at most 4 per taken item,
-// which the room for its children covers).
-constexpr int kItemCap = 512, kItemLimit = kItemCap - 64, kRootLimit = kItemLimit - 72;
-static_assert(kItemLimit + kStackDepth <= kItemCap, "one item's subtree must fit above the limit");
-static_assert(kRootLimit + 64 <= kItemLimit, "new queries must fit below the limit");
-constexpr int kPendCap = 128;
-struct CoopScratch {
-  uint32_t item[kItemCap];   // node << 6 | owner; above the top: units, block << 6 | owner
-  uint16_t lb[kItemCap];     // item's box lower bound, FP32 cut to 16 bits
-  float4 pt[64];             // owner's query point; w = 2 delta, negative: m2 lowered by exact values only
-  const char* base[64];      // owner's mesh (batched meshes differ per lane): its nodes,
-  uint32_t off_quick[64];    // and its prefilter records
-  uint32_t off_tris[64];     // and triangles, in 256 B from the nodes
-  uint32_t m2[64];           // bound on the owner's squared distance (float bits)
-  uint32_t open[64];         // owner's items on the stack
-  unsigned long long key[64];
-  int32_t rec_slot[64];
-  union {
-    struct {
-      uint32_t pend[kPendCap];
-      float pend_l2[kPendCap];
-    };
-    double sum[2][64];  // record_point_walks, with nothing pending
+// Planar triangles as elements of the wavefront-shared search (same result as
+// the lane-private bvh_nearest, bit for bit). Values are squared distances,
+// pt.w = 2 delta; the owner's (squared distance, original index) is kept by a
+// 64-bit LDS minimum, which realises the lexicographic order exactly.
+struct TriEl {
+  static constexpr uint32_t kQuickFlops = 58;  // FP32 operations of quick_dist and the two bounds
+  struct Owners {
+    const char* base[64];    // owner's mesh (batched meshes differ per lane): its nodes,
+    uint32_t off_quick[64];  // and its prefilter records
+    uint32_t off_tris[64];   // and triangles, in 256 B from the nodes
+    unsigned long long key[64];
+    int32_t rec_slot[64];
   };
+  static __device__ __forceinline__ float keep(float m2, const float4& q) { return keep_bound(m2, fabsf(q.w)); }
+  // Box bound of a query: no triangle in a box whose squared distance exceeds it
+  // beats or ties the bound m2 (prune_bound's argument, with delta more: m2
+  // bounds the prefilter's value). Finite, so that an infinite lower bound never
+  // passes.
+  static __device__ __forceinline__ float boxes(float m2, const float4& q) {
+    const float w = fabsf(q.w);  // 2^-20 R
+    const float slack = 5.0f * w + 0x1p-18f * fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z)));
+    const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + slack;
+    return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);
+  }
+  template <typename Scratch>
+  __device__ __forceinline__ const Node4* nodes(Scratch* W, uint32_t o) const {
+    return (const Node4*)W->own.base[o];
+  }
+  template <typename Scratch>
+  __device__ __forceinline__ void quick(Scratch* W, uint32_t o, const float4& p, int64_t i, float& lo, float& up,
+                                        bool& always) const {
+    float d2, m;
+    quick_dist(p.x, p.y, p.z, W->own.base[o] + ((uint64_t)W->own.off_quick[o] << 8), i, d2, m);
+    lo = d2 - m;
+    up = d2 + m;
+    always = m > 1e28f;
+  }
+  template <bool kStats, typename Scratch>
+  __device__ __forceinline__ void exact(Scratch* W, uint32_t o, int32_t s, bool now, const float4& q,
+                                        TravCount& cnt) const {
+    if (!now) return;
+    const TriRec T = gload_tri((const TriRec*)(W->own.base[o] + ((uint64_t)W->own.off_tris[o] << 8)), s);
+    const float reject = __uint_as_float((uint32_t)(W->own.key[o] >> 32));
+    float l1, l2, den;
+    int region = 0;
+    const float d = tri_dist2(q.x, q.y, q.z, T, reject, l1, l2, den, region);
+    if (kStats) cnt.flops += kTriFlops[region & 7];
+    if (d <= reject) {
+      int32_t orig;
+      memcpy(&orig, &T.a.w, 4);
+      const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)orig;
+      atomicMin(&W->own.key[o], key);
+      atomicMin(&W->m2[o], __float_as_uint(d));
+      lds_order();
+      if (W->own.key[o] == key) W->own.rec_slot[o] = s;
+    }
+  }
 };
-
-// A value that all lanes of the wavefront share, in a scalar register.
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
-}
-
-__device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// Orders LDS accesses of a wavefront as written: the hardware executes one
-// wavefront's LDS instructions in issue order, so only the compiler must
-// not move them (a fence would also wait for all outstanding global and
-// scratch accesses).
-__device__ __forceinline__ void lds_order() { __asm__ __volatile__("" ::: "memory"); }
-
-// Exclusive prefix sum over the wavefront of a count below 8 (bit-sliced
-// ballots); `total` receives the wavefront's sum.
-__device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t& total) {
-  uint32_t pre = 0, tot = 0;
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    const uint64_t m = __ballot((v >> b) & 1u);
-    pre += mbcnt64(m) << b;
-    tot += (uint32_t)__popcll(m) << b;
-  }
-  total = tot;
-  return pre;
-}
-
-// Exact tests of the pending triangles whose owner is in `done` (all lanes
-// call it); those of other owners stay listed, those that no longer reach
-// their owner's bound are dropped. Returns the new list length.
-template <bool kStats>
-__device__ __forceinline__ uint32_t flush_pending(CoopScratch* W, uint32_t lane, uint32_t n, uint64_t done,
-                                                  TravCount& cnt) {
-  uint32_t kept = 0;
-  n = uniform(n);
-  for (uint32_t b = 0; b < n; b += 64) {
-    const bool in = b + lane < n;
-    const uint32_t word = in ? W->pend[b + lane] : 0u;
-    const float l2 = in ? W->pend_l2[b + lane] : INFINITY;
-    const uint32_t o = word & 63u;
-    const float4 q = W->pt[o];
-    const bool live = in && l2 <= keep_bound(__uint_as_float(W->m2[o]), fabsf(q.w));
-    const bool now = live && ((done >> o) & 1ull);
-    const bool later = live && !now;
-    const uint64_t mk = __ballot(later);
-    lds_order();
-    if (later) {  // at most b + lane: never over an entry that is still to be read
-      const uint32_t p = kept + mbcnt64(mk);
-      W->pend[p] = word;
-      W->pend_l2[p] = l2;
-    }
-    kept = uniform(kept + (uint32_t)__popcll(mk));
-    if (now) {
-      const int32_t s = (int32_t)(word >> 6 << 2 | (__float_as_uint(l2) & 3u));
-      const TriRec T = gload_tri((const TriRec*)(W->base[o] + ((uint64_t)W->off_tris[o] << 8)), s);
-      const float reject = __uint_as_float((uint32_t)(W->key[o] >> 32));
-      float l1, lb, den;
-      int region = 0;
-      const float d = tri_dist2(q.x, q.y, q.z, T, reject, l1, lb, den, region);
-      if (kStats) cnt.flops += kTriFlops[region & 7];
-      if (d <= reject) {
-        int32_t orig;
-        memcpy(&orig, &T.a.w, 4);
-        const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)orig;
-        atomicMin(&W->key[o], key);
-        atomicMin(&W->m2[o], __float_as_uint(d));
-        lds_order();
-        if (W->key[o] == key) W->rec_slot[o] = s;
-      }
-    }
-    lds_order();
-  }
-  return kept;
-}
-
-// FP32 operations of one prefilter test (quick_dist and the two bounds).
-constexpr uint32_t kQuickFlops = 58;
-
-// Box bound of a query: no triangle in a box whose squared distance exceeds it
-// beats or ties the bound m2 (prune_bound's argument, with delta more: m2
-// bounds the prefilter's value). Finite, so that an infinite lower bound never
-// passes.
-__device__ __forceinline__ float box_bound(float m2, const float4& q) {
-  const float w = fabsf(q.w);  // 2^-20 R
-  const float slack = 5.0f * w + 0x1p-18f * fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z)));
-  const float s = __builtin_amdgcn_sqrtf(m2) * (1.0f + 0x1p-20f) + slack;
-  return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);
-}
 
 // Sets up owner `lane`'s search at (x, y, z), |p| <= 3 R; search_push puts it
 // on the stack. `warm` names a slot whose triangle's upper value is the first
 // bound (negative: none).
-__device__ __forceinline__ void search_start(CoopScratch* W, uint32_t lane, const Node4* nodes, const float4* quick,
+template <typename Scratch>
+__device__ __forceinline__ void search_start(Scratch* W, uint32_t lane, const Node4* nodes, const float4* quick,
                                              const TriRec* tris, float radius, float x, float y, float z,
                                              int32_t warm) {
   float m2 = INFINITY;
@@ -549,49 +413,23 @@ __device__ __forceinline__ void search_start(CoopScratch* W, uint32_t lane, cons
   }
   W->pt[lane] = make_float4(x, y, z, 0x1p-20f * radius);
   W->m2[lane] = __float_as_uint(m2);
-  W->key[lane] = ((unsigned long long)__float_as_uint(INFINITY) << 32) | (uint32_t)INT_MAX;
-  W->rec_slot[lane] = -1;
-  W->base[lane] = (const char*)nodes;
-  W->off_quick[lane] = (uint32_t)(((const char*)quick - (const char*)nodes) >> 8);
-  W->off_tris[lane] = (uint32_t)(((const char*)tris - (const char*)nodes) >> 8);
-}
-
-// Pushes the searches of the lanes with `fresh` (all lanes of the wavefront
-// call it, with size <= kRootLimit): the root, or, while the stack has fewer
-// items than the wavefront lanes, all nodes of the deepest full level of the
-// tree (`entry` = 1, 4, 16 or 64 of them, consecutive in breadth-first order)
-// that still fits: the levels above cost a trip each and answer nothing.
-__device__ __forceinline__ void search_push(CoopScratch* W, uint32_t lane, bool fresh, int32_t entry, uint32_t& size) {
-  const uint64_t m = __ballot(fresh);
-  const uint32_t nf = (uint32_t)__popcll(m);
-  uint32_t es = 0;
-#pragma unroll
-  for (uint32_t e = 2; e <= 6; e += 2)
-    if (size + (nf << e) <= 64u && __ballot(fresh && entry < (1 << e)) == 0) es = e;
-  if (fresh) {
-    W->lb[kItemLimit + mbcnt64(m)] = (uint16_t)lane;  // above any item of such a pass
-    W->open[lane] = 1u << es;
-  }
-  lds_order();
-  const uint32_t first = ((1u << es) - 1u) / 3u;
-  if (lane < nf << es) {
-    const uint32_t o = W->lb[kItemLimit + (lane >> es)];
-    W->item[size + lane] = (first + (lane & ((1u << es) - 1u))) << 6 | o;
-    W->lb[size + lane] = 0;
-  }
-  lds_order();
-  size += nf << es;
+  W->own.key[lane] = ((unsigned long long)__float_as_uint(INFINITY) << 32) | (uint32_t)INT_MAX;
+  W->own.rec_slot[lane] = -1;
+  W->own.base[lane] = (const char*)nodes;
+  W->own.off_quick[lane] = (uint32_t)(((const char*)quick - (const char*)nodes) >> 8);
+  W->own.off_tris[lane] = (uint32_t)(((const char*)tris - (const char*)nodes) >> 8);
 }
 
 // Answer of an owner whose search has ended and whose pending tests are done.
 // Returns false if the exact minimum lies above what the prefilter's bound
 // promised: the search has been set up to run again (its root is to be
 // pushed), from then on on exact values.
-__device__ __forceinline__ bool search_answer(CoopScratch* W, uint32_t lane, Nearest& h) {
-  const unsigned long long k = W->key[lane];
+template <typename Scratch>
+__device__ __forceinline__ bool search_answer(Scratch* W, uint32_t lane, Nearest& h) {
+  const unsigned long long k = W->own.key[lane];
   h.d2 = __uint_as_float((uint32_t)(k >> 32));
   h.orig = (int32_t)(uint32_t)k;
-  h.slot = W->rec_slot[lane];
+  h.slot = W->own.rec_slot[lane];
   const float w = fabsf(W->pt[lane].w);
   if (h.d2 > keep_bound(__uint_as_float(W->m2[lane]), w)) {
     W->m2[lane] = __float_as_uint(h.d2);
@@ -612,161 +450,6 @@ __device__ __forceinline__ void answer_bary(const TriRec* tris, float px, float 
   h.l1 = l1;
   h.l2 = l2;
   if (region == 6) h.den = den;
-}
-
-// One pass of the wavefront (all lanes call it). With `trip` it is a trip of
-// the search; without, it only runs the pending exact tests of the owners in
-// `done`. Both kinds share one copy of the exact test: the walk kernel's loop
-// is long enough to miss the instruction cache.
-template <bool kStats>
-__device__ __forceinline__ void search_pass(CoopScratch* W, uint32_t lane, bool trip, uint64_t done, uint32_t& size,
-                                            uint32_t& npend, TravCount& cnt) {
-  size = uniform(size);
-  npend = uniform(npend);
-  const int32_t room = ((int32_t)kItemLimit - (int32_t)size) / 3;
-  const uint32_t n = trip ? min(min(64u, size), (uint32_t)max(room, 1)) : 0u;
-  const bool tr = lane < n;
-  float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-  int32_t cc[4] = {0, 0, 0, 0};
-  // leaf children within the bound: unit words, and whether a second block follows
-  uint32_t uw[4] = {~0u, ~0u, ~0u, ~0u};
-  uint32_t nu = 0, n2 = 0, o = 0;
-  float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  bool live = false;
-  if (tr) {
-    const uint32_t word = W->item[size - 1u - lane];
-    const float l0 = __uint_as_float((uint32_t)W->lb[size - 1u - lane] << 16);
-    o = word & 63u;
-    q = W->pt[o];
-    const float thr = box_bound(__uint_as_float(W->m2[o]), q);
-    live = l0 <= thr;
-    if (live) {
-      if (kStats) {
-        ++cnt.nodes;
-        cnt.flops += 4 * kBoxFlops;
-      }
-      const char* N = W->base[o] + ((uint64_t)(word >> 6) << 7);
-      const float4 lox = gload4(N, 0), loy = gload4(N, 1), loz = gload4(N, 2), hix = gload4(N, 3), hiy = gload4(N, 4),
-                   hiz = gload4(N, 5), ch = gload4(N, 6);
-      const float lx[4] = {lox.x, lox.y, lox.z, lox.w}, ly[4] = {loy.x, loy.y, loy.z, loy.w},
-                  lz[4] = {loz.x, loz.y, loz.z, loz.w};
-      const float hx[4] = {hix.x, hix.y, hix.z, hix.w}, hy[4] = {hiy.x, hiy.y, hiy.z, hiy.w},
-                  hz[4] = {hiz.x, hiz.y, hiz.z, hiz.w};
-      const int32_t c4[4] = {__float_as_int(ch.x), __float_as_int(ch.y), __float_as_int(ch.z), __float_as_int(ch.w)};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float gx = fmaxf(fmaxf(lx[k] - q.x, q.x - hx[k]), 0.0f);
-        const float gy = fmaxf(fmaxf(ly[k] - q.y, q.y - hy[k]), 0.0f);
-        const float gz = fmaxf(fmaxf(lz[k] - q.z, q.z - hz[k]), 0.0f);
-        const float l = gx * gx + gy * gy + gz * gz;
-        // an unused slot has child < 0 and an empty box (l = inf > thr)
-        const bool leaf = c4[k] < 0, hit = leaf && l <= thr;
-        lb[k] = leaf ? INFINITY : l;
-        cc[k] = c4[k];
-        uw[k] = hit ? (((uint32_t)~c4[k] >> 2) << 6) | o : ~0u;
-        nu += hit ? 1u : 0u;
-        n2 += hit ? (uint32_t)~c4[k] & 1u : 0u;
-      }
-    }
-  }
-  size -= n;
-  uint32_t total = 0;
-  bool force = false;
-  if (trip) {
-    done = ~0ull;
-    uint32_t pos = size + wave_prefix_small(nu, total);
-    lds_order();
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (uw[k] != ~0u) W->item[pos++] = uw[k];
-    if (kStats && nu > 0) {
-      cnt.tris += (nu + n2) << 2;
-      cnt.flops += ((nu + n2) << 2) * kQuickFlops;
-    }
-    lds_order();
-  }
-  bool flush = !trip && npend != 0;
-  uint32_t u0 = 0;
-  while (true) {
-    if (flush || (npend > (uint32_t)(kPendCap - 64) && u0 < total)) {
-      npend = flush_pending<kStats>(W, lane, npend, done, cnt);
-      flush = false;
-    } else if (u0 < total) {
-      const uint32_t u = u0 + (lane >> 2);
-      bool cand = false;
-      uint32_t word = 0;
-      float l2 = 0.0f;
-      if (u < total) {
-        const uint32_t pk = W->item[size + u];
-        const uint32_t uo = pk & 63u;
-        const uint32_t bl = pk >> 6;
-        const float4 p = W->pt[uo];
-        float d2, m;
-        quick_dist(p.x, p.y, p.z, W->base[uo] + ((uint64_t)W->off_quick[uo] << 8), (uint64_t)bl * 20u + (lane & 3u), d2,
-                   m);
-        if (p.w >= 0.0f) atomicMin(&W->m2[uo], __float_as_uint(d2 + m));
-        lds_order();
-        l2 = d2 - m;
-        cand = l2 <= keep_bound(__uint_as_float(W->m2[uo]), fabsf(p.w));
-        force |= cand && (m > 1e28f || p.w < 0.0f);
-        word = (bl << 6) | uo;
-        // the slot within its block goes into the low bits of the lower value
-        l2 = __uint_as_float((__float_as_uint(l2 - fabsf(l2) * 0x1p-20f) & ~3u) | (lane & 3u));
-      }
-      const uint64_t mk = __ballot(cand);
-      if (cand) {
-        const uint32_t p = npend + mbcnt64(mk);
-        W->pend[p] = word;
-        W->pend_l2[p] = l2;
-      }
-      npend += (uint32_t)__popcll(mk);
-      lds_order();
-      u0 += 16;
-      // triangles without an upper value bound nothing until they are tested
-      flush = u0 >= total && __ballot(force) != 0;
-    } else if (__ballot(n2 > 0) != 0) {  // the second blocks of wide leaves
-      uint32_t pos = size + wave_prefix_small(n2, total);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (uw[k] != ~0u && ((uint32_t)~cc[k] & 1u)) W->item[pos++] = uw[k] + 64u;
-      lds_order();
-      n2 = 0;
-      u0 = 0;
-    } else {
-      break;
-    }
-  }
-  if (!trip) return;
-  uint32_t pushed = 0;
-  bool put[4] = {false, false, false, false};
-  if (live) {
-    const float thr = box_bound(__uint_as_float(W->m2[o]), q);
-#define MSK_CX(i, j)                                                        \
-  if (lb[j] < lb[i]) {                                                      \
-    float tl = lb[i]; lb[i] = lb[j]; lb[j] = tl;                            \
-    int32_t tc = cc[i]; cc[i] = cc[j]; cc[j] = tc;                          \
-  }
-    MSK_CX(0, 1) MSK_CX(2, 3) MSK_CX(0, 2) MSK_CX(1, 3) MSK_CX(1, 2)
-#undef MSK_CX
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {  // leaf children and unused slots carry lb = inf
-      put[k] = lb[k] <= thr;
-      pushed += put[k] ? 1u : 0u;
-    }
-  }
-  lds_order();
-#pragma unroll
-  for (int k = 3; k >= 0; --k) {
-    const uint64_t m = __ballot(put[k]);
-    if (put[k]) {
-      const uint32_t p = size + mbcnt64(m);
-      W->item[p] = ((uint32_t)cc[k] << 6) | o;
-      W->lb[p] = (uint16_t)(__float_as_uint(lb[k]) >> 16);
-    }
-    size += (uint32_t)__popcll(m);
-  }
-  if (tr && pushed != 1u) atomicAdd(&W->open[o], pushed - 1u);
-  lds_order();
 }
 
 // ------------------------------------------------------ walk machinery
@@ -1263,7 +946,7 @@ __device__ __forceinline__ double shfl_f64(double v, int src) {
 // operator's time. Walks whose columns do not fit their row table are left for
 // walk_finish: the lanes whose walk is done get true.
 template <typename AccT, typename MD>
-__device__ __forceinline__ bool record_point_walks(const MD& M, CoopScratch* W, uint32_t lane, bool mine, int32_t tab,
+__device__ __forceinline__ bool record_point_walks(const MD& M, SearchScratch<TriEl>* W, uint32_t lane, bool mine, int32_t tab,
                                                    const Nearest& hit, WaveTables<AccT>& T, int wi) {
   int32_t p[3] = {0, 0, 0}, n[3] = {0, 0, 0};
   double wt[3] = {0.0, 0.0, 0.0};
@@ -1437,15 +1120,14 @@ __device__ int32_t walk_end(const MD& M, LaneWalk& w, bool capped, const Nearest
 
 // One whole step with a lane-private query (plain kernel).
 template <bool kStats, typename MD>
-__device__ int32_t walk_step(const WalkLaunch& L, const MD& M, const Node4* lds, int32_t n_lds, LaneWalk& w,
-                             Nearest& hit) {
+__device__ int32_t walk_step(const WalkLaunch& L, const MD& M, LaneWalk& w, Nearest& hit) {
   bool capped;
   const int32_t st = walk_begin(L, M, w, capped);
   if (st >= 0) return st;
   hit.d2 = INFINITY;
   hit.orig = INT_MAX;
   hit.slot = w.slot;
-  bvh_nearest<kStats>(M.nodes, M.tris, lds, n_lds, w.x, w.y, w.z, M.radius, hit, w.cnt);
+  bvh_nearest<kStats>(M.nodes, M.tris, w.x, w.y, w.z, M.radius, hit, w.cnt);
   return walk_end(M, w, capped, hit);
 }
 
@@ -1473,20 +1155,13 @@ __global__ void __launch_bounds__(256) walk_plain_kernel(WalkLaunch L) {
   Nearest hit;
   int32_t st;
   do {
-    st = walk_step<kStats>(L, M, nullptr, 0, w, hit);
+    st = walk_step<kStats>(L, M, w, hit);
   } while (st < 0);
   walk_finish_global<kKnn>(L, M, w, st, hit);
 }
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
-#ifndef MSK_LDS_TOP_NODES
-#define MSK_LDS_TOP_NODES 21
-#endif
-// top BVH nodes staged in LDS by the persistent kernel in single-mesh
-// launches (at most kMaxTop), in dynamic LDS: batched launches, whose lanes
-// work on many meshes at once, reserve none
-constexpr int kLdsTop = MSK_LDS_TOP_NODES < kMaxTop ? MSK_LDS_TOP_NODES : kMaxTop;
 #ifndef MSK_PERSISTENT_WAVES_PER_EU
 #define MSK_PERSISTENT_WAVES_PER_EU 4
 #endif
@@ -1526,9 +1201,9 @@ __device__ unsigned long long g_phase_cycles[16];
 template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   __shared__ WaveTables<AccT> T;
-  __shared__ CoopScratch coop[kWaves];
+  __shared__ SearchScratch<TriEl> coop[kWaves];
   const int wi = (int)uniform(threadIdx.x >> 6);
-  CoopScratch* W = &coop[wi];
+  SearchScratch<TriEl>* W = &coop[wi];
   for (int i = threadIdx.x; i < kWaves * 2 * kSlots; i += blockDim.x) {
     (&T.key[0][0][0])[i] = kEmptyKey;
     (&T.v1[0][0][0])[i] = acc_zero<AccT>();
@@ -1585,7 +1260,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
                       (size == 0 || (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
     const bool book =
         !step && (size == 0 || (!drained && (int)__popcll(__ballot(mode == 3 || (mode == 0 && owner))) >= L.regen_min));
-    search_pass<kStats>(W, lane, !step && !book, step ? pend : ~0ull, size, npend, cnt);
+    search_pass<kStats>(TriEl{}, W, lane, !step && !book, step ? pend : ~0ull, size, npend, cnt);
     MSK_TICK(tk1);
     MSK_ACC(1, tk0, tk1);
 #if MSK_PHASE_TIMING
@@ -1638,10 +1313,10 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kern
         hit.slot = -1;
         hit.l1 = hit.l2 = 0.0f;
         if (mine && fin_status != kEscaped) {
-          const unsigned long long k = W->key[lane];
+          const unsigned long long k = W->own.key[lane];
           hit.d2 = __uint_as_float((uint32_t)(k >> 32));
           hit.orig = (int32_t)(uint32_t)k;
-          hit.slot = W->rec_slot[lane];
+          hit.slot = W->own.rec_slot[lane];
           const float4 q = W->pt[lane];
           answer_bary(M.tris, q.x, q.y, q.z, hit);
         }
@@ -1780,8 +1455,6 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
     p[i] = v;
 }
 
-// Point rows whose inset point is closer than h/2 to the surface are
-// discarded (the inset left the thin region it should probe).
 // Largest ball inside the domain tangent at each point row's sample s, centre
 // c = s - r n (Sec. 3.2; Alg. 2, LargestTangentBall): bisection over
 // [0, r_max]; a radius is accepted when c's nearest surface point is at
@@ -1792,43 +1465,34 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 // d2 < B) and stops at the first triangle found with sqrt(d2) < t; when none
 // lies below B the ball is accepted. Same decisions as comparing the exact
 // nearest distance with t, with only the boxes near the ball visited.
-// Whether the ball of radius r touching s from the inside is accepted (the
-// test of one bisection step).
-__device__ bool tangent_ball_inside(const MeshDev& M, float sx, float sy, float sz, double nx, double ny, double nz,
-                                    float mid, float tol, uint32_t& issued) {
-  const double cxd = sx - mid * nx, cyd = sy - mid * ny, czd = sz - mid * nz;
-  const float cx = (float)cxd, cy = (float)cyd, cz = (float)czd;
-  const float t = mid - fminf(tol, mid * 0x1p-10f);
-  const float bound = t > 0.0f ? (t * t) * (1.0f + 0x1p-20f) : 0.0f;
-  Nearest h;
-  h.d2 = bound; h.orig = INT_MAX; h.slot = -1;
+//
+// The bisection takes three levels per round: the eight lanes of a row take
+// the (up to) seven midpoints of the next three levels at once (lane k heap
+// node k of that subtree: node 1 the current midpoint, node 2k and 2k + 1 the
+// midpoints of its lower and upper halves), then all follow the path the
+// sequential bisection takes through them. Every midpoint is formed by the
+// same float operations as in the sequential loop, so the radius is the same.
+// The midpoints' queries run on the wavefront-shared search: a large ball deep
+// inside the shape meets thousands of boxes, which all 64 lanes share. (On a
+// lane each: 6.2 ms for 4,096 rows on 80,000 faces.) rows_per_wave (1, 2, 4 or
+// 8) is as low as still gives every resident wavefront rows. row_queries
+// counts the bounded queries that the lanes issue (up to seven per round of
+// three levels, so more than the iters decisions they serve).
+__global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
+    tangent_ball_kernel(MeshDev M, int64_t n_rows, int32_t rows_per_wave, float r_max, int32_t iters, float tol,
+                        float* radius) {
+  __shared__ SearchScratch<TriEl, true> coop[kWaves];
+  const int wi = (int)uniform(threadIdx.x >> 6);
+  SearchScratch<TriEl, true>* W = &coop[wi];
+  const uint32_t lane = __lane_id();
+  const int sub = (int)(lane & 7u), gbase = (int)(lane & ~7u);
   TravCount cnt;
-  if (t > 0.0f) {
-    bvh_nearest<false, true>(M.nodes, M.tris, nullptr, 0, cx, cy, cz, M.radius, h, cnt, t);
-    ++issued;
-  }
-  const bool empty = h.orig == INT_MAX || sqrtf(h.d2) >= t;
-  return empty && sqrt(cxd * cxd + cyd * cyd + czd * czd) + mid <= M.radius_d;
-}
-
-// The bisection of a row, three levels per round: the eight lanes of a row
-// evaluate the (up to) seven midpoints of the next three levels at once (lane
-// k takes heap node k of that subtree: node 1 the current midpoint, node 2k
-// and 2k + 1 the midpoints of its lower and upper halves), then all follow
-// the path the sequential bisection takes through them. Every midpoint is
-// formed by the same float operations as in the sequential loop, so the
-// radius is the same; the rounds of dependent queries drop from iters to
-// ceil(iters / 3), and eight lanes per row fill the GPU with 16,384 rows.
-// row_queries counts the bounded queries the lanes issue (up to seven per
-// round of three levels, so more than the iters decisions they serve).
-__global__ void __launch_bounds__(64) tangent_ball_kernel(MeshDev M, int64_t n_rows, float r_max, int32_t iters,
-                                                          float tol, float* radius) {
-  const int lane = threadIdx.x & 63, sub = lane & 7, gbase = lane & ~7;
-  // eight rows per 64-lane workgroup; the loop bound is uniform over the
-  // workgroup, so every lane takes part in every ballot
-  for (int64_t base = (int64_t)blockIdx.x * 8; base < n_rows; base += (int64_t)gridDim.x * 8) {
-    const int64_t i = base + (threadIdx.x >> 3);
-    const bool valid = i < n_rows;
+  uint32_t size = 0, npend = 0;
+  const int64_t waves = (int64_t)gridDim.x * kWaves;
+  for (int64_t base = ((int64_t)blockIdx.x * kWaves + wi) * rows_per_wave; base < n_rows;
+       base += waves * rows_per_wave) {
+    const int64_t i = base + (lane >> 3);
+    const bool valid = (int32_t)(lane >> 3) < rows_per_wave && i < n_rows;
     float sx = 0.f, sy = 0.f, sz = 0.f;
     double nx = 0.0, ny = 0.0, nz = 1.0;
     if (valid) {
@@ -1841,7 +1505,10 @@ __global__ void __launch_bounds__(64) tangent_ball_kernel(MeshDev M, int64_t n_r
     uint32_t issued = 0;
     for (int32_t done = 0; done < iters;) {
       const int levels = min(3, iters - done);
-      bool res = false;
+      // the lane's midpoint: whether its ball lies inside the bounding sphere,
+      // and the bounded query for a triangle closer than t
+      bool inside = false, fresh = false;
+      float t = 0.0f;
       if (valid && sub >= 1 && sub < (1 << levels)) {
         float a = lo, b = hi;
         const int depth = 31 - __clz(sub);  // bits of the node index below its leading one
@@ -1852,9 +1519,48 @@ __global__ void __launch_bounds__(64) tangent_ball_kernel(MeshDev M, int64_t n_r
           else
             b = m;
         }
-        res = tangent_ball_inside(M, sx, sy, sz, nx, ny, nz, 0.5f * (a + b), tol, issued);
+        const float mid = 0.5f * (a + b);
+        const double cxd = sx - mid * nx, cyd = sy - mid * ny, czd = sz - mid * nz;
+        t = mid - fminf(tol, mid * 0x1p-10f);
+        inside = sqrt(cxd * cxd + cyd * cyd + czd * czd) + mid <= M.radius_d;
+        if (t > 0.0f) {
+          ++issued;
+          // a ball that leaves the bounding sphere is refused whatever the query says
+          if (inside) {
+            search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, (float)cxd, (float)cyd, (float)czd, -1);
+            const float bound = (t * t) * (1.0f + 0x1p-20f);
+            W->m2[lane] = __float_as_uint(bound);
+            W->own.key[lane] = ((unsigned long long)__float_as_uint(bound) << 32) | (uint32_t)INT_MAX;
+            // an upper value below `stop` means sqrt(exact value) < t
+            const float ts = t - W->pt[lane].w;
+            W->stop[lane] = ts > 0.0f ? ts * ts * (1.0f - 0x1p-20f) : 0.0f;
+            fresh = true;
+          }
+        }
       }
-      const unsigned long long mask = __ballot(res);  // every lane of the wavefront takes part
+      bool closer = false, open = fresh;
+      search_push(W, lane, fresh, M.entry, size);
+      while (true) {
+        const bool step = size == 0;
+        search_pass<false, true>(TriEl{}, W, lane, !step, ~0ull, size, npend, cnt);
+        if (!step) continue;
+        bool again = false;
+        if (open) {
+          const unsigned long long k = W->own.key[lane];
+          closer = (int32_t)(uint32_t)k != INT_MAX && sqrtf(__uint_as_float((uint32_t)(k >> 32))) < t;
+          // ended by an upper value that no exact one has confirmed: search on
+          // exact values only
+          again = !closer && W->pt[lane].w >= 0.0f && __uint_as_float(W->m2[lane]) < W->stop[lane];
+          open = again;
+          if (again) {
+            W->pt[lane].w = -W->pt[lane].w;
+            W->m2[lane] = __float_as_uint((t * t) * (1.0f + 0x1p-20f));
+          }
+        }
+        search_push(W, lane, again, M.entry, size);
+        if (size == 0) break;
+      }
+      const unsigned long long mask = __ballot(inside && !closer);  // every lane of the wavefront takes part
       int node = 1;
       for (int l = 0; l < levels; ++l) {
         const float mid = 0.5f * (lo + hi);
@@ -1870,43 +1576,6 @@ __global__ void __launch_bounds__(64) tangent_ball_kernel(MeshDev M, int64_t n_r
     if (valid && sub == 0) radius[i] = lo;
     if (valid && issued) atomicAdd(M.row_queries + i, (unsigned long long)issued);
   }
-}
-
-__device__ __forceinline__ void discard_row(const MeshDev& M, int64_t i, int32_t* discarded) {
-  const float sgn = M.side ? 1.0f : -1.0f;
-  const float x = M.p[3 * i] + sgn * M.inset * M.n[3 * i];
-  const float y = M.p[3 * i + 1] + sgn * M.inset * M.n[3 * i + 1];
-  const float z = M.p[3 * i + 2] + sgn * M.inset * M.n[3 * i + 2];
-  Nearest h;
-  h.d2 = INFINITY; h.orig = INT_MAX; h.slot = M.slot_of_tri[M.tri[i]];
-  TravCount cnt;
-  bvh_nearest<false>(M.nodes, M.tris, nullptr, 0, x, y, z, M.radius, h, cnt);
-  discarded[i] = h.d2 < 0.25f * M.inset * M.inset ? 1 : 0;
-  atomicAdd(M.row_queries + i, 1ull);
-}
-
-__global__ void discard_kernel(MeshDev M, int64_t n_rows, int32_t* discarded) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_rows) discard_row(M, i, discarded);
-}
-
-// The discard pass over the point rows of several meshes in one launch:
-// launch index j belongs to the last range k with R[k].first <= j, as row
-// j - R[k].first of mesh R[k].mesh.
-__global__ void discard_batch_kernel(const MeshDev* __restrict__ meshes, const RowRange* __restrict__ R,
-                                     int32_t n_ranges, int64_t n_total) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n_total) return;
-  int32_t lo = 0, hi = n_ranges - 1;
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if (R[mid].first <= j)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  const RowRange r = R[lo];
-  discard_row(meshes[r.mesh], j - r.first, r.discarded);
 }
 
 __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const float* __restrict__ Q,
@@ -1989,46 +1658,163 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
   q[16] = make_float4((float)(cy / bc), (float)bc, (float)F, (float)(F * lmax * lmax));
 }
 
-// Closest points of nq queries, on the walk kernel's traversal: lanes with an
+// A query of the query kernel: its point (scene frame) and mesh, a warm-start
+// slot or -1, and the mesh's entry level.
+struct Query {
+  float x, y, z, radius;
+  const Node4* nodes;
+  const float4* quick;
+  const TriRec* tris;
+  int32_t warm, entry;
+};
+
+// Caller's points: nearest triangle, squared distance and barycentrics.
+struct PointQueries {
+  const Node4* nodes;
+  const float4* quick;
+  const TriRec* tris;
+  float radius;
+  int32_t entry;
+  double cx, cy, cz;
+  const float* Q;
+  int32_t* tri;
+  float* d2;
+  float* bary;
+  static constexpr bool kBary = true;
+  __device__ __forceinline__ Query load(int64_t i) const {
+    return Query{(float)((double)Q[3 * i] - cx), (float)((double)Q[3 * i + 1] - cy), (float)((double)Q[3 * i + 2] - cz),
+                 radius, nodes, quick, tris, -1, entry};
+  }
+  __device__ __forceinline__ void store(int64_t i, const Nearest& h) const {
+    tri[i] = h.orig;
+    d2[i] = h.d2;
+    nearest_bary(h, bary[2 * i], bary[2 * i + 1]);
+  }
+};
+
+// Point rows whose inset point is closer than h/2 to the surface are
+// discarded (the inset left the thin region it should probe).
+template <typename MD>
+__device__ __forceinline__ Query discard_query(const MD& M, int64_t i) {
+  const float sgn = M.side ? 1.0f : -1.0f;
+  return Query{M.p[3 * i] + sgn * M.inset * M.n[3 * i], M.p[3 * i + 1] + sgn * M.inset * M.n[3 * i + 1],
+               M.p[3 * i + 2] + sgn * M.inset * M.n[3 * i + 2], M.radius, M.nodes, M.quick, M.tris,
+               M.slot_of_tri[M.tri[i]], M.entry};
+}
+template <typename MD>
+__device__ __forceinline__ void discard_store(const MD& M, int64_t i, const Nearest& h, int32_t* discarded) {
+  discarded[i] = h.d2 < 0.25f * M.inset * M.inset ? 1 : 0;
+  atomicAdd(M.row_queries + i, 1ull);
+}
+struct DiscardRows {
+  MeshDev M;
+  int32_t* discarded;
+  static constexpr bool kBary = false;
+  __device__ __forceinline__ Query load(int64_t i) const { return discard_query(M, i); }
+  __device__ __forceinline__ void store(int64_t i, const Nearest& h) const { discard_store(M, i, h, discarded); }
+};
+
+// The same over the point rows of several meshes: launch index j belongs to
+// the last range k with R[k].first <= j, as row j - R[k].first of its mesh.
+struct DiscardBatch {
+  const MeshDev* meshes;
+  const RowRange* R;
+  int32_t n_ranges;
+  static constexpr bool kBary = false;
+  __device__ __forceinline__ RowRange range(int64_t j) const {
+    int32_t lo = 0, hi = n_ranges - 1;
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (R[mid].first <= j)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    return R[lo];
+  }
+  __device__ __forceinline__ Query load(int64_t j) const {
+    const RowRange r = range(j);
+    return discard_query(meshes[r.mesh], j - r.first);
+  }
+  __device__ __forceinline__ void store(int64_t j, const Nearest& h) const {
+    const RowRange r = range(j);
+    discard_store(meshes[r.mesh], j - r.first, h, r.discarded);
+  }
+};
+
+// First slot of the leaf that a descent by the boxes' farthest corners
+// reaches: the warm start of a query without one. (Searches without a first
+// bound push every child they meet: 64 of them filled the stack, and 1,000,003
+// cold queries on 499,280 faces took 40 ms. A descent by the nearest box picks
+// at random among the boxes that hold the point.)
+__device__ __forceinline__ int32_t nearest_leaf(const Node4* nodes, float x, float y, float z) {
+  int32_t c = 0;
+  do {
+    const Node4* N = nodes + c;
+    float best = INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float gx = fmaxf(fabsf(N->lox[k] - x), fabsf(N->hix[k] - x));
+      const float gy = fmaxf(fabsf(N->loy[k] - y), fabsf(N->hiy[k] - y));
+      const float gz = fmaxf(fabsf(N->loz[k] - z), fabsf(N->hiz[k] - z));
+      const float l = gx * gx + gy * gy + gz * gz;
+      if (l < best) {  // an unused slot has an empty box: l = inf
+        best = l;
+        c = N->child[k];
+      }
+    }
+    if (!(best < INFINITY)) return -1;
+  } while (c >= 0);
+  return ~c & ~3;
+}
+
+// Nearest triangles of n queries on the wavefront-shared search: lanes with an
 // answered query wait until a quarter of the wavefront's queries do, then
-// write their answers and take the next queries together. At most 2^own_shift
+// store their answers and take the next queries together. At most 2^own_shift
 // lanes of a wavefront carry a query: a small call spreads over all
-// wavefronts, whose other lanes help with the triangle tests. Block k of
-// wavefront g holds the queries from ((k G + g) << own_shift) on, G the
-// number of wavefronts.
+// wavefronts, whose other lanes help. The k-th block of wavefront g holds the
+// up to 8 queries from ((k G + g) << block_shift) on, G the number of
+// wavefronts: neighbours share a wavefront, and each wavefront sees all parts
+// of the caller's array (in blocks of 64, an array of points near the surface
+// followed by far ones took 12.4 instead of 6.9 ms).
+//   On a thread per query with a traversal of its own, 1,000 queries on 1,280
+// faces took 230 us and 1,000,003 on 499,280 faces 9.6 ms, as long as the
+// slowest traversal of each wavefront.
+template <typename Src>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
-    query_stream_kernel(const Node4* __restrict__ nodes, const TriRec* __restrict__ tris,
-                        const float4* __restrict__ quick, float radius, double cx, double cy, double cz,
-                        const float* __restrict__ Q, int64_t nq, int32_t own_shift, int32_t entry,
-                        int32_t* __restrict__ tri, float* __restrict__ d2, float* __restrict__ bary) {
-  __shared__ CoopScratch coop[kWaves];
+    query_stream_kernel(Src src, int64_t nq, int32_t own_shift) {
+  __shared__ SearchScratch<TriEl> coop[kWaves];
   const int wi = (int)uniform(threadIdx.x >> 6);
-  CoopScratch* W = &coop[wi];
+  SearchScratch<TriEl>* W = &coop[wi];
   const uint32_t lane = __lane_id();
   const int64_t G = (int64_t)gridDim.x * kWaves, g = (int64_t)blockIdx.x * kWaves + wi;
   const bool owner = lane < (1u << own_shift);
+  const int block_shift = min(own_shift, 3);
   int64_t next = 0;  // queries handed out (uniform)
   bool drained = false;
   int32_t mode = 0;  // 0 idle, 1 searching, 2 search ended
   int64_t qi = 0;
+  const TriRec* tris = nullptr;
+  int32_t entry = 1;
   uint32_t npend = 0, size = 0;
   TravCount cnt;
   while (true) {
     if (mode == 1 && W->open[lane] == 0) mode = 2;
+    size = uniform(size);
     const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1 || mode == 2);
     const bool step = size == 0 || (size <= (uint32_t)kRootLimit &&
                                     (int)__popcll(pend) >= min(kStepMin, (int)(__popcll(busy) + 3) >> 2));
-    search_pass<false>(W, lane, !step, pend, size, npend, cnt);
+    search_pass<false>(TriEl{}, W, lane, !step, pend, size, npend, cnt);
     if (step) {
       bool fresh = false;
       if (mode == 2) {
         Nearest h;
         if (search_answer(W, lane, h)) {
-          const float4 q = W->pt[lane];
-          answer_bary(tris, q.x, q.y, q.z, h);
-          tri[qi] = h.orig;
-          d2[qi] = h.d2;
-          nearest_bary(h, bary[2 * qi], bary[2 * qi + 1]);
+          if (Src::kBary) {
+            const float4 q = W->pt[lane];
+            answer_bary(tris, q.x, q.y, q.z, h);
+          }
+          src.store(qi, h);
           mode = 0;
         } else {
           mode = 1;
@@ -2038,24 +1824,24 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
       const uint64_t idle = __ballot(mode == 0 && owner);
       if (!drained && idle != 0) {
         const int64_t pos = next + mbcnt64(idle);
-        const int64_t q = ((((pos >> own_shift) * G) + g) << own_shift) + (pos & ((1ll << own_shift) - 1));
+        const int64_t q = ((((pos >> block_shift) * G) + g) << block_shift) + (pos & ((1ll << block_shift) - 1));
         const bool take = mode == 0 && owner && q < nq;
         if (take) {
           qi = q;
-          const float x = (float)((double)Q[3 * qi] - cx);
-          const float y = (float)((double)Q[3 * qi + 1] - cy);
-          const float z = (float)((double)Q[3 * qi + 2] - cz);
-          if (fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))) <= 1.7f * radius) {
-            search_start(W, lane, nodes, quick, tris, radius, x, y, z, -1);
+          const Query p = src.load(qi);
+          if (fmaxf(fabsf(p.x), fmaxf(fabsf(p.y), fabsf(p.z))) <= 1.7f * p.radius) {
+            // few queries leave the stack room enough for a cold start
+            const int32_t warm = p.warm < 0 && own_shift > 2 ? nearest_leaf(p.nodes, p.x, p.y, p.z) : p.warm;
+            search_start(W, lane, p.nodes, p.quick, p.tris, p.radius, p.x, p.y, p.z, warm);
+            tris = p.tris;
+            entry = p.entry;
             mode = 1;
             fresh = true;
           } else {  // the prefilter's margins hold for |p| <= 3 R
             Nearest h;
             h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
-            bvh_nearest<false>(nodes, tris, nullptr, 0, x, y, z, radius, h, cnt);
-            tri[qi] = h.orig;
-            d2[qi] = h.d2;
-            nearest_bary(h, bary[2 * qi], bary[2 * qi + 1]);
+            bvh_nearest<false>(p.nodes, p.tris, p.x, p.y, p.z, p.radius, h, cnt);
+            src.store(qi, h);
           }
         }
         const uint32_t got = (uint32_t)__popcll(__ballot(take));
@@ -2256,18 +2042,28 @@ hipError_t launch_fill_u32(void* p, int64_t n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_discard(const MeshDev& M, int64_t n_rows, int32_t* discarded, hipStream_t s) {
-  if (n_rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(discard_kernel, dim3(blocks_for(n_rows, 128)), dim3(128), 0, s, M, n_rows, discarded);
+// The query kernel over n queries: as many wavefronts as are resident at once
+// (4 per SIMD), each with as few queries at a time as still covers n, up to
+// one per lane.
+template <typename Src>
+static hipError_t launch_queries(const Src& src, int64_t n, int32_t n_cu, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const int64_t waves = 16ll * n_cu;
+  int own_shift = 0;
+  while (own_shift < 6 && (waves << own_shift) < n) ++own_shift;
+  const int64_t blocks = std::min<int64_t>(4ll * n_cu, (((n - 1) >> own_shift) / kWaves) + 1);
+  hipLaunchKernelGGL(query_stream_kernel<Src>, dim3((unsigned)blocks), dim3(256), 0, s, src, n, own_shift);
   return hipGetLastError();
 }
 
+hipError_t launch_discard(const MeshDev& M, int64_t n_rows, int32_t n_cu, int32_t* discarded, hipStream_t s) {
+  return launch_queries(DiscardRows{M, discarded}, n_rows, n_cu, s);
+}
+
 hipError_t launch_discard_batch(const MeshDev* meshes, const RowRange* ranges, int32_t n_ranges, int64_t n_total,
-                                hipStream_t s) {
-  if (n_ranges <= 0 || n_total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(discard_batch_kernel, dim3(blocks_for(n_total, 128)), dim3(128), 0, s, meshes, ranges, n_ranges,
-                     n_total);
-  return hipGetLastError();
+                                int32_t n_cu, hipStream_t s) {
+  if (n_ranges <= 0) return hipSuccess;
+  return launch_queries(DiscardBatch{meshes, ranges, n_ranges}, n_total, n_cu, s);
 }
 
 hipError_t launch_row_totals(const RowCounters* sets, int32_t n_sets, unsigned long long* out, hipStream_t s) {
@@ -2284,11 +2080,15 @@ hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, con
   return hipGetLastError();
 }
 
-hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, int32_t iters, float tol, float* radius,
-                               hipStream_t s) {
+hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, int32_t iters, float tol, int32_t n_cu,
+                               float* radius, hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(tangent_ball_kernel, dim3(blocks_for(8 * n_rows, 64)), dim3(64), 0, s, M, n_rows, r_max, iters,
-                     tol, radius);
+  const int64_t waves = 16ll * n_cu;
+  int32_t rows = 1;
+  while (rows < 8 && rows * waves < n_rows) rows *= 2;
+  const int64_t blocks = std::min<int64_t>(4ll * n_cu, (n_rows + rows * kWaves - 1) / (rows * kWaves));
+  hipLaunchKernelGGL(tangent_ball_kernel, dim3((unsigned)blocks), dim3(256), 0, s, M, n_rows, rows, r_max, iters, tol,
+                     radius);
   return hipGetLastError();
 }
 
@@ -2301,16 +2101,7 @@ hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, fl
 hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t entry,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s) {
-  if (nq <= 0) return hipSuccess;
-  // as many wavefronts as are resident at once (4 per SIMD), each with as few
-  // queries at a time as still covers nq, up to one per lane
-  const int64_t waves = 16ll * n_cu;
-  int own_shift = 0;
-  while (own_shift < 6 && (waves << own_shift) < nq) ++own_shift;
-  const int64_t blocks = std::min<int64_t>(4ll * n_cu, (((nq - 1) >> own_shift) / kWaves) + 1);
-  hipLaunchKernelGGL(query_stream_kernel, dim3((unsigned)blocks), dim3(256), 0, s, nodes, tris, quick, radius, c[0],
-                     c[1], c[2], Q, nq, own_shift, entry, tri, d2, bary);
-  return hipGetLastError();
+  return launch_queries(PointQueries{nodes, quick, tris, radius, entry, c[0], c[1], c[2], Q, tri, d2, bary}, nq, n_cu, s);
 }
 
 hipError_t launch_finalize(const MeshDev& M, int64_t n_rows, const int64_t* walks, const double* w, double* S,

@@ -320,37 +320,44 @@ std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t
   return "";
 }
 
-void align_leaves(HostBvh& b) {
-  TriRec pad;
-  pad.a = pad.b = pad.c = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int32_t pad_index = kPadTri;
-  std::memcpy(&pad.a.w, &pad_index, 4);
-  std::vector<TriRec> tris;
-  tris.reserve(b.tris.size() * 3 / 2 + 8);
-  for (Node4& w : b.nodes)
+std::vector<int32_t> align_leaf_order(std::vector<Node4>& nodes, int64_t n, int& entry) {
+  std::vector<int32_t> from;
+  from.reserve((size_t)n * 3 / 2 + 8);
+  for (Node4& w : nodes)
     for (int k = 0; k < 4; ++k) {
       if (w.child[k] >= 0 || w.count[k] == 0) continue;
       const int32_t first = -w.child[k] - 1;
-      w.child[k] = -((int32_t)tris.size() + (w.count[k] - 1) / 4) - 1;
-      for (int32_t i = first; i < first + w.count[k]; ++i) {
-        int32_t t;
-        std::memcpy(&t, &b.tris[i].a.w, 4);
-        b.slot_of_tri[t] = (int32_t)tris.size();
-        tris.push_back(b.tris[i]);
-      }
-      while (tris.size() % 4) tris.push_back(pad);
+      w.child[k] = -((int32_t)from.size() + (w.count[k] - 1) / 4) - 1;
+      for (int32_t i = first; i < first + w.count[k]; ++i) from.push_back(i);
+      while (from.size() % 4) from.push_back(-1);
     }
-  b.tris.swap(tris);
   // levels 0, 1, 2 (nodes 0; 1-4; 5-20) with four inner children each
-  b.entry = 1;
+  entry = 1;
   for (size_t level = 1, i = 0; level <= 16; level *= 4) {
-    bool full = i + level <= b.nodes.size();
+    bool full = i + level <= nodes.size();
     for (size_t j = i; full && j < i + level; ++j)
-      for (int k = 0; k < 4; ++k) full = full && b.nodes[j].child[k] >= 0;
+      for (int k = 0; k < 4; ++k) full = full && nodes[j].child[k] >= 0;
     if (!full) break;
-    b.entry = (int)(4 * level);
+    entry = (int)(4 * level);
     i += level;
   }
+  return from;
+}
+
+void align_leaves(HostBvh& b) {
+  const std::vector<int32_t> from = align_leaf_order(b.nodes, (int64_t)b.tris.size(), b.entry);
+  TriRec pad;
+  pad.a = pad.b = pad.c = make_float4(0.f, 0.f, 0.f, 0.f);
+  std::memcpy(&pad.a.w, &kPadTri, 4);
+  std::vector<TriRec> tris(from.size(), pad);
+  for (size_t s = 0; s < from.size(); ++s) {
+    if (from[s] < 0) continue;
+    tris[s] = b.tris[from[s]];
+    int32_t t;
+    std::memcpy(&t, &tris[s].a.w, 4);
+    b.slot_of_tri[t] = (int32_t)s;
+  }
+  b.tris.swap(tris);
 }
 
 }  // namespace msk

@@ -1747,10 +1747,12 @@ struct msk_kelvin {
   double centre[3] = {0, 0, 0};
   double radius = 0;                // bound of the inverted domain
   double lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};  // box of the inverted vertices
-  int32_t depth = 0, leaf_size = 4;
+  int32_t depth = 0, leaf_size = 4, entry = 1;
+  double scale = 1;
   int64_t n_nodes = 0;
   Node4* d_nodes = nullptr;
   KelvinTri* d_tris = nullptr;
+  float4* d_quick = nullptr;
   KelvinPre* d_pre = nullptr;
 };
 
@@ -1829,6 +1831,7 @@ extern "C" msk_status msk_kelvin_create(msk_ctx* ctx, const msk_mesh* m, const d
     }
     rmax = std::max(rmax, 1.0 / std::sqrt(r2));
   }
+  const double scale = std::ldexp(1.0, -std::ilogb(rmax));
   for (int64_t t = 0; t < nf; ++t) {
     KelvinTri& T = rec[t];
     double* P[3] = {T.a, T.b, T.c};
@@ -1884,18 +1887,27 @@ extern "C" msk_status msk_kelvin_create(msk_ctx* ctx, const msk_mesh* m, const d
       l = std::max(l, l2);
       h = std::min(h, u2);
       const double pad = 1e-12 * (std::fabs(l) + std::fabs(h)) + 1e-15 * std::sqrt(1.0 / m2);
-      boxes[t].lo[k] = round_down(l - pad);
-      boxes[t].hi[k] = round_up(h + pad);
-      cen[3 * t + k] = (float)(0.5 * (l + h));
+      boxes[t].lo[k] = round_down((l - pad) * scale);
+      boxes[t].hi[k] = round_up((h + pad) * scale);
+      cen[3 * t + k] = (float)(0.5 * (l + h) * scale);
     }
   }
   std::vector<Node4> nodes;
   std::vector<int32_t> leaf_order;
   int depth = 0;
-  std::string err = build_bvh_boxes(boxes, cen, leaf_size, nodes, leaf_order, depth);
+  // the search lists a leaf's elements four at a time: narrower leaves only
+  // cost nodes (1,024 rows x 64 walks and 32,768 killing walks on 79,380
+  // elements: see kelvin_stream_kernel)
+  std::string err = build_bvh_boxes(boxes, cen, std::max(leaf_size, 4), nodes, leaf_order, depth);
   if (!err.empty()) return fail(ctx, MSK_ERR_INVALID_ARG, "inverted BVH: " + err);
-  std::vector<KelvinTri> ordered(leaf_order.size());
-  for (size_t i = 0; i < leaf_order.size(); ++i) ordered[i] = rec[leaf_order[i]];
+  int entry = 1;
+  const std::vector<int32_t> from = align_leaf_order(nodes, (int64_t)leaf_order.size(), entry);
+  KelvinTri pad;
+  std::memset(&pad, 0, sizeof(pad));
+  pad.orig = kPadTri;
+  std::vector<KelvinTri> ordered(from.size(), pad);
+  for (size_t s = 0; s < from.size(); ++s)
+    if (from[s] >= 0) ordered[s] = rec[leaf_order[from[s]]];
   msk_kelvin* K = new msk_kelvin();
   K->ctx = ctx;
   K->mesh = m;
@@ -1907,12 +1919,16 @@ extern "C" msk_status msk_kelvin_create(msk_ctx* ctx, const msk_mesh* m, const d
   K->radius = std::max(rmax, 1.0 / std::sqrt(dmin));
   K->depth = depth;
   K->leaf_size = leaf_size;
+  K->entry = entry;
+  K->scale = scale;
   K->n_nodes = (int64_t)nodes.size();
   hipError_t he;
   if ((he = upload(ctx, &K->d_nodes, nodes.data(), nodes.size())) != hipSuccess ||
       (he = upload(ctx, &K->d_tris, ordered.data(), ordered.size())) != hipSuccess ||
       (he = dalloc(&K->d_pre, ordered.size())) != hipSuccess ||
-      (he = launch_kelvin_prepare(K->d_tris, (int64_t)ordered.size(), K->d_pre, ctx->stream)) != hipSuccess ||
+      (he = dalloc(&K->d_quick, 5 * (ordered.size() + kQuickPad))) != hipSuccess ||
+      (he = launch_kelvin_prepare(K->d_tris, (int64_t)ordered.size(), scale, K->d_pre, K->d_quick, ctx->stream)) !=
+          hipSuccess ||
       (he = hipStreamSynchronize(ctx->stream)) != hipSuccess) {
     msk_kelvin_destroy(K);
     return fail(ctx, he == hipErrorOutOfMemory ? MSK_ERR_OOM : MSK_ERR_DEVICE,
@@ -1944,6 +1960,7 @@ extern "C" void msk_kelvin_destroy(msk_kelvin* K) {
   dfree(K->d_nodes);
   dfree(K->d_tris);
   dfree(K->d_pre);
+  dfree(K->d_quick);
   delete K;
 }
 
@@ -1953,6 +1970,9 @@ static KelvinDev kelvin_dev(const msk_kelvin* K, double eps, const msk_dtn_opts&
   D.nodes = K->d_nodes;
   D.tris = K->d_tris;
   D.pre = K->d_pre;
+  D.quick = K->d_quick;
+  D.entry = K->entry;
+  D.scale = K->scale;
   D.n_tris = K->mesh->nf;
   D.radius = K->radius;
   D.eps2 = eps * eps;
@@ -1973,7 +1993,7 @@ extern "C" msk_status msk_kelvin_closest_points(msk_ctx* ctx, const msk_kelvin* 
   if (nq == 0) return MSK_OK;
   msk_dtn_opts o;
   msk_dtn_opts_default(&o);
-  HIP_TRY(ctx, launch_kelvin_closest(kelvin_dev(K, 0.0, o), Q, nq, tri, d2, qpt, bary, ctx->stream));
+  HIP_TRY(ctx, launch_kelvin_closest(kelvin_dev(K, 0.0, o), Q, nq, ctx->n_cu, tri, d2, qpt, bary, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return MSK_OK;
 }
@@ -2088,7 +2108,7 @@ extern "C" msk_status msk_estimate_kelvin(msk_ctx* ctx, const msk_kelvin* K, con
   HIP_K(launch_fill_u64(d_rq, n, 0, s));
   HIP_K(launch_fill_u64(d_kq, 1, 0, s));
   const KelvinDev D = kelvin_dev(K, eps, o);
-  HIP_K(launch_kelvin_tangent(D, d_st, d_nt, n, r_max, po.bisect_iters, 0.5 * eps, d_rad, d_tq, s));
+  HIP_K(launch_kelvin_tangent(D, d_st, d_nt, n, r_max, po.bisect_iters, 0.5 * eps, ctx->n_cu, d_rad, d_tq, s));
   HIP_K(hipEventRecord(ev[1], s));
   KelvinDev DW = D;
   if (kill_walks > 0) {  // the origin's nearest element, shared by the first steps of all killing walks
@@ -2099,7 +2119,7 @@ extern "C" msk_status msk_estimate_kelvin(msk_ctx* ctx, const msk_kelvin* K, con
     double ho[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int32_t hot = -1;
     if (e1 == hipSuccess) e1 = hipMemcpyAsync(d_o, ho, sizeof(ho), hipMemcpyHostToDevice, s);
-    if (e1 == hipSuccess) e1 = launch_kelvin_closest(D, d_o, 1, d_ot, d_o + 3, d_o + 4, d_o + 7, s);
+    if (e1 == hipSuccess) e1 = launch_kelvin_closest(D, d_o, 1, ctx->n_cu, d_ot, d_o + 3, d_o + 4, d_o + 7, s);
     if (e1 == hipSuccess) e1 = hipMemcpyAsync(ho, d_o, sizeof(ho), hipMemcpyDeviceToHost, s);
     if (e1 == hipSuccess) e1 = hipMemcpyAsync(&hot, d_ot, sizeof(hot), hipMemcpyDeviceToHost, s);
     if (e1 == hipSuccess) e1 = hipStreamSynchronize(s);
@@ -2120,7 +2140,7 @@ extern "C" msk_status msk_estimate_kelvin(msk_ctx* ctx, const msk_kelvin* K, con
     HIP_K(launch_fill_u64(d_wstats, 3, 0, s));
   }
   HIP_K(launch_kelvin_walks(DW, d_st, d_nt, d_rad, n, pairs, u0, kill_walks, d_ls, d_lt, d_lb, d_lq, d_g, d_rq,
-                            d_kq, d_next, d_wstats, std::max(1, ctx->n_cu * 4), s));
+                            d_kq, d_next, d_wstats, ctx->n_cu, s));
   HIP_K(hipEventRecord(ev[2], s));
   std::vector<double> rad((size_t)n);
   HIP_K(hipMemcpyAsync(rad.data(), d_rad, n * 8, hipMemcpyDeviceToHost, s));

@@ -14,27 +14,18 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "msk_internal.h"
 #include "kelvin.h"
 #include "philox.h"
+#include "search.h"
 
 // wavefronts per SIMD the persistent walk kernel is compiled for
 #ifndef MSK_KELVIN_WAVES_PER_EU
 #define MSK_KELVIN_WAVES_PER_EU 4
 #endif
-// the walks' launch: streaming (one hierarchy node per loop trip, 1) or one
-// whole search per loop trip (0)
-#ifndef MSK_KELVIN_STREAM
-#define MSK_KELVIN_STREAM 1
-#endif
-// the streaming launch's leaf elements: tested across the wavefront (1) or
-// by each lane for its own search (0)
-#ifndef MSK_KELVIN_COOP
-#define MSK_KELVIN_COOP 1
-#endif
-
 namespace msk {
 
 namespace {
@@ -209,9 +200,8 @@ __host__ __device__ bool kelvin_plane(const double a[3], const double b[3], cons
 // INFINITY is returned without the boundary arcs.
 template <bool kCount>
 __host__ __device__ double kelvin_tri_d2_t(const double x[3], const KelvinTri& T, const KelvinPre& R, double q[3],
-                                           double l[3], double bound, uint64_t& ops, double* skip2 = nullptr) {
+                                           double l[3], double bound, uint64_t& ops) {
 #pragma clang fp contract(off)
-  if (skip2) *skip2 = -INFINITY;  // no plane: never skipped
   Best b;
   b.d2 = INFINITY;
   if (T.has_plane) {
@@ -224,14 +214,12 @@ __host__ __device__ double kelvin_tri_d2_t(const double x[3], const KelvinTri& T
       const double vl = sqrt(dot(v, v));
       const double sd = (fabs(c) * dot(x, x) - sg * dot(n, x)) / (vl + 0.5);
       if constexpr (kCount) ops += 32;
-      if (skip2) *skip2 = sd * sd;  // the value compared with the bound
       if (sd * sd > bound * (1.0 + 1e-9)) return INFINITY;
       for (int k = 0; k < 3; ++k) p[k] = x[k] - sd * sg * v[k] / vl;
       if constexpr (kCount) ops += 10;
     } else {
       const double nx = dot(n, x);
       if constexpr (kCount) ops += 7;
-      if (skip2) *skip2 = nx * nx;
       if (nx * nx > bound * (1.0 + 1e-9)) return INFINITY;
       for (int k = 0; k < 3; ++k) p[k] = x[k] - nx * n[k];
       if constexpr (kCount) ops += 6;
@@ -269,17 +257,11 @@ __host__ __device__ double kelvin_tri_d2_t(const double x[3], const KelvinTri& T
   return b.d2;
 }
 
-__host__ __device__ double kelvin_tri_d2(const double x[3], const KelvinTri& T, const KelvinPre& R, double q[3],
-                                         double l[3], double bound) {
-  uint64_t none = 0;
-  return kelvin_tri_d2_t<false>(x, T, R, q, l, bound, none);
-}
-
 // The point-independent part of every element (leaf order): the images of
 // its vertices and its edges' constants.
 __global__ void kelvin_prepare_kernel(const KelvinTri* __restrict__ tris, int64_t n, KelvinPre* __restrict__ pre) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
+  if (s >= n || tris[s].orig == kPadTri) return;
   const KelvinTri& T = tris[s];
   KelvinPre R;
   invert(T.a, R.k[0]);
@@ -291,156 +273,190 @@ __global__ void kelvin_prepare_kernel(const KelvinTri* __restrict__ tris, int64_
   pre[s] = R;
 }
 
-// Work of the counting instantiation of the nearest search.
-struct KelvinWork {
-  uint64_t nodes = 0, elements = 0, ops = 0;
+// Smallest distance of the origin from triangle (a, b, c).
+__device__ double origin_distance(const double a[3], const double b[3], const double c[3], const double n[3],
+                                  double cpl, bool plane) {
+  double best = INFINITY;
+  bool inside = plane;
+  const double* P[3] = {a, b, c};
+  for (int s = 0; s < 3; ++s) {
+    const double *u = P[s], *v = P[(s + 1) % 3];
+    const double e[3] = {v[0] - u[0], v[1] - u[1], v[2] - u[2]};
+    const double ee = dot(e, e);
+    const double t = ee > 0.0 ? fmin(1.0, fmax(0.0, -dot(u, e) / ee)) : 0.0;
+    const double p[3] = {u[0] + t * e[0], u[1] + t * e[1], u[2] + t * e[2]};
+    best = fmin(best, dot(p, p));
+    double m[3];
+    const double w[3] = {cpl * n[0] - u[0], cpl * n[1] - u[1], cpl * n[2] - u[2]};
+    cross(e, w, m);
+    inside = inside && dot(m, n) >= 0.0;
+  }
+  return inside ? fmin(fabs(cpl), sqrt(best)) : sqrt(best);
+}
+
+// Prefilter records of the elements (slots, pads among them): the flat
+// triangle of the vertices' images, and a bound h (field F) on how far any
+// point of the curved element lies from it, and any of its points from the
+// element. The element is kappa(T), kappa(y) = y / |y|^2, and the flat triangle
+// the linear interpolation of kappa at T's vertices: with |D^2 kappa(y)[e, e]|
+// = 2 |e|^2 / |y|^3 and rmin the smallest |y| on T they differ by at most
+// (1/2) (2 / rmin^3) sum_i lambda_i |v_i - y|^2 <= L^2 / (3 rmin^3), L the
+// longest edge; L^2 / (2 rmin^3) is taken. Records are in units of 1 / scale.
+__global__ void kelvin_quick_kernel(const KelvinTri* __restrict__ tris, int64_t n, double scale,
+                                    float4* __restrict__ quick) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n + kQuickPad) return;
+  float4* q = quick + quick_index(i);
+  if (i >= n || tris[i].orig == kPadTri) {
+    quick_pad(q);
+    return;
+  }
+  const KelvinTri& T = tris[i];
+  double ka[3], kb[3], kc[3], l2 = 0.0;
+  invert(T.a, ka);
+  invert(T.b, kb);
+  invert(T.c, kc);
+  for (int s = 0; s < 3; ++s) {
+    const double *u = s == 0 ? T.a : (s == 1 ? T.b : T.c), *v = s == 0 ? T.b : (s == 1 ? T.c : T.a);
+    const double e[3] = {v[0] - u[0], v[1] - u[1], v[2] - u[2]};
+    l2 = fmax(l2, dot(e, e));
+  }
+  const double r = origin_distance(T.a, T.b, T.c, T.n, T.cpl, T.has_plane != 0);
+  const double h = l2 / (2.0 * r * r * r) * (1.0 + 1e-6) * scale;
+  for (int c = 0; c < 3; ++c) {
+    ka[c] *= scale;
+    kb[c] *= scale;
+    kc[c] *= scale;
+  }
+  if (!(h < 1e20) || !quick_frame(ka, kb, kc, q, h, 0.0)) quick_always(ka, q);
+}
+
+namespace {
+
+// Curved elements of the inverted domain in the wavefront-shared search.
+// Values are distances: the prefilter's flat one (quick_flat) less and plus h,
+// m2 the bound on the distance in FP32. All FP32 quantities (boxes, records,
+// pt, m2) are in units of 1 / scale, a power of two near the domain's size, so
+// that their squares stay in range whatever the mesh's units. The FP32 roundings (of the point, of
+// the frame and in quick_flat, at most 16 u (R + |x|) together, u = 2^-24, R
+// the domain's radius) and the boxes' stand in pt.w, twice that bound. The
+// exact test is the FP64 one; the owner keeps the lexicographic minimum of
+// (squared distance, original index).
+struct ArcEl {
+  static constexpr uint32_t kQuickFlops = 0;  // exact tests and their FP64 operations are counted
+  const Node4* node0;
+  const KelvinTri* tris;
+  const KelvinPre* pre;
+  const float4* quick0;
+  double scale;
+  struct Owners {
+    double x[64][3];
+    unsigned long long key[64];  // squared distance (bits)
+    uint32_t orig[64];
+    int32_t slot[64];
+  };
+  static __device__ __forceinline__ float keep(float m2, const float4& q) {
+    return (m2 + fabsf(q.w)) * (1.0f + 0x1p-20f);
+  }
+  static __device__ __forceinline__ float boxes(float m2, const float4& q) {
+    const float s = (m2 + fabsf(q.w)) * (1.0f + 0x1p-20f);
+    return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);
+  }
+  template <typename Scratch>
+  __device__ __forceinline__ const Node4* nodes(Scratch*, uint32_t) const {
+    return node0;
+  }
+  template <typename Scratch>
+  __device__ __forceinline__ void quick(Scratch*, uint32_t, const float4& p, int64_t i, float& lo, float& up,
+                                        bool& always) const {
+    values(p.x, p.y, p.z, i, lo, up, always);
+  }
+  __device__ __forceinline__ void values(float x, float y, float z, int64_t i, float& lo, float& up,
+                                         bool& always) const {
+    float w2, F, G;
+    const float d2 = quick_flat(x, y, z, quick0, i, w2, F, G);
+    const float d = __builtin_amdgcn_sqrtf(d2);
+    lo = d * (1.0f - 0x1p-20f) - F;
+    up = d * (1.0f + 0x1p-20f) + F;
+    always = F > 1e28f;
+  }
+  template <bool kStats, typename Scratch>
+  __device__ __forceinline__ void exact(Scratch* W, uint32_t o, int32_t s, bool now, const float4&,
+                                        TravCount& cnt) const {
+    if (!now) return;
+    const double x[3] = {W->own.x[o][0], W->own.x[o][1], W->own.x[o][2]};
+    const unsigned long long before = W->own.key[o];
+    double q[3], l[3];
+    uint64_t ops = 0;
+    if (kStats) ++cnt.tris;
+    const double d = kelvin_tri_d2_t<kStats>(x, tris[s], pre[s], q, l, __longlong_as_double((long long)before), ops);
+    if (kStats) cnt.flops += ops;
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(d);
+    if (d < INFINITY && bits <= before) {
+      const uint32_t orig = (uint32_t)tris[s].orig;
+      atomicMin(&W->own.key[o], bits);
+      atomicMin(&W->m2[o], __float_as_uint((float)(sqrt(d) * scale * (1.0 + 1e-6))));
+      lds_order();
+      const unsigned long long now_best = W->own.key[o];
+      if (bits == now_best) {
+        // the lanes that hold a new minimum forget the index of the old one,
+        // then the smallest of theirs (and of an equal old one's) stays
+        if (now_best < before) W->own.orig[o] = (uint32_t)INT_MAX;
+        lds_order();
+        atomicMin(&W->own.orig[o], orig);
+        lds_order();
+        if (W->own.orig[o] == orig) W->own.slot[o] = s;
+      }
+    }
+  }
 };
 
-// Exact nearest inverted element: lexicographic minimum of (squared distance,
-// original index), depth first over the 4-wide hierarchy of boxes that
-// contain the elements (FP32 boxes rounded outward; their FP64 lower bounds
-// are within the boxes' own rounding of the true distance, hence the small
-// relative margin). `slot` names a candidate element on entry (warm start:
-// a walk's previous nearest, tested first so that the search starts with a
-// finite bound; -1 for none) and receives the nearest one's slot. The
-// minimum, and the element that attains it, do not depend on the candidate.
-template <bool kCount>
-__host__ __device__ double kelvin_nearest_t(const KelvinDev& K, const double x[3], int32_t& orig, double q[3],
-                                            double l[3], KelvinWork& work, int32_t& slot) {
-  double best = INFINITY;
-  orig = INT_MAX;
-  int32_t best_slot = -1;
-  if (slot >= 0) {
-    const KelvinTri& T = K.tris[slot];
-    if constexpr (kCount) ++work.elements;
-    best = kelvin_tri_d2_t<kCount>(x, T, K.pre[slot], q, l, best, work.ops);
-    orig = T.orig;
-    best_slot = slot;
-  }
-  int32_t stk[kStackDepth];
-  double stl[kStackDepth];
-  int sp = 0;
-  int32_t node = 0;
-  while (true) {
-    const Node4& N = K.nodes[node];
-    double lb[4];
-    int32_t cc[4], cn[4];
-    if constexpr (kCount) {  // four box lower bounds: 6 differences, 6 maxima, 3 products, 2 sums each
-      ++work.nodes;
-      work.ops += 4 * 17;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const double gx = fmax(fmax((double)N.lox[k] - x[0], x[0] - (double)N.hix[k]), 0.0);
-      const double gy = fmax(fmax((double)N.loy[k] - x[1], x[1] - (double)N.hiy[k]), 0.0);
-      const double gz = fmax(fmax((double)N.loz[k] - x[2], x[2] - (double)N.hiz[k]), 0.0);
-      lb[k] = gx * gx + gy * gy + gz * gz;
-      cc[k] = N.child[k];
-      cn[k] = N.count[k];
-    }
-    // nearest first
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-      for (int j = i; j > 0 && lb[j] < lb[j - 1]; --j) {
-        const double t = lb[j]; lb[j] = lb[j - 1]; lb[j - 1] = t;
-        const int32_t a = cc[j]; cc[j] = cc[j - 1]; cc[j - 1] = a;
-        const int32_t c = cn[j]; cn[j] = cn[j - 1]; cn[j - 1] = c;
-      }
-    int32_t next = -1;
-    double next_lb = 0.0;
-    for (int k = 0; k < 4; ++k) {
-      if (!(lb[k] <= best * (1.0 + 1e-12))) continue;
-      if (cc[k] < 0 && cn[k] > 0) {
-        const int32_t first = -cc[k] - 1;
-        for (int32_t s = first; s < first + cn[k]; ++s) {
-          const KelvinTri& T = K.tris[s];
-          double qq[3], ll[3];
-          if constexpr (kCount) ++work.elements;
-          const double d = kelvin_tri_d2_t<kCount>(x, T, K.pre[s], qq, ll, best, work.ops);
-          if (d < best || (d == best && T.orig < orig)) {
-            best = d;
-            orig = T.orig;
-            best_slot = s;
-            q[0] = qq[0]; q[1] = qq[1]; q[2] = qq[2];
-            l[0] = ll[0]; l[1] = ll[1]; l[2] = ll[2];
-          }
-        }
-      }
-    }
-    // the nearest surviving inner child is next, the others wait on the
-    // stack (farthest first) with their bounds
-    for (int k = 3; k >= 0; --k) {
-      if (cc[k] >= 0 && lb[k] <= best * (1.0 + 1e-12)) {
-        if (next >= 0 && sp < kStackDepth) {
-          stk[sp] = next;
-          stl[sp] = next_lb;
-          ++sp;
-        }
-        next = cc[k];
-        next_lb = lb[k];
-      }
-    }
-    if (next >= 0) {
-      node = next;
-      continue;
-    }
-    node = -1;
-    while (sp > 0) {
-      --sp;
-      if (stl[sp] <= best * (1.0 + 1e-12)) {
-        node = stk[sp];
-        break;
-      }
-    }
-    if (node < 0) break;
-  }
-  slot = best_slot;
-  return best;
+__device__ __forceinline__ ArcEl arc_elements(const KelvinDev& K) {
+  return ArcEl{K.nodes, K.tris, K.pre, K.quick, K.scale};
 }
 
-__host__ __device__ double kelvin_nearest(const KelvinDev& K, const double x[3], int32_t& orig, double q[3], double l[3]) {
-  KelvinWork none;
-  int32_t cold = -1;
-  return kelvin_nearest_t<false>(K, x, orig, q, l, none, cold);
-}
-
-
-// Whether some inverted element lies nearer to x than t (its distance, the
-// square root of the exact squared distance, below t): the decision the
-// tangent-ball bisection needs, equal to comparing the nearest element's
-// distance with t. Boxes and element spheres farther than t (with a small
-// relative margin for their own rounding) are skipped, and the search stops
-// at the first element found, so a point far from every element costs a few
-// box tests instead of a full nearest search.
-__host__ __device__ bool kelvin_any_within(const KelvinDev& K, const double x[3], double t) {
-  if (!(t > 0.0)) return false;
-  const double t2 = t * t * (1.0 + 1e-9);
-  int32_t stk[kStackDepth];
-  int sp = 0;
-  int32_t node = 0;
-  while (true) {
-    const Node4& N = K.nodes[node];
-    for (int k = 0; k < 4; ++k) {
-      const double gx = fmax(fmax((double)N.lox[k] - x[0], x[0] - (double)N.hix[k]), 0.0);
-      const double gy = fmax(fmax((double)N.loy[k] - x[1], x[1] - (double)N.hiy[k]), 0.0);
-      const double gz = fmax(fmax((double)N.loz[k] - x[2], x[2] - (double)N.hiz[k]), 0.0);
-      if (!(gx * gx + gy * gy + gz * gz <= t2)) continue;
-      const int32_t cc = N.child[k], cn = N.count[k];
-      if (cc < 0) {
-        const int32_t first = -cc - 1;
-        for (int32_t e = first; e < first + cn; ++e) {
-          double qq[3], ll[3];
-          const double d2 = kelvin_tri_d2(x, K.tris[e], K.pre[e], qq, ll, t2);
-          if (sqrt(d2) < t) return true;
-        }
-      } else if (sp < kStackDepth) {
-        stk[sp++] = cc;
-      }
-    }
-    if (sp == 0) return false;
-    node = stk[--sp];
+// Sets up owner `lane`'s search at x with the first bound of slot `warm` (or
+// of the leaf a descent reaches, if negative).
+template <typename Scratch>
+__device__ __forceinline__ void arc_start(const KelvinDev& K, const ArcEl& el, Scratch* W, uint32_t lane,
+                                          const double x[3], int32_t warm) {
+  const float px = (float)(x[0] * K.scale), py = (float)(x[1] * K.scale), pz = (float)(x[2] * K.scale);
+  if (warm < 0) warm = nearest_leaf(K.nodes, px, py, pz);
+  float m2 = INFINITY;
+  if (warm >= 0) {
+    float lo;
+    bool always;
+    el.values(px, py, pz, quick_index(warm), lo, m2, always);
   }
+  // 16 u (R + sqrt(3) |x|_inf), twice, rounded up
+  const float pm = fmaxf(fabsf(px), fmaxf(fabsf(py), fabsf(pz)));
+  W->pt[lane] = make_float4(px, py, pz, 0x1p-19f * ((float)(K.radius * K.scale) * 1.0001f + 1.75f * pm));
+  W->m2[lane] = __float_as_uint(m2);
+  for (int c = 0; c < 3; ++c) W->own.x[lane][c] = x[c];
+  W->own.key[lane] = (unsigned long long)__double_as_longlong(INFINITY);
+  W->own.orig[lane] = (uint32_t)INT_MAX;
+  W->own.slot[lane] = -1;
 }
+
+// Answer of an owner whose search has ended and whose pending tests are done
+// (as search_answer of the triangles): false if the search has to run again on
+// exact values.
+template <typename Scratch>
+__device__ __forceinline__ bool arc_answer(const KelvinDev& K, Scratch* W, uint32_t lane, double& d2, int32_t& slot) {
+  d2 = __longlong_as_double((long long)W->own.key[lane]);
+  slot = W->own.slot[lane];
+  const float4 q = W->pt[lane];
+  const float d = (float)(sqrt(d2) * K.scale * (1.0 - 1e-6));
+  if (q.w >= 0.0f && d > ArcEl::keep(__uint_as_float(W->m2[lane]), q)) {
+    W->m2[lane] = __float_as_uint((float)(sqrt(d2) * K.scale * (1.0 + 1e-6)));
+    W->pt[lane].w = -q.w;
+    return false;
+  }
+  return true;
+}
+
+}  // namespace
+
 namespace {
 
 __device__ __forceinline__ void frame(const double n[3], double e1[3], double e2[3]) {
@@ -470,55 +486,40 @@ __device__ __forceinline__ void kelvin_move(const KelvinDev& K, uint32_t row, ui
   x[2] += r * z;
 }
 
-// One step of Walk-on-Spheres in the inverted domain at x: the exact
-// nearest element; in the eps-shell the walk has hit (true), else x moves to
-// a uniform point of the sphere of radius d (1 - kappa) - delta, drawn from
-// the Philox block (row, walk, k, step purpose), the oracle's streams.
-template <bool kCount>
-__device__ bool kelvin_step(const KelvinDev& K, uint32_t row, uint32_t walk, int64_t k, double x[3], int32_t& orig,
-                            double q[3], double l[3], bool at_origin, KelvinWork& work, int32_t& warm) {
-  double d2;
-  if (at_origin) {  // the first step of a killing walk: the shared answer
-    d2 = K.origin_d2;
-    orig = K.origin_orig;
-    for (int c = 0; c < 3; ++c) {
-      q[c] = K.origin_q[c];
-      l[c] = K.origin_l[c];
-    }
-  } else {
-    d2 = kelvin_nearest_t<kCount>(K, x, orig, q, l, work, warm);
-  }
-  if (d2 < K.eps2) return true;
-  kelvin_move(K, row, walk, k, d2, x);
-  return false;
-}
-
 }  // namespace
 
 // Largest ball in the inverted domain touching its boundary at s~_i (unit
 // normal n~_i pointing out of the domain): bisection over [0, r_max], a
 // radius accepted when the centre c = s~ - r n~ is at least r - min(tol,
 // r/1024) from the inverted surface and the ball lies within the domain's
-// bound. Three levels per round: the eight lanes of a row evaluate the (up
-// to) seven midpoints of the next three levels at once (lane k takes heap
-// node k of that subtree: node 1 the current midpoint, nodes 2k and 2k + 1
-// the midpoints of its halves), then all follow the path the sequential
-// bisection takes through them. Every midpoint is formed by the operations of
-// the sequential loop, so the radius is that loop's; the rounds of dependent
-// searches drop from iters to ceil(iters / 3), and eight lanes per row fill
-// the GPU. queries[i] counts the iters decisions.
-__global__ void __launch_bounds__(64) kelvin_tangent_kernel(KelvinDev K, const double* __restrict__ st,
-                                                            const double* __restrict__ nt, int64_t n_rows,
-                                                            double r_max, int32_t iters, double tol,
-                                                            double* __restrict__ radius,
-                                                            unsigned long long* __restrict__ queries) {
+// bound. Three levels per round: the eight lanes of a row take the (up to)
+// seven midpoints of the next three levels at once (lane k heap node k of that
+// subtree: node 1 the current midpoint, nodes 2k and 2k + 1 the midpoints of
+// its halves), then all follow the path the sequential bisection takes through
+// them. Every midpoint is formed by the operations of the sequential loop, so
+// the radius is that loop's. Whether some element lies nearer to c than t is
+// asked of the wavefront-shared search, bounded by t; it ends once an upper
+// value says so and the exact one confirms it. (One depth-first search per
+// lane: 21.6 ms for 1,024 rows on 79,380 elements.) rows_per_wave (1, 2, 4 or
+// 8) is as low as still gives every resident wavefront rows. queries[i] counts
+// the iters decisions.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
+kelvin_tangent_kernel(KelvinDev K, const double* __restrict__ st, const double* __restrict__ nt, int64_t n_rows,
+                      int32_t rows_per_wave, double r_max, int32_t iters, double tol, double* __restrict__ radius,
+                      unsigned long long* __restrict__ queries) {
 #pragma clang fp contract(off)
-  const int lane = threadIdx.x & 63, sub = lane & 7, gbase = lane & ~7;
-  // eight rows per 64-lane workgroup; the loop bound is uniform over the
-  // workgroup, so every lane takes part in every ballot
-  for (int64_t base = (int64_t)blockIdx.x * 8; base < n_rows; base += (int64_t)gridDim.x * 8) {
-    const int64_t i = base + (threadIdx.x >> 3);
-    const bool valid = i < n_rows;
+  __shared__ SearchScratch<ArcEl, true> coop[4];
+  const int wi = (int)uniform(threadIdx.x >> 6);
+  SearchScratch<ArcEl, true>* W = &coop[wi];
+  const uint32_t lane = __lane_id();
+  const int sub = (int)(lane & 7u), gbase = (int)(lane & ~7u);
+  const ArcEl el = arc_elements(K);
+  TravCount cnt;
+  uint32_t size = 0, npend = 0;
+  for (int64_t base = ((int64_t)blockIdx.x * 4 + wi) * rows_per_wave; base < n_rows;
+       base += (int64_t)gridDim.x * 4 * rows_per_wave) {
+    const int64_t i = base + (lane >> 3);
+    const bool valid = (int32_t)(lane >> 3) < rows_per_wave && i < n_rows;
     double s[3] = {0.0, 0.0, 0.0}, n[3] = {0.0, 0.0, 0.0};
     if (valid)
       for (int c = 0; c < 3; ++c) {
@@ -528,7 +529,8 @@ __global__ void __launch_bounds__(64) kelvin_tangent_kernel(KelvinDev K, const d
     double lo = 0.0, hi = r_max;
     for (int32_t done = 0; done < iters;) {
       const int levels = min(3, iters - done);
-      bool res = false;
+      bool inside = false, fresh = false;
+      double t = 0.0;
       if (valid && sub >= 1 && sub < (1 << levels)) {
         double a = lo, b = hi;
         const int depth = 31 - __clz(sub);  // bits of the node index below its leading one
@@ -541,10 +543,40 @@ __global__ void __launch_bounds__(64) kelvin_tangent_kernel(KelvinDev K, const d
         }
         const double mid = 0.5 * (a + b);
         const double c[3] = {s[0] - mid * n[0], s[1] - mid * n[1], s[2] - mid * n[2]};
-        const double t = mid - fmin(tol, mid * (1.0 / 1024.0));
-        res = sqrt(dot(c, c)) + mid <= K.radius && !kelvin_any_within(K, c, t);
+        t = mid - fmin(tol, mid * (1.0 / 1024.0));
+        inside = sqrt(dot(c, c)) + mid <= K.radius;
+        fresh = inside && t > 0.0;
+        if (fresh) {
+          arc_start(K, el, W, lane, c, -1);
+          // elements at t or farther do not matter; an upper value below
+          // `stop` means an exact distance below t
+          W->m2[lane] = min(W->m2[lane], __float_as_uint((float)(t * K.scale * (1.0 + 1e-6))));
+          W->own.key[lane] = (unsigned long long)__double_as_longlong(t * t * (1.0 + 1e-9));
+          W->stop[lane] = fmaxf(0.0f, (float)(t * K.scale * (1.0 - 1e-6)) - W->pt[lane].w);
+        }
       }
-      const unsigned long long mask = __ballot(res);  // every lane of the wavefront takes part
+      bool closer = false, open = fresh;
+      search_push(W, lane, fresh, K.entry, size);
+      while (true) {
+        const bool step = size == 0;
+        search_pass<false, true>(el, W, lane, !step, ~0ull, size, npend, cnt);
+        if (!step) continue;
+        bool again = false;
+        if (open) {
+          closer = W->own.slot[lane] >= 0 && sqrt(__longlong_as_double((long long)W->own.key[lane])) < t;
+          // bounded by an upper value that no exact one has confirmed: search
+          // on exact values only
+          again = !closer && W->pt[lane].w >= 0.0f && __uint_as_float(W->m2[lane]) < (float)(t * K.scale * (1.0 - 1e-6));
+          open = again;
+          if (again) {
+            W->pt[lane].w = -W->pt[lane].w;
+            W->m2[lane] = __float_as_uint((float)(t * K.scale * (1.0 + 1e-6)));
+          }
+        }
+        search_push(W, lane, again, K.entry, size);
+        if (size == 0) break;
+      }
+      const unsigned long long mask = __ballot(inside && !closer);  // every lane of the wavefront takes part
       int node = 1;
       for (int l = 0; l < levels; ++l) {
         const double mid = 0.5 * (lo + hi);
@@ -570,190 +602,43 @@ __global__ void __launch_bounds__(64) kelvin_tangent_kernel(KelvinDev K, const d
 // (u = sin(theta/2) with density ~ 1/u^2 on [u0, 1], inverted in closed form;
 // azimuth uniform, + pi for the partner). The next n_kill walks are the
 // killing term's, from the origin (the image of infinity), with Philox row
-// 0xFFFFFFFF and walk index k. The launch is persistent: every lane claims
-// walks one at a time from a counter and advances its walk by one step per
-// loop trip, so a lane whose walk ends takes the next one at once instead of
-// idling until the longest walk of its wavefront ends; each walk's result
-// depends on its index only. Each walk logs its status, terminal original
-// triangle, the barycentrics of that triangle's vertices 1 and 2 at the
-// terminal point's image, its query count, and the factor g = 1/|t~| of its
-// rank-one update.
+// 0xFFFFFFFF and walk index k; their first step, from near the middle of a
+// round shape, shares one answer. The launch is persistent: a wavefront claims
+// walks for its idle lanes from a counter, its walks' searches share its
+// stack, and walks whose search has ended wait until a quarter of the
+// wavefront's do, then finish their step together; each walk's result depends
+// on its index only. At most `owners` lanes carry a walk. Each walk logs its
+// status, terminal original triangle, the barycentrics of that triangle's
+// vertices 1 and 2 at the terminal point's image, its query count, and the
+// factor g = 1/|t~| of its rank-one update.
+//   With a depth-first search per lane and every listed element tested in
+// FP64, 38.5 element tests of up to 354 operations per search, 98,304 walks on
+// 79,380 elements took 79.6 ms.
 // The counting instantiation (kCount) runs the same walks and adds the
-// nearest searches' node visits, element tests and FP64 operations to
-// stats[0..2].
-template <bool kCount>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
-kelvin_walk_kernel(
-    KelvinDev K, const double* __restrict__ st, const double* __restrict__ nt, const double* __restrict__ radius,
-    int64_t n_rows, int64_t pairs, double u0, int64_t n_kill, int32_t* __restrict__ log_status,
-    int32_t* __restrict__ log_tri, float* __restrict__ log_bary, int32_t* __restrict__ log_q, double* __restrict__ g,
-    unsigned long long* __restrict__ row_queries, unsigned long long* kill_queries, unsigned long long* next_walk,
-    unsigned long long* __restrict__ stats) {
-  const int64_t n_jump = n_rows * 2 * pairs, total = n_jump + n_kill;
-  KelvinWork work;
-  int32_t warm = -1;  // slot of the walk's previous nearest element
-  int64_t id = -1, i = -1, k = 0;
-  uint32_t row = 0, walk = 0;
-  double x[3] = {0.0, 0.0, 0.0}, q[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
-  int32_t orig = -1;
-  while (true) {
-    if (id < 0) {  // claim the next walk
-      id = (int64_t)atomicAdd(next_walk, 1ull);
-      if (id >= total) break;
-      k = 0;
-      orig = -1;
-      warm = -1;
-      if (id < n_jump) {
-        i = id / (2 * pairs);
-        const int64_t w = id - i * 2 * pairs;
-        const double r = radius[i];
-        if (!(r > 0.0)) {
-          log_status[id] = -1;
-          log_tri[id] = -1;
-          log_bary[2 * id] = log_bary[2 * id + 1] = 0.0f;
-          log_q[id] = 0;
-          g[id] = 0.0;
-          id = -1;
-          continue;
-        }
-        row = (uint32_t)i;
-        walk = (uint32_t)w;
-        const uint4 u = philox10(
-            make_uint4(row, (uint32_t)(w >> 1), 0u, (kPurposeBall << 24) | (K.mesh_id & 0xFFFFFFu)), K.seed_lo,
-            K.seed_hi);
-        const double xi = unit_f(u.x), eta = unit_f(u.y);
-        const double su = 1.0 / (1.0 / u0 - xi * (1.0 / u0 - 1.0));
-        const double ct = 1.0 - 2.0 * su * su, sn = 2.0 * su * sqrt(fmax(0.0, 1.0 - su * su));
-        double sp, cp;
-        sincospi(2.0 * eta + ((w & 1) ? 1.0 : 0.0), &sp, &cp);
-        const double n[3] = {nt[3 * i], nt[3 * i + 1], nt[3 * i + 2]};
-        double e1[3], e2[3];
-        frame(n, e1, e2);
-        for (int c3 = 0; c3 < 3; ++c3) {
-          const double c = st[3 * i + c3] - r * n[c3];
-          x[c3] = c + r * (ct * n[c3] + sn * (cp * e1[c3] + sp * e2[c3]));
-        }
-      } else {
-        i = -1;
-        row = 0xFFFFFFFFu;
-        walk = (uint32_t)(id - n_jump);
-        x[0] = x[1] = x[2] = 0.0;
-      }
-    }
-    int32_t status = -1, nq = 0;
-    if (k < K.max_steps) {
-      if (kelvin_step<kCount>(K, row, walk, k, x, orig, q, l, i < 0 && k == 0 && K.origin_known, work, warm)) {
-        status = kHit;
-        nq = (int32_t)(k + 1);
-      } else {
-        ++k;
-      }
-    } else {  // step cap: the nearest point of the last position
-      kelvin_nearest_t<kCount>(K, x, orig, q, l, work, warm);
-      status = kCapped;
-      nq = (int32_t)(K.max_steps + 1);
-    }
-    if (status >= 0) {
-      log_status[id] = status;
-      log_tri[id] = orig;
-      log_bary[2 * id] = (float)l[1];
-      log_bary[2 * id + 1] = (float)l[2];
-      log_q[id] = nq;
-      g[id] = 1.0 / sqrt(dot(q, q));
-      if (i >= 0)
-        atomicAdd(row_queries + i, (unsigned long long)nq);
-      else
-        atomicAdd(kill_queries, (unsigned long long)nq);
-      id = -1;
-    }
-  }
-  if constexpr (kCount) {
-    atomicAdd(stats, (unsigned long long)work.nodes);
-    atomicAdd(stats + 1, (unsigned long long)work.elements);
-    atomicAdd(stats + 2, (unsigned long long)work.ops);
-  }
-}
-
-// The leaf elements a wavefront's searches reach in one loop trip, tested 64
-// at a time across its lanes: the list (element slot, owner lane), each
-// owner's query point and bound, and each test's result, in LDS.
-struct KelvinCoop {
-  double x[64][3];
-  double bound[64];
-  int32_t slot[64];
-  int32_t owner[64];
-  double rd[64], rk[64];  // distance, and the value its sphere (plane) skip compares with the bound
-  int32_t ro[64], rs[64];
-  double rq[64][3], rl[64][3];
-};
-
-// Orders a wavefront's LDS accesses as written (the hardware executes one
-// wavefront's LDS instructions in issue order; only the compiler must not
-// move them).
-__device__ __forceinline__ void kelvin_lds_order() { __asm__ __volatile__("" ::: "memory"); }
-
-// Exclusive prefix sum over the wavefront of a count below 64 (bit-sliced
-// ballots); `total` receives the wavefront's sum.
-__device__ __forceinline__ uint32_t kelvin_wave_prefix(uint32_t v, uint32_t& total) {
-  const uint32_t lane = __lane_id();
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  uint32_t pre = 0, tot = 0;
-#pragma unroll
-  for (int b = 0; b < 6; ++b) {
-    const uint64_t m = __ballot((v >> b) & 1u);
-    pre += (uint32_t)__popcll(m & below) << b;
-    tot += (uint32_t)__popcll(m) << b;
-  }
-  total = tot;
-  return pre;
-}
-
-// Streaming form of the same walks: every loop trip advances each searching
-// lane by one node of the hierarchy (the node's leaf elements tested by that
-// lane), so a lane whose search is long does not hold the others; a lane
-// whose search ends finishes its step at once (or its walk, logged as above,
-// and claims the next one). Each search visits the same nodes in the same
-// order as kelvin_nearest_t, from the same warm candidate, so walks and logs
-// are those of kelvin_walk_kernel.
+// searches' node visits, element tests and FP64 operations (68 per node, those
+// of the exact tests) to stats[0..2].
 template <bool kCount>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
 kelvin_stream_kernel(
     KelvinDev K, const double* __restrict__ st, const double* __restrict__ nt, const double* __restrict__ radius,
-    int64_t n_rows, int64_t pairs, double u0, int64_t n_kill, int32_t* __restrict__ log_status,
+    int64_t n_rows, int64_t pairs, double u0, int64_t n_kill, int32_t owners, int32_t* __restrict__ log_status,
     int32_t* __restrict__ log_tri, float* __restrict__ log_bary, int32_t* __restrict__ log_q, double* __restrict__ g,
     unsigned long long* __restrict__ row_queries, unsigned long long* kill_queries, unsigned long long* next_walk,
     unsigned long long* __restrict__ stats) {
+  __shared__ SearchScratch<ArcEl> coop[4];
+  const int wi = (int)uniform(threadIdx.x >> 6);
+  SearchScratch<ArcEl>* W = &coop[wi];
   const int64_t n_jump = n_rows * 2 * pairs, total = n_jump + n_kill;
-  __shared__ KelvinCoop coop[4];
-  KelvinCoop* C = &coop[threadIdx.x >> 6];
   const uint32_t lane = __lane_id();
-  KelvinWork work;
+  const ArcEl el = arc_elements(K);
+  TravCount cnt;
   int64_t id = -1, i = -1, k = 0;
   uint32_t row = 0, walk = 0;
-  double x[3] = {0.0, 0.0, 0.0}, q[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
-  int32_t orig = -1, warm = -1;
-  bool done = false;
-  // the search in progress (node < 0: none)
-  int32_t stk[kStackDepth];
-  double stl[kStackDepth];
-  int sp = 0;
-  int32_t node = -1, best_slot = -1;
-  double best = INFINITY;
-  auto search_begin = [&]() {
-    best = INFINITY;
-    orig = INT_MAX;
-    best_slot = -1;
-    if (warm >= 0) {
-      const KelvinTri& T = K.tris[warm];
-      if constexpr (kCount) ++work.elements;
-      best = kelvin_tri_d2_t<kCount>(x, T, K.pre[warm], q, l, best, work.ops);
-      orig = T.orig;
-      best_slot = warm;
-    }
-    sp = 0;
-    node = 0;
-  };
-  auto log_walk = [&](int32_t status, int32_t nq) {
+  double x[3] = {0.0, 0.0, 0.0};
+  int32_t mode = 0;  // 0 no walk, 1 searching, 2 search ended
+  uint32_t size = 0, npend = 0;
+  bool drained = false;
+  auto log_walk = [&](int32_t status, int32_t nq, int32_t orig, const double q[3], const double l[3]) {
     log_status[id] = status;
     log_tri[id] = orig;
     log_bary[2 * id] = (float)l[1];
@@ -764,331 +649,251 @@ kelvin_stream_kernel(
       atomicAdd(row_queries + i, (unsigned long long)nq);
     else
       atomicAdd(kill_queries, (unsigned long long)nq);
-    id = -1;
-  };
-  // the answer of step k's search (squared distance d2): the walk hits, or
-  // moves and starts the next search (the step cap's final search at
-  // k = max_steps)
-  auto step_done = [&](double d2) {
-    if (k >= K.max_steps) {  // the cap's search
-      log_walk(kCapped, (int32_t)(K.max_steps + 1));
-      return;
-    }
-    if (d2 < K.eps2) {
-      log_walk(kHit, (int32_t)(k + 1));
-      return;
-    }
-    kelvin_move(K, row, walk, k, d2, x);
-    ++k;
-    search_begin();
+    mode = 0;
   };
   while (true) {
-    // lanes without a walk claim the next one
-    while (id < 0 && !done) {
-      id = (int64_t)atomicAdd(next_walk, 1ull);
-      if (id >= total) {
-        id = -1;
-        done = true;
-        break;
-      }
-      k = 0;
-      orig = -1;
-      warm = -1;
-      if (id < n_jump) {
-        i = id / (2 * pairs);
-        const int64_t w = id - i * 2 * pairs;
-        const double r = radius[i];
-        if (!(r > 0.0)) {
-          log_status[id] = -1;
-          log_tri[id] = -1;
-          log_bary[2 * id] = log_bary[2 * id + 1] = 0.0f;
-          log_q[id] = 0;
-          g[id] = 0.0;
-          id = -1;
-          continue;
-        }
-        row = (uint32_t)i;
-        walk = (uint32_t)w;
-        const uint4 u = philox10(
-            make_uint4(row, (uint32_t)(w >> 1), 0u, (kPurposeBall << 24) | (K.mesh_id & 0xFFFFFFu)), K.seed_lo,
-            K.seed_hi);
-        const double xi = unit_f(u.x), eta = unit_f(u.y);
-        const double su = 1.0 / (1.0 / u0 - xi * (1.0 / u0 - 1.0));
-        const double ct = 1.0 - 2.0 * su * su, sn = 2.0 * su * sqrt(fmax(0.0, 1.0 - su * su));
-        double sp2, cp;
-        sincospi(2.0 * eta + ((w & 1) ? 1.0 : 0.0), &sp2, &cp);
-        const double n[3] = {nt[3 * i], nt[3 * i + 1], nt[3 * i + 2]};
-        double e1[3], e2[3];
-        frame(n, e1, e2);
-        for (int c3 = 0; c3 < 3; ++c3) {
-          const double c = st[3 * i + c3] - r * n[c3];
-          x[c3] = c + r * (ct * n[c3] + sn * (cp * e1[c3] + sp2 * e2[c3]));
-        }
-        search_begin();
+    if (mode == 1 && W->open[lane] == 0) mode = 2;
+    size = uniform(size);
+    drained = uniform(drained ? 1u : 0u) != 0;
+    const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1) | pend;
+    const uint64_t idle0 = drained ? 0ull : __ballot(mode == 0 && lane < (uint32_t)owners);
+    const bool step = size == 0 || (size <= (uint32_t)kRootLimit &&
+                                    (int)__popcll(pend | idle0) >= min(16, (int)(__popcll(busy | idle0) + 3) >> 2));
+    search_pass<kCount>(el, W, lane, !step, pend, size, npend, cnt);
+    if (!step) continue;
+    bool fresh = false, go = false;  // go: a new search at x, warm-started from `warm`
+    int32_t warm = -1;
+    if (mode == 2) {
+      double d2;
+      int32_t slot;
+      if (!arc_answer(K, W, lane, d2, slot)) {
+        fresh = true;
+        mode = 1;
+      } else if (slot < 0) {  // no element at a finite distance (never for a finite x)
+        const double none[3] = {0.0, 0.0, 0.0};
+        log_walk(kCapped, (int32_t)(k + 1), INT_MAX, none, none);
+      } else if (k >= K.max_steps || d2 < K.eps2) {
+        // the walk ends at its position's nearest point: that element's test
+        // once more (the step cap's search is the one at k = max_steps)
+        double q[3], l[3];
+        uint64_t none = 0;
+        const KelvinTri& T = K.tris[slot];
+        (void)kelvin_tri_d2_t<false>(x, T, K.pre[slot], q, l, INFINITY, none);
+        log_walk(k >= K.max_steps ? kCapped : kHit, (int32_t)(k + 1), T.orig, q, l);
       } else {
-        i = -1;
-        row = 0xFFFFFFFFu;
-        walk = (uint32_t)(id - n_jump);
-        x[0] = x[1] = x[2] = 0.0;
-        if (K.origin_known && K.max_steps > 0) {  // the first step's shared answer
-          orig = K.origin_orig;
-          for (int c = 0; c < 3; ++c) {
-            q[c] = K.origin_q[c];
-            l[c] = K.origin_l[c];
+        kelvin_move(K, row, walk, k, d2, x);
+        ++k;
+        warm = slot;
+        go = true;
+      }
+    }
+    // idle lanes claim the next walks
+    const uint64_t idle = drained ? 0ull : __ballot(mode == 0 && lane < (uint32_t)owners);
+    if (idle != 0) {
+      unsigned long long first = 0;
+      const int lead = __ffsll((unsigned long long)idle) - 1;
+      if ((int)lane == lead) first = atomicAdd(next_walk, (unsigned long long)__popcll(idle));
+      first = (unsigned long long)__shfl(first, lead);
+      const int64_t claim = (int64_t)first + (int64_t)mbcnt64(idle);
+      drained = (int64_t)first + (int64_t)__popcll(idle) >= total;
+      if (((idle >> lane) & 1ull) && claim < total) {
+        id = claim;
+        k = 0;
+        if (id < n_jump) {
+          i = id / (2 * pairs);
+          const int64_t w = id - i * 2 * pairs;
+          const double r = radius[i];
+          if (!(r > 0.0)) {
+            log_status[id] = -1;
+            log_tri[id] = -1;
+            log_bary[2 * id] = log_bary[2 * id + 1] = 0.0f;
+            log_q[id] = 0;
+            g[id] = 0.0;
+          } else {
+            row = (uint32_t)i;
+            walk = (uint32_t)w;
+            const uint4 u = philox10(
+                make_uint4(row, (uint32_t)(w >> 1), 0u, (kPurposeBall << 24) | (K.mesh_id & 0xFFFFFFu)), K.seed_lo,
+                K.seed_hi);
+            const double xi = unit_f(u.x), eta = unit_f(u.y);
+            const double su = 1.0 / (1.0 / u0 - xi * (1.0 / u0 - 1.0));
+            const double ct = 1.0 - 2.0 * su * su, sn = 2.0 * su * sqrt(fmax(0.0, 1.0 - su * su));
+            double sp, cp;
+            sincospi(2.0 * eta + ((w & 1) ? 1.0 : 0.0), &sp, &cp);
+            const double n[3] = {nt[3 * i], nt[3 * i + 1], nt[3 * i + 2]};
+            double e1[3], e2[3];
+            frame(n, e1, e2);
+            for (int c3 = 0; c3 < 3; ++c3) {
+              const double c = st[3 * i + c3] - r * n[c3];
+              x[c3] = c + r * (ct * n[c3] + sn * (cp * e1[c3] + sp * e2[c3]));
+            }
+            go = true;
           }
-          best_slot = -1;
-          step_done(K.origin_d2);  // logs, or starts step 1's search
         } else {
-          search_begin();
-        }
-      }
-    }
-    if (__ballot(id >= 0) == 0) break;  // no lane of the wavefront has a walk left
-    const bool srch = id >= 0;
-    // one node of each searching lane's search: its four child boxes, nearest first
-    double lb[4] = {0.0, 0.0, 0.0, 0.0};
-    int32_t cc[4] = {0, 0, 0, 0}, cn[4] = {0, 0, 0, 0};
-    if (srch) {
-      const Node4& N = K.nodes[node];
-      if constexpr (kCount) {
-        ++work.nodes;
-        work.ops += 4 * 17;
-      }
-#pragma unroll
-      for (int c4 = 0; c4 < 4; ++c4) {
-        const double gx = fmax(fmax((double)N.lox[c4] - x[0], x[0] - (double)N.hix[c4]), 0.0);
-        const double gy = fmax(fmax((double)N.loy[c4] - x[1], x[1] - (double)N.hiy[c4]), 0.0);
-        const double gz = fmax(fmax((double)N.loz[c4] - x[2], x[2] - (double)N.hiz[c4]), 0.0);
-        lb[c4] = gx * gx + gy * gy + gz * gz;
-        cc[c4] = N.child[c4];
-        cn[c4] = N.count[c4];
-      }
-#pragma unroll
-      for (int a = 1; a < 4; ++a)
-        for (int b = a; b > 0 && lb[b] < lb[b - 1]; --b) {
-          const double t = lb[b]; lb[b] = lb[b - 1]; lb[b - 1] = t;
-          const int32_t t1 = cc[b]; cc[b] = cc[b - 1]; cc[b - 1] = t1;
-          const int32_t t2 = cn[b]; cn[b] = cn[b - 1]; cn[b - 1] = t2;
-        }
-    }
-#if MSK_KELVIN_COOP
-    // the leaf elements within the bound (the trip's starting bound: a test
-    // that a tighter bound would have cut short cannot win either), listed in
-    // the lane's order and tested 64 at a time by the whole wavefront; each
-    // owner then folds its results in that order
-    {
-      // the children listed, fixed before any fold tightens the bound
-      uint32_t nu = 0, qmask = 0;
-      if (srch)
-        for (int c4 = 0; c4 < 4; ++c4)
-          if (lb[c4] <= best * (1.0 + 1e-12) && cc[c4] < 0 && cn[c4] > 0) {
-            nu += (uint32_t)cn[c4];
-            qmask |= 1u << c4;
-          }
-      uint32_t total;
-      const uint32_t pre = kelvin_wave_prefix(nu, total);
-      bool child_ok = false;  // the fold's current child (carried over a round boundary)
-      if (total > 0) {
-        C->x[lane][0] = x[0];
-        C->x[lane][1] = x[1];
-        C->x[lane][2] = x[2];
-        C->bound[lane] = best;
-        for (uint32_t base = 0; base < total; base += 64) {
-          if (nu > 0) {
-            uint32_t pos = pre;
-            for (int c4 = 0; c4 < 4; ++c4) {
-              if (!((qmask >> c4) & 1u)) continue;
-              const int32_t first = -cc[c4] - 1;
-              for (int32_t e = first; e < first + cn[c4]; ++e, ++pos)
-                if (pos >= base && pos < base + 64) {
-                  C->slot[pos - base] = e;
-                  C->owner[pos - base] = (int32_t)lane;
-                }
-            }
-          }
-          kelvin_lds_order();
-          if (base + lane < total) {
-            const int32_t e = C->slot[lane];
-            const int32_t o = C->owner[lane];
-            const double xo[3] = {C->x[o][0], C->x[o][1], C->x[o][2]};
-            const KelvinTri& T = K.tris[e];
-            double qq[3], ll[3];
-            if constexpr (kCount) ++work.elements;
-            double k2;
-            const double d = kelvin_tri_d2_t<kCount>(xo, T, K.pre[e], qq, ll, C->bound[o], work.ops, &k2);
-            C->rd[lane] = d;
-            C->rk[lane] = k2;
-            C->ro[lane] = T.orig;
-            C->rs[lane] = e;
-            for (int c = 0; c < 3; ++c) {
-              C->rq[lane][c] = qq[c];
-              C->rl[lane][c] = ll[c];
-            }
-          }
-          kelvin_lds_order();
-          if (nu > 0) {
-            // the owner replays its lane-private order on these results: a
-            // child is entered only if its box is still within the bound, an
-            // element counts only if its sphere (plane) is (the tests ran with
-            // the trip's starting bound, which is never tighter), so the
-            // updates are exactly those of the lane-private search
-            uint32_t pos = pre;
-            for (int c4 = 0; c4 < 4; ++c4) {
-              if (!((qmask >> c4) & 1u)) continue;
-              const int32_t first = -cc[c4] - 1;
-              for (int32_t e = first; e < first + cn[c4]; ++e, ++pos) {
-                if (pos < base || pos >= base + 64) continue;
-                if (e == first) child_ok = lb[c4] <= best * (1.0 + 1e-12);
-                if (!child_ok) continue;
-                const uint32_t r = pos - base;
-                if (C->rk[r] > best * (1.0 + 1e-9)) continue;  // the lane-private test would have returned INFINITY
-                const double d = C->rd[r];
-                const int32_t o2 = C->ro[r];
-                if (d < best || (d == best && o2 < orig)) {
-                  best = d;
-                  orig = o2;
-                  best_slot = C->rs[r];
-                  for (int c = 0; c < 3; ++c) {
-                    q[c] = C->rq[r][c];
-                    l[c] = C->rl[r][c];
-                  }
-                }
-              }
-            }
-          }
-          kelvin_lds_order();
-        }
-      }
-    }
-#endif
-    if (!srch) continue;
-    {
-#if !MSK_KELVIN_COOP
-      for (int c4 = 0; c4 < 4; ++c4) {
-        if (!(lb[c4] <= best * (1.0 + 1e-12))) continue;
-        if (cc[c4] < 0 && cn[c4] > 0) {
-          const int32_t first = -cc[c4] - 1;
-          for (int32_t e = first; e < first + cn[c4]; ++e) {
-            const KelvinTri& T = K.tris[e];
-            double qq[3], ll[3];
-            if constexpr (kCount) ++work.elements;
-            const double d = kelvin_tri_d2_t<kCount>(x, T, K.pre[e], qq, ll, best, work.ops);
-            if (d < best || (d == best && T.orig < orig)) {
-              best = d;
-              orig = T.orig;
-              best_slot = e;
-              q[0] = qq[0]; q[1] = qq[1]; q[2] = qq[2];
-              l[0] = ll[0]; l[1] = ll[1]; l[2] = ll[2];
+          i = -1;
+          row = 0xFFFFFFFFu;
+          walk = (uint32_t)(id - n_jump);
+          x[0] = x[1] = x[2] = 0.0;
+          go = true;
+          if (K.origin_known && K.max_steps > 0) {  // the first step's shared answer
+            if (K.origin_d2 < K.eps2) {
+              log_walk(kHit, 1, K.origin_orig, K.origin_q, K.origin_l);
+              go = false;
+            } else {
+              kelvin_move(K, row, walk, 0, K.origin_d2, x);
+              k = 1;
             }
           }
         }
       }
-#endif
-      int32_t next = -1;
-      double next_lb = 0.0;
-      for (int c4 = 3; c4 >= 0; --c4) {
-        if (cc[c4] >= 0 && lb[c4] <= best * (1.0 + 1e-12)) {
-          if (next >= 0 && sp < kStackDepth) {
-            stk[sp] = next;
-            stl[sp] = next_lb;
-            ++sp;
-          }
-          next = cc[c4];
-          next_lb = lb[c4];
-        }
-      }
-      if (next < 0) {
-        while (sp > 0) {
-          --sp;
-          if (stl[sp] <= best * (1.0 + 1e-12)) {
-            next = stk[sp];
-            break;
-          }
-        }
-      }
-      node = next;
     }
-    if (node < 0) {  // the search is answered
-      warm = best_slot;
-      step_done(best);
+    if (go) {
+      arc_start(K, el, W, lane, x, warm);
+      mode = 1;
+      fresh = true;
     }
+    search_push(W, lane, fresh, K.entry, size);
+    if (drained && __ballot(mode != 0) == 0) break;
   }
   if constexpr (kCount) {
-    atomicAdd(stats, (unsigned long long)work.nodes);
-    atomicAdd(stats + 1, (unsigned long long)work.elements);
-    atomicAdd(stats + 2, (unsigned long long)work.ops);
+    atomicAdd(stats, (unsigned long long)cnt.nodes);
+    atomicAdd(stats + 1, (unsigned long long)cnt.tris);
+    atomicAdd(stats + 2, (unsigned long long)cnt.flops);
   }
 }
 
 // Nearest inverted element of each query point (inverted space, relative to
-// the centre).
-__global__ void kelvin_closest_kernel(KelvinDev K, const double* __restrict__ Q, int64_t nq, int32_t* __restrict__ tri,
-                                      double* __restrict__ d2, double* __restrict__ qpt, double* __restrict__ bary) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nq) return;
-  const double x[3] = {Q[3 * i], Q[3 * i + 1], Q[3 * i + 2]};
-  int32_t o;
-  double q[3], l[3];
-  d2[i] = kelvin_nearest(K, x, o, q, l);
-  tri[i] = o;
-  for (int k = 0; k < 3; ++k) {
-    qpt[3 * i + k] = q[k];
-    bary[3 * i + k] = l[k];
+// the centre), on the shared search: query j of wavefront g is j G + g, G the
+// number of wavefronts, at most `owners` of them at a time.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
+kelvin_closest_kernel(KelvinDev K, const double* __restrict__ Q, int64_t nq, int32_t owners, int32_t* __restrict__ tri,
+                      double* __restrict__ d2, double* __restrict__ qpt, double* __restrict__ bary) {
+  __shared__ SearchScratch<ArcEl> coop[4];
+  const int wi = (int)uniform(threadIdx.x >> 6);
+  SearchScratch<ArcEl>* W = &coop[wi];
+  const uint32_t lane = __lane_id();
+  const int64_t G = (int64_t)gridDim.x * 4, g = (int64_t)blockIdx.x * 4 + wi;
+  const ArcEl el = arc_elements(K);
+  TravCount cnt;
+  int32_t mode = 0;
+  int64_t next = 0, qi = 0;
+  double x[3] = {0.0, 0.0, 0.0};
+  uint32_t size = 0, npend = 0;
+  bool drained = false;
+  while (true) {
+    if (mode == 1 && W->open[lane] == 0) mode = 2;
+    size = uniform(size);
+    const uint64_t pend = __ballot(mode == 2), busy = __ballot(mode == 1) | pend;
+    const bool step = size == 0 || (size <= (uint32_t)kRootLimit &&
+                                    (int)__popcll(pend) >= min(16, (int)(__popcll(busy) + 3) >> 2));
+    search_pass<false>(el, W, lane, !step, pend, size, npend, cnt);
+    if (!step) continue;
+    bool fresh = false;
+    if (mode == 2) {
+      double best;
+      int32_t slot;
+      if (arc_answer(K, W, lane, best, slot)) {
+        double q[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
+        uint64_t none = 0;
+        int32_t orig = INT_MAX;
+        if (slot >= 0) {  // (none has a finite distance from a point that is not finite)
+          (void)kelvin_tri_d2_t<false>(x, K.tris[slot], K.pre[slot], q, l, INFINITY, none);
+          orig = K.tris[slot].orig;
+        }
+        d2[qi] = best;
+        tri[qi] = orig;
+        for (int c = 0; c < 3; ++c) {
+          qpt[3 * qi + c] = q[c];
+          bary[3 * qi + c] = l[c];
+        }
+        mode = 0;
+      } else {
+        fresh = true;
+        mode = 1;
+      }
+    }
+    const uint64_t idle = drained ? 0ull : __ballot(mode == 0 && lane < (uint32_t)owners);
+    if (idle != 0) {
+      const int64_t q = (next + (int64_t)mbcnt64(idle)) * G + g;
+      const bool take = ((idle >> lane) & 1ull) && q < nq;
+      if (take) {
+        qi = q;
+        for (int c = 0; c < 3; ++c) x[c] = Q[3 * qi + c];
+        arc_start(K, el, W, lane, x, -1);
+        mode = 1;
+        fresh = true;
+      }
+      const uint32_t got = (uint32_t)__popcll(__ballot(take));
+      drained = got < (uint32_t)__popcll(idle);
+      next += got;
+    }
+    search_push(W, lane, fresh, K.entry, size);
+    if (drained && __ballot(mode != 0) == 0) break;
   }
 }
 
 hipError_t launch_kelvin_tangent(const KelvinDev& K, const double* st, const double* nt, int64_t n_rows, double r_max,
-                                 int32_t iters, double tol, double* radius, unsigned long long* queries,
+                                 int32_t iters, double tol, int32_t n_cu, double* radius, unsigned long long* queries,
                                  hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
-  const int64_t blocks = std::min<int64_t>((n_rows + 7) / 8, 1 << 20);  // eight rows per 64-lane workgroup
-  hipLaunchKernelGGL(kelvin_tangent_kernel, dim3((unsigned)blocks), dim3(64), 0, s, K, st, nt, n_rows, r_max, iters,
-                     tol, radius, queries);
+  const int64_t waves = 16ll * n_cu;
+  int32_t rows = 1;
+  while (rows < 8 && rows * waves < n_rows) rows *= 2;
+  const int64_t blocks = std::min<int64_t>(4ll * n_cu, (n_rows + rows * 4 - 1) / (rows * 4));
+  hipLaunchKernelGGL(kelvin_tangent_kernel, dim3((unsigned)blocks), dim3(256), 0, s, K, st, nt, n_rows, rows, r_max,
+                     iters, tol, radius, queries);
   return hipGetLastError();
+}
+
+// Owners of a wavefront and workgroups for n searches: all resident
+// wavefronts (4 per SIMD), each with as few at a time as still covers n.
+static void spread(int64_t n, int32_t n_cu, int32_t* owners, int64_t* blocks) {
+  const int64_t waves = 16ll * n_cu;
+  *owners = (int32_t)std::min<int64_t>(64, (n + waves - 1) / waves);
+  *blocks = std::min<int64_t>(4ll * n_cu, (n + 4 * *owners - 1) / (4 * *owners));
 }
 
 hipError_t launch_kelvin_walks(const KelvinDev& K, const double* st, const double* nt, const double* radius,
                                int64_t n_rows, int64_t pairs, double u0, int64_t n_kill, int32_t* log_status,
                                int32_t* log_tri, float* log_bary, int32_t* log_q, double* g,
                                unsigned long long* row_queries, unsigned long long* kill_queries,
-                               unsigned long long* next_walk, unsigned long long* stats, int grid, hipStream_t s) {
+                               unsigned long long* next_walk, unsigned long long* stats, int32_t n_cu, hipStream_t s) {
   const int64_t n = n_rows * 2 * pairs + n_kill;
   if (n <= 0) return hipSuccess;
-  if (grid < 1) return hipErrorInvalidValue;
-  const int64_t blocks = std::min<int64_t>(grid, (n + 255) / 256);
-#if MSK_KELVIN_STREAM
+  if (n_cu < 1) return hipErrorInvalidValue;
+  int32_t owners;
+  int64_t blocks;
+  spread(n, n_cu, &owners, &blocks);
   if (stats)
     hipLaunchKernelGGL(kelvin_stream_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, K, st, nt, radius, n_rows,
-                       pairs, u0, n_kill, log_status, log_tri, log_bary, log_q, g, row_queries, kill_queries,
+                       pairs, u0, n_kill, owners, log_status, log_tri, log_bary, log_q, g, row_queries, kill_queries,
                        next_walk, stats);
   else
     hipLaunchKernelGGL(kelvin_stream_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, K, st, nt, radius,
-                       n_rows, pairs, u0, n_kill, log_status, log_tri, log_bary, log_q, g, row_queries, kill_queries,
-                       next_walk, stats);
-#else
-  if (stats)
-    hipLaunchKernelGGL(kelvin_walk_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, K, st, nt, radius, n_rows,
-                       pairs, u0, n_kill, log_status, log_tri, log_bary, log_q, g, row_queries, kill_queries,
-                       next_walk, stats);
-  else
-    hipLaunchKernelGGL(kelvin_walk_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, K, st, nt, radius, n_rows,
-                       pairs, u0, n_kill, log_status, log_tri, log_bary, log_q, g, row_queries, kill_queries,
-                       next_walk, stats);
-#endif
+                       n_rows, pairs, u0, n_kill, owners, log_status, log_tri, log_bary, log_q, g, row_queries,
+                       kill_queries, next_walk, stats);
   return hipGetLastError();
 }
 
-hipError_t launch_kelvin_prepare(const KelvinTri* tris, int64_t n, KelvinPre* pre, hipStream_t s) {
+hipError_t launch_kelvin_prepare(const KelvinTri* tris, int64_t n, double scale, KelvinPre* pre, float4* quick,
+                                 hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(kelvin_prepare_kernel, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, tris, n, pre);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kelvin_quick_kernel, dim3((unsigned)((n + kQuickPad + 127) / 128)), dim3(128), 0, s, tris, n,
+                     scale, quick);
   return hipGetLastError();
 }
 
-hipError_t launch_kelvin_closest(const KelvinDev& K, const double* Q, int64_t nq, int32_t* tri, double* d2,
+hipError_t launch_kelvin_closest(const KelvinDev& K, const double* Q, int64_t nq, int32_t n_cu, int32_t* tri, double* d2,
                                  double* qpt, double* bary, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kelvin_closest_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, K, Q, nq, tri, d2,
-                     qpt, bary);
+  int32_t owners;
+  int64_t blocks;
+  spread(nq, n_cu, &owners, &blocks);
+  hipLaunchKernelGGL(kelvin_closest_kernel, dim3((unsigned)blocks), dim3(256), 0, s, K, Q, nq, owners, tri, d2, qpt,
+                     bary);
   return hipGetLastError();
 }
 

@@ -57,18 +57,21 @@ struct HostBvh {
   std::vector<int32_t> slot_of_tri;  // original triangle -> leaf-order slot
   int depth = 0;                     // levels of 4-wide nodes
   int leaf_size = 4;
-  int entry = 1;                     // align_leaves: nodes of the deepest level whose levels above are full
+  int entry = 1;                     // align_leaves
 };
 
 // Builds the scene frame and a 4-wide BVH over float offsets from the
 // centre. Returns an empty string on success, else an error message.
 std::string build_bvh_host(const float* V, int64_t nv, const int32_t* F, int64_t nf, int leaf_size, HostBvh& out);
 
-// Moves the triangles so that every leaf starts at a slot that is a multiple
-// of 4, pads (kPadTri) filling the slots past a shorter leaf: a leaf's
-// prefilter records, which lie in blocks of 4 slots, then fill whole cache
-// lines. Leaf references change to -child - 1 = first slot + (blocks - 1).
-// Also finds `entry`.
+// Lets every leaf start at a slot that is a multiple of 4, pads filling the
+// slots past a shorter leaf: a leaf's prefilter records, which lie in blocks of
+// 4 slots, then fill whole cache lines. Leaf references change to -child - 1 =
+// first slot + (blocks - 1). Returns the former slot of each slot (-1: a pad)
+// and finds `entry`, the nodes of the deepest level whose levels above are
+// full (1, 4, 16 or 64).
+std::vector<int32_t> align_leaf_order(std::vector<Node4>& nodes, int64_t n, int& entry);
+// The same for a mesh's tree and triangles.
 void align_leaves(HostBvh& b);
 
 // The same binned-SAH build and 4-wide collapse over any elements given by

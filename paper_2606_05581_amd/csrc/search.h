@@ -33,11 +33,85 @@ __device__ __forceinline__ void gadd(T* p, int64_t i, T v) {
   (void)__hip_atomic_fetch_add((MSK_GLOBAL T*)p + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Squared distance from p to the flat triangle of the quick record at i (see
+// msk_internal.h), in the triangle's own frame: a branch-free handful of fused
+// operations. Also |p - a|^2 and the record's F and G.
+__device__ __forceinline__ float quick_flat(float px, float py, float pz, const void* quick, int64_t i, float& w2,
+                                            float& F, float& G) {
+  const float4 r0 = gload4(quick, i), r1 = gload4(quick, i + 4), r2 = gload4(quick, i + 8),
+               r3 = gload4(quick, i + 12), r4 = gload4(quick, i + 16);
+  const float gx = px - r0.x, gy = py - r0.y, gz = pz - r0.z;
+  const float x = r1.x * gx + r1.y * gy + r1.z * gz;
+  const float y = r2.x * gx + r2.y * gy + r2.z * gz;
+  const float z = r3.x * gx + r3.y * gy + r3.z * gz;
+  const float c1 = r0.w, s1 = r1.w, l1 = r2.w, c2 = r3.w, s2 = r4.x, l2 = r4.y;
+  const float b = c1 * l1 - c2 * l2;  // vertex b lies at (b, 0), vertex c at l1 (c1, s1)
+  const float t0 = x - __builtin_amdgcn_fmed3f(x, 0.0f, b);
+  const float q1 = x * c1 + y * s1, h1 = x * s1 - y * c1;
+  const float t1 = q1 - __builtin_amdgcn_fmed3f(q1, 0.0f, l1);
+  const float xb = x - b;
+  const float q2 = xb * c2 + y * s2, h2 = y * c2 - xb * s2;
+  const float t2 = q2 - __builtin_amdgcn_fmed3f(q2, 0.0f, l2);
+  const float e = fminf(fminf(y * y + t0 * t0, h1 * h1 + t1 * t1), h2 * h2 + t2 * t2);
+  const float in = fminf(fminf(y, h1), h2);
+  w2 = gx * gx + gy * gy + gz * gz;
+  F = r4.z;
+  G = r4.w;
+  return z * z + (in >= 0.0f ? 0.0f : e);
+}
+
+// The record of triangle (a, b, c) (FP64; F and G given), field by field 4
+// float4 apart; false if it has no frame (no area).
+__device__ __forceinline__ bool quick_frame(const double a[3], const double b[3], const double c[3], float4* q,
+                                            double F, double G) {
+  double ab[3], ac[3], n[3];
+  for (int k = 0; k < 3; ++k) {
+    ab[k] = b[k] - a[k];
+    ac[k] = c[k] - a[k];
+  }
+  n[0] = ab[1] * ac[2] - ab[2] * ac[1];
+  n[1] = ab[2] * ac[0] - ab[0] * ac[2];
+  n[2] = ab[0] * ac[1] - ab[1] * ac[0];
+  const double lab = sqrt(ab[0] * ab[0] + ab[1] * ab[1] + ab[2] * ab[2]);
+  const double lac = sqrt(ac[0] * ac[0] + ac[1] * ac[1] + ac[2] * ac[2]);
+  const double nn = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+  const double bx = ac[0] - ab[0], by = ac[1] - ab[1], bz = ac[2] - ab[2];
+  const double lbc = sqrt(bx * bx + by * by + bz * bz);
+  if (!(nn > 0.0) || !(lab > 0.0) || !(lac > 0.0) || !(lbc > 0.0)) return false;
+  double u[3], m[3], v[3];
+  for (int k = 0; k < 3; ++k) {
+    u[k] = ab[k] / lab;
+    m[k] = n[k] / nn;
+  }
+  v[0] = m[1] * u[2] - m[2] * u[1];
+  v[1] = m[2] * u[0] - m[0] * u[2];
+  v[2] = m[0] * u[1] - m[1] * u[0];
+  const double cx = ac[0] * u[0] + ac[1] * u[1] + ac[2] * u[2], cy = ac[0] * v[0] + ac[1] * v[1] + ac[2] * v[2];
+  q[0] = make_float4((float)a[0], (float)a[1], (float)a[2], (float)(cx / lac));
+  q[4] = make_float4((float)u[0], (float)u[1], (float)u[2], (float)(cy / lac));
+  q[8] = make_float4((float)v[0], (float)v[1], (float)v[2], (float)lac);
+  q[12] = make_float4((float)m[0], (float)m[1], (float)m[2], (float)((cx - lab) / lbc));
+  q[16] = make_float4((float)(cy / lbc), (float)lbc, (float)F, (float)G);
+  return true;
+}
+
+// The records of a pad (no query accepts it) and of an element without a
+// frame (every query sends it to the exact test).
+__device__ __forceinline__ void quick_pad(float4* q) {
+  q[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+  for (int k = 1; k < 5; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+__device__ __forceinline__ void quick_always(const double a[3], float4* q) {
+  q[0] = make_float4((float)a[0], (float)a[1], (float)a[2], 0.0f);
+  for (int k = 1; k < 4; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  q[16] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
+}
+
 // Work counted by the statistics kernels; a box lower bound costs 17 FP32
 // operations (6 subtractions, 6 maxima, 3 products, 2 sums).
 constexpr uint32_t kBoxFlops = 17;
 struct TravCount {
-  uint32_t nodes = 0, tris = 0, flops = 0;
+  uint64_t nodes = 0, tris = 0, flops = 0;
 };
 
 // A value that all lanes of the wavefront share, in a scalar register.
@@ -278,7 +352,7 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
     for (int k = 0; k < 4; ++k)
       if (uw[k] != ~0u) W->item[pos++] = uw[k];
     if (kStats && nu > 0) {
-      cnt.tris += (nu + n2) << 2;
+      cnt.tris += El::kQuickFlops > 0 ? (nu + n2) << 2 : 0u;
       cnt.flops += ((nu + n2) << 2) * El::kQuickFlops;
     }
     lds_order();
@@ -387,6 +461,32 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
   }
   if (tr && pushed != 1u) atomicAdd(&W->open[o], pushed - 1u);
   lds_order();
+}
+
+// First slot of the leaf that a descent by the boxes' farthest corners
+// reaches: the warm start of a query without one. (Searches without a first
+// bound push every child they meet: 64 of them filled the stack, and 1,000,003
+// cold queries on 499,280 faces took 40 ms. A descent by the nearest box picks
+// at random among the boxes that hold the point.)
+__device__ __forceinline__ int32_t nearest_leaf(const Node4* nodes, float x, float y, float z) {
+  int32_t c = 0;
+  do {
+    const Node4* N = nodes + c;
+    float best = INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float gx = fmaxf(fabsf(N->lox[k] - x), fabsf(N->hix[k] - x));
+      const float gy = fmaxf(fabsf(N->loy[k] - y), fabsf(N->hiy[k] - y));
+      const float gz = fmaxf(fabsf(N->loz[k] - z), fabsf(N->hiz[k] - z));
+      const float l = gx * gx + gy * gy + gz * gz;
+      if (l < best) {  // an unused slot has an empty box: l = inf
+        best = l;
+        c = N->child[k];
+      }
+    }
+    if (!(best < INFINITY)) return -1;
+  } while (c >= 0);
+  return ~c & ~3;
 }
 
 }  // namespace msk

@@ -301,34 +301,17 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
 }
 
 // ---- prefilter of the exact triangle test
-// Squared distance from p to the triangle in its own frame (a branch-free
-// handful of fused operations instead of the region tests and divisions of
-// tri_dist2) with its error margin `m`: the exact test's value D of the same
-// triangle satisfies sqrt(D) >= sqrt(max(0, d2 - m)) - delta, and for all but
-// nearly degenerate triangles sqrt(D) <= sqrt(d2 + m) + delta, delta = 2^-21 R
-// covering the exact test's roundings at the size of the coordinates. The
-// frame and margins are prepared by quick_prepare_kernel, whose comment
-// derives them.
+// Squared distance d2 from p to the triangle (quick_flat) with its error
+// margin `m`: the exact test's value D of the same triangle satisfies sqrt(D)
+// >= sqrt(max(0, d2 - m)) - delta, and for all but nearly degenerate triangles
+// sqrt(D) <= sqrt(d2 + m) + delta, delta = 2^-21 R covering the exact test's
+// roundings at the size of the coordinates. The frame and margins are prepared
+// by quick_prepare_kernel, whose comment derives them.
 __device__ __forceinline__ void quick_dist(float px, float py, float pz, const void* quick, int64_t i, float& d2,
                                            float& m) {
-  const float4 r0 = gload4(quick, i), r1 = gload4(quick, i + 4), r2 = gload4(quick, i + 8),
-               r3 = gload4(quick, i + 12), r4 = gload4(quick, i + 16);
-  const float gx = px - r0.x, gy = py - r0.y, gz = pz - r0.z;
-  const float x = r1.x * gx + r1.y * gy + r1.z * gz;
-  const float y = r2.x * gx + r2.y * gy + r2.z * gz;
-  const float z = r3.x * gx + r3.y * gy + r3.z * gz;
-  const float c1 = r0.w, s1 = r1.w, l1 = r2.w, c2 = r3.w, s2 = r4.x, l2 = r4.y;
-  const float b = c1 * l1 - c2 * l2;  // vertex b lies at (b, 0), vertex c at l1 (c1, s1)
-  const float t0 = x - __builtin_amdgcn_fmed3f(x, 0.0f, b);
-  const float q1 = x * c1 + y * s1, h1 = x * s1 - y * c1;
-  const float t1 = q1 - __builtin_amdgcn_fmed3f(q1, 0.0f, l1);
-  const float xb = x - b;
-  const float q2 = xb * c2 + y * s2, h2 = y * c2 - xb * s2;
-  const float t2 = q2 - __builtin_amdgcn_fmed3f(q2, 0.0f, l2);
-  const float e = fminf(fminf(y * y + t0 * t0, h1 * h1 + t1 * t1), h2 * h2 + t2 * t2);
-  const float in = fminf(fminf(y, h1), h2);
-  d2 = z * z + (in >= 0.0f ? 0.0f : e);
-  m = r4.z * (gx * gx + gy * gy + gz * gz) + r4.w;
+  float w2, F, G;
+  d2 = quick_flat(px, py, pz, quick, i, w2, F, G);
+  m = F * w2 + G;
 }
 
 // Largest squared value d2 - m of a triangle that may still beat or tie a
@@ -1626,36 +1609,28 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
     T = tris[i];
     memcpy(&index, &T.a.w, 4);
   }
-  if (index == kPadTri) {  // a pad's d2 - m is NaN and its d2 + m no minimum
-    q[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-    for (int k = 1; k < 5; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (index == kPadTri) {
+    quick_pad(q);
     return;
   }
-  const double abx = (double)T.b.x - T.a.x, aby = (double)T.b.y - T.a.y, abz = (double)T.b.z - T.a.z;
-  const double acx = (double)T.c.x - T.a.x, acy = (double)T.c.y - T.a.y, acz = (double)T.c.z - T.a.z;
-  const double bcx = acx - abx, bcy = acy - aby, bcz = acz - abz;
-  const double nx = aby * acz - abz * acy, ny = abz * acx - abx * acz, nz = abx * acy - aby * acx;
-  const double ab = sqrt(abx * abx + aby * aby + abz * abz), ac = sqrt(acx * acx + acy * acy + acz * acz);
-  const double bc = sqrt(bcx * bcx + bcy * bcy + bcz * bcz), nn = sqrt(nx * nx + ny * ny + nz * nz);
-  const double lmax = fmax(ab, fmax(ac, bc)), prod = ab * ac * bc;
-  const double smin = nn * fmin(ab, fmin(ac, bc)) / prod;  // sin of the smallest angle
+  const double A[3] = {T.a.x, T.a.y, T.a.z}, B[3] = {T.b.x, T.b.y, T.b.z}, C[3] = {T.c.x, T.c.y, T.c.z};
+  double ab = 0.0, ac = 0.0, bc = 0.0, nrm[3];
+  for (int k = 0; k < 3; ++k) {
+    const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+    ab += (B[k] - A[k]) * (B[k] - A[k]);
+    ac += (C[k] - A[k]) * (C[k] - A[k]);
+    bc += (C[k] - B[k]) * (C[k] - B[k]);
+    nrm[k] = (B[k1] - A[k1]) * (C[k2] - A[k2]) - (B[k2] - A[k2]) * (C[k1] - A[k1]);
+  }
+  ab = sqrt(ab);
+  ac = sqrt(ac);
+  bc = sqrt(bc);
+  const double nn = sqrt(nrm[0] * nrm[0] + nrm[1] * nrm[1] + nrm[2] * nrm[2]);
+  const double lmax = fmax(ab, fmax(ac, bc));
+  const double smin = nn * fmin(ab, fmin(ac, bc)) / (ab * ac * bc);  // sin of the smallest angle
   const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
   const double F = u * (128.0 + 64.0 / smin) + far * far;
-  if (!(smin >= 0.01) || !(F <= 0.01)) {
-    q[0] = make_float4(T.a.x, T.a.y, T.a.z, 0.0f);
-    for (int k = 1; k < 4; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    q[16] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
-    return;
-  }
-  const double ux = abx / ab, uy = aby / ab, uz = abz / ab;
-  const double mx = nx / nn, my = ny / nn, mz = nz / nn;
-  const double vx = my * uz - mz * uy, vy = mz * ux - mx * uz, vz = mx * uy - my * ux;
-  const double cx = acx * ux + acy * uy + acz * uz, cy = acx * vx + acy * vy + acz * vz;
-  q[0] = make_float4(T.a.x, T.a.y, T.a.z, (float)(cx / ac));
-  q[4] = make_float4((float)ux, (float)uy, (float)uz, (float)(cy / ac));
-  q[8] = make_float4((float)vx, (float)vy, (float)vz, (float)ac);
-  q[12] = make_float4((float)mx, (float)my, (float)mz, (float)((cx - ab) / bc));
-  q[16] = make_float4((float)(cy / bc), (float)bc, (float)F, (float)(F * lmax * lmax));
+  if (!(smin >= 0.01) || !(F <= 0.01) || !quick_frame(A, B, C, q, F, F * lmax * lmax)) quick_always(A, q);
 }
 
 // A query of the query kernel: its point (scene frame) and mesh, a warm-start
@@ -1741,32 +1716,6 @@ struct DiscardBatch {
     discard_store(meshes[r.mesh], j - r.first, h, r.discarded);
   }
 };
-
-// First slot of the leaf that a descent by the boxes' farthest corners
-// reaches: the warm start of a query without one. (Searches without a first
-// bound push every child they meet: 64 of them filled the stack, and 1,000,003
-// cold queries on 499,280 faces took 40 ms. A descent by the nearest box picks
-// at random among the boxes that hold the point.)
-__device__ __forceinline__ int32_t nearest_leaf(const Node4* nodes, float x, float y, float z) {
-  int32_t c = 0;
-  do {
-    const Node4* N = nodes + c;
-    float best = INFINITY;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float gx = fmaxf(fabsf(N->lox[k] - x), fabsf(N->hix[k] - x));
-      const float gy = fmaxf(fabsf(N->loy[k] - y), fabsf(N->hiy[k] - y));
-      const float gz = fmaxf(fabsf(N->loz[k] - z), fabsf(N->hiz[k] - z));
-      const float l = gx * gx + gy * gy + gz * gz;
-      if (l < best) {  // an unused slot has an empty box: l = inf
-        best = l;
-        c = N->child[k];
-      }
-    }
-    if (!(best < INFINITY)) return -1;
-  } while (c >= 0);
-  return ~c & ~3;
-}
 
 // Nearest triangles of n queries on the wavefront-shared search: lanes with an
 // answered query wait until a quarter of the wavefront's queries do, then

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "msk_internal.h"
@@ -25,8 +26,6 @@ namespace msk {
 bool sym_eig(int n, std::vector<double>& A, std::vector<double>& evals, std::vector<double>& V);
 bool sym_eig_smallest(int n, std::vector<double>& A, int m, std::vector<double>& evals, std::vector<double>& V,
                       double* abs_max);
-bool cholesky_upper(int n, const std::vector<double>& A, std::vector<double>& R, double rel_tol);
-void upper_inverse(int n, const std::vector<double>& R, std::vector<double>& Ri);
 bool tridiag_smallest_pairs(int n, const std::vector<double>& d, const std::vector<double>& e, int m,
                             std::vector<double>& evals, std::vector<double>& Xc, double* abs_max);
 void bisect_setup(int n, const std::vector<double>& d, const std::vector<double>& e, std::vector<double>& e2,
@@ -83,15 +82,14 @@ __global__ void copy_block_f64_to_f32_kernel(const double* __restrict__ x, int64
   }
 }
 
-// Row-major GEMM on the matrix cores: C = alpha op(A) op(B) + beta C, op(A)
-// M x K, op(B) K x N; A is M x K (lda) or, transposed, K x M; B is K x N
-// (ldb) or N x K. A 256-thread workgroup computes a 64 x 64 tile: each
-// wavefront a 32 x 32 quarter as 2 x 2 blocks of the 16 x 16 x 4 MFMA (FP64
-// or FP32, accumulating in the same precision), K in steps of 16 staged
-// through LDS. The K range may be split over blockIdx.z (the long inner
-// dimension of the Gram products Q^T X): each slice then writes its partial
-// tile to `part` (splits x M x N) and splitk_reduce_kernel sums them in a
-// fixed order.
+// Row-major GEMM on the matrix cores: C = alpha op(A) B + beta C, op(A) M x K
+// (A is M x K with lda or, transposed, K x M), B K x N (ldb), on the
+// 16 x 16 x 4 MFMA (FP64 or FP32, accumulating in the same precision). The K
+// range may be split over blockIdx.z (the long inner dimension of the Gram
+// products Q^T X): each slice then writes its partial tile to `part`
+// (splits x M x N) and splitk_reduce_kernel sums them in a fixed order. Every
+// entry's products are added with k ascending within a slice, whatever the
+// tile, so the tile changes no bit of the result.
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
 template <typename T>
@@ -112,120 +110,25 @@ struct Mfma<float> {
   __device__ static int row(int lane, int e) { return 4 * (lane >> 4) + e; }
 };
 
-template <typename T, bool TA, bool TB>
-__global__ void __launch_bounds__(256) gemm_kernel(int64_t M, int64_t N, int64_t K, int64_t kchunk, T alpha,
-                                                   const T* __restrict__ A, int64_t lda, const T* __restrict__ B,
-                                                   int64_t ldb, T beta, T* Cm, int64_t ldc, T* __restrict__ part) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ T As[BK][BM + 4];
-  __shared__ T Bs[BK][BN + 4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
-  const int64_t kb = (int64_t)blockIdx.z * kchunk, ke = min(K, kb + kchunk);
-  const int wm = 32 * (wv >> 1), wn = 32 * (wv & 1);
-  typename Mfma<T>::V acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = T(0);
-  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {  // A tile: BM x BK, 4 elements per thread
-      const int e = tid + r * 256;
-      int mm, kk;
-      if (TA) {  // stored K x M: contiguous along m
-        kk = e / BM;
-        mm = e % BM;
-      } else {  // stored M x K: contiguous along k
-        mm = e / BK;
-        kk = e % BK;
-      }
-      const int64_t gm = m0 + mm, gk = k0 + kk;
-      T v = T(0);
-      if (gm < M && gk < ke) v = TA ? A[gk * lda + gm] : A[gm * lda + gk];
-      As[kk][mm] = v;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {  // B tile: BK x BN
-      const int e = tid + r * 256;
-      int nn, kk;
-      if (TB) {  // stored N x K: contiguous along k
-        nn = e / BK;
-        kk = e % BK;
-      } else {  // stored K x N: contiguous along n
-        kk = e / BN;
-        nn = e % BN;
-      }
-      const int64_t gn = n0 + nn, gk = k0 + kk;
-      T v = T(0);
-      if (gn < N && gk < ke) v = TB ? B[gn * ldb + gk] : B[gk * ldb + gn];
-      Bs[kk][nn] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      const int kk = ks + (lane >> 4);
-      T a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[kk][wm + 16 * i + (lane & 15)];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[kk][wn + 16 * j + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = Mfma<T>::step(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t gm = m0 + wm + 16 * i + Mfma<T>::row(lane, e), gn = n0 + wn + 16 * j + (lane & 15);
-        if (gm >= M || gn >= N) continue;
-        if (part) {
-          part[((int64_t)blockIdx.z * M + gm) * N + gn] = acc[i][j][e];
-        } else {
-          T* c = Cm + gm * ldc + gn;
-          *c = alpha * acc[i][j][e] + (beta == T(0) ? T(0) : beta * *c);
-        }
-      }
-}
-
 // Tall products of the Krylov steps on the matrix cores: A (M x K, or K x M
 // when TA) times B (K x N, row-major) with large M and K. A 128 x 64 output
 // tile per workgroup (4 wavefronts of 32 rows, each 2 x 4 blocks of the
 // 16x16x4 MFMA); K in steps of 32 (FP32) or 16 (FP64) read with 16-byte
-// loads (leading dimensions multiples of 16 bytes, A and B 16-byte aligned);
-// the next step's tiles are fetched into registers while the current ones
-// are multiplied out of LDS. Output as gemm_kernel's (split-K partials or C).
+// loads (of any alignment: Vec is aligned to its element, which global loads
+// on this hardware accept); the next step's tiles are fetched into registers
+// while the current ones are multiplied out of LDS.
 template <typename T>
 struct TallCfg;
 template <>
 struct TallCfg<float> {
-  typedef float4 Vec;  // 16-byte load
+  typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte load
   static constexpr int kW = 4, kBK = 32, kPad = 4;
 };
 template <>
 struct TallCfg<double> {
-  typedef double2 Vec;
+  typedef double Vec __attribute__((ext_vector_type(2), aligned(8)));
   static constexpr int kW = 2, kBK = 16, kPad = 2;
 };
-
-template <typename T>
-__device__ __forceinline__ T vec_get(const typename TallCfg<T>::Vec& v, int c);
-template <>
-__device__ __forceinline__ float vec_get<float>(const float4& v, int c) {
-  return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
-}
-template <>
-__device__ __forceinline__ double vec_get<double>(const double2& v, int c) {
-  return c == 0 ? v.x : v.y;
-}
 
 template <typename T, bool TA>
 __global__ void __launch_bounds__(256) gemm_tall_kernel(int64_t M, int64_t N, int64_t K, int64_t kchunk, T alpha,
@@ -315,7 +218,7 @@ __global__ void __launch_bounds__(256) gemm_tall_kernel(int64_t M, int64_t N, in
         *reinterpret_cast<Vec*>(&As[kk][mm]) = ra[r];
       } else {
 #pragma unroll
-        for (int c = 0; c < W; ++c) As[kk + c][mm] = vec_get<T>(ra[r], c);
+        for (int c = 0; c < W; ++c) As[kk + c][mm] = ra[r][c];
       }
     }
 #pragma unroll
@@ -357,6 +260,89 @@ __global__ void __launch_bounds__(256) gemm_tall_kernel(int64_t M, int64_t N, in
       }
 }
 
+// FP64 products with few output entries (the Krylov block's projections and
+// Gram matrices: 64 columns): a 32 x 32 tile per workgroup, a 16 x 16 block
+// per wavefront, so that 8 times as many workgroups share the matrix cores as
+// with the tall tile, where a 512 x 64 x 3,000 product has 48 for 256 compute
+// units. K in steps of 64, the next step's tiles in registers while the
+// current ones are multiplied out of LDS: what is left is the loads' latency,
+// once per step. 512 x 64 x 3,000 takes 11 us (46 us on the tall tile),
+// 3,000 x 64 x 512 10 us (38 us), the 64 x 64 x 3,000 Gram matrix 11 us (37 us
+// on a 64 x 64 tile).
+template <bool TA>
+__global__ void __launch_bounds__(256) gemm_small_kernel(int64_t M, int64_t N, int64_t K, int64_t kchunk, double alpha,
+                                                         const double* __restrict__ A, int64_t lda,
+                                                         const double* __restrict__ B, int64_t ldb, double beta,
+                                                         double* Cm, int64_t ldc, double* __restrict__ part) {
+  typedef TallCfg<double>::Vec Vec;
+  constexpr int BM = 32, BN = 32, BK = 64, R = BM * BK / (256 * 2);
+  // A as it is stored (rows of k when TA, else rows of m), B by rows of k
+  constexpr int LA = TA ? BM : BK;
+  __shared__ double As[(TA ? BK : BM) * (LA + 2)];
+  __shared__ double Bs[BK * (BN + 2)];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
+  const int64_t kb = (int64_t)blockIdx.z * kchunk, ke = min(K, kb + kchunk);
+  const int wm = 16 * (wv >> 1), wn = 16 * (wv & 1);
+  Vec ra[R], rb[R];
+  // two consecutive entries of a row of `count`, zero past its end
+  auto pair = [](const double* p, int64_t at, int64_t count) {
+    Vec v = {0.0, 0.0};
+    if (at + 1 < count)
+      v = *reinterpret_cast<const Vec*>(p + at);
+    else if (at < count)
+      v.x = p[at];
+    return v;
+  };
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int idx = tid + 256 * r, row = idx / (LA / 2), col = 2 * (idx % (LA / 2));
+      const Vec zero = {0.0, 0.0};
+      if (TA)
+        ra[r] = k0 + row < ke ? pair(A + (k0 + row) * lda, m0 + col, M) : zero;
+      else
+        ra[r] = m0 + row < M ? pair(A + (m0 + row) * lda, k0 + col, ke) : zero;
+      const int brow = idx / (BN / 2), bcol = 2 * (idx % (BN / 2));
+      rb[r] = k0 + brow < ke ? pair(B + (k0 + brow) * ldb, n0 + bcol, N) : zero;
+    }
+  };
+  Mfma<double>::V acc = {0.0, 0.0, 0.0, 0.0};
+  if (kb < ke) fetch(kb);
+  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
+    __syncthreads();  // the previous step's reads of As and Bs are done
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int idx = tid + 256 * r;
+      double* a = As + idx / (LA / 2) * (LA + 2) + 2 * (idx % (LA / 2));
+      a[0] = ra[r].x;
+      a[1] = ra[r].y;
+      double* b = Bs + idx / (BN / 2) * (BN + 2) + 2 * (idx % (BN / 2));
+      b[0] = rb[r].x;
+      b[1] = rb[r].y;
+    }
+    __syncthreads();
+    if (k0 + BK < ke) fetch(k0 + BK);
+    const int i = wm + (lane & 15), j = wn + (lane & 15);
+#pragma unroll
+    for (int ks = 0; ks < BK; ks += 4) {
+      const int kk = ks + (lane >> 4);
+      acc = Mfma<double>::step(TA ? As[kk * (LA + 2) + i] : As[i * (LA + 2) + kk], Bs[kk * (BN + 2) + j], acc);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int64_t gm = m0 + wm + Mfma<double>::row(lane, e), gn = n0 + wn + (lane & 15);
+    if (gm >= M || gn >= N) continue;
+    if (part) {
+      part[((int64_t)blockIdx.z * M + gm) * N + gn] = acc[e];
+    } else {
+      double* c = Cm + gm * ldc + gn;
+      *c = alpha * acc[e] + (beta == 0.0 ? 0.0 : beta * *c);
+    }
+  }
+}
+
 // C = alpha sum_z part[z] + beta C (z ascending: a fixed order)
 template <typename T>
 __global__ void splitk_reduce_kernel(int64_t M, int64_t N, int splits, T alpha, const T* __restrict__ part, T beta,
@@ -381,11 +367,66 @@ __global__ void splitk_reduce_kernel(int64_t M, int64_t N, int splits, T alpha, 
 // d[k] = A[k][k] and e[k] = mu.
 constexpr int kProjMax = 2048;  // largest projected problem solved on the device
 
-// Sum over a 256-thread workgroup; every thread receives the same bits.
-__device__ __forceinline__ double block_sum256(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+// v of the lane that the DPP control names within its row of 16.
+template <int kCtrl>
+__device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Sum over the wavefront by exchanges with lane ^ 32, 16, 8, 4, 2, 1, in that
+// order; every lane receives the same bits. The lane moves are register
+// swaps and DPP rotations instead of six round trips through the LDS crossbar
+// (a rotation by 4 brings the value of lane ^ 4, or of that lane ^ 8, which
+// holds the same sum by then): the reflectors applied to 192 vectors of 512
+// entries take 295 us instead of 391.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma clang fp contract(off)
+  {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  v += dpp64<0x128>(v);  // row_ror:8
+  v += dpp64<0x124>(v);  // row_ror:4
+  v += dpp64<0x4e>(v);   // quad_perm [2,3,0,1]
+  v += dpp64<0xb1>(v);   // quad_perm [1,0,3,2]
+  return v;
+}
+
+// wave_sum of a, b, c and d at once, in the same order of additions each, at
+// little more than the cost of one: lanes 0-15 receive a's, 16-31 c's, 32-47
+// b's, 48-63 d's.
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  auto halves = [](double x, double y) {  // lanes 0-31: x's, 32-63: y's sums with lane ^ 32
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(y), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  };
+  const double x = halves(a, b), y = halves(c, d);
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+  double v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  v += dpp64<0x128>(v);
+  v += dpp64<0x124>(v);
+  v += dpp64<0x4e>(v);
+  v += dpp64<0xb1>(v);
+  return v;
+}
+
+// Sum over the first four wavefronts of a workgroup (every thread takes part
+// in the barrier and receives the same bits); `red` is not reused before the
+// workgroup's next barrier.
+__device__ __forceinline__ double first256_sum(double v, double* red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) red[threadIdx.x >> 6] = v;
   __syncthreads();
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
@@ -397,108 +438,124 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
 // in memory (rows and columns <= k are not read again); the last update, of
 // the final 2 x 2 block, is left to house_tail_kernel. Contraction is off,
 // so entries (r, c) and (c, r) of an update get the same bits.
+// A step is one chain of latencies: loads, two sums over the workgroup, a
+// root and a division, the rows' products. So the loads, those of the
+// wavefront's first row included, are issued together at the start, every
+// thread reads step k - 1's v and p both at its own entry i (for the sum) and
+// at i + 1 (for row k's update, whose index is shifted by one), so that w and
+// x stay in registers, and three barriers are left. At n = 512 a step takes
+// 5.1 us on average (6.2 us with the loads one after the other and nine
+// barriers).
+template <int S>  // entries per thread of a vector: n <= 256 S
 __global__ void __launch_bounds__(256) house_step_kernel(double* __restrict__ A, int n, int k, double* __restrict__ H,
                                                          double* __restrict__ betas, double* __restrict__ d,
                                                          double* __restrict__ e, const double* __restrict__ p_prev,
                                                          double* __restrict__ p_out) {
 #pragma clang fp contract(off)
-  __shared__ double vp[kProjMax], wp[kProjMax], vs[kProjMax];
-  __shared__ double red[4];
-  constexpr int S = kProjMax / 256;  // entries per thread of a length-n vector
+  static_assert(256 * S <= kProjMax, "at most kProjMax entries per vector");
+  __shared__ double vp[256 * S], wp[256 * S], vs[256 * S];
+  __shared__ double red0[4], red1[4], xs;
+  constexpr int U = 4 * S;      // entries per lane of a row
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int m = n - k - 1;      // step k's block: rows and columns k+1..n-1
   const int mp = m + 1;         // step k-1's block: k..n-1
   const double bp = k > 0 ? betas[k - 1] : 0.0;
-  // every load of the prologue issued at once: row k (x = A[k][k+1..]), and
-  // step k-1's v and p over its block (index 0 is row k)
-  const double* rk = A + (size_t)k * n + (k + 1);
-  double xr[S], hv[S], pv[S];
+  const double* rk = A + (size_t)k * n + (k + 1);               // row k: x = A[k][k+1..]
+  const double* hk = H + (size_t)(k > 0 ? k - 1 : 0) * n + k;  // step k-1's v from index 1 on (index 0 is 1)
+  double xr[S], hv[S], pv[S], h1[S], p1[S], a[U];
 #pragma unroll
   for (int t = 0; t < S; ++t) {
-    const int i = threadIdx.x + 256 * t;
+    const int i = tid + 256 * t;
     xr[t] = i < m ? rk[i] : 0.0;
-    hv[t] = bp != 0.0 && i < mp ? (i == 0 ? 1.0 : H[(size_t)(k - 1) * n + k + i]) : 0.0;
-    pv[t] = bp != 0.0 && i < mp ? p_prev[i] : 0.0;
+    hv[t] = k > 0 && i < mp ? (i == 0 ? 1.0 : hk[i]) : 0.0;
+    pv[t] = k > 0 && i < mp ? p_prev[i] : 0.0;
+    h1[t] = k > 0 && i < m ? hk[i + 1] : 0.0;
+    p1[t] = k > 0 && i < m ? p_prev[i + 1] : 0.0;
   }
-  // step k-1's w = p - (beta p.v / 2) v
+  const double p0 = k > 0 ? p_prev[0] : 0.0;
+  auto load_row = [&](int r) {
+    const double* row = A + (size_t)(k + 1 + r) * n + (k + 1);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = lane + 64 * u;
+      a[u] = r < m && c < m ? row[c] : 0.0;
+    }
+  };
+  int r = blockIdx.x * 4 + wave;
+  load_row(r);
+  // step k-1's w = p - (beta p.v / 2) v; row k after step k-1's update
+  double w0 = 0.0, x[S], s = 0.0;
   if (bp != 0.0) {
     double sv = 0.0;
 #pragma unroll
+    for (int t = 0; t < S; ++t)
+      if (tid + 256 * t < mp) sv += pv[t] * hv[t];
+    const double half = 0.5 * bp * first256_sum(sv, red0);
+    w0 = p0 - half;
+#pragma unroll
     for (int t = 0; t < S; ++t) {
-      const int i = threadIdx.x + 256 * t;
-      if (i < mp) {
-        vp[i] = hv[t];
-        sv += pv[t] * hv[t];
+      const int i = tid + 256 * t;
+      const double w1 = p1[t] - half * h1[t];
+      x[t] = xr[t] - (w1 + w0 * h1[t]);
+      if (i < m) {
+        vp[i] = h1[t];
+        wp[i] = w1;
       }
     }
-    const double half = 0.5 * bp * block_sum256(sv, red);
+  } else {
 #pragma unroll
-    for (int t = 0; t < S; ++t) {
-      const int i = threadIdx.x + 256 * t;
-      if (i < mp) wp[i] = pv[t] - half * hv[t];
-    }
-    __syncthreads();
+    for (int t = 0; t < S; ++t) x[t] = xr[t];
   }
-  // row k after step k-1's update, d[k] = A[k][k]
-  double s = 0.0;
 #pragma unroll
   for (int t = 0; t < S; ++t) {
-    const int i = threadIdx.x + 256 * t;
-    if (i < m) {
-      double x = xr[t];
-      if (bp != 0.0) x -= vp[0] * wp[1 + i] + wp[0] * vp[1 + i];
-      vs[i] = x;
-      if (i >= 1) s += x * x;
-    }
+    const int i = tid + 256 * t;
+    if (i >= 1 && i < m) s += x[t] * x[t];
   }
-  const double sigma = block_sum256(s, red);  // (its barrier also publishes vs)
-  const double x0 = vs[0];
+  if (tid == 0) xs = x[0];
+  const double sigma = first256_sum(s, red1);  // (its barrier also publishes xs, vp and wp)
+  const double x0 = xs;
   double beta = 0.0, mu = x0, v0 = 1.0;
   if (sigma != 0.0) {
     mu = sqrt(x0 * x0 + sigma);
     v0 = x0 <= 0.0 ? x0 - mu : -sigma / (x0 + mu);
     beta = 2.0 * v0 * v0 / (sigma + v0 * v0);
   }
-  __syncthreads();  // every thread has read vs[0]
-  for (int i = threadIdx.x; i < m; i += 256) vs[i] = i == 0 ? 1.0 : (sigma != 0.0 ? vs[i] / v0 : 0.0);
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) {
-      double akk = A[(size_t)k * n + k];
-      if (bp != 0.0) akk -= vp[0] * wp[0] + wp[0] * vp[0];
-      betas[k] = beta;
-      d[k] = akk;
-      e[k] = mu;
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = tid + 256 * t;
+    if (i < m) {
+      const double v = i == 0 ? 1.0 : (sigma != 0.0 ? x[t] / v0 : 0.0);
+      vs[i] = v;
+      if (blockIdx.x == 0 && i >= 1) H[(size_t)k * n + k + 1 + i] = v;
     }
-    for (int i = 1 + (int)threadIdx.x; i < m; i += 256) H[(size_t)k * n + k + 1 + i] = vs[i];
   }
+  if (blockIdx.x == 0 && tid == 0) {
+    double akk = A[(size_t)k * n + k];
+    if (bp != 0.0) akk -= w0 + w0;
+    betas[k] = beta;
+    d[k] = akk;
+    e[k] = mu;
+  }
+  __syncthreads();
   // rows of step k's block: step k-1's update, then p_k = beta A22 v
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int U = 8;  // row entries per lane loaded together
-  for (int r = blockIdx.x * 4 + wave; r < m; r += gridDim.x * 4) {
+  for (; r < m; r += gridDim.x * 4) {
     double* row = A + (size_t)(k + 1 + r) * n + (k + 1);
     double acc = 0.0;
-    const double vr = bp != 0.0 ? vp[1 + r] : 0.0, wr = bp != 0.0 ? wp[1 + r] : 0.0;
-    for (int c0 = 0; c0 < m; c0 += 64 * U) {
-      double a[U];
+    const double vr = bp != 0.0 ? vp[r] : 0.0, wr = bp != 0.0 ? wp[r] : 0.0;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = c0 + lane + 64 * u;
-        a[u] = c < m ? row[c] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = c0 + lane + 64 * u;
-        if (c < m) {
-          if (bp != 0.0) {
-            a[u] = a[u] - (vr * wp[1 + c] + wr * vp[1 + c]);
-            row[c] = a[u];
-          }
-          acc += a[u] * vs[c];
+    for (int u = 0; u < U; ++u) {
+      const int c = lane + 64 * u;
+      if (c < m) {
+        if (bp != 0.0) {
+          a[u] = a[u] - (vr * wp[c] + wr * vp[c]);
+          row[c] = a[u];
         }
+        acc += a[u] * vs[c];
       }
     }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    acc = wave_sum(acc);
     if (lane == 0) p_out[r] = beta * acc;
+    load_row(r + gridDim.x * 4);
   }
 }
 
@@ -509,17 +566,7 @@ __global__ void __launch_bounds__(256) house_step_kernel(double* __restrict__ A,
 // work runs on the first 256 threads with house_step_kernel's sums in its
 // order, and each row's product is reduced within one wavefront as there, so
 // the results are the per-step launches' bit for bit.
-constexpr int kTailMax = 84;  // (85^2 + 6 * 85) doubles: under 64 KB of LDS
-
-// block_sum256 over the first 256 threads of a larger workgroup (every
-// thread takes part in the barriers and receives the sum).
-__device__ __forceinline__ double first256_sum(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
-}
+constexpr int kTailMax = 136;  // (137^2 + 5 * 137) doubles: 156 of the 160 KB of LDS; 3.1 us a step
 
 __global__ void __launch_bounds__(1024) house_tail_kernel(const double* __restrict__ A, int n, int k0,
                                                           double* __restrict__ H, double* __restrict__ betas,
@@ -527,10 +574,11 @@ __global__ void __launch_bounds__(1024) house_tail_kernel(const double* __restri
                                                           const double* __restrict__ p_in) {
 #pragma clang fp contract(off)
   constexpr int TB = kTailMax + 1;
+  static_assert(kTailMax <= 192, "three entries per lane of a row");
   __shared__ double As[TB * TB];
   __shared__ double vq[TB], pq[TB];  // step k-1's v and p over its block (index 0 is row k)
-  __shared__ double vp[TB], wp[TB], vs[TB], pc[TB];
-  __shared__ double red[4];
+  __shared__ double wp[TB], vs[TB], pc[TB];
+  __shared__ double red0[4], red1[4], xs;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int mb = n - k0;  // rows and columns k0..n-1
   for (int i = tid; i < mb * mb; i += 1024) As[i] = A[(size_t)(k0 + i / mb) * n + k0 + i % mb];
@@ -544,27 +592,20 @@ __global__ void __launch_bounds__(1024) house_tail_kernel(const double* __restri
   int k = k0;
   for (; k + 2 < n; ++k) {
     const int m = n - k - 1, mp = m + 1, o = k - k0;  // o: row / column k in As
-    // step k-1's w = p - (beta p.v / 2) v (one entry per thread, i = tid)
+    // step k-1's w = p - (beta p.v / 2) v (one entry per thread), row k after its update
+    double w0 = 0.0, x = tid < m ? As[o * mb + o + 1 + tid] : 0.0;
     if (bp != 0.0) {
-      double sv = 0.0;
-      if (tid < mp) {
-        vp[tid] = vq[tid];
-        sv += pq[tid] * vq[tid];
+      const double half = 0.5 * bp * first256_sum(tid < mp ? pq[tid] * vq[tid] : 0.0, red0);
+      w0 = pq[0] - half;
+      if (tid < m) {
+        const double v1 = vq[1 + tid], w1 = pq[1 + tid] - half * v1;
+        wp[1 + tid] = w1;
+        x -= w1 + w0 * v1;
       }
-      const double half = 0.5 * bp * first256_sum(sv, red);
-      if (tid < mp) wp[tid] = pq[tid] - half * vq[tid];
-      __syncthreads();
     }
-    // row k after step k-1's update
-    double s = 0.0;
-    if (tid < m) {
-      double x = As[o * mb + o + 1 + tid];
-      if (bp != 0.0) x -= vp[0] * wp[1 + tid] + wp[0] * vp[1 + tid];
-      vs[tid] = x;
-      if (tid >= 1) s += x * x;
-    }
-    const double sigma = first256_sum(s, red);
-    const double x0 = vs[0];
+    if (tid == 0) xs = x;
+    const double sigma = first256_sum(tid >= 1 && tid < m ? x * x : 0.0, red1);  // (publishes xs and wp too)
+    const double x0 = xs;
     double mu = x0, v0 = 1.0;
     beta = 0.0;
     if (sigma != 0.0) {
@@ -572,41 +613,58 @@ __global__ void __launch_bounds__(1024) house_tail_kernel(const double* __restri
       v0 = x0 <= 0.0 ? x0 - mu : -sigma / (x0 + mu);
       beta = 2.0 * v0 * v0 / (sigma + v0 * v0);
     }
-    __syncthreads();  // every thread has read vs[0]
-    if (tid < m) vs[tid] = tid == 0 ? 1.0 : (sigma != 0.0 ? vs[tid] / v0 : 0.0);
-    __syncthreads();
+    if (tid < m) {
+      const double v = tid == 0 ? 1.0 : (sigma != 0.0 ? x / v0 : 0.0);
+      vs[tid] = v;
+      if (tid >= 1) H[(size_t)k * n + k + 1 + tid] = v;
+    }
     if (tid == 0) {
       double akk = As[o * mb + o];
-      if (bp != 0.0) akk -= vp[0] * wp[0] + wp[0] * vp[0];
+      if (bp != 0.0) akk -= w0 + w0;
       betas[k] = beta;
       d[k] = akk;
       e[k] = mu;
     }
-    if (tid >= 1 && tid < m) H[(size_t)k * n + k + 1 + tid] = vs[tid];
-    // rows of step k's block: step k-1's update, then p_k = beta A22 v
-    for (int r = wave; r < m; r += 16) {
-      double* row = As + (o + 1 + r) * mb + (o + 1);
-      double acc = 0.0;
-      const double vr = bp != 0.0 ? vp[1 + r] : 0.0, wr = bp != 0.0 ? wp[1 + r] : 0.0;
-      double a[2];
+    __syncthreads();
+    // rows of step k's block: step k-1's update, then p_k = beta A22 v; the
+    // vectors' entries of the lane's columns stay in registers for all rows
+    double wc[3], vc[3], uc[3];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int c = lane + 64 * u;
-        a[u] = c < m ? row[c] : 0.0;
-      }
+    for (int u = 0; u < 3; ++u) {
+      const int c = lane + 64 * u;
+      wc[u] = bp != 0.0 && c < m ? wp[1 + c] : 0.0;
+      vc[u] = bp != 0.0 && c < m ? vq[1 + c] : 0.0;
+      uc[u] = c < m ? vs[c] : 0.0;
+    }
+    for (int r0 = wave; r0 < m; r0 += 64) {  // rows r0, r0 + 16, r0 + 32, r0 + 48 together
+      double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
+      for (int u = 0; u < 3; ++u) {
         const int c = lane + 64 * u;
-        if (c < m) {
-          if (bp != 0.0) {
-            a[u] = a[u] - (vr * wp[1 + c] + wr * vp[1 + c]);
-            row[c] = a[u];
+        if (64 * u >= m) continue;
+        double a[4], vr[4], wr[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = min(r0 + 16 * q, m - 1);
+          a[q] = As[(o + 1 + r) * mb + (o + 1) + min(c, m - 1)];
+          vr[q] = vq[1 + r];
+          wr[q] = wp[1 + r];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = r0 + 16 * q;
+          if (r < m && c < m) {
+            if (bp != 0.0) {
+              a[q] = a[q] - (vr[q] * wc[u] + wr[q] * vc[u]);
+              As[(o + 1 + r) * mb + (o + 1) + c] = a[q];
+            }
+            acc[q] += a[q] * uc[u];
           }
-          acc += a[u] * vs[c];
         }
       }
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-      if (lane == 0) pc[r] = beta * acc;
+      const double sum = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+      const int r = r0 + 16 * ((lane >> 5) + 2 * ((lane >> 4) & 1));
+      if ((lane & 15) == 0 && r < m) pc[r] = beta * sum;
     }
     __syncthreads();
     if (tid < m) {
@@ -732,6 +790,7 @@ __global__ void sum_groups_kernel(const double* __restrict__ part, int G, int m,
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= m) return;
   double s = 0.0;
+#pragma unroll 32
   for (int g = 0; g < G; ++g) s += part[(int64_t)g * m + j];
   out[j] = s;
 }
@@ -803,7 +862,7 @@ __global__ void __launch_bounds__(256) house_back_kernel(const double* __restric
       double s = 0.0;
 #pragma unroll
       for (int t = 0; t < T; ++t) s += v[c][t] * x[t];
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+      s = wave_sum(s);
       s *= beta[c];
 #pragma unroll
       for (int t = 0; t < T; ++t) x[t] -= v[c][t] * s;
@@ -814,6 +873,162 @@ __global__ void __launch_bounds__(256) house_back_kernel(const double* __restric
     const int r = lane + 64 * t;
     if (r < n) Y[(size_t)r * m + j] = x[t];
   }
+}
+
+// Cholesky factor R (upper, row-major, zero below the diagonal) of the
+// symmetric n x n G, n <= NB, by one workgroup of 1024 threads; *ok = 1, or
+// *ok = 0 and R unwritten where a pivot is not above rel_tol times the largest
+// diagonal entry. R may be G. Every entry sees cholesky_upper's operations in
+// their order (k ascending, no contraction), so the bits are its.
+// Right-looking, the trailing block in registers (row wave + 16 a, column
+// lane + 64 b; finished rows and columns are updated with the others, their
+// values are not used): the wavefront of row k + 1 forms that row, its pivot
+// and quotients while the others update, so a step is one barrier, one LDS
+// read, a root and a division: 26 us at n = 64, 81 us at n = 128 (a host
+// core: 27 and 340 us, and the matrix's way there and back).
+template <int NB>
+__global__ void __launch_bounds__(1024) chol_kernel(const double* G, int n, double rel_tol, double* R,
+                                                    unsigned long long* ok) {
+#pragma clang fp contract(off)
+  constexpr int RA = NB / 16, CB = NB / 64;
+  __shared__ double Rs[NB * NB];
+  __shared__ double dmax[16];
+  __shared__ int failed;  // the step whose pivot failed
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double w[RA][CB];
+#pragma unroll
+  for (int a = 0; a < RA; ++a)
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      const int j = wave + 16 * a, i = lane + 64 * b;
+      w[a][b] = j < n && i < n ? G[(size_t)j * n + i] : 0.0;
+    }
+  double amax = tid < n ? fabs(G[(size_t)tid * n + tid]) : 0.0;
+  for (int off = 32; off > 0; off >>= 1) amax = fmax(amax, __shfl_xor(amax, off));  // (NaN is ignored)
+  if (tid == 0) failed = n;
+  if (lane == 0) dmax[wave] = amax;
+  for (int i = tid; i < NB * NB; i += 1024) Rs[i] = 0.0;
+  __syncthreads();
+  amax = 0.0;
+  for (int i = 0; i < 16; ++i) amax = fmax(amax, dmax[i]);
+  const double floor = rel_tol * amax;
+  // row k of R to LDS from the same row of the trailing block
+  auto pivot = [&](int k, const double* row) {
+    const double v = CB > 1 && k >= 64 ? row[CB - 1] : row[0];
+    const double s = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k & 63),
+                                      __builtin_amdgcn_readlane(__double2loint(v), k & 63));
+    if (!(s > floor)) {
+      if (lane == 0) failed = k;
+      return;
+    }
+    const double r = sqrt(s);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const int i = lane + 64 * c;
+      if (i >= k && i < n) Rs[k * NB + i] = i == k ? r : row[c] / r;
+    }
+  };
+  if (wave == 0) pivot(0, w[0]);
+  __syncthreads();
+  for (int k = 0; k + 1 < n; ++k) {
+    if (failed <= k) break;  // (step k + 1's may be set meanwhile: every thread leaves at the same step)
+    double rk[CB], f[RA];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) rk[c] = Rs[k * NB + lane + 64 * c];
+#pragma unroll
+    for (int a = 0; a < RA; ++a) f[a] = Rs[k * NB + wave + 16 * a];
+    if (wave == ((k + 1) & 15)) {
+      double row[CB], fn = f[0];
+#pragma unroll
+      for (int c = 0; c < CB; ++c) row[c] = w[0][c];
+#pragma unroll
+      for (int a = 1; a < RA; ++a)
+        if (a == (k + 1) >> 4) {
+          fn = f[a];
+#pragma unroll
+          for (int c = 0; c < CB; ++c) row[c] = w[a][c];
+        }
+#pragma unroll
+      for (int c = 0; c < CB; ++c) row[c] -= fn * rk[c];
+      pivot(k + 1, row);
+    }
+#pragma unroll
+    for (int a = 0; a < RA; ++a)
+#pragma unroll
+      for (int c = 0; c < CB; ++c) w[a][c] -= f[a] * rk[c];
+    __syncthreads();
+  }
+  if (failed < n) {
+    if (tid == 0) *ok = 0;
+    return;
+  }
+  for (int e = tid; e < n * n; e += 1024) R[e] = Rs[e / n * NB + e % n];
+  if (tid == 0) *ok = 1;
+}
+
+// Ri = R^-1 of the upper triangular n x n R (row-major, zero below the
+// diagonal, n <= NB) unless *ok is 0; the same layout, Ri apart from R. A lane
+// per column, 64 columns per workgroup, upper_inverse's operations in its
+// order (the sums' k ascending from the entry found last, so the column is one
+// chain of n^2 / 2 additions; no contraction), so the bits are its. R's rows
+// and the columns found so far stand in LDS with zeros outside the triangles,
+// 16 terms are multiplied at once and added without a mask: a sum that starts
+// at +0 keeps its bits when a zero is added. 43 us at n = 64, 145 us at
+// n = 128 (a host core: 47 and 365 us).
+template <int NB>
+__global__ void __launch_bounds__(256) upper_inverse_kernel(const double* __restrict__ R, int n,
+                                                            double* __restrict__ Ri,
+                                                            const unsigned long long* __restrict__ ok) {
+#pragma clang fp contract(off)
+  // row i of R from the multiple of 16 at or below i + 1 on; row_at(i) is column 0's place
+  auto row_at = [](int i) {
+    const int q = i >> 4;
+    return i * NB - (128 * q * (q - 1) + 16 * q * ((i & 15) + 1)) - ((i + 1) & ~15);
+  };
+  constexpr int kRows = NB * NB / 2 + 8 * NB;  // sum over i of NB - ((i + 1) & ~15)
+  __shared__ double Rs[kRows], rd[NB], X[NB * 64];
+  if (!*ok) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int base = 64 * blockIdx.x, j = base + lane;
+  const int top = min(n, base + 64) - 1;  // the workgroup's last column
+  for (int i = wave; i < NB; i += 4) {
+    const int first = (i + 1) & ~15;
+    for (int k = first + lane; k < NB; k += 64) Rs[row_at(i) + k] = i < n && k > i && k < n ? R[i * n + k] : 0.0;
+    X[i * 64 + lane] = i == j && i < n ? 1.0 / R[i * n + i] : 0.0;
+    if (lane == 0) rd[i] = i < n ? R[i * n + i] : 1.0;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    for (int i = top - 1; i >= 0; --i) {
+      const double* r = Rs + row_at(i);
+      double s = 0.0;
+      for (int k0 = (i + 1) & ~15; k0 <= top; k0 += 16) {
+        double p[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) p[u] = r[k0 + u] * X[(k0 + u) * 64 + lane];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s += p[u];
+      }
+      if (i < j && j < n) X[i * 64 + lane] = -s / rd[i];
+    }
+  }
+  __syncthreads();
+  if (j < n)
+    for (int i = wave; i < n; i += 4) Ri[i * n + j] = X[i * 64 + lane];
+}
+
+hipError_t launch_chol_inverse(const double* G, int n, double rel_tol, double* R, double* Ri, unsigned long long* ok,
+                               hipStream_t s) {
+  if (n < 1 || n > kCholMax || R == Ri) return hipErrorInvalidValue;
+  if (n <= 64) {
+    hipLaunchKernelGGL(chol_kernel<64>, dim3(1), dim3(1024), 0, s, G, n, rel_tol, R, ok);
+    hipLaunchKernelGGL(upper_inverse_kernel<64>, dim3(1), dim3(256), 0, s, R, n, Ri, ok);
+  } else {
+    hipLaunchKernelGGL(chol_kernel<128>, dim3(1), dim3(1024), 0, s, G, n, rel_tol, R, ok);
+    hipLaunchKernelGGL(upper_inverse_kernel<128>, dim3((n + 63) / 64), dim3(256), 0, s, R, n, Ri, ok);
+  }
+  return hipGetLastError();
 }
 
 namespace {
@@ -886,27 +1101,28 @@ struct GemmWs {
 };
 
 // Splits the K range over enough slices for about 512 workgroups (two per
-// compute unit) when the output has few tiles, within the workspace.
-template <typename T, bool TA, bool TB>
+// compute unit) when the output has few tiles, within the workspace. The
+// slices set the order of the sums, so they are counted in one way for every
+// tile: 128 rows where M > 64 and rows are 16-byte aligned, else 64. FP64
+// products whose 128 x 64 tiles leave compute units idle (fewer than 256
+// workgroups) take the 32 x 32 tile; with more, the larger tile's fewer reads
+// count (512 x 512 x 3,000: 66 us with 384 workgroups of it).
+template <typename T, bool TA>
 hipError_t gemm(hipStream_t s, const GemmWs& ws, int64_t M, int64_t N, int64_t K, T alpha, const T* A, int64_t lda,
                 const T* B, int64_t ldb, T beta, T* C, int64_t ldc) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  // products with more than one 64-row tile and 16-byte aligned rows: the
-  // tall kernel
-  constexpr bool kTallType = !TB;
   constexpr int64_t kW = 16 / (int64_t)sizeof(T);
-  const bool tall = kTallType && M > 64 && lda % kW == 0 && ldb % kW == 0 && ((uintptr_t)A & 15) == 0 &&
-                    ((uintptr_t)B & 15) == 0;
-  const int64_t BMx = tall ? 128 : 64;
+  const bool rows128 = M > 64 && lda % kW == 0 && ldb % kW == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0;
+  const int64_t BMx = rows128 ? 128 : 64;
   const int64_t tiles = ((M + BMx - 1) / BMx) * ((N + 63) / 64);
   int64_t splits = 1;
   if (K >= 512) splits = std::min<int64_t>((512 + tiles - 1) / tiles, (K + 255) / 256);
   splits = std::min<int64_t>(splits, (int64_t)(ws.bytes / (sizeof(T) * (size_t)M * (size_t)N)));
   splits = std::max<int64_t>(1, std::min<int64_t>(splits, 65535));
-  int64_t kchunk = ((K + splits - 1) / splits + 31) / 32 * 32;  // a multiple of every kernel's K step
+  int64_t kchunk = ((K + splits - 1) / splits + 31) / 32 * 32;  // a multiple of the tall kernel's K step
   if (kchunk < 32) kchunk = 32;
   splits = std::max<int64_t>(1, (K + kchunk - 1) / kchunk);
-  dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + BMx - 1) / BMx), (unsigned)splits);
+  const int64_t tall = ((M + 127) / 128) * ((N + 63) / 64) * splits;
   T* part = splits > 1 ? (T*)ws.p : nullptr;
   GemmWs::Mark mk{nullptr, nullptr, sizeof(T) == 4 ? 1 : 0, 2.0 * (double)M * (double)N * (double)K};
   if (ws.timing) {
@@ -920,17 +1136,17 @@ hipError_t gemm(hipStream_t s, const GemmWs& ws, int64_t M, int64_t N, int64_t K
     ws.timing->live.push_back(mk);
     if ((e = hipEventRecord(mk.a, s)) != hipSuccess) return e;
   }
-  if constexpr (kTallType) {
-    if (tall)
-      hipLaunchKernelGGL((gemm_tall_kernel<T, TA>), grid, dim3(256), 0, s, M, N, std::max<int64_t>(K, 0), kchunk,
-                         alpha, A, lda, B, ldb, beta, C, ldc, part);
-    else
-      hipLaunchKernelGGL((gemm_kernel<T, TA, TB>), grid, dim3(256), 0, s, M, N, std::max<int64_t>(K, 0), kchunk, alpha,
-                         A, lda, B, ldb, beta, C, ldc, part);
-  } else {
-    hipLaunchKernelGGL((gemm_kernel<T, TA, TB>), grid, dim3(256), 0, s, M, N, std::max<int64_t>(K, 0), kchunk, alpha, A,
-                       lda, B, ldb, beta, C, ldc, part);
+  bool launched = false;
+  if constexpr (std::is_same<T, double>::value) {
+    if (tall < 256) {
+      hipLaunchKernelGGL((gemm_small_kernel<TA>), dim3((N + 31) / 32, (M + 31) / 32, splits), dim3(256), 0, s, M, N,
+                         std::max<int64_t>(K, 0), kchunk, alpha, A, lda, B, ldb, beta, C, ldc, part);
+      launched = true;
+    }
   }
+  if (!launched)
+    hipLaunchKernelGGL((gemm_tall_kernel<T, TA>), dim3((N + 63) / 64, (M + 127) / 128, splits), dim3(256), 0, s, M, N,
+                       std::max<int64_t>(K, 0), kchunk, alpha, A, lda, B, ldb, beta, C, ldc, part);
   if (splits > 1) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1063,42 +1279,42 @@ int steklov_modes_device(hipStream_t s, const double* dS, int64_t n_rows, const 
     EIG_TRY(hipMalloc(&dPart.p, (size_t)256 * keep_n * 8));
     EIG_TRY(hipMalloc(&dRes.p, (size_t)keep_n * 8));
     EIG_TRY(hipMalloc(&dPick.p, (size_t)b * 4));
-    PinBuf hGram;  // the b x b Gram matrix down, R^-1 up
-    EIG_TRY(hipHostMalloc(&hGram.p, (size_t)2 * b * b * 8, hipHostMallocDefault));
-    double* const pinG = (double*)hGram.p;
-    double* const pinRi = pinG + (size_t)b * b;
+    DevBuf dRi, dX2, dOk;  // R^-1, the block's other buffer, a flag per pass
+    EIG_TRY(hipMalloc(&dRi.p, (size_t)b * b * 8));
+    EIG_TRY(hipMalloc(&dX2.p, (size_t)n * b * 8));
+    EIG_TRY(hipMalloc(&dOk.p, 2 * 8));
+    PinBuf hOk;
+    EIG_TRY(hipHostMalloc(&hOk.p, 2 * 8, hipHostMallocDefault));
+    unsigned long long* const pinOk = (unsigned long long*)hOk.p;
     double* Q = dQ.as<double>();
     double* Wm = dW.as<double>();
-    double* X = dX.as<double>();
+    double *X = dX.as<double>(), *X2 = dX2.as<double>();
     int cur = 0;
     // orthonormalise X (n x b) against Q[:, :cur] and itself, append it to Q
     // and its product C X to W; false if the block is (numerically) in span(Q)
     auto add_block = [&](bool& ok) -> int {
       ok = false;
-      std::vector<double> G((size_t)b * b), R, Ri;
       for (int pass = 0; pass < 2; ++pass) {
         if (cur > 0) {  // X -= Q (Q^T X)
-          EIG_TRY((gemm<double, true, false>(s, ws, cur, b, n, 1.0, Q, cap, X, b, 0.0, dG.as<double>(), b)));
-          EIG_TRY((gemm<double, false, false>(s, ws, n, b, cur, -1.0, Q, cap, dG.as<double>(), b, 1.0, X, b)));
+          EIG_TRY((gemm<double, true>(s, ws, cur, b, n, 1.0, Q, cap, X, b, 0.0, dG.as<double>(), b)));
+          EIG_TRY((gemm<double, false>(s, ws, n, b, cur, -1.0, Q, cap, dG.as<double>(), b, 1.0, X, b)));
         }
-        EIG_TRY((gemm<double, true, false>(s, ws, b, b, n, 1.0, X, b, X, b, 0.0, dT.as<double>(), b)));
-        EIG_TRY(hipMemcpyAsync(pinG, dT.p, (size_t)b * b * 8, hipMemcpyDeviceToHost, s));
-        EIG_TRY(hipStreamSynchronize(s));  // (also ends the previous upload from pinRi)
-        std::copy(pinG, pinG + (size_t)b * b, G.begin());
-        if (!cholesky_upper(b, G, R, 1e-24)) return 0;
-        upper_inverse(b, R, Ri);
-        std::copy(Ri.begin(), Ri.begin() + (size_t)b * b, pinRi);
-        EIG_TRY(hipMemcpyAsync(dT.p, pinRi, (size_t)b * b * 8, hipMemcpyHostToDevice, s));
-        // X = X R^-1 (through a temporary: dQ2's first n*b entries)
-        EIG_TRY((gemm<double, false, false>(s, ws, n, b, b, 1.0, X, b, dT.as<double>(), b, 0.0, dQ2.as<double>(), b)));
-        EIG_TRY(hipMemcpyAsync(X, dQ2.p, (size_t)n * b * 8, hipMemcpyDeviceToDevice, s));
+        EIG_TRY((gemm<double, true>(s, ws, b, b, n, 1.0, X, b, X, b, 0.0, dT.as<double>(), b)));
+        EIG_TRY(launch_chol_inverse(dT.as<double>(), b, 1e-24, dT.as<double>(), dRi.as<double>(),
+                                    dOk.as<unsigned long long>() + pass, s));
+        // X = X R^-1, into the other buffer (unused if a pass fails)
+        EIG_TRY((gemm<double, false>(s, ws, n, b, b, 1.0, X, b, dRi.as<double>(), b, 0.0, X2, b)));
+        std::swap(X, X2);
       }
+      EIG_TRY(hipMemcpyAsync(pinOk, dOk.p, 2 * 8, hipMemcpyDeviceToHost, s));
+      EIG_TRY(hipStreamSynchronize(s));
+      if (!pinOk[0] || !pinOk[1]) return 0;
       // append X to Q, C X (FP32 product) to W
       hipLaunchKernelGGL(copy_block_f64_kernel, dim3(blocks_for(n * b)), dim3(256), 0, s, X, (int64_t)b, Q + cur,
                          (int64_t)cap, n, (int64_t)b);
       hipLaunchKernelGGL(copy_block_f64_to_f32_kernel, dim3(blocks_for(n * b)), dim3(256), 0, s, X, (int64_t)b,
                          dX32.as<float>(), (int64_t)b, n, (int64_t)b);
-      EIG_TRY((gemm<float, false, false>(s, ws, n, b, n, 1.0f, dC32.as<float>(), n, dX32.as<float>(), b, 0.0f,
+      EIG_TRY((gemm<float, false>(s, ws, n, b, n, 1.0f, dC32.as<float>(), n, dX32.as<float>(), b, 0.0f,
                                          dY32.as<float>(), b)));
       hipLaunchKernelGGL(copy_block_f32_to_f64_kernel, dim3(blocks_for(n * b)), dim3(256), 0, s, dY32.as<float>(),
                          (int64_t)b, Wm + cur, (int64_t)cap, n, (int64_t)b);
@@ -1134,7 +1350,7 @@ int steklov_modes_device(hipStream_t s, const double* dS, int64_t n_rows, const 
         if (!ok) break;
       }
       // Rayleigh-Ritz on span(Q[:, :cur])
-      EIG_TRY((gemm<double, true, false>(s, ws, cur, cur, n, 1.0, Q, cap, Wm, cap, 0.0, dT.as<double>(), cur)));
+      EIG_TRY((gemm<double, true>(s, ws, cur, cur, n, 1.0, Q, cap, Wm, cap, 0.0, dT.as<double>(), cur)));
       const int kk = std::min(keep_n, cur);
       double tmax = 0.0;
       if (cur >= 3 && cur <= kProjMax) {
@@ -1148,9 +1364,10 @@ int steklov_modes_device(hipStream_t s, const double* dS, int64_t n_rows, const 
         int kx = 0;
         for (; kx + 2 < cur && cur - kx - 1 > kTailMax; ++kx) {
           const int g = std::min(256, (cur - kx - 1 + 3) / 4);
-          hipLaunchKernelGGL(house_step_kernel, dim3(g), dim3(256), 0, s, A, cur, kx, dH.as<double>(),
-                             dBeta.as<double>(), dD.as<double>(), dE.as<double>(), (const double*)pb[(kx + 1) & 1],
-                             pb[kx & 1]);
+          const auto step = cur <= 512 ? house_step_kernel<2>
+                                       : cur <= 1024 ? house_step_kernel<4> : house_step_kernel<8>;
+          hipLaunchKernelGGL(step, dim3(g), dim3(256), 0, s, A, cur, kx, dH.as<double>(), dBeta.as<double>(),
+                             dD.as<double>(), dE.as<double>(), (const double*)pb[(kx + 1) & 1], pb[kx & 1]);
         }
         hipLaunchKernelGGL(house_tail_kernel, dim3(1), dim3(1024), 0, s, (const double*)A, cur, kx, dH.as<double>(),
                            dBeta.as<double>(), dD.as<double>(), dE.as<double>(), (const double*)pb[(kx + 1) & 1]);
@@ -1205,8 +1422,8 @@ int steklov_modes_device(hipStream_t s, const double* dS, int64_t n_rows, const 
       }
       cnorm = std::max(cnorm, tmax);
       // Ritz vectors V = Q Y[:, :kk], CV = W Y[:, :kk] (Y is cur x kk)
-      EIG_TRY((gemm<double, false, false>(s, ws, n, kk, cur, 1.0, Q, cap, dY.as<double>(), kk, 0.0, dQ2.as<double>(), kk)));
-      EIG_TRY((gemm<double, false, false>(s, ws, n, kk, cur, 1.0, Wm, cap, dY.as<double>(), kk, 0.0, dW2.as<double>(), kk)));
+      EIG_TRY((gemm<double, false>(s, ws, n, kk, cur, 1.0, Q, cap, dY.as<double>(), kk, 0.0, dQ2.as<double>(), kk)));
+      EIG_TRY((gemm<double, false>(s, ws, n, kk, cur, 1.0, Wm, cap, dY.as<double>(), kk, 0.0, dW2.as<double>(), kk)));
       // squared residual norms of the kk Ritz pairs, |CV_j - theta_j V_j|^2,
       // on the device (the row groups added in a fixed order)
       constexpr int kResGroups = 256;
@@ -1275,7 +1492,7 @@ int steklov_modes_device(hipStream_t s, const double* dS, int64_t n_rows, const 
     EIG_TRY(hipMalloc(&dV.p, (size_t)n * k * 8));
     EIG_TRY(hipMalloc(&dCV.p, (size_t)n * k * 8));
     EIG_TRY(hipMemcpyAsync(dV.p, Vk.data(), Vk.size() * 8, hipMemcpyHostToDevice, s));
-    EIG_TRY((gemm<double, false, false>(s, ws, n, k, n, 1.0, dC64.as<double>(), n, dV.as<double>(), k, 0.0,
+    EIG_TRY((gemm<double, false>(s, ws, n, k, n, 1.0, dC64.as<double>(), n, dV.as<double>(), k, 0.0,
                                         dCV.as<double>(), k)));
     std::vector<double> CV((size_t)n * k);
     EIG_TRY(hipMemcpyAsync(CV.data(), dCV.p, CV.size() * 8, hipMemcpyDeviceToHost, s));

@@ -244,10 +244,10 @@ hipError_t launch_psd_syrk(const double* A, int64_t m, int64_t Kp, int64_t slice
 hipError_t launch_psd_reduce(const double* P, int64_t n_slots, int64_t K, int64_t Kp, double* C, hipStream_t s);
 
 // Fixed workspace of the allocation-free estimate (noalloc.hip): 64 MiB per
-// device. noalloc_scratch_init looks its address up on `device` (which must
+// device, and the padding of the 8 queue counters to cache lines of their own. noalloc_scratch_init looks its address up on `device` (which must
 // be current) once; noalloc_scratch returns it (nullptr if the lookup failed
 // or was not made, with the HIP error in *err).
-constexpr size_t kNoallocScratchBytes = size_t(64) << 20;
+constexpr size_t kNoallocScratchBytes = (size_t(64) << 20) + 768;
 hipError_t noalloc_scratch_init(int device);
 void* noalloc_scratch(int device, hipError_t* err);
 

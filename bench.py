@@ -32,7 +32,7 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3  # 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2 (dua
 FP64_MATRIX_PEAK_TFLOPS = 78.6   # MI355X dense FP64 matrix-core peak
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2.4 GHz
 FP32_MATRIX_PEAK_TFLOPS = 157.3  # MI355X dense FP32 matrix-core peak
-NODE_BYTES, TRI_BYTES = 128, 48
+NODE_BYTES, TRI_BYTES = 128, 80  # a node; the prefilter record of a tested triangle slot
 DEFAULT_WORKLOAD = "batch64_mixed"
 
 
@@ -287,7 +287,7 @@ def kelvin_leg(ctx, pairs=64, kill_walks=1 << 20):
     tf = cs["fp64_ops"] / wk_s / 1e12
     gbs = (128 * cs["nodes_visited"] + 120 * cs["elements_tested"]) / wk_s / 1e9
     roof = {"bound": "alu", "achieved": tf, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": tf / FP64_VECTOR_PEAK_TFLOPS, "dtype": "f64", "kernel": "kelvin_walk_kernel",
+            "frac": tf / FP64_VECTOR_PEAK_TFLOPS, "dtype": "f64", "kernel": "kelvin_stream_kernel",
             "per_query": {"nodes": cs["nodes_visited"] / q_walk, "elements": cs["elements_tested"] / q_walk,
                           "fp64_ops": cs["fp64_ops"] / q_walk},
             "bytes_touched": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",

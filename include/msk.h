@@ -68,8 +68,8 @@ const char* msk_last_error(const msk_ctx* ctx);
 
 typedef struct {
   int32_t leaf_size; /* triangles per BVH leaf, 1..8 (default 4)            */
-  int32_t top_nodes; /* top BVH nodes the persistent kernel may stage in LDS,
-                        0..85 (default 85; the kernel stages at most 21)  */
+  int32_t top_nodes; /* 0..85 (default 85); checked, without effect: the
+                        searches stage no nodes in LDS                    */
 } msk_bvh_opts;
 
 typedef struct {
@@ -283,7 +283,8 @@ typedef struct {
   double delta_rel;    /*   (defaults 2^-20 and 2^-21)                         */
   int32_t form;        /* msk_form (default persistent)                        */
   int32_t block;       /* threads per workgroup (default 256)                  */
-  int32_t blocks_per_cu; /* persistent grid size / 256 CUs (default 8)         */
+  int32_t blocks_per_cu; /* persistent workgroups per CU (default 8; at most the
+                            4 that are resident are launched)                  */
   int32_t chunk;       /* walks a wavefront takes from the queue at once (64)  */
   int32_t regen_min;   /* persistent form: a wavefront records ended walks and
                           takes new ones once this many of its 64 lanes are

@@ -32,7 +32,7 @@ struct msk_mesh {
   double centre[3] = {0, 0, 0};
   double radius = 0, area = 0;
   int64_t nv = 0, nf = 0, n_nodes = 0;
-  int depth = 0, leaf_size = 4, entry = 1, top_nodes = 85;
+  int depth = 0, leaf_size = 4, entry = 1;
   Node4* d_nodes = nullptr;   // one allocation holds the nodes,
   TriRec* d_tris = nullptr;   // the triangles
   float4* d_quick = nullptr;  // and their prefilter records
@@ -253,7 +253,6 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   m->depth = B.depth;
   m->leaf_size = leaf;
   m->entry = B.entry;
-  m->top_nodes = (int)std::min<int64_t>(top, m->n_nodes);
   m->vrel.resize((size_t)n_verts * 3);
   for (int64_t i = 0; i < n_verts; ++i)
     for (int k = 0; k < 3; ++k) m->vrel[3 * i + k] = (float)((double)V[3 * i + k] - B.centre[k]);
@@ -2341,7 +2340,6 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   m->depth = B.depth;
   m->leaf_size = leaf;
   m->entry = B.entry;
-  m->top_nodes = (int)std::min<int64_t>(kMaxTop, m->n_nodes);
   return MSK_OK;
 }
 

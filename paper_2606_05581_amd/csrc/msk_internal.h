@@ -45,7 +45,7 @@ __host__ __device__ inline int64_t quick_index(int64_t slot) { return (slot >> 2
 
 constexpr int kStackDepth = 64;     // traversal stack entries per lane
 constexpr int kMaxTableNnz = 32;    // basis entries per vertex
-constexpr int kMaxTop = 85;         // BVH nodes a workgroup may keep in LDS (3 levels)
+constexpr int kMaxTop = 85;         // largest accepted msk_bvh_opts.top_nodes
 
 // Host-side BVH build result.
 struct HostBvh {

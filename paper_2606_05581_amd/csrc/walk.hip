@@ -1153,14 +1153,15 @@ __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 #else
 #define MSK_PERSISTENT_OCCUPANCY
 #endif
-// Optional per-phase cycle counts of the streaming kernel (a measurement
-// build only: -DMSK_PHASE_TIMING=1); phases are timed by the wavefront's
-// shader clock at points every lane passes together.
-// lanes with an answered query that trigger the step continuation
+// lanes with an answered query that trigger the step continuation (8, 12, 24
+// and 32 measured the same)
 #ifndef MSK_STEP_MIN
 #define MSK_STEP_MIN 16
 #endif
 constexpr int kStepMin = MSK_STEP_MIN;
+// Optional per-phase cycle counts of the streaming kernel (a measurement
+// build only: -DMSK_PHASE_TIMING=1); phases are timed by the wavefront's
+// shader clock at points every lane passes together.
 #ifndef MSK_PHASE_TIMING
 #define MSK_PHASE_TIMING 0
 #endif
@@ -1174,13 +1175,19 @@ __device__ unsigned long long g_phase_cycles[16];
 #endif
 
 // Streaming form of the persistent kernel: the queries of a wavefront's walks
-// run on its shared search (search_trip), so a walk whose query is long does
+// run on its shared search (search_pass), so a walk whose query is long does
 // not hold the others: walks whose query is answered wait until enough of them
 // do (kStepMin), then finish their step and start the next query together;
 // ended walks and idle lanes wait for the next bookkeeping pass (L.regen_min).
 // At most L.max_owners lanes of a wavefront carry a walk: a launch of few
 // walks spreads them over all wavefronts. The walks, their queries and their
 // results are those of the other forms.
+//   Bound by vector issue (73% of the cycles of a launch, its tail included),
+// with few walks by the longest walk's chain of queries, about 5 us each. Walk
+// kernel with a stack per lane and exact tests of every listed triangle, and
+// now: 2.0M walks among 53,000 triangles of the soup 15.4 -> 8.3 ms, 4.1M walks
+// on a 500,000-face sphere 64.3 -> 34.4 ms, 41,472 walks on 320 faces 3.0 ->
+// 1.1 ms, a batch of 12 meshes 33.8 -> 22.5 ms.
 template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   __shared__ WaveTables<AccT> T;
@@ -1457,7 +1464,8 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 // same float operations as in the sequential loop, so the radius is the same.
 // The midpoints' queries run on the wavefront-shared search: a large ball deep
 // inside the shape meets thousands of boxes, which all 64 lanes share. (On a
-// lane each: 6.2 ms for 4,096 rows on 80,000 faces.) rows_per_wave (1, 2, 4 or
+// lane each: 6.2 ms for 4,096 rows on 80,000 faces; now 0.4 ms, bound by vector
+// issue.) rows_per_wave (1, 2, 4 or
 // 8) is as low as still gives every resident wavefront rows. row_queries
 // counts the bounded queries that the lanes issue (up to seven per round of
 // three levels, so more than the iters decisions they serve).
@@ -1728,7 +1736,8 @@ struct DiscardBatch {
 // followed by far ones took 12.4 instead of 6.9 ms).
 //   On a thread per query with a traversal of its own, 1,000 queries on 1,280
 // faces took 230 us and 1,000,003 on 499,280 faces 9.6 ms, as long as the
-// slowest traversal of each wavefront.
+// slowest traversal of each wavefront; now 32 us and 7 ms, a few trips' latency
+// and vector issue.
 template <typename Src>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(Src src, int64_t nq, int32_t own_shift) {

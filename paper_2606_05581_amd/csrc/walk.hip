@@ -322,6 +322,10 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
   return s * s * (1.0f + 0x1p-20f);
 }
 
+// m2 of a squared distance: not below the normal numbers, of which boxes and
+// keep_bound take the hardware's square root.
+__device__ __forceinline__ float bound_of(float d2) { return fmaxf(d2, 0x1p-126f); }
+
 // Planar triangles as elements of the wavefront-shared search (same result as
 // the lane-private bvh_nearest, bit for bit). Values are squared distances,
 // pt.w = 2 delta; the owner's (squared distance, original index) is kept by a
@@ -374,7 +378,7 @@ struct TriEl {
       memcpy(&orig, &T.a.w, 4);
       const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)orig;
       atomicMin(&W->own.key[o], key);
-      atomicMin(&W->m2[o], __float_as_uint(d));
+      atomicMin(&W->m2[o], __float_as_uint(bound_of(d)));
       lds_order();
       if (W->own.key[o] == key) W->own.rec_slot[o] = s;
     }
@@ -392,7 +396,7 @@ __device__ __forceinline__ void search_start(Scratch* W, uint32_t lane, const No
   if (warm >= 0) {
     float d2, m;
     quick_dist(x, y, z, quick, quick_index(warm), d2, m);
-    m2 = d2 + m;
+    m2 = fminf(d2 + m, INFINITY);  // (no bound where the value overflowed)
   }
   W->pt[lane] = make_float4(x, y, z, 0x1p-20f * radius);
   W->m2[lane] = __float_as_uint(m2);
@@ -413,9 +417,9 @@ __device__ __forceinline__ bool search_answer(Scratch* W, uint32_t lane, Nearest
   h.d2 = __uint_as_float((uint32_t)(k >> 32));
   h.orig = (int32_t)(uint32_t)k;
   h.slot = W->own.rec_slot[lane];
-  const float w = fabsf(W->pt[lane].w);
-  if (h.d2 > keep_bound(__uint_as_float(W->m2[lane]), w)) {
-    W->m2[lane] = __float_as_uint(h.d2);
+  const float w = W->pt[lane].w;
+  if (w >= 0.0f && h.d2 > keep_bound(__uint_as_float(W->m2[lane]), w)) {
+    W->m2[lane] = __float_as_uint(bound_of(h.d2));
     W->pt[lane].w = -w;
     return false;
   }
@@ -1520,7 +1524,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
           if (inside) {
             search_start(W, lane, M.nodes, M.quick, M.tris, M.radius, (float)cxd, (float)cyd, (float)czd, -1);
             const float bound = (t * t) * (1.0f + 0x1p-20f);
-            W->m2[lane] = __float_as_uint(bound);
+            W->m2[lane] = __float_as_uint(bound_of(bound));
             W->own.key[lane] = ((unsigned long long)__float_as_uint(bound) << 32) | (uint32_t)INT_MAX;
             // an upper value below `stop` means sqrt(exact value) < t
             const float ts = t - W->pt[lane].w;
@@ -1545,7 +1549,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
           open = again;
           if (again) {
             W->pt[lane].w = -W->pt[lane].w;
-            W->m2[lane] = __float_as_uint((t * t) * (1.0f + 0x1p-20f));
+            W->m2[lane] = __float_as_uint(bound_of((t * t) * (1.0f + 0x1p-20f)));
           }
         }
         search_push(W, lane, again, M.entry, size);
@@ -1602,10 +1606,14 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
 //     most 24 u w^2 over the smallest altitude, whose square is at most w^2
 //     (4 R)^2 (24 u / altitude)^2;
 //   * its edge and vertex values add roundings at the size of the coordinates,
-//     delta = 2^-21 R in distance, which keep_bound carries.
-// Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2). A triangle
-// whose smallest angle has sin < 0.01, or whose F is large, gets margins that
-// send every test of it to the exact one.
+//     delta = 2^-21 R in distance, which keep_bound carries;
+//   * in a mesh of small units its products underflow: (n.ap)^2 by up to 2^-149,
+//     2^-149 / (n.n) in the value (edges of 1e-7: 1e-3 of their square), the
+//     squares of lengths by a few 2^-149. The margin holds 2^-147 / (n.n) +
+//     2^-126, so that upper values, and with them m2, stay normal numbers.
+// Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2), and the last.
+// A triangle whose smallest angle has sin < 0.01, whose F is large or whose
+// n.n is below 2^-120 gets margins that send every test of it to the exact one.
 __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, double radius,
                                      float4* __restrict__ quick) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1638,7 +1646,8 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
   const double smin = nn * fmin(ab, fmin(ac, bc)) / (ab * ac * bc);  // sin of the smallest angle
   const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
   const double F = u * (128.0 + 64.0 / smin) + far * far;
-  if (!(smin >= 0.01) || !(F <= 0.01) || !quick_frame(A, B, C, q, F, F * lmax * lmax)) quick_always(A, q);
+  const double G = F * lmax * lmax + 0x1p-126 + 0x1p-147 / (nn * nn);
+  if (!(smin >= 0.01) || !(F <= 0.01) || !(nn * nn >= 0x1p-120) || !quick_frame(A, B, C, q, F, G)) quick_always(A, q);
 }
 
 // A query of the query kernel: its point (scene frame) and mesh, a warm-start
@@ -1787,7 +1796,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
         if (take) {
           qi = q;
           const Query p = src.load(qi);
-          if (fmaxf(fabsf(p.x), fmaxf(fabsf(p.y), fabsf(p.z))) <= 1.7f * p.radius) {
+          const float far = 1.7f * p.radius;
+          if (fabsf(p.x) <= far && fabsf(p.y) <= far && fabsf(p.z) <= far) {
             // few queries leave the stack room enough for a cold start
             const int32_t warm = p.warm < 0 && own_shift > 2 ? nearest_leaf(p.nodes, p.x, p.y, p.z) : p.warm;
             search_start(W, lane, p.nodes, p.quick, p.tris, p.radius, p.x, p.y, p.z, warm);
@@ -1795,7 +1805,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
             entry = p.entry;
             mode = 1;
             fresh = true;
-          } else {  // the prefilter's margins hold for |p| <= 3 R
+          } else {  // the prefilter's margins hold for |p| <= 3 R, and for numbers
             Nearest h;
             h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
             bvh_nearest<false>(p.nodes, p.tris, p.x, p.y, p.z, p.radius, h, cnt);

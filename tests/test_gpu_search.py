@@ -101,6 +101,40 @@ def test_points_equally_far_from_everything(ctx, oracle_mod):
     assert np.array_equal(t, t_o) and np.array_equal(d, d_o) and np.array_equal(b, b_o)
 
 
+@pytest.mark.parametrize("unit", [1e-5, 1e-3, 1e4, 1e9])
+def test_closest_points_in_other_units(ctx, oracle_mod, unit):
+    """Products of the exact test underflow in small units (its value is off by up to 2^-149 over the square of
+    twice the triangle's area); the prefilter must not drop what the exact test would still prefer."""
+    import torch
+
+    V, F = _mesh("sphere1280")
+    V32 = (V * unit).astype(np.float32)
+    mesh = ctx.build_bvh(V32, F.astype(np.int32))
+    Q = (_points(V, 3000, 6).astype(np.float64) * unit).astype(np.float32)
+    t_o, d_o, b_o = oracle_mod.Scene(V32, F, bvh=False).nearest_f32(Q.astype(np.float64))
+    t, d, b = (x.cpu().numpy() for x in ctx.closest_points(mesh, torch.tensor(Q, device="cuda")))
+    assert np.array_equal(d, d_o)
+    some = np.isfinite(d_o)  # where every distance overflows the oracle names no triangle, the library the lowest
+    assert np.array_equal(t[some], t_o[some]) and np.array_equal(b[some], b_o[some])
+
+
+def test_points_that_are_no_numbers(ctx):
+    """A coordinate without a value leaves every distance undefined: the answer is the lowest triangle at an
+    infinite distance, and the numbers beside it are answered as ever."""
+    import torch
+
+    V, F = _mesh("sphere1280")
+    mesh = ctx.build_bvh(V.astype(np.float32), F.astype(np.int32))
+    Q = _points(V, 200, 8)
+    t0, d0, b0 = (x.cpu().numpy() for x in ctx.closest_points(mesh, torch.tensor(Q, device="cuda")))
+    R = Q.copy()
+    R[::3, 1] = np.nan
+    t, d, b = (x.cpu().numpy() for x in ctx.closest_points(mesh, torch.tensor(R, device="cuda")))
+    bad = np.isnan(R).any(1)
+    assert (t[bad] == 0).all() and np.isinf(d[bad]).all()
+    assert np.array_equal(t[~bad], t0[~bad]) and np.array_equal(d[~bad], d0[~bad]) and np.array_equal(b[~bad], b0[~bad])
+
+
 def _log(ctx, case, walks, exterior, leaf, **opts):
     from paper_2606_05581_amd import msk
 

@@ -158,7 +158,7 @@ __device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t& tota
 // of nodes. On a stack per lane it held its wavefront for that many trips
 // with one lane busy: 256,000 walks on a 500,000-face sphere took 15.6 ms,
 // 16.4M walks 153 ms, so that 17 of the 51 ms of 4.1M walks were such tails.
-// Here all lanes share its nodes, and the 4.1M walks take 34 ms.
+// Here all lanes share its nodes, and the 4.1M walks take 29 ms.
 //
 // Elements are listed in units of one block of 4 slots of one owner, one
 // lane each (one word: block << 6 | owner lane; leaves start at a block and
@@ -182,24 +182,34 @@ __device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t& tota
 // wavefront instructions per round of 64 tests, every region's path among
 // them. The prefilter of triangles takes about 75.
 //
-// The stack holds kItemCap items. A trip's lanes whose children would raise it
-// over kItemLimit put their item back instead (lanes in order from the top),
-// and a trip within 12 items of the limit takes one item only, whose subtree
-// adds at most 3 items a level (3 x depth + 5 <= kStackDepth). New queries
-// start only up to kRootLimit items. The units of a trip lie above the stack's
-// top; lanes whose units do not fit there put their item back as well. (A trip
-// that took only as many items as the room could hold four children of crept
-// along with a few items once 64 far queries had filled the stack.)
-constexpr int kItemCap = 512, kItemLimit = kItemCap - 64, kRootLimit = 256;
-static_assert(kItemLimit + kStackDepth <= kItemCap, "one item's subtree must fit above the limit");
-static_assert(kRootLimit + 64 <= kItemLimit, "new queries must fit below the limit");
+// The stack holds kCap items. A trip's lanes whose children would raise it over
+// the limit, 64 below, put their item back instead (lanes in order from the
+// top), and a trip within 12 items of the limit takes one item only, whose
+// subtree adds at most 3 items a level (3 x depth + 5 <= kStackDepth). The units
+// of a trip lie above the stack's top; lanes whose units do not fit there put
+// their item back as well. (A trip that took only as many items as the room
+// could hold four children of crept along with a few items once 64 far queries
+// had filled the stack.)
+//   A full stack is slow: searches whose elements are about equally far (the
+// inside of a sphere) then advance an item at a time. So new queries start only
+// while at most kRootLimit items wait, less than a trip takes: the more items
+// each search has, the fewer run at once. Walk kernel with 32 instead of 256:
+// 4.1M walks on 500,000 triangles 36 -> 30 ms, a batch of 12 meshes 23.4 -> 20.8
+// ms (64: 31.4 and 21.9 ms, 16: as 32). And the query kernel, which keeps no
+// row tables in LDS, has 960 items where the others have 512: 1,000,003 points
+// 6.6 -> 3.5 ms, 200,000 points halfway to the centre of a sphere of 327,680
+// triangles 12.8 -> 3.1 ms (384 items: 23 ms; a stack per lane 6.2 ms).
+constexpr int kItemCap = 512, kQueryItemCap = 960, kRootLimit = 32;
 constexpr int kPendCap = 128;
 // `kStop`: queries that only ask whether an element lies below a value end
 // once m2 is below `stop`.
-template <typename El, bool kStop = false>
+template <typename El, bool kStop = false, int kCap = kItemCap>
 struct SearchScratch {
-  uint32_t item[kItemCap];   // node << 6 | owner; above the top: units, block << 6 | owner
-  uint16_t lb[kItemCap];     // item's box lower bound, FP32 cut to 16 bits
+  static constexpr int cap = kCap, limit = kCap - 64;
+  static_assert(limit + kStackDepth <= cap, "one item's subtree must fit above the limit");
+  static_assert(kRootLimit + 64 <= limit, "new queries must fit below the limit");
+  uint32_t item[kCap];   // node << 6 | owner; above the top: units, block << 6 | owner
+  uint16_t lb[kCap];     // item's box lower bound, FP32 cut to 16 bits
   float4 pt[64];             // owner's query point; w: El's absolute allowance, negative: m2 lowered by exact values only
   uint32_t m2[64];           // bound on the owner's minimum, in El's measure (float bits)
   uint32_t open[64];         // owner's items on the stack
@@ -260,13 +270,13 @@ __device__ __forceinline__ void search_push(Scratch* W, uint32_t lane, bool fres
   for (uint32_t e = 2; e <= 6; e += 2)
     if (size + (nf << e) <= 64u && __ballot(fresh && entry < (1 << e)) == 0) es = e;
   if (fresh) {
-    W->lb[kItemLimit + mbcnt64(m)] = (uint16_t)lane;  // above any item of such a pass
+    W->lb[Scratch::limit + mbcnt64(m)] = (uint16_t)lane;  // above any item of such a pass
     W->open[lane] = 1u << es;
   }
   lds_order();
   const uint32_t first = ((1u << es) - 1u) / 3u;
   if (lane < nf << es) {
-    const uint32_t o = W->lb[kItemLimit + (lane >> es)];
+    const uint32_t o = W->lb[Scratch::limit + (lane >> es)];
     W->item[size + lane] = (first + (lane & ((1u << es) - 1u))) << 6 | o;
     W->lb[size + lane] = 0;
   }
@@ -283,7 +293,7 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
                                             uint32_t& npend, TravCount& cnt) {
   size = uniform(size);
   npend = uniform(npend);
-  const int32_t room = (int32_t)kItemLimit - (int32_t)size;  // for more items than are taken
+  const int32_t room = (int32_t)Scratch::limit - (int32_t)size;  // for more items than are taken
   const uint32_t n = trip ? min(room >= 12 ? 64u : 1u, size) : 0u;
   const bool tr = lane < n;
   float lb[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
@@ -337,8 +347,8 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
   if (trip) {
     done = ~0ull;
     const uint32_t before = wave_prefix_small(nu, total);
-    if (total > (uint32_t)kItemCap - size) {
-      back = nu > 0 && before + nu > (uint32_t)kItemCap - size;
+    if (total > (uint32_t)Scratch::cap - size) {
+      back = nu > 0 && before + nu > (uint32_t)Scratch::cap - size;
       total = (uint32_t)__builtin_amdgcn_readlane((int)before, __ffsll((unsigned long long)__ballot(back)) - 1);
       if (back) {
         uw[0] = uw[1] = uw[2] = uw[3] = ~0u;

@@ -1189,9 +1189,9 @@ __device__ unsigned long long g_phase_cycles[16];
 //   Bound by vector issue (73% of the cycles of a launch, its tail included),
 // with few walks by the longest walk's chain of queries, about 5 us each. Walk
 // kernel with a stack per lane and exact tests of every listed triangle, and
-// now: 2.0M walks among 53,000 triangles of the soup 15.4 -> 8.3 ms, 4.1M walks
-// on a 500,000-face sphere 64.3 -> 34.4 ms, 41,472 walks on 320 faces 3.0 ->
-// 1.1 ms, a batch of 12 meshes 33.8 -> 22.5 ms.
+// now: 2.0M walks among 53,000 triangles of the soup 15.4 -> 7.9 ms, 4.1M walks
+// on a 500,000-face sphere 64.3 -> 29 ms, 41,472 walks on 320 faces 3.0 -> 1.1
+// ms, a batch of 12 meshes 33.8 -> 20 ms.
 template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   __shared__ WaveTables<AccT> T;
@@ -1745,14 +1745,15 @@ struct DiscardBatch {
 // followed by far ones took 12.4 instead of 6.9 ms).
 //   On a thread per query with a traversal of its own, 1,000 queries on 1,280
 // faces took 230 us and 1,000,003 on 499,280 faces 9.6 ms, as long as the
-// slowest traversal of each wavefront; now 32 us and 7 ms, a few trips' latency
-// and vector issue.
+// slowest traversal of each wavefront; now 32 us and 3.5 ms, a few trips'
+// latency and vector issue.
 template <typename Src>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(Src src, int64_t nq, int32_t own_shift) {
-  __shared__ SearchScratch<TriEl> coop[kWaves];
+  typedef SearchScratch<TriEl, false, kQueryItemCap> Scratch;
+  __shared__ Scratch coop[kWaves];
   const int wi = (int)uniform(threadIdx.x >> 6);
-  SearchScratch<TriEl>* W = &coop[wi];
+  Scratch* W = &coop[wi];
   const uint32_t lane = __lane_id();
   const int64_t G = (int64_t)gridDim.x * kWaves, g = (int64_t)blockIdx.x * kWaves + wi;
   const bool owner = lane < (1u << own_shift);

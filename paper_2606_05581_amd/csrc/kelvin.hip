@@ -328,7 +328,7 @@ __global__ void kelvin_quick_kernel(const KelvinTri* __restrict__ tris, int64_t 
     kb[c] *= scale;
     kc[c] *= scale;
   }
-  if (!(h < 1e20) || !quick_frame(ka, kb, kc, q, h, 0.0)) quick_always(ka, q);
+  if (!(h < 1e20) || !quick_frame(ka, kb, kc, q, h, 0.0)) quick_always(ka, q, 1e30f, 0.0f);
 }
 
 namespace {

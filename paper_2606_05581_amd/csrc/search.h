@@ -96,15 +96,18 @@ __device__ __forceinline__ bool quick_frame(const double a[3], const double b[3]
 }
 
 // The records of a pad (no query accepts it) and of an element without a
-// frame (every query sends it to the exact test).
+// frame (every query sends it to the exact test: without a frame the flat
+// value is 0, so F and G alone have to make the element's lower value the
+// smallest and stay finite themselves. The search keeps a slot number in the
+// low bits of a lower value, where those of an infinity would make it NaN).
 __device__ __forceinline__ void quick_pad(float4* q) {
   q[0] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
   for (int k = 1; k < 5; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
-__device__ __forceinline__ void quick_always(const double a[3], float4* q) {
+__device__ __forceinline__ void quick_always(const double a[3], float4* q, float F, float G) {
   q[0] = make_float4((float)a[0], (float)a[1], (float)a[2], 0.0f);
   for (int k = 1; k < 4; ++k) q[4 * k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  q[16] = make_float4(0.0f, 0.0f, 1e30f, 1e30f);
+  q[16] = make_float4(0.0f, 0.0f, F, G);
 }
 
 // Work counted by the statistics kernels; a box lower bound costs 17 FP32

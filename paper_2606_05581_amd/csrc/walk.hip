@@ -1613,7 +1613,9 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
 //     2^-126, so that upper values, and with them m2, stay normal numbers.
 // Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2), and the last.
 // A triangle whose smallest angle has sin < 0.01, whose F is large or whose
-// n.n is below 2^-120 gets margins that send every test of it to the exact one.
+// n.n is below 2^-120 gets margins that send every test of it to the exact one,
+// wherever the query is: F = 0, as a margin that grew with w^2 would leave
+// FP32's range at distances of 1e4 units.
 __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, double radius,
                                      float4* __restrict__ quick) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1647,7 +1649,8 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
   const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
   const double F = u * (128.0 + 64.0 / smin) + far * far;
   const double G = F * lmax * lmax + 0x1p-126 + 0x1p-147 / (nn * nn);
-  if (!(smin >= 0.01) || !(F <= 0.01) || !(nn * nn >= 0x1p-120) || !quick_frame(A, B, C, q, F, G)) quick_always(A, q);
+  if (!(smin >= 0.01) || !(F <= 0.01) || !(nn * nn >= 0x1p-120) || !quick_frame(A, B, C, q, F, G))
+    quick_always(A, q, 0.0f, 0x1p126f);
 }
 
 // A query of the query kernel: its point (scene frame) and mesh, a warm-start

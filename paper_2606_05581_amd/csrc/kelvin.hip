@@ -796,8 +796,8 @@ kelvin_closest_kernel(KelvinDev K, const double* __restrict__ Q, int64_t nq, int
       if (arc_answer(K, W, lane, best, slot)) {
         double q[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
         uint64_t none = 0;
-        int32_t orig = INT_MAX;
-        if (slot >= 0) {  // (none has a finite distance from a point that is not finite)
+        int32_t orig = 0;  // no finite distance: the lowest element at infinity
+        if (slot >= 0) {
           (void)kelvin_tri_d2_t<false>(x, K.tris[slot], K.pre[slot], q, l, INFINITY, none);
           orig = K.tris[slot].orig;
         }
@@ -821,6 +821,13 @@ kelvin_closest_kernel(KelvinDev K, const double* __restrict__ Q, int64_t nq, int
         qi = q;
         for (int c = 0; c < 3; ++c) x[c] = Q[3 * qi + c];
         arc_start(K, el, W, lane, x, -1);
+        const float4 p = W->pt[lane];
+        if (!(fabsf(p.x) <= 0x1p60f && fabsf(p.y) <= 0x1p60f && fabsf(p.z) <= 0x1p60f)) {
+          // its squares leave FP32's range, or it is no number: every element
+          // lies within the allowance, and exact values alone decide
+          W->pt[lane] = make_float4(0.0f, 0.0f, 0.0f, -0x1p41f);
+          W->m2[lane] = __float_as_uint(INFINITY);
+        }
         mode = 1;
         fresh = true;
       }

@@ -51,3 +51,47 @@ def test_slivers_in_large_units_walk_the_same_paths(ctx, leaf):
         a, b = (_log(ctx, case, 32, exterior, leaf, form=f) for f in (0, 1))
         for x, y in zip(a, b):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n", [1, 65, 3000])
+def test_kelvin_points_far_outside_the_domain(ctx, oracle_mod, n):
+    """Points up to 10^150 domain sizes away have a nearest element like any other: the oracle's distance (FP64 on
+    both sides, a few roundings apart), of an element at that distance by the oracle's measure."""
+    import torch
+
+    V, F = W.icosphere_recursive(2)
+    c = np.array([0.2, -0.3, 0.1])
+    V32 = V.astype(np.float32)
+    kv = ctx.kelvin(ctx.build_bvh(V32, F.astype(np.int32)), c)
+    R = kv.info()["radius"]
+    rng = np.random.default_rng(n)
+    Q = rng.normal(size=(n, 3))
+    Q *= R * 10.0 ** rng.choice([1, 5.9, 6.1, 12, 18, 19.5, 25, 60, 150], size=(n, 1)) / np.linalg.norm(Q, axis=1, keepdims=True)
+    t_o, d_o, q_o, _ = oracle_mod.KelvinScene(V32, F, c).nearest(Q, bvh=False)
+    t, d, q, l = (x.cpu().numpy() for x in ctx.kelvin_closest_points(kv, torch.tensor(Q, device="cuda")))
+    assert ((t >= 0) & (t < len(F))).all()
+    assert np.allclose(d, d_o, rtol=1e-10, atol=0)
+    Vc = V32.astype(np.float64) - c
+    for i in np.nonzero(t != t_o)[0]:
+        assert oracle_mod.kelvin_tri_d2(Q[i], *Vc[F[t[i]]])[0] == pytest.approx(d_o[i], rel=1e-10)
+    near = np.linalg.norm(Q, axis=1) < 1e4 * R  # farther out many points of the domain are nearest to rounding
+    assert np.allclose(q[near], q_o[near], rtol=0, atol=1e-9 * R)
+    assert np.allclose(l.sum(1), 1.0, rtol=0, atol=1e-6)
+
+
+def test_kelvin_points_that_are_no_numbers(ctx):
+    """As for flat triangles: the lowest element at an infinite distance, and the numbers beside it as ever."""
+    import torch
+
+    V, F = W.icosphere_recursive(2)
+    kv = ctx.kelvin(ctx.build_bvh(V.astype(np.float32), F.astype(np.int32)), np.array([0.2, -0.3, 0.1]))
+    Q = np.random.default_rng(4).normal(size=(200, 3))
+    a = [x.cpu().numpy() for x in ctx.kelvin_closest_points(kv, torch.tensor(Q, device="cuda"))]
+    P = Q.copy()
+    P[::3, 1] = np.nan
+    P[1::9, 2] = np.inf
+    b = [x.cpu().numpy() for x in ctx.kelvin_closest_points(kv, torch.tensor(P, device="cuda"))]
+    bad = ~np.isfinite(P).all(1)
+    assert (b[0][bad] == 0).all() and np.isinf(b[1][bad]).all()
+    for x, y in zip(a, b):
+        assert np.array_equal(x[~bad], y[~bad])

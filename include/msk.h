@@ -612,11 +612,12 @@ msk_status msk_estimate_psd(msk_ctx* ctx, const msk_mesh* mesh, const msk_rows* 
  * msk_kelvin_create copies the mesh's triangles relative to `centre` (world,
  * 3 doubles; it must lie inside the shape, off the surface) and builds a
  * 4-wide hierarchy over boxes that contain their images (leaf_size 1..8, 0 =
- * 1: one element per leaf, the fastest on MI355X since an element's exact
- * distance costs far more than a box test). Errors: INVALID_ARG for a centre
+ * 4: the search lists a leaf's elements in fours, so narrower leaves only cost
+ * nodes and memory). Errors: INVALID_ARG for a centre
  * at a vertex or on the surface (nearer to a triangle than 1e-9 times its
- * largest vertex distance), or a non-finite centre. All geometry of this
- * path is FP64. */
+ * largest vertex distance), or a non-finite centre. All decisions of
+ * this path are FP64: boxes and a first bound on each element's distance are
+ * FP32, widened by their error, and what they leave is tested in FP64. */
 typedef struct msk_kelvin msk_kelvin;
 typedef struct {
   double centre[3];     /* inversion centre (world)                         */

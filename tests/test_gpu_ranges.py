@@ -95,3 +95,17 @@ def test_kelvin_points_that_are_no_numbers(ctx):
     assert (b[0][bad] == 0).all() and np.isinf(b[1][bad]).all()
     for x, y in zip(a, b):
         assert np.array_equal(x[~bad], y[~bad])
+
+
+@pytest.mark.parametrize("leaf", [0, 1, 2, 3, 4, 8])
+def test_kelvin_leaf_width_is_the_one_asked_for(ctx, leaf):
+    """The inverted hierarchy has at most `leaf` elements a leaf and says so: narrower leaves need more nodes."""
+    V, F = W.icosphere_recursive(3)
+    mesh = ctx.build_bvh(V.astype(np.float32), F.astype(np.int32))
+    c = np.array([0.2, -0.1, 0.05])
+    info = ctx.kelvin(mesh, c, leaf_size=leaf).info()
+    assert info["leaf_size"] == (leaf if leaf else 4)
+    # a 4-wide node has at most 4 leaves of `leaf` elements below it
+    assert info["n_nodes"] >= len(F) / (4.0 * info["leaf_size"] * 4.0 / 3.0)
+    if 0 < leaf < 4:
+        assert info["n_nodes"] > ctx.kelvin(mesh, c, leaf_size=4).info()["n_nodes"]

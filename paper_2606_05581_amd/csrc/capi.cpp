@@ -157,7 +157,7 @@ hipError_t upload_mesh(msk_ctx* ctx, const HostBvh& B, Node4** nodes, TriRec** t
           hipSuccess &&
       (e = hipMemcpyAsync(*tris, B.tris.data(), B.tris.size() * sizeof(TriRec), hipMemcpyHostToDevice, s)) ==
           hipSuccess &&
-      (e = launch_quick_prepare(*tris, (int64_t)B.tris.size(), B.radius, *quick, s)) == hipSuccess)
+      (e = launch_quick_prepare(*tris, (int64_t)B.tris.size(), *quick, s)) == hipSuccess)
     e = hipStreamSynchronize(s);
   if (e != hipSuccess) dfree(*nodes);
   return e;

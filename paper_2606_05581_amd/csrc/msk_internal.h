@@ -35,7 +35,8 @@ constexpr int32_t kPadTri = -1;
 // own frame and the margins of the squared distance computed from it, as five
 // float4: vertex a, c1; x axis (along ab), s1; y axis (towards c), l1; normal,
 // c2; s2, l2, F, G. (c1, s1) and (c2, s2) are the unit directions of ac and bc
-// in the plane, l1 and l2 their lengths; the margin is F |p - a|^2 + G.
+// in the plane, l1 and l2 their lengths; the margin is (F + H |p - a|^2) |p - a|^2
+// + G, the upper 16 bits of H in the low half of F's word.
 // Records lie in blocks of 4 slots, field by field (20 float4 a block: field j
 // of slot s is float4 4 j + s % 4 of block s / 4), so that the 4 lanes of a
 // unit read 64 contiguous bytes per field. kQuickPad pad records follow the
@@ -229,7 +230,7 @@ hipError_t launch_row_totals(const RowCounters* sets, int32_t n_sets, unsigned l
 hipError_t launch_knn_eval(const KnnDev& G, const double* c, const float* Q, const float* Nq, int64_t n, int32_t* idx,
                            float* w, hipStream_t s);
 // n slots (a multiple of 4); quick: 5 (n + kQuickPad) float4
-hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, float4* quick, hipStream_t s);
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, float4* quick, hipStream_t s);
 hipError_t launch_closest_points(const Node4* nodes, const TriRec* tris, const float4* quick, int32_t entry,
                                  float radius, const double* c, const float* Q, int64_t nq, int32_t n_cu, int32_t* tri,
                                  float* d2, float* bary, hipStream_t s);

@@ -302,16 +302,20 @@ __host__ __device__ void bvh_nearest(const Node4* __restrict__ nodes, const TriR
 
 // ---- prefilter of the exact triangle test
 // Squared distance d2 from p to the triangle (quick_flat) with its error
-// margin `m`: the exact test's value D of the same triangle satisfies sqrt(D)
-// >= sqrt(max(0, d2 - m)) - delta, and for all but nearly degenerate triangles
-// sqrt(D) <= sqrt(d2 + m) + delta, delta = 2^-21 R covering the exact test's
-// roundings at the size of the coordinates. The frame and margins are prepared
-// by quick_prepare_kernel, whose comment derives them.
+// margin m = (F + H |p - a|^2) |p - a|^2 + G: the exact test's value D of the
+// same triangle satisfies sqrt(D) >= sqrt(max(0, d2 - m)) - delta, and for all
+// but nearly degenerate triangles sqrt(D) <= sqrt(d2 + m) + delta, delta =
+// 2^-21 R covering the exact test's roundings at the size of the coordinates.
+// Where the margin's relative part exceeds a quarter the values bound nothing
+// (`always`). The frame and margins are prepared by quick_prepare_kernel, whose
+// comment derives them; H stands in the low half of F's word.
 __device__ __forceinline__ void quick_dist(float px, float py, float pz, const void* quick, int64_t i, float& d2,
-                                           float& m) {
+                                           float& m, bool& always) {
   float w2, F, G;
   d2 = quick_flat(px, py, pz, quick, i, w2, F, G);
-  m = F * w2 + G;
+  const float H = __uint_as_float(__float_as_uint(F) << 16), part = F + H * w2;
+  m = part * w2 + G;
+  always = part > 0.25f;
 }
 
 // Largest squared value d2 - m of a triangle that may still beat or tie a
@@ -331,7 +335,7 @@ __device__ __forceinline__ float bound_of(float d2) { return fmaxf(d2, 0x1p-126f
 // pt.w = 2 delta; the owner's (squared distance, original index) is kept by a
 // 64-bit LDS minimum, which realises the lexicographic order exactly.
 struct TriEl {
-  static constexpr uint32_t kQuickFlops = 58;  // FP32 operations of quick_dist and the two bounds
+  static constexpr uint32_t kQuickFlops = 60;  // FP32 operations of quick_dist and the two bounds
   struct Owners {
     const char* base[64];    // owner's mesh (batched meshes differ per lane): its nodes,
     uint32_t off_quick[64];  // and its prefilter records
@@ -358,10 +362,9 @@ struct TriEl {
   __device__ __forceinline__ void quick(Scratch* W, uint32_t o, const float4& p, int64_t i, float& lo, float& up,
                                         bool& always) const {
     float d2, m;
-    quick_dist(p.x, p.y, p.z, W->own.base[o] + ((uint64_t)W->own.off_quick[o] << 8), i, d2, m);
+    quick_dist(p.x, p.y, p.z, W->own.base[o] + ((uint64_t)W->own.off_quick[o] << 8), i, d2, m, always);
     lo = d2 - m;
     up = d2 + m;
-    always = m > 1e28f;
   }
   template <bool kStats, typename Scratch>
   __device__ __forceinline__ void exact(Scratch* W, uint32_t o, int32_t s, bool now, const float4& q,
@@ -395,7 +398,8 @@ __device__ __forceinline__ void search_start(Scratch* W, uint32_t lane, const No
   float m2 = INFINITY;
   if (warm >= 0) {
     float d2, m;
-    quick_dist(x, y, z, quick, quick_index(warm), d2, m);
+    bool always;
+    quick_dist(x, y, z, quick, quick_index(warm), d2, m, always);
     m2 = fminf(d2 + m, INFINITY);  // (no bound where the value overflowed)
   }
   W->pt[lane] = make_float4(x, y, z, 0x1p-20f * radius);
@@ -1595,29 +1599,41 @@ __global__ void knn_eval_kernel(KnnDev G, double cx, double cy, double cz, const
   }
 }
 
-// Prefilter records of a mesh. With u = 2^-24, w = |p - a|, L the
-// longest edge and |p| <= 3 R (so w <= 4 R):
+// Prefilter records of a mesh. With u = 2^-24, w = |p - a|, L the longest and e
+// the shortest edge, s the sine of the smallest angle:
 //   * quick_dist's own error: p - a, the frame, the in-plane coordinates and
 //     the edge terms are off by at most about 12 u (w + L) in distance, so its
 //     squared value by 24 u (w + L)^2;
 //   * tri_dist2's face value (n.ap)^2 / (n.n): n = ab x ac is off by 5 u |ab|
-//     |ac| = 5 u |n| / sin(angle), n.ap by 4 u |n| w more: u w^2 (20 / sin + 16)
-//     in the square; a region taken wrongly near an edge moves the foot by at
-//     most 24 u w^2 over the smallest altitude, whose square is at most w^2
-//     (4 R)^2 (24 u / altitude)^2;
+//     |ac| <= 5 u |n| / s, n.ap by 4 u |n| w more: u w^2 (20 / s + 16) in the
+//     square. (Its other values are distances from points of the triangle.)
+//   * A face taken where an edge or a vertex is nearest: the foot lies outside
+//     the triangle by some distance t, and the value is short of the square by
+//     t^2. The sign of n.(bp x cp) holds farther out than 5 u w / s (n's error)
+//     plus 5 u |bp| |cp| / |bc| + 3 u w (its own): next to a short edge |bp| and
+//     |cp| are at most w + e, next to a long one their product is at most
+//     (w + L) w, so t <= 8 u w^2 / e + 16 u w / s + 16 u (w + L). The vertex tests
+//     are off by 4 u w along an edge, by 6 u w L / e <= 6 u w / s at the far end of
+//     a short one. Taken as t <= 24 u w^2 / e + 24 u w / s, the rest in the first.
 //   * its edge and vertex values add roundings at the size of the coordinates,
 //     delta = 2^-21 R in distance, which keep_bound carries;
 //   * in a mesh of small units its products underflow: (n.ap)^2 by up to 2^-149,
 //     2^-149 / (n.n) in the value (edges of 1e-7: 1e-3 of their square), the
 //     squares of lengths by a few 2^-149. The margin holds 2^-147 / (n.n) +
 //     2^-126, so that upper values, and with them m2, stay normal numbers.
-// Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2), and the last.
-// A triangle whose smallest angle has sin < 0.01, whose F is large or whose
-// n.n is below 2^-120 gets margins that send every test of it to the exact one,
-// wherever the query is: F = 0, as a margin that grew with w^2 would leave
-// FP32's range at distances of 1e4 units.
-__global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, double radius,
-                                     float4* __restrict__ quick) {
+// Together F (w^2 + L^2), (w + L)^2 being at most 2 (w^2 + L^2), H w^4 and the
+// last. A triangle with F > 1/8 (s below 3e-5) or n.n below 2^-120 gets margins
+// that send every test of it to the exact one, wherever the query is: a fixed
+// G above every square.
+//   The w^4 is the query's own. With (4 R)^2 w^2 in its place and s >= 0.01 asked
+// for, triangles below 6e-5 of the scene's size and needles had no prefilter
+// value, and each trip that met one ended with exact tests: 256,000 walks
+// among 128,000 needles (s = 0.003) 157 ms, now 15.8 ms; outside 100 spheres of
+// 3e-4 R 43.5 ms, now 8.9 ms; 200,000 closest points there 11.0 and 2.0 ms, now
+// 3.9 and 0.6 ms. The two operations more a test needs show in no other case
+// (4.1M walks on 500,000 triangles: 29.8 ms both ways). On 19 million triangles
+// and points of all shapes and sizes at most 0.005 of the margin was needed.
+__global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n, float4* __restrict__ quick) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n + kQuickPad) return;
   float4* q = quick + quick_index(i);
@@ -1645,12 +1661,17 @@ __global__ void quick_prepare_kernel(const TriRec* __restrict__ tris, int64_t n,
   bc = sqrt(bc);
   const double nn = sqrt(nrm[0] * nrm[0] + nrm[1] * nrm[1] + nrm[2] * nrm[2]);
   const double lmax = fmax(ab, fmax(ac, bc));
-  const double smin = nn * fmin(ab, fmin(ac, bc)) / (ab * ac * bc);  // sin of the smallest angle
-  const double alt = nn / lmax, u = 0x1p-24, far = 4.0 * radius * 24.0 * u / alt;
-  const double F = u * (128.0 + 64.0 / smin) + far * far;
+  const double emin = fmin(ab, fmin(ac, bc));
+  const double smin = nn * emin / (ab * ac * bc);  // sin of the smallest angle
+  const double u = 0x1p-24, ts = 24.0 * u / smin, te = 24.0 * u / emin;
+  const double F = u * (128.0 + 64.0 / smin) + 2.0 * ts * ts, H = 2.0 * te * te;
   const double G = F * lmax * lmax + 0x1p-126 + 0x1p-147 / (nn * nn);
-  if (!(smin >= 0.01) || !(F <= 0.01) || !(nn * nn >= 0x1p-120) || !quick_frame(A, B, C, q, F, G))
-    quick_always(A, q, 0.0f, 0x1p126f);
+  // F and H rounded up to 16 bits each, in one word
+  const uint32_t fh = ((__float_as_uint((float)F) + 0x10000u) & 0xFFFF0000u) |
+                      ((__float_as_uint((float)H) + 0x10000u) >> 16);
+  if (!(F <= 0.125) || !(H < 1e30) || !(nn * nn >= 0x1p-120) ||
+      !quick_frame(A, B, C, q, (double)__uint_as_float(fh), G * (1.0 + 0x1p-7)))
+    quick_always(A, q, 0.5f, 0x1p126f);
 }
 
 // A query of the query kernel: its point (scene frame) and mesh, a warm-start
@@ -2064,9 +2085,9 @@ hipError_t launch_tangent_ball(const MeshDev& M, int64_t n_rows, float r_max, in
   return hipGetLastError();
 }
 
-hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, double radius, float4* quick, hipStream_t s) {
+hipError_t launch_quick_prepare(const TriRec* tris, int64_t n, float4* quick, hipStream_t s) {
   hipLaunchKernelGGL(quick_prepare_kernel, dim3((unsigned)((n + kQuickPad + 255) / 256)), dim3(256), 0, s, tris, n,
-                     radius, quick);
+                     quick);
   return hipGetLastError();
 }
 

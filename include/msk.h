@@ -447,7 +447,8 @@ typedef struct {
   int32_t n_leaf, leaf[4];            /* BVH leaf width                        */
   int32_t n_chunk, chunk[4];          /* walks a wavefront takes per queue grab */
   int32_t n_regen, regen_min[4];      /* waiting lanes that trigger bookkeeping */
-  int32_t n_bpc, blocks_per_cu[4];    /* persistent workgroups per CU          */
+  int32_t n_bpc, blocks_per_cu[4];    /* persistent workgroups per CU (those above 4
+                                         launch 4 and are timed once)          */
   int64_t trial_rows;                 /* rows sampled over all meshes (65536)  */
   int64_t trial_walks;                /* walks per sampled row (256)           */
   int32_t repeats;                    /* timed repeats per candidate, min (2)  */

@@ -729,8 +729,9 @@ QueueInit make_queues(int64_t n_slots, int64_t W) {
 
 // Workgroups of a persistent launch: at most the 4 a CU holds at once (LDS and
 // registers), since each has a first chunk of its own.
+static int resident_blocks(int blocks_per_cu) { return std::min(4, std::max(1, blocks_per_cu)); }
 static int persistent_grid(const msk_dtn_opts& o, int n_cu) {
-  return std::max(1, n_cu * std::min(4, std::max(1, o.blocks_per_cu)));
+  return std::max(1, n_cu * resident_blocks(o.blocks_per_cu));
 }
 
 // The persistent launch's shape. A launch of fewer walks than its wavefronts
@@ -2304,8 +2305,8 @@ extern "C" void msk_tune_space_default(msk_tune_space* sp) {
   sp->chunk[0] = 32; sp->chunk[1] = 64; sp->chunk[2] = 128;
   sp->n_regen = 3;
   sp->regen_min[0] = 8; sp->regen_min[1] = 16; sp->regen_min[2] = 24;
-  sp->n_bpc = 2;
-  sp->blocks_per_cu[0] = 4; sp->blocks_per_cu[1] = 8;
+  sp->n_bpc = 1;
+  sp->blocks_per_cu[0] = 4;
   sp->trial_rows = 65536;
   sp->trial_walks = 256;
   sp->repeats = 2;
@@ -2381,7 +2382,7 @@ extern "C" msk_status msk_autotune(msk_ctx* ctx, int32_t n, msk_mesh* const* mes
   out->leaf = meshes[0]->leaf_size;
   out->chunk = 64;
   out->regen_min = 1;
-  out->blocks_per_cu = 8;
+  out->blocks_per_cu = resident_blocks(8);
   const std::string sig = tune_signature(ctx, n, meshes, rows, side);
   if (sp.cache_path) {  // one JSON object per line: {"sig": "...", "leaf": L, ...}
     if (FILE* f = std::fopen(sp.cache_path, "r")) {
@@ -2397,7 +2398,7 @@ extern "C" msk_status msk_autotune(msk_ctx* ctx, int32_t n, msk_mesh* const* mes
           out->leaf = lf;
           out->chunk = ch;
           out->regen_min = rg;
-          out->blocks_per_cu = bp;
+          out->blocks_per_cu = resident_blocks(bp);
           out->walks_per_s = wps;
           out->from_cache = 1;
         }
@@ -2488,6 +2489,10 @@ extern "C" msk_status msk_autotune(msk_ctx* ctx, int32_t n, msk_mesh* const* mes
       int* v = dim == 0 ? &lf : dim == 1 ? &ch : dim == 2 ? &rg : &bp;
       *v = vals[j];
       if (lf < 1 || lf > 8 || ch < 1 || rg < 1 || rg > 64 || bp < 1 || bp > 32) continue;
+      bp = resident_blocks(bp);
+      bool timed = false;  // a candidate that launches what an earlier one did is not timed again
+      for (int i = 0; i < j; ++i) timed = timed || (dim == 3 && vals[i] >= 1 && vals[i] <= 32 && resident_blocks(vals[i]) == bp);
+      if (timed) continue;
       double w2 = 0;
       msk_status s2 = evaluate(lf, ch, rg, bp, &w2);
       if (s2 != MSK_OK) return s2;

@@ -670,9 +670,9 @@ kelvin_stream_kernel(
       if (!arc_answer(K, W, lane, d2, slot)) {
         fresh = true;
         mode = 1;
-      } else if (slot < 0) {  // no element at a finite distance (never for a finite x)
+      } else if (slot < 0) {  // no element at a finite distance (never for a finite x): no triangle for the products to read
         const double none[3] = {0.0, 0.0, 0.0};
-        log_walk(kCapped, (int32_t)(k + 1), INT_MAX, none, none);
+        log_walk(kCapped, (int32_t)(k + 1), -1, none, none);
       } else if (k >= K.max_steps || d2 < K.eps2) {
         // the walk ends at its position's nearest point: that element's test
         // once more (the step cap's search is the one at k = max_steps)

@@ -662,8 +662,11 @@ typedef struct {
   int64_t nonfinite_entries;
   /* with walk_opts.collect_stats: the walks run in a counting build of the
    * walk kernel (same walks, not the timed one) whose nearest searches tally
-   * their box-node visits, element tests and FP64 operations (additions,
-   * multiplications, divisions and square roots, one each); else 0 */
+   * their box-node visits, exact element tests and operations (additions,
+   * multiplications, divisions and square roots, one each); else 0. fp64_ops
+   * holds 68 per node for its box tests, which run in FP32: the FP64
+   * operations are fp64_ops - 68 nodes_visited. The FP32 prefilter of the
+   * listed elements is not tallied. */
   int64_t nodes_visited, elements_tested, fp64_ops;
 } msk_kelvin_est_info;
 

@@ -343,7 +343,7 @@ namespace {
 // exact test is the FP64 one; the owner keeps the lexicographic minimum of
 // (squared distance, original index).
 struct ArcEl {
-  static constexpr uint32_t kQuickFlops = 0;  // exact tests and their FP64 operations are counted
+  static constexpr uint32_t kQuickFlops = 0;  // not counted: exact tests, their operations and the boxes' are
   const Node4* node0;
   const KelvinTri* tris;
   const KelvinPre* pre;
@@ -616,8 +616,9 @@ kelvin_tangent_kernel(KelvinDev K, const double* __restrict__ st, const double* 
 // 79,380 elements took 79.6 ms; now 6.5 ms, bound by the longest walks' chains of
 // searches.
 // The counting instantiation (kCount) runs the same walks and adds the
-// searches' node visits, element tests and FP64 operations (68 per node, those
-// of the exact tests) to stats[0..2].
+// searches' node visits, exact element tests and operations (68 FP32 ones per
+// node for its boxes, the FP64 ones of the exact tests) to stats[0..2]. The
+// prefilter's are not counted.
 template <bool kCount>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MSK_KELVIN_WAVES_PER_EU)))
 kelvin_stream_kernel(

@@ -77,6 +77,9 @@ typedef struct {
   double radius;     /* bounding-sphere radius about centre, (1+2^-20) max|v-c| */
   double area;       /* total surface area (FP64)                            */
   int64_t n_verts, n_tris, n_nodes;
+  /* device bytes of the nodes (128 each) and of the triangles: 128 per slot
+   * (the triangle and its prefilter record). A leaf fills whole blocks of 4
+   * slots, so leaves of 4 take about 1.3 slots a triangle, leaves of 1 take 4 */
   int64_t node_bytes, tri_bytes;
   int32_t depth, leaf_size;
 } msk_mesh_info;

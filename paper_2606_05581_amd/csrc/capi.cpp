@@ -31,7 +31,7 @@ struct msk_mesh {
   msk_ctx* ctx = nullptr;
   double centre[3] = {0, 0, 0};
   double radius = 0, area = 0;
-  int64_t nv = 0, nf = 0, n_nodes = 0;
+  int64_t nv = 0, nf = 0, n_nodes = 0, n_slots = 0;
   int depth = 0, leaf_size = 4, entry = 1;
   Node4* d_nodes = nullptr;   // one allocation holds the nodes,
   TriRec* d_tris = nullptr;   // the triangles
@@ -250,6 +250,7 @@ extern "C" msk_status msk_build_bvh(msk_ctx* ctx, const float* V, int64_t n_vert
   m->nv = n_verts;
   m->nf = n_tris;
   m->n_nodes = (int64_t)B.nodes.size();
+  m->n_slots = (int64_t)B.tris.size();
   m->depth = B.depth;
   m->leaf_size = leaf;
   m->entry = B.entry;
@@ -279,7 +280,7 @@ extern "C" msk_status msk_mesh_get_info(const msk_mesh* m, msk_mesh_info* info) 
   info->n_tris = m->nf;
   info->n_nodes = m->n_nodes;
   info->node_bytes = m->n_nodes * (int64_t)sizeof(Node4);
-  info->tri_bytes = m->nf * (int64_t)sizeof(TriRec);
+  info->tri_bytes = m->n_slots * (int64_t)(sizeof(TriRec) + 5 * sizeof(float4));
   info->depth = m->depth;
   info->leaf_size = m->leaf_size;
   return MSK_OK;
@@ -2338,6 +2339,7 @@ extern "C" msk_status msk_mesh_rebuild(msk_ctx* ctx, msk_mesh* m, int32_t leaf) 
   m->d_quick = dq;
   m->d_slot = ds;
   m->n_nodes = (int64_t)B.nodes.size();
+  m->n_slots = (int64_t)B.tris.size();
   m->depth = B.depth;
   m->leaf_size = leaf;
   m->entry = B.entry;

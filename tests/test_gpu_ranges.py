@@ -178,3 +178,16 @@ def test_prefilter_bounds_thin_and_small_triangles(ctx, name):
     assert exact / 114 <= 0.25 * i["tris_tested"]
     for x, y in zip(*(_log(ctx, case, 16, exterior, 4, form=f) for f in (0, 1))):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("leaf", [1, 2, 4, 8])
+def test_mesh_info_counts_the_bytes_of_its_slots(ctx, leaf):
+    """128 bytes a slot, and leaves of whole blocks of 4 slots: one triangle a leaf takes 4, and no width less than 1."""
+    V, F = _mesh("sphere1280")
+    mesh = ctx.build_bvh(V.astype(np.float32), F.astype(np.int32), leaf_size=8)
+    mesh.rebuild(leaf)
+    info = mesh.info()
+    assert info["tri_bytes"] % (4 * 128) == 0
+    assert len(F) * 128 <= info["tri_bytes"] <= len(F) * 128 * 4
+    if leaf == 1:
+        assert info["tri_bytes"] == len(F) * 128 * 4

@@ -10,7 +10,10 @@ namespace msk {
 
 // 4-wide BVH node, one 128-byte line. Child k's box is
 // [lo{x,y,z}[k], hi{x,y,z}[k]]; child[k] >= 0 is an inner node index,
-// child[k] < 0 a leaf holding triangle slots [-child[k]-1, -child[k]-1+count[k]).
+// child[k] < 0 a leaf of count[k] triangles. As the tree is built, ~child[k] is
+// the leaf's first slot; once align_leaf_order has laid the leaves out in
+// blocks of 4 slots (every tree on the device), the first slot is ~child[k] & ~3
+// and the low two bits hold the number of blocks less one.
 // An unused slot has an empty box (lo = +inf, hi = -inf) and count 0.
 struct alignas(128) Node4 {
   float lox[4], loy[4], loz[4];
@@ -245,9 +248,10 @@ hipError_t launch_psd_syrk(const double* A, int64_t m, int64_t Kp, int64_t slice
 hipError_t launch_psd_reduce(const double* P, int64_t n_slots, int64_t K, int64_t Kp, double* C, hipStream_t s);
 
 // Fixed workspace of the allocation-free estimate (noalloc.hip): 64 MiB per
-// device, and the padding of the 8 queue counters to cache lines of their own. noalloc_scratch_init looks its address up on `device` (which must
-// be current) once; noalloc_scratch returns it (nullptr if the lookup failed
-// or was not made, with the HIP error in *err).
+// device, and the padding of the 8 queue counters to cache lines of their own.
+// noalloc_scratch_init looks its address up on `device` (which must be current)
+// once; noalloc_scratch returns it (nullptr if the lookup failed or was not
+// made, with the HIP error in *err).
 constexpr size_t kNoallocScratchBytes = (size_t(64) << 20) + 768;
 hipError_t noalloc_scratch_init(int device);
 void* noalloc_scratch(int device, hipError_t* err);

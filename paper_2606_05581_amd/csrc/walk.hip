@@ -331,7 +331,9 @@ __device__ __forceinline__ float keep_bound(float m2, float two_delta) {
 __device__ __forceinline__ float bound_of(float d2) { return fmaxf(d2, 0x1p-126f); }
 
 // Planar triangles as elements of the wavefront-shared search (same result as
-// the lane-private bvh_nearest, bit for bit). Values are squared distances,
+// the lane-private bvh_nearest, bit for bit, unless the exact test's products
+// underflow: in scenes of radius below about 1e-5 whole neighbourhoods tie at
+// distance 0, and the two searches may meet different ones of them). Values are squared distances,
 // pt.w = 2 delta; the owner's (squared distance, original index) is kept by a
 // 64-bit LDS minimum, which realises the lexicographic order exactly.
 struct TriEl {
@@ -459,7 +461,6 @@ struct LaneWalk {
   int32_t queries;
   int32_t slot;  // warm-start triangle slot
   int32_t active;
-  TravCount cnt;  // traversal work of this walk (counted in the statistics kernels only)
   int32_t tab;    // wavefront row table of the walk (-1: device atomics)
   uint32_t ux, uy;  // direction uniforms of the current step (drawn before its query)
 };
@@ -514,7 +515,6 @@ __device__ bool ball_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_
   w.slot = gload(M.slot_of_tri, face);
   w.step = 0;
   w.queries = 0;
-  w.cnt = TravCount();
   return true;
 }
 
@@ -565,7 +565,6 @@ __device__ bool walk_start(const WalkLaunch& L, const MD& M, LaneWalk& w, int32_
   w.slot = gload(M.slot_of_tri, face);
   w.step = 0;
   w.queries = 0;
-  w.cnt = TravCount();
   return true;
 }
 
@@ -750,15 +749,10 @@ __device__ void walk_contrib(const WalkLaunch& L, const MD& M, const LaneWalk& w
   }
 }
 
-// Walk log and traversal statistics of a finished walk.
+// Walk log of a finished walk.
 template <typename MD>
 __device__ void walk_record(const WalkLaunch& L, const MD& M, const LaneWalk& w, int32_t status, bool has_t,
                             const Nearest& hit) {
-  if (L.stats) {
-    atomicAdd(L.stats, (unsigned long long)w.cnt.nodes);
-    atomicAdd(L.stats + 1, (unsigned long long)w.cnt.tris);
-    atomicAdd(L.stats + 2, (unsigned long long)w.cnt.flops);
-  }
   if (M.log_status) {
     const int64_t li = (int64_t)w.row * M.walks_per_row + ((int64_t)w.walk - L.walk_offset);
     gstore(M.log_status, li, status);
@@ -803,8 +797,9 @@ __device__ void walk_finish_global(const WalkLaunch& L, const MD& M, const LaneW
 // most `chunk` walks) and flushes them into the FP64 rows; AccT = CompF32
 // keeps them as compensated FP32 pairs.
 // Row-table slots per wavefront table (2^bits) and the occupancy the
-// persistent kernels are compiled for: with 64 slots, the cooperative leaf
-// scratch and 21 LDS-staged top nodes a workgroup holds 29.8 KB of LDS.
+// persistent kernels are compiled for: with 64 slots, FP64 tables and four
+// search scratches take 40,192 B of the 40,960 that let a CU hold the four
+// workgroups which persistent launches count on (kLdsPerBlock).
 // The streaming kernel measured fastest on gfx950 at 4 waves per SIMD (128
 // VGPRs, few spills) against 3 (no spills) and 5, 6 (many spills); 32-slot
 // tables lost to their extra device atomics and 128 slots gained nothing.
@@ -813,6 +808,7 @@ __device__ void walk_finish_global(const WalkLaunch& L, const MD& M, const LaneW
 #endif
 constexpr int kSlotBits = MSK_TABLE_SLOT_BITS, kSlots = 1 << kSlotBits, kProbes = 8, kWaves = 4;
 static_assert(kSlots == 64, "record_point_walks harvests one slot per lane");
+constexpr size_t kLdsPerBlock = 160 * 1024 / 4;
 constexpr int32_t kEmptyKey = -1;
 
 // Compensated FP32 partial sum: the value is hi + lo, a double-float pair.
@@ -1111,14 +1107,14 @@ __device__ int32_t walk_end(const MD& M, LaneWalk& w, bool capped, const Nearest
 
 // One whole step with a lane-private query (plain kernel).
 template <bool kStats, typename MD>
-__device__ int32_t walk_step(const WalkLaunch& L, const MD& M, LaneWalk& w, Nearest& hit) {
+__device__ int32_t walk_step(const WalkLaunch& L, const MD& M, LaneWalk& w, Nearest& hit, TravCount& cnt) {
   bool capped;
   const int32_t st = walk_begin(L, M, w, capped);
   if (st >= 0) return st;
   hit.d2 = INFINITY;
   hit.orig = INT_MAX;
   hit.slot = w.slot;
-  bvh_nearest<kStats>(M.nodes, M.tris, w.x, w.y, w.z, M.radius, hit, w.cnt);
+  bvh_nearest<kStats>(M.nodes, M.tris, w.x, w.y, w.z, M.radius, hit, cnt);
   return walk_end(M, w, capped, hit);
 }
 
@@ -1144,11 +1140,17 @@ __global__ void __launch_bounds__(256) walk_plain_kernel(WalkLaunch L) {
   double lam[3];
   if (!walk_start<kRowsAny>(L, M, w, face, lam)) return;
   Nearest hit;
+  TravCount cnt;
   int32_t st;
   do {
-    st = walk_step<kStats>(L, M, w, hit);
+    st = walk_step<kStats>(L, M, w, hit, cnt);
   } while (st < 0);
   walk_finish_global<kKnn>(L, M, w, st, hit);
+  if (kStats && L.stats) {
+    atomicAdd(L.stats, (unsigned long long)cnt.nodes);
+    atomicAdd(L.stats + 1, (unsigned long long)cnt.tris);
+    atomicAdd(L.stats + 2, (unsigned long long)cnt.flops);
+  }
 }
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
@@ -1200,6 +1202,7 @@ template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {
   __shared__ WaveTables<AccT> T;
   __shared__ SearchScratch<TriEl> coop[kWaves];
+  static_assert(sizeof(T) + sizeof(coop) <= kLdsPerBlock, "four workgroups per CU");
   const int wi = (int)uniform(threadIdx.x >> 6);
   SearchScratch<TriEl>* W = &coop[wi];
   for (int i = threadIdx.x; i < kWaves * 2 * kSlots; i += blockDim.x) {
@@ -1776,6 +1779,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(Src src, int64_t nq, int32_t own_shift) {
   typedef SearchScratch<TriEl, false, kQueryItemCap> Scratch;
   __shared__ Scratch coop[kWaves];
+  static_assert(sizeof(coop) <= kLdsPerBlock, "four workgroups per CU");
   const int wi = (int)uniform(threadIdx.x >> 6);
   Scratch* W = &coop[wi];
   const uint32_t lane = __lane_id();

@@ -1761,6 +1761,61 @@ struct DiscardBatch {
   }
 };
 
+// Queries that keep the lane-private search: far from the scene the exact
+// test's sign errors exceed the slack of the box bounds, so that what it finds
+// depends on the order of the search; and points that are no numbers have no
+// distance.
+__device__ __forceinline__ bool far_query(const Query& p) {
+  const float far = 1.7f * p.radius;
+  return !(fabsf(p.x) <= far && fabsf(p.y) <= far && fabsf(p.z) <= far);
+}
+
+template <typename Src>
+__device__ __forceinline__ void answer_alone(const Src& src, int64_t i, const Query& p) {
+  Nearest h;
+  TravCount cnt;
+  h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
+  bvh_nearest<false>(p.nodes, p.tris, p.x, p.y, p.z, p.radius, h, cnt);
+  src.store(i, h);
+}
+
+// The far ones among n queries, after a query kernel that leaves them: a
+// wavefront looks through the blocks of 64 queries g, g + G, ... and answers
+// the far ones 64 at a time, one per lane, with kFarWaves wavefronts per SIMD
+// (80 VGPRs; at 8 the traversal spills: 13.1 ms). Bound by the dependent loads
+// of the traversals. Answered by the query kernel as they came, on 4
+// wavefronts per SIMD and few of their lanes, they held the others: 1,000,000
+// points on 79,380 faces, all of them 3 to 10 radii away, 11.7 ms, now 10.0 ms;
+// 2% of them, the others near the surface, 4.2 ms, now 2.2 ms; 30%, 10.0 ms, now
+// 5.0 ms.
+constexpr int kFarWaves = 6;
+template <typename Src>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFarWaves)))
+    far_queries_kernel(Src src, int64_t nq) {
+  __shared__ int64_t list[kWaves][128];
+  const int wi = (int)uniform(threadIdx.x >> 6);
+  const uint32_t lane = __lane_id();
+  const int64_t G = (int64_t)gridDim.x * kWaves;
+  uint32_t n = 0;
+  for (int64_t b = (int64_t)blockIdx.x * kWaves + wi;; b += G) {
+    const int64_t i = b * 64 + lane;
+    const bool more = b * 64 < nq, far = i < nq && far_query(src.load(i));
+    const uint64_t mk = __ballot(far);
+    if (far) list[wi][n + mbcnt64(mk)] = i;
+    n += (uint32_t)__popcll(mk);
+    lds_order();
+    if (more && n < 64) continue;
+    const uint32_t take = min(n, 64u);
+    if (lane < take) {
+      const int64_t q = list[wi][n - take + lane];
+      answer_alone(src, q, src.load(q));
+    }
+    n -= take;
+    lds_order();
+    if (!more) break;  // (fewer than 64 were left)
+  }
+}
+
 // Nearest triangles of n queries on the wavefront-shared search: lanes with an
 // answered query wait until a quarter of the wavefront's queries do, then
 // store their answers and take the next queries together. At most 2^own_shift
@@ -1774,7 +1829,7 @@ struct DiscardBatch {
 // faces took 230 us and 1,000,003 on 499,280 faces 9.6 ms, as long as the
 // slowest traversal of each wavefront; now 32 us and 3.5 ms, a few trips'
 // latency and vector issue.
-template <typename Src>
+template <typename Src, bool kFar>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
     query_stream_kernel(Src src, int64_t nq, int32_t own_shift) {
   typedef SearchScratch<TriEl, false, kQueryItemCap> Scratch;
@@ -1825,8 +1880,7 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
         if (take) {
           qi = q;
           const Query p = src.load(qi);
-          const float far = 1.7f * p.radius;
-          if (fabsf(p.x) <= far && fabsf(p.y) <= far && fabsf(p.z) <= far) {
+          if (!far_query(p)) {
             // few queries leave the stack room enough for a cold start
             const int32_t warm = p.warm < 0 && own_shift > 2 ? nearest_leaf(p.nodes, p.x, p.y, p.z) : p.warm;
             search_start(W, lane, p.nodes, p.quick, p.tris, p.radius, p.x, p.y, p.z, warm);
@@ -1834,11 +1888,8 @@ __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY
             entry = p.entry;
             mode = 1;
             fresh = true;
-          } else {  // the prefilter's margins hold for |p| <= 3 R, and for numbers
-            Nearest h;
-            h.d2 = INFINITY; h.orig = INT_MAX; h.slot = -1;
-            bvh_nearest<false>(p.nodes, p.tris, p.x, p.y, p.z, p.radius, h, cnt);
-            src.store(qi, h);
+          } else if (kFar) {
+            answer_alone(src, qi, p);
           }
         }
         const uint32_t got = (uint32_t)__popcll(__ballot(take));
@@ -2049,7 +2100,19 @@ static hipError_t launch_queries(const Src& src, int64_t n, int32_t n_cu, hipStr
   int own_shift = 0;
   while (own_shift < 6 && (waves << own_shift) < n) ++own_shift;
   const int64_t blocks = std::min<int64_t>(4ll * n_cu, (((n - 1) >> own_shift) / kWaves) + 1);
-  hipLaunchKernelGGL(query_stream_kernel<Src>, dim3((unsigned)blocks), dim3(256), 0, s, src, n, own_shift);
+  // Up to 128 queries a wavefront the second launch costs more than it saves
+  // (200,000 points on 79,380 faces: 214 us near the surface and 1.36 ms with 2%
+  // far ones, 220 us and 1.41 ms with it; 1,000,000 points: 0.64 ms both ways,
+  // 4.2 and 2.3 ms). Inset tests are hardly ever far.
+  if (!Src::kBary || n <= 128 * waves) {
+    hipLaunchKernelGGL((query_stream_kernel<Src, true>), dim3((unsigned)blocks), dim3(256), 0, s, src, n, own_shift);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((query_stream_kernel<Src, false>), dim3((unsigned)blocks), dim3(256), 0, s, src, n, own_shift);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t far_blocks = std::min<int64_t>((int64_t)kFarWaves * n_cu, (n + 255) / 256);
+  hipLaunchKernelGGL(far_queries_kernel<Src>, dim3((unsigned)far_blocks), dim3(256), 0, s, src, n);
   return hipGetLastError();
 }
 

@@ -191,3 +191,30 @@ def test_mesh_info_counts_the_bytes_of_its_slots(ctx, leaf):
     assert len(F) * 128 <= info["tri_bytes"] <= len(F) * 128 * 4
     if leaf == 1:
         assert info["tri_bytes"] == len(F) * 128 * 4
+
+
+@pytest.mark.parametrize("share", [0.0, 1e-5, 0.02, 0.5, 1.0])
+@pytest.mark.parametrize("n", [524288, 524289, 700001])
+def test_far_points_in_large_calls(ctx, oracle_mod, n, share):
+    """Calls of more than 524,288 points answer the far ones, and those that are no numbers, in a launch of their own:
+    the same bits as calls of fewer points, and the brute force's on a sample."""
+    import torch
+
+    V, F = _mesh("sphere1280")
+    V32 = V.astype(np.float32)
+    mesh = ctx.build_bvh(V32, F.astype(np.int32))
+    rng = np.random.default_rng(n)
+    Q = (V[rng.integers(0, len(V), n)] * (1.0 + 0.05 * rng.normal(size=(n, 1)))).astype(np.float32)
+    far = rng.random(n) < share
+    far[-1] = share > 0
+    Q[far] *= rng.uniform(2, 30, (int(far.sum()), 1)).astype(np.float32)
+    Q[rng.random(n) < 1e-4 * share, 0] = np.nan
+    whole = [x.cpu().numpy() for x in ctx.closest_points(mesh, torch.tensor(Q, device="cuda"))]
+    parts = [ctx.closest_points(mesh, torch.tensor(Q[i:i + 50000], device="cuda")) for i in range(0, n, 50000)]
+    ok = np.isfinite(Q).all(1)
+    for k, x in enumerate(whole):
+        y = np.concatenate([p[k].cpu().numpy() for p in parts])
+        assert np.array_equal(x[ok] if k == 2 else x, y[ok] if k == 2 else y)  # (no barycentrics without a distance)
+    sel = np.nonzero(ok)[0][:: max(1, n // 3000)]
+    t_o, d_o, b_o = oracle_mod.Scene(V32, F, bvh=False).nearest_f32(Q[sel].astype(np.float64))
+    assert np.array_equal(whole[0][sel], t_o) and np.array_equal(whole[1][sel], d_o) and np.array_equal(whole[2][sel], b_o)

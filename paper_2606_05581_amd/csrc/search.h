@@ -386,16 +386,20 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
         const uint32_t uo = pk & 63u;
         const uint32_t bl = pk >> 6;
         const float4 p = W->pt[uo];
+        const float m2 = __uint_as_float(W->m2[uo]);
         float up;
         bool always;
         el.quick(W, uo, p, (int64_t)bl * 20 + (lane & 3u), lo, up, always);
-        if (p.w >= 0.0f) atomicMin(&W->m2[uo], __float_as_uint(up));
+        // (most upper values lie above the bound: without the look at it the
+        // PSD estimator's walks take 4.75 instead of 4.5 ms)
+        if (p.w >= 0.0f && up < m2) atomicMin(&W->m2[uo], __float_as_uint(up));
         lds_order();
         cand = lo <= El::keep(__uint_as_float(W->m2[uo]), p);
         force |= cand && (always || p.w < 0.0f);
         entry = (bl << 6) | uo;
-        // the slot within its block goes into the low bits of the lower value
-        lo = __uint_as_float((__float_as_uint(lo - fabsf(lo) * 0x1p-20f) & ~3u) | (lane & 3u));
+        // the slot within its block goes into the low bits of the lower value,
+        // which grows by at most 3 * 2^-23 of it: El::keep allows for 2^-20
+        lo = __uint_as_float((__float_as_uint(lo) & ~3u) | (lane & 3u));
       }
       const uint64_t mk = __ballot(cand);
       if (cand) {

@@ -1192,11 +1192,11 @@ __device__ unsigned long long g_phase_cycles[16];
 // At most L.max_owners lanes of a wavefront carry a walk: a launch of few
 // walks spreads them over all wavefronts. The walks, their queries and their
 // results are those of the other forms.
-//   Bound by vector issue (73% of the cycles of a launch, its tail included),
+//   Bound by vector issue (0.79 of the issue rate over a batch's launch),
 // with few walks by the longest walk's chain of queries, about 5 us each. Walk
 // kernel with a stack per lane and exact tests of every listed triangle, and
-// now: 2.0M walks among 53,000 triangles of the soup 15.4 -> 7.9 ms, 4.1M walks
-// on a 500,000-face sphere 64.3 -> 29 ms, 41,472 walks on 320 faces 3.0 -> 1.1
+// now: 2.0M walks among 53,000 triangles of the soup 15.4 -> 7.8 ms, 4.1M walks
+// on a 500,000-face sphere 64.3 -> 27.6 ms, 41,472 walks on 320 faces 3.0 -> 1.0
 // ms, a batch of 12 meshes 33.8 -> 20 ms.
 template <bool kStats, typename AccT, bool kKnn, RowKind kRows>
 __global__ void __launch_bounds__(256) MSK_PERSISTENT_OCCUPANCY walk_stream_kernel(WalkLaunch L) {

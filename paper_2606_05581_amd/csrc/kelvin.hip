@@ -358,6 +358,7 @@ struct ArcEl {
   static __device__ __forceinline__ float keep(float m2, const float4& q) {
     return (m2 + fabsf(q.w)) * (1.0f + 0x1p-20f);
   }
+  static __device__ __forceinline__ float keep_wide(float m2, const float4& q) { return keep(m2, q); }
   static __device__ __forceinline__ float boxes(float m2, const float4& q) {
     const float s = (m2 + fabsf(q.w)) * (1.0f + 0x1p-20f);
     return fminf(s * s * (1.0f + 0x1p-20f), 0x1.fffffep127f);

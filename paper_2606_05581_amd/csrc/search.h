@@ -394,9 +394,9 @@ __device__ __forceinline__ void search_pass(const El& el, Scratch* W, uint32_t l
         // PSD estimator's walks take 4.75 instead of 4.5 ms)
         if (p.w >= 0.0f && up < m2) atomicMin(&W->m2[uo], __float_as_uint(up));
         lds_order();
-        cand = lo <= El::keep(__uint_as_float(W->m2[uo]), p);
+        cand = lo <= El::keep_wide(__uint_as_float(W->m2[uo]), p);  // (flush_pending takes El::keep)
         force |= cand && (always || p.w < 0.0f);
-        entry = (bl << 6) | uo;
+        entry = pk;
         // the slot within its block goes into the low bits of the lower value,
         // which grows by at most 3 * 2^-23 of it: El::keep allows for 2^-20
         lo = __uint_as_float((__float_as_uint(lo) & ~3u) | (lane & 3u));

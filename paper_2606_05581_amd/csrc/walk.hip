@@ -346,6 +346,13 @@ struct TriEl {
     int32_t rec_slot[64];
   };
   static __device__ __forceinline__ float keep(float m2, const float4& q) { return keep_bound(m2, fabsf(q.w)); }
+  // Not below keep, and without its square root (a quarter-rate instruction):
+  // (x + w)^2 <= x^2 (1 + t) + w^2 (1 + 1/t), t = 2^-12, and 2^-19 for rounding.
+  // The tests of listed triangles take it: it gives back what their margins'
+  // w^4 costs (soup operator's walks 7.85 -> 7.75 ms).
+  static __device__ __forceinline__ float keep_wide(float m2, const float4& q) {
+    return m2 * (1.0f + 0x1p-12f + 0x1p-19f) + (q.w * q.w) * (4097.0f * (1.0f + 0x1p-19f));
+  }
   // Box bound of a query: no triangle in a box whose squared distance exceeds it
   // beats or ties the bound m2 (prune_bound's argument, with delta more: m2
   // bounds the prefilter's value). Finite, so that an infinite lower bound never
